@@ -87,7 +87,7 @@ Workspace carve(const el_attn_ctx *c) { return carve_from(c->ws_base, ws_layout(
 
 void free_weights(el_attn_ctx *c)
 {
-    void *ptrs[] = {c->w.Wq, c->w.Wk, c->w.Wv, c->w.Wo, c->w.bq, c->w.WqT, c->w.WkH, c->w.WvT, c->w.WoT, (void *)c->w.c_out,
+    void *ptrs[] = {c->w.WqT, c->w.Wk, c->w.bq, c->w.WkH, c->w.WvT, c->w.WoT, c->w.WvTs, c->w.WoTs, (void *)c->w.c_out,
                     (void *)c->w.bk32, (void *)c->w.bv32, (void *)c->w.bo32};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -204,17 +204,18 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
     } else {
         if (launch_qproj_generic(ctx, p, ws, s) != hipSuccess) return EL_ERR_HIP;
         if (launch_elq_generic(ctx, p, ws.Qp, (float *)ws.ELQ, s) != hipSuccess) return EL_ERR_HIP;
-        const int parts = ctx->splits_override ? ctx->splits_override : auto_parts_generic(p);
+        const bool scored = scores_fit(p);
+        const int parts = scored ? 1 : ctx->splits_override ? ctx->splits_override : auto_parts_generic(p);
         fmt->pm.E = nullptr; fmt->pm.parts = parts; fmt->pm.G = 0; fmt->pm.lfloor = 0; fmt->pm.B = p.B; fmt->pm.kcost = 0;
         fmt->Rstride = p.R; fmt->ml_to_nat = 1.f;
         const bool timed = ctx->ev && ctx->ev_used < ctx->ev_cap;
         if (timed && hipEventRecord(ctx->ev[2 * ctx->ev_used], s) != hipSuccess) return EL_ERR_HIP;
-        if (launch_core_generic(ctx, p, ws, parts, s) != hipSuccess) return EL_ERR_HIP;
+        if ((scored ? launch_core_scores(ctx, p, ws, s) : launch_core_generic(ctx, p, ws, parts, s)) != hipSuccess) return EL_ERR_HIP;
         if (timed) {
             if (hipEventRecord(ctx->ev[2 * ctx->ev_used + 1], s) != hipSuccess) return EL_ERR_HIP;
             ctx->ev_used++;
         }
-        if (launch_merge_generic(ctx, p, ws, parts, p.R, s) != hipSuccess) return EL_ERR_HIP;
+        if (!scored && launch_merge_generic(ctx, p, ws, parts, p.R, s) != hipSuccess) return EL_ERR_HIP;
     }
     if (launch_vproj_generic(ctx, p, ws, s) != hipSuccess) return EL_ERR_HIP;
     fmt->a_f16 = fmt->qp_f16 = false; fmt->c_to_nat = 1.f;
@@ -226,6 +227,14 @@ el_status run_a7(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const 
     const hipError_t e = (el_attn_uses_mfma(ctx) && ctx->use_mfma_gemm) ? launch_oproj_mfma(ctx, p, ws, bias32, s)
                                                                        : launch_oproj_generic(ctx, p, ws, bias32, s);
     return e == hipSuccess ? EL_OK : EL_ERR_HIP;
+}
+
+// a1..a7
+el_status run_step(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s)
+{
+    StepFormats fmt;
+    const el_status st = run_a1_to_a6(ctx, p, ws, s, &fmt);
+    return st != EL_OK ? st : run_a7(ctx, p, ws, ctx->w.c_out, s);
 }
 
 el_status check_keys(const el_attn_ctx *ctx, const void *H, int64_t H_batch_stride, const int32_t *lengths, int32_t n)
@@ -279,7 +288,8 @@ el_status el_attn_prepare(const el_attn_config *cfg,
     c->hd = cfg->heads * cfg->d_k;
     c->Rpad_max = round_up64(cfg->heads * cfg->max_beam);
     c->ws_need = ws_layout(c).total;
-    c->use_mfma_core = core_mfma_supported(cfg->dtype, cfg->d_model) ? 1 : 0;
+    c->use_mfma_core = core_mfma_supported(cfg->dtype, cfg->d_model) && !(cfg->flags & EL_FLAG_FORCE_GENERIC) ? 1 : 0;
+    c->use_mfma_gemm = (c->use_mfma_core && gemm_mfma_supported(cfg->dtype, cfg->d_model, cfg->d_k)) ? 1 : 0;
 
     hipStream_t s = (hipStream_t)stream;
     forget_foreign_errors();
@@ -291,21 +301,33 @@ el_status el_attn_prepare(const el_attn_config *cfg,
 
     const size_t es = dtype_size(cfg->dtype);
     const size_t wbytes = (size_t)cfg->d_model * c->hd * es;
-    struct { void **dst; const void *src; size_t bytes; } copies[] = {
-        {&c->w.Wq, Wq, wbytes}, {&c->w.Wk, Wk, wbytes}, {&c->w.Wv, Wv, wbytes}, {&c->w.Wo, Wo, wbytes},
-        {&c->w.bq, bq, (size_t)c->hd * es},
+    // copies and transposes in the storage type (those the path of this context reads)
+    const bool gemm = c->use_mfma_gemm != 0;
+    struct { void **dst; const void *src; size_t bytes; int rows, cols; } packed[] = {
+        {&c->w.WqT, Wq, wbytes, cfg->d_model, c->hd},
+        {&c->w.Wk, Wk, wbytes, 0, 0},
+        {&c->w.bq, bq, (size_t)c->hd * es, 0, 0},
+        {gemm ? &c->w.WvT : &c->w.WvTs, Wv, wbytes, cfg->d_model, c->hd},
+        {gemm ? &c->w.WoT : &c->w.WoTs, Wo, wbytes, c->hd, cfg->d_model},
+        {&c->w.WkH, gemm ? Wk : nullptr, wbytes, 0, 0},
     };
-    for (auto &cp : copies) {
-        if (!cp.src) continue;
-        if (hipMalloc(cp.dst, cp.bytes) != hipSuccess) { free_weights(c); delete c; return EL_ERR_ALLOC; }
-        if (hipMemcpyAsync(*cp.dst, cp.src, cp.bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) {
-            free_weights(c); delete c; return EL_ERR_HIP;
-        }
+    for (auto &t : packed) {
+        if (!t.src) continue;
+        if (hipMalloc(t.dst, t.bytes) != hipSuccess) { free_weights(c); delete c; return EL_ERR_ALLOC; }
+        const hipError_t e = t.rows ? launch_transpose(es, t.src, *t.dst, t.rows, t.cols, s)
+                                    : hipMemcpyAsync(*t.dst, t.src, t.bytes, hipMemcpyDeviceToDevice, s);
+        if (e != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
     }
     if (hipMalloc((void **)&c->w.c_out, (size_t)cfg->d_model * sizeof(float)) != hipSuccess) {
         free_weights(c); delete c; return EL_ERR_ALLOC;
     }
-    if (launch_cout(c, bv, bo, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
+    if (launch_cout(c, gemm ? c->w.WoT : c->w.WoTs, bv, bo, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
+    // everything after a1 of the MFMA projections runs in fp16: bf16 weights of a2, a6, a7 are converted once here
+    if (gemm && cfg->dtype == EL_BF16) {
+        const size_t nel = (size_t)cfg->d_model * c->hd;
+        for (void *m : {c->w.WkH, c->w.WvT, c->w.WoT})
+            if (launch_bf16_to_f16(m, m, nel, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
+    }
     // fp32 copies of the three biases the segment form needs (b^K enters its statistics, Eq. 7)
     struct { float **dst; const void *src; int n; } vecs[] = {
         {&c->w.bk32, bk, c->hd}, {&c->w.bv32, bv, c->hd}, {&c->w.bo32, bo, cfg->d_model},
@@ -313,23 +335,6 @@ el_status el_attn_prepare(const el_attn_config *cfg,
     for (auto &v : vecs) {
         if (hipMalloc((void **)v.dst, (size_t)v.n * sizeof(float)) != hipSuccess) { free_weights(c); delete c; return EL_ERR_ALLOC; }
         if (launch_vec_f32(cfg->dtype, v.src, *v.dst, v.n, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
-    }
-    c->use_mfma_gemm = (c->use_mfma_core && gemm_mfma_supported(cfg->dtype, cfg->d_model, cfg->d_k)) ? 1 : 0;
-    if (c->use_mfma_gemm) {
-        // transposed copies so that every MFMA operand is contiguous along k; everything after a1 runs
-        // in fp16, so bf16 weights of a2, a6, a7 are converted once here
-        struct { void **dst; const void *src; int rows, cols; bool to_f16; } tr[] = {
-            {&c->w.WqT, c->w.Wq, cfg->d_model, c->hd, false}, {&c->w.WvT, c->w.Wv, cfg->d_model, c->hd, true},
-            {&c->w.WoT, c->w.Wo, c->hd, cfg->d_model, true},  {&c->w.WkH, c->w.Wk, 0, 0, true},
-        };
-        const size_t nel = (size_t)cfg->d_model * c->hd;
-        for (auto &t : tr) {
-            if (hipMalloc(t.dst, wbytes) != hipSuccess) { free_weights(c); delete c; return EL_ERR_ALLOC; }
-            hipError_t e = t.rows ? launch_transpose16(t.src, *t.dst, t.rows, t.cols, s)
-                                  : hipMemcpyAsync(*t.dst, t.src, wbytes, hipMemcpyDeviceToDevice, s);
-            if (e == hipSuccess && t.to_f16 && cfg->dtype == EL_BF16) e = launch_bf16_to_f16(*t.dst, *t.dst, nel, s);
-            if (e != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
-        }
     }
 
     *out_ctx = c;
@@ -391,7 +396,7 @@ el_status el_attn_check_step_operands(const el_attn_config *cfg, int32_t mfma, c
 
 int32_t el_attn_uses_mfma(const el_attn_ctx *ctx)
 {
-    return (ctx && ctx->use_mfma_core && !(ctx->cfg.flags & EL_FLAG_FORCE_GENERIC)) ? 1 : 0;
+    return (ctx && ctx->use_mfma_core) ? 1 : 0;
 }
 
 el_status el_attn_expand_query(el_attn_ctx *ctx, const void *queries, float *elq_out,
@@ -423,9 +428,7 @@ el_status el_attn_decode_step(el_attn_ctx *ctx, const void *H, int64_t H_batch_s
     forget_foreign_errors();
     const Workspace ws = carve(ctx);
     const Problem p = make_problem(ctx, H, H_batch_stride, lengths, queries, out, B, beam, n);
-    StepFormats fmt;
-    if ((st = run_a1_to_a6(ctx, p, ws, s, &fmt)) != EL_OK) return st;
-    return run_a7(ctx, p, ws, ctx->w.c_out, s);
+    return run_step(ctx, p, ws, s);
 }
 
 el_status el_attn_decode_step_static(el_attn_ctx *ctx, const void *H, int64_t H_batch_stride,
@@ -446,9 +449,7 @@ el_status el_attn_decode_step_static(el_attn_ctx *ctx, const void *H, int64_t H_
     forget_foreign_errors();
     const Workspace ws = carve_from(base, L);
     const Problem p = make_problem(ctx, H, H_batch_stride, lengths, queries, out, B, beam, n);
-    StepFormats fmt;
-    if ((st = run_a1_to_a6(ctx, p, ws, s, &fmt)) != EL_OK) return st;
-    return run_a7(ctx, p, ws, ctx->w.c_out, s);
+    return run_step(ctx, p, ws, s);
 }
 
 el_status el_attn_decode_segment(el_attn_ctx *ctx, const void *H, int64_t H_batch_stride,

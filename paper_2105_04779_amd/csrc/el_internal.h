@@ -163,10 +163,10 @@ struct Workspace {
     int slots;      // pieces Xp and ML have room for (batch elements the workspace was laid out for x kMaxParts)
 };
 
-struct Weights {    // library-owned copies in the storage dtype
-    void *Wq, *Wk, *Wv, *Wo, *bq;   // original layout (x . W form)
-    void *WqT;                      // (W^Q)^T in the storage dtype (16-bit dtypes only)
-    void *WkH, *WvT, *WoT;          // W^K, (W^V)^T, (W^O)^T in fp16 (converted from bf16 when needed)
+struct Weights {    // library-owned copies; every product reads both operands along the contraction, hence the transposes
+    void *WqT, *Wk, *bq;            // (W^Q)^T and W^K as it is (a head's slice of a row is the contraction), storage dtype
+    void *WkH, *WvT, *WoT;          // MFMA projections: W^K, (W^V)^T, (W^O)^T in fp16 (converted from bf16 when needed)
+    void *WvTs, *WoTs;              // fp32-arithmetic projections: (W^V)^T, (W^O)^T in the storage dtype
     float *c_out;                   // [d_m] = b_o + b_v . W_o, fp32
     float *bk32, *bv32, *bo32;      // [h*d_k], [h*d_k], [d_m] in fp32 (zeros when absent): only the segment form reads them
 };
@@ -196,9 +196,11 @@ struct el_attn_ctx {
 namespace el {
 
 // generic (fp32 arithmetic) kernels -- generic_kernels.hip
-hipError_t launch_cout(const el_attn_ctx *ctx, const void *bv, const void *bo, hipStream_t s);
+hipError_t launch_cout(const el_attn_ctx *ctx, const void *WoT, const void *bv, const void *bo, hipStream_t s);   // WoT in the storage dtype
 hipError_t launch_qproj_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s);
 hipError_t launch_elq_generic(const el_attn_ctx *ctx, const Problem &p, const float *Qp, float *elq, hipStream_t s);
+bool scores_fit(const Problem &p);                    // the core through scores in memory applies; the next two are for the rest
+hipError_t launch_core_scores(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s);
 hipError_t launch_core_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int parts, hipStream_t s);
 hipError_t launch_merge_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int parts, int Rstride, hipStream_t s);
 hipError_t launch_vproj_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s);
@@ -262,7 +264,7 @@ hipError_t launch_merge_exp2(const el_attn_ctx *ctx, const Problem &p, const Wor
 
 // MFMA projection GEMMs -- gemm_mfma.hip
 bool gemm_mfma_supported(int dtype, int d_m, int d_k);
-hipError_t launch_transpose16(const void *src, void *dst, int rows, int cols, hipStream_t s);
+hipError_t launch_transpose(size_t elem, const void *src, void *dst, int rows, int cols, hipStream_t s);
 hipError_t launch_bf16_to_f16(const void *src, void *dst, size_t n, hipStream_t s);
 hipError_t launch_qproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, float scale, hipStream_t s);
 hipError_t launch_elq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int Rs, hipStream_t s);

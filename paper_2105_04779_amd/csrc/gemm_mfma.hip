@@ -388,10 +388,11 @@ hipError_t launch_bf16_to_f16(const void *src, void *dst, size_t n, hipStream_t 
     return hipGetLastError();
 }
 
-// Transpose a [rows, cols] matrix of 16-bit elements (prepare-time packing of W^Q, W^V, W^O).
-__global__ void k_transpose16(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int rows, int cols)
+// Transpose a [rows, cols] matrix of 16- or 32-bit elements (prepare-time packing of W^Q, W^V, W^O).
+template <typename E>
+__global__ void k_transpose(const E *__restrict__ src, E *__restrict__ dst, int rows, int cols)
 {
-    __shared__ uint16_t tile[32][33];
+    __shared__ E tile[32][33];
     const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
     for (int i = ty; i < 32; i += 8)
@@ -401,10 +402,11 @@ __global__ void k_transpose16(const uint16_t *__restrict__ src, uint16_t *__rest
         if (bx + i < cols && by + tx < rows) dst[(size_t)(bx + i) * rows + by + tx] = tile[tx][i];
 }
 
-hipError_t launch_transpose16(const void *src, void *dst, int rows, int cols, hipStream_t s)
+hipError_t launch_transpose(size_t elem, const void *src, void *dst, int rows, int cols, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_transpose16, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(256), 0, s,
-                       (const uint16_t *)src, (uint16_t *)dst, rows, cols);
+    const dim3 grid((cols + 31) / 32, (rows + 31) / 32), block(256);
+    if (elem == 2) hipLaunchKernelGGL(k_transpose<uint16_t>, grid, block, 0, s, (const uint16_t *)src, (uint16_t *)dst, rows, cols);
+    else hipLaunchKernelGGL(k_transpose<uint32_t>, grid, block, 0, s, (const uint32_t *)src, (uint32_t *)dst, rows, cols);
     return hipGetLastError();
 }
 

@@ -1,65 +1,193 @@
-// Plain fp32-arithmetic kernels for every step of the EL-attention decode step.
+// fp32-arithmetic kernels for every step of the EL-attention decode step.
 //
-// They cover every dtype and shape (the fp32 configuration runs on them alone) and are
-// the fallback wherever no MFMA kernel applies.  Arithmetic is fp32 fused multiply-add on
-// storage values widened exactly; nothing is rounded to the storage type in between.
+// They cover every dtype and shape (the fp32 configuration runs on them alone) and are the fallback wherever
+// no 16-bit MFMA kernel applies.  Storage values are widened exactly and every product and sum is fp32: the
+// contractions run on the fp32 matrix instruction (16x16x4: fp32 operands, fp32 accumulators, 64 FLOP a clock
+// and SIMD, twice the vector ALU without its operand traffic).  Weights are stored transposed at prepare time,
+// so every operand is contiguous along the contraction and a lane fetches four consecutive k at once: step j of
+// four instructions then contracts k = 16 s + 4 g + j over the lane groups g, the same permutation on both sides.
 //
 // Steps follow Algorithm 3's attention routine (appendix A) and Eq. 5 / Eq. 9:
 //   qproj  a1  Qp = (q W^Q + b^Q) / sqrt(d_k)
 //   elq    a2  EL-Q_i = Qp_i (W_i^K)^T                      rows r = i*beam + j
-//   core   a3-a5  scores against H, softmax over the valid prefix, weighted sum of H
-//   merge     log-sum-exp combination of key-range partials
+//   core   a3-a5  scores against H (k_gemm_f32 per batch element), softmax over the valid prefix and weighted
+//                 sum of H (k_sum_f32)
 //   vproj  a6  A_i = X_i W_i^V
 //   oproj  a7  out = A W^O + c_out,  c_out = b^O + sum_i b_i^V W_i^O (Eq. 8/9)
 #include "el_internal.h"
 
 namespace el {
 
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+
 constexpr int kBlock = 256;
-constexpr int kChunk = 512; // key positions scored per pass of the generic core
+constexpr int kGemmWaves = 8;
+constexpr int kChunk = 512; // key positions scored per pass of k_core_generic and of k_sum_f32
+
+static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// four consecutive elements, widened
+__device__ __forceinline__ f4 load4(const float *p) { return *(const f4 *)p; }
+__device__ __forceinline__ f4 load4(const bf16_t *p)
+{
+    const u2v u = *(const u2v *)p;
+    return f4{__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u), __uint_as_float(u[1] << 16), __uint_as_float(u[1] & 0xffff0000u)};
+}
+__device__ __forceinline__ f4 load4(const f16_t *p)
+{
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    const h4 h = *(const h4 *)p;
+    return f4{(float)h[0], (float)h[1], (float)h[2], (float)h[3]};
+}
+// elements k .. k + 3 of a row of K, zero where they do not exist.  VEC: K and the row's address are multiples of four elements.
+template <bool VEC, typename T>
+__device__ __forceinline__ f4 load_k4(const T *row, int k, int K)
+{
+    if (VEC) { if (k < K) return load4(row + k); return f4{0.f, 0.f, 0.f, 0.f}; }
+    f4 v = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (k + e < K) v[e] = to_f32(row[k + e]);
+    return v;
+}
+template <bool VEC, typename T>
+__device__ __forceinline__ f4 load_full4(const T *p)
+{
+    if (VEC) return load4(p);
+    return f4{to_f32(p[0]), to_f32(p[1]), to_f32(p[2]), to_f32(p[3])};
+}
 
 // ---------------------------------------------------------------------------------------------
+// c_out[d] = b^O[d] + sum_c b^V[c] W^O[c, d]: a wavefront per output, W^O transposed.
 template <typename T>
-__global__ void k_cout(const T *__restrict__ bv, const T *__restrict__ bo, const T *__restrict__ Wo,
-                       float *__restrict__ c_out, int hd, int d_m)
+__global__ void __launch_bounds__(kBlock)
+k_cout(const T *__restrict__ bv, const T *__restrict__ bo, const T *__restrict__ WoT, float *__restrict__ c_out, int hd, int d_m)
 {
-    int d = blockIdx.x * kBlock + threadIdx.x;
+    const int d = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), l = threadIdx.x & 63;
     if (d >= d_m) return;
-    float acc = bo ? to_f32(bo[d]) : 0.f;
+    float acc = 0.f;
     if (bv)
-        for (int c = 0; c < hd; ++c) acc = fmaf(to_f32(bv[c]), to_f32(Wo[(size_t)c * d_m + d]), acc);
-    c_out[d] = acc;
+        for (int c = l; c < hd; c += 64) acc = fmaf(to_f32(bv[c]), to_f32(WoT[(size_t)d * hd + c]), acc);
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if (l == 0) c_out[d] = acc + (bo ? to_f32(bo[d]) : 0.f);
 }
 
-// a1: Qp[row, c] = (sum_k q[row,k] Wq[k,c] + bq[c]) * scale
-template <typename T>
-__global__ void k_qproj(const T *__restrict__ q, const T *__restrict__ Wq, const T *__restrict__ bq,
-                        float *__restrict__ Qp, int d_m, int hd, float scale)
-{
-    int c = blockIdx.x * kBlock + threadIdx.x;
-    int row = blockIdx.y;
-    if (c >= hd) return;
-    const T *qr = q + (size_t)row * d_m;
-    float acc = 0.f;
-    for (int k = 0; k < d_m; ++k) acc = fmaf(to_f32(qr[k]), to_f32(Wq[(size_t)k * hd + c]), acc);
-    if (bq) acc += to_f32(bq[c]);
-    Qp[(size_t)row * hd + c] = acc * scale;
-}
+// ---------------------------------------------------------------------------------------------
+// C[m, n] = (sum_k A[m, k] Bt[n, k] + bias[n]) * scale, batched over z (a head, or a batch element for the
+// scores).  One workgroup owns (16 MT) x (16 NT) outputs; its eight wavefronts each take an eighth of k straight from
+// global memory into registers (consecutive slices, so both halves of a cache line go to one wavefront), four
+// 16-wide slices of both operands requested before the first is used (up to K = 512 the whole contraction is one
+// round trip), and add up through LDS.  Bound: memory latency at decode batch sizes, the fp32 matrix rate beyond.
+// 64 x 512 x 512: 5.4 us, 119 us for the kernel it replaces (one output per thread, a serial loop over k); the
+// scores of 16 x 32 rows over 300 positions, K = 512: 9.5 us.
+struct GemmF32 {
+    const void *A, *Bt;
+    void *C;
+    const void *bias;        // storage type, may be null
+    const float *bias32;     // may be null
+    const int32_t *lengths;  // scores: valid rows of Bt of element z (null elsewhere or: all N)
+    float scale;
+    int M, N, K;
+    int64_t lda, ldb, ldc;
+    int64_t za, zb, zc;      // element offsets per z
+    int x, R;                // for the row maps: logical row m of head z is row (m / x) R + z x + m % x
+    int map_a, map_c;
+    int use_lengths, vec_c;
+};
 
-// a2: ELQ[b, r=i*beam+j, d] = sum_c Qp[b*beam+j, i*d_k+c] * Wk[d, i*d_k+c]
-template <typename T>
-__global__ void k_elq(const float *__restrict__ Qp, const T *__restrict__ Wk, float *__restrict__ elq,
-                      int beam, int d_m, int d_k, int hd, int R)
+template <typename TA, typename TB, typename TO, bool VEC, int MT, int NT>
+__global__ void __launch_bounds__(64 * kGemmWaves)
+k_gemm_f32(const GemmF32 g)
 {
-    int d = blockIdx.x * kBlock + threadIdx.x;
-    int r = blockIdx.y, b = blockIdx.z;
-    if (d >= d_m) return;
-    int i = r / beam, j = r % beam;
-    const float *qp = Qp + ((size_t)b * beam + j) * hd + (size_t)i * d_k;
-    const T *wk = Wk + (size_t)d * hd + (size_t)i * d_k;
-    float acc = 0.f;
-    for (int c = 0; c < d_k; ++c) acc = fmaf(qp[c], to_f32(wk[c]), acc);
-    elq[((size_t)b * R + r) * d_m + d] = acc;
+    constexpr int NW = kGemmWaves, U = 4;
+    __shared__ f4 red[NW * MT * NT * 64];
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = l & 15, q = l >> 4, z = blockIdx.z;
+    const int n0 = blockIdx.x * (16 * NT), m0 = blockIdx.y * (16 * MT);
+    int N = g.N;
+    if (g.use_lengths) {
+        if (g.lengths) N = min(max(g.lengths[z], 1), N);
+        if (n0 >= N) return;
+    }
+    auto mapped = [&](int m) -> int64_t { return (int64_t)(m / g.x) * g.R + (int64_t)z * g.x + m % g.x; };
+    const TA *ap[MT];
+    const TB *bp[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const int m = min(m0 + 16 * i + r16, g.M - 1);
+        ap[i] = (const TA *)g.A + (g.map_a ? mapped(m) : (int64_t)m) * g.lda + z * g.za + 4 * q;
+    }
+#pragma unroll
+    for (int j = 0; j < NT; ++j) bp[j] = (const TB *)g.Bt + (int64_t)min(n0 + 16 * j + r16, N - 1) * g.ldb + z * g.zb + 4 * q;
+
+    f4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    // weights (or H) as the instruction's A operand: a lane ends up with four consecutive n of one m
+    auto product = [&](const f4 *a, const f4 *b) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = mfma4(b[j][e], a[i][e], acc[i][j]);
+    };
+    const int full = g.K >> 4, per = (full + NW - 1) / NW, s_end = min(full, (w + 1) * per);
+    for (int s0 = w * per; s0 < s_end; s0 += U) {
+        f4 a[U][MT], b[U][NT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= s_end) continue;                    // uniform
+            const int k = 16 * (s0 + u);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[u][i] = load_full4<VEC>(ap[i] + k);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[u][j] = load_full4<VEC>(bp[j] + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= s_end) continue;
+            product(a[u], b[u]);
+        }
+    }
+    if ((g.K & 15) && w == NW - 1) {                          // the slice that is not full
+        f4 a[MT], b[NT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) a[i] = load_k4<VEC>(ap[i] - 4 * q, 16 * full + 4 * q, g.K);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[j] = load_k4<VEC>(bp[j] - 4 * q, 16 * full + 4 * q, g.K);
+        product(a, b);
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) red[(w * MT * NT + i * NT + j) * 64 + l] = acc[i][j];
+    __syncthreads();
+    for (int tile = w; tile < MT * NT; tile += NW) {
+        f4 v = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NW; ++s) v += red[(s * MT * NT + tile) * 64 + l];
+        const int m = m0 + 16 * (tile / NT) + r16, n = n0 + 16 * (tile % NT) + 4 * q;
+        if (m >= g.M) continue;
+        TO *c = (TO *)g.C + (g.map_c ? mapped(m) : (int64_t)m) * g.ldc + z * g.zc + n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (n + e >= N) break;
+            if (g.bias) v[e] += to_f32(((const TB *)g.bias)[n + e]);
+            if (g.bias32) v[e] += g.bias32[n + e];
+            v[e] *= g.scale;
+        }
+        if (sizeof(TO) == 4 && g.vec_c && n + 4 <= N) *(f4 *)c = v;
+        else
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < N) from_f32(v[e], c + e);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -74,7 +202,130 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
-// a3-a5 for one (row r, key-range part p, batch element b) per workgroup.
+// a4 + a5: softmax of the scores S [B, R, ldS] over the valid prefix and the weighted sum of H, normalised:
+// Xn[b, r, d0 .. d0 + 63] for 16 rows r.  Every workgroup works its 16 rows' probabilities out for itself (R n
+// exponentials against the R n d_m / 8 products of a 64-column block) and keeps them in LDS, 512 positions at a
+// time; the wavefronts take every eighth 16-position slice.  The scores and the first slices of H are requested
+// together, before anything waits.  A lane fetches four consecutive columns of one row of H, so a load instruction
+// reads 4 rows x 256 contiguous bytes, and column c of the block is column c / 4 of accumulator c % 4.  Bound: memory
+// latency, then the fp32 matrix rate.  16 x 32 rows, 300 positions, d_m 512: 7.6 us; with the scores (above) 17 us
+// against the 125 us of the kernels with one row per workgroup and their merge.
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(512)
+k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int64_t h_stride, const int32_t *__restrict__ lengths,
+          int n, int d_m, int R, float *__restrict__ Xn, float *__restrict__ ML)
+{
+    constexpr int NW = 8, RW = 16 / NW, PS = kChunk + 4, U = 4, PL = kChunk / 64;
+    __shared__ __attribute__((aligned(16))) float Ps[16 * PS];
+    __shared__ float Li[16];
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = l & 15, q = l >> 4;
+    const int d0 = blockIdx.x * 64, r0 = blockIdx.y * 16, b = blockIdx.z;
+    int len = lengths ? lengths[b] : n;
+    len = min(max(len, 1), n);
+    const T *Hb = H + (size_t)b * h_stride;
+    const float *srow[RW];
+#pragma unroll
+    for (int i = 0; i < RW; ++i) srow[i] = S + ((size_t)b * R + min(r0 + RW * w + i, R - 1)) * ldS;
+    // the scores of one chunk of this wavefront's four rows, all requested together
+    float sv[RW][PL];
+    auto load_scores = [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+#pragma unroll
+            for (int k = 0; k < PL; ++k) sv[i][k] = c0 + 64 * k + l < len ? srow[i][c0 + 64 * k + l] : -INFINITY;
+    };
+    // a slice of H per wavefront in flight: U slices of 16 positions
+    const int col = d0 + 4 * r16;
+    f4 h[U][4];
+    auto load_h = [&](int c0, int s0, int slices) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + NW * u >= slices) continue;               // uniform
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // a position that does not exist has probability zero: any valid row stands in for it
+                const int t = min(c0 + 16 * (s0 + NW * u) + 4 * q + j, len - 1);
+                h[u][j] = load_k4<VEC>(Hb + (size_t)t * d_m, col, d_m);
+            }
+        }
+    };
+    load_scores(0);
+    load_h(0, w, (min(kChunk, len) + 15) >> 4);
+    float mx[RW], sum[RW];
+#pragma unroll
+    for (int i = 0; i < RW; ++i) { mx[i] = -INFINITY; sum[i] = 0.f; }
+    auto fold_max = [&]() {
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+#pragma unroll
+            for (int k = 0; k < PL; ++k) mx[i] = fmaxf(mx[i], sv[i][k]);
+    };
+    fold_max();
+    if (len > kChunk) {
+        for (int c0 = kChunk; c0 < len; c0 += kChunk) { load_scores(c0); fold_max(); }
+        load_scores(0);
+    }
+#pragma unroll
+    for (int i = 0; i < RW; ++i) mx[i] = wave_max(mx[i]);
+    f4 acc[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < len; c0 += kChunk) {
+        const int slices = (min(kChunk, len - c0) + 15) >> 4;
+        if (c0 > 0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+#pragma unroll
+            for (int k = 0; k < PL; ++k) {
+                const float p = expf(sv[i][k] - mx[i]);       // zero where the position does not exist
+                sum[i] += p;
+                Ps[(RW * w + i) * PS + 64 * k + l] = p;
+            }
+        __syncthreads();
+        if (c0 + kChunk < len) load_scores(c0 + kChunk);
+        for (int s0 = w; s0 < slices; s0 += NW * U) {
+            if (c0 > 0 || s0 > w) load_h(c0, s0, slices);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (s0 + NW * u >= slices) continue;
+                const f4 p = *(const f4 *)(Ps + r16 * PS + 16 * (s0 + NW * u) + 4 * q);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[e] = mfma4(p[j], h[u][j][e], acc[e]);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+        const float s = wave_sum(sum[i]);
+        const int r = r0 + RW * w + i;
+        if (l == 0) {
+            Li[RW * w + i] = s;
+            if (d0 == 0 && r < R) { ML[((size_t)b * R + r) * 2] = mx[i]; ML[((size_t)b * R + r) * 2 + 1] = s; }
+        }
+    }
+    __syncthreads();                                          // the probabilities are no longer needed
+    f4 *red = (f4 *)Ps;                                       // [wavefront][row][16 quads]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[(w * 16 + 4 * q + i) * 16 + r16] = f4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
+    __syncthreads();
+    const int row = threadIdx.x >> 4, quad = threadIdx.x & 15, d = d0 + 4 * quad;
+    if (row >= 16 || r0 + row >= R) return;
+    f4 v = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NW; ++s) v += red[(s * 16 + row) * 16 + quad];
+    const float inv = Li[row];
+    float *xo = Xn + ((size_t)b * R + r0 + row) * d_m + d;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (d + e < d_m) xo[e] = v[e] / inv;
+}
+
+// ---------------------------------------------------------------------------------------------
+// a3-a5 without scores in memory, for keys so long next to d_m that the scores do not fit the workspace
+// (n > 8 d_m): one (row r, key-range part p, batch element b) per workgroup, on the vector ALU.
 // Writes the un-normalised weighted sum, and the running max / sum of its range.
 template <typename T, int MAXD>
 __global__ void __launch_bounds__(kBlock)
@@ -180,35 +431,6 @@ __global__ void k_merge(const float *__restrict__ Xp, const float *__restrict__ 
     Xn[((size_t)b * R + r) * d_m + d] = num / den;
 }
 
-// a6: A[b*beam+j, i*d_k+c] = sum_d Xn[b, i*beam+j, d] * Wv[d, i*d_k+c]
-template <typename T>
-__global__ void k_vproj(const float *__restrict__ Xn, const T *__restrict__ Wv, float *__restrict__ A,
-                        int beam, int d_m, int d_k, int hd, int R)
-{
-    const int cg = blockIdx.x * kBlock + threadIdx.x;
-    const int row = blockIdx.y;
-    if (cg >= hd) return;
-    const int b = row / beam, j = row % beam, i = cg / d_k;
-    const float *x = Xn + ((size_t)b * R + (size_t)i * beam + j) * d_m;
-    float acc = 0.f;
-    for (int d = 0; d < d_m; ++d) acc = fmaf(x[d], to_f32(Wv[(size_t)d * hd + cg]), acc);
-    A[(size_t)row * hd + cg] = acc;
-}
-
-// a7: out[row, d] = sum_c A[row,c] * Wo[c,d] + c_out[d]
-template <typename T, typename TO>
-__global__ void k_oproj(const float *__restrict__ A, const T *__restrict__ Wo, const float *__restrict__ c_out,
-                        TO *__restrict__ out, int d_m, int hd)
-{
-    const int d = blockIdx.x * kBlock + threadIdx.x;
-    const int row = blockIdx.y;
-    if (d >= d_m) return;
-    const float *a = A + (size_t)row * hd;
-    float acc = 0.f;
-    for (int c = 0; c < hd; ++c) acc = fmaf(a[c], to_f32(Wo[(size_t)c * d_m + d]), acc);
-    from_f32(acc + c_out[d], out + (size_t)row * d_m + d);
-}
-
 // ---------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------
@@ -219,32 +441,87 @@ __global__ void k_oproj(const float *__restrict__ A, const T *__restrict__ Wo, c
     default:     { using T = bf16_t; __VA_ARGS__; } break;                           \
     }
 
-static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
-hipError_t launch_cout(const el_attn_ctx *ctx, const void *bv, const void *bo, hipStream_t s)
+hipError_t launch_cout(const el_attn_ctx *ctx, const void *WoT, const void *bv, const void *bo, hipStream_t s)
 {
     const int d_m = ctx->cfg.d_model, hd = ctx->hd;
     EL_DISPATCH_DTYPE(ctx->cfg.dtype,
-        hipLaunchKernelGGL((k_cout<T>), dim3(cdiv(d_m, kBlock)), dim3(kBlock), 0, s,
-                           (const T *)bv, (const T *)bo, (const T *)ctx->w.Wo, ctx->w.c_out, hd, d_m));
+        hipLaunchKernelGGL((k_cout<T>), dim3(cdiv(d_m, kBlock / 64)), dim3(kBlock), 0, s,
+                           (const T *)bv, (const T *)bo, (const T *)WoT, ctx->w.c_out, hd, d_m));
     return hipGetLastError();
+}
+
+// 32 x 32 outputs per workgroup where that still leaves two workgroups per compute unit of a full chip, 32 x 16
+// where it leaves one (less operand traffic); 16 x 16 below, where workgroups are what is missing.
+template <typename TA, typename TB, typename TO>
+static hipError_t launch_gemm_f32(const GemmF32 &g, int batches, hipStream_t s)
+{
+    auto four = [](const void *p, size_t es) { return ((uintptr_t)p & (4 * es - 1)) == 0; };
+    const bool vec = g.K % 4 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.za % 4 == 0 && g.zb % 4 == 0 &&
+                     four(g.A, sizeof(TA)) && four(g.Bt, sizeof(TB));
+    const int tm = g.M > 16 && (long)cdiv(g.N, 16) * cdiv(g.M, 32) * batches >= 256 ? 2 : 1;
+    const int tn = tm == 2 && (long)cdiv(g.N, 32) * cdiv(g.M, 32) * batches >= 512 ? 2 : 1;
+    const dim3 grid(cdiv(g.N, 16 * tn), cdiv(g.M, 16 * tm), batches), block(64 * kGemmWaves);
+#define EL_GEMM_F32(V, MT, NT) hipLaunchKernelGGL((k_gemm_f32<TA, TB, TO, V, MT, NT>), grid, block, 0, s, g)
+    if (tn == 2) { if (vec) EL_GEMM_F32(true, 2, 2); else EL_GEMM_F32(false, 2, 2); }
+    else if (tm == 2) { if (vec) EL_GEMM_F32(true, 2, 1); else EL_GEMM_F32(false, 2, 1); }
+    else { if (vec) EL_GEMM_F32(true, 1, 1); else EL_GEMM_F32(false, 1, 1); }
+#undef EL_GEMM_F32
+    return hipGetLastError();
+}
+
+static GemmF32 gemm_args(const Problem &p, const void *A, const void *Bt, void *C, int N, int K)
+{
+    GemmF32 g{};
+    g.A = A; g.Bt = Bt; g.C = C; g.scale = 1.0f;
+    g.M = p.B * p.beam; g.N = N; g.K = K;
+    g.lda = K; g.ldb = K; g.ldc = N;
+    g.x = p.beam; g.R = p.R;
+    g.vec_c = N % 4 == 0 && ((uintptr_t)C & 15) == 0;
+    return g;
 }
 
 hipError_t launch_qproj_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s)
 {
-    const float scale = 1.0f / sqrtf((float)p.d_k);
-    EL_DISPATCH_DTYPE(p.dtype,
-        hipLaunchKernelGGL((k_qproj<T>), dim3(cdiv(p.hd, kBlock), p.B * p.beam), dim3(kBlock), 0, s,
-                           (const T *)p.queries, (const T *)ctx->w.Wq, (const T *)ctx->w.bq, ws.Qp,
-                           p.d_m, p.hd, scale));
-    return hipGetLastError();
+    GemmF32 g = gemm_args(p, p.queries, ctx->w.WqT, ws.Qp, p.hd, p.d_m);
+    g.bias = ctx->w.bq;
+    g.scale = 1.0f / sqrtf((float)p.d_k);
+    EL_DISPATCH_DTYPE(p.dtype, return (launch_gemm_f32<T, T, float>(g, 1, s)));
+    return hipErrorUnknown;
 }
 
 hipError_t launch_elq_generic(const el_attn_ctx *ctx, const Problem &p, const float *Qp, float *elq, hipStream_t s)
 {
+    GemmF32 g = gemm_args(p, Qp, ctx->w.Wk, elq, p.d_m, p.d_k);
+    g.lda = p.hd; g.za = p.d_k; g.ldb = p.hd; g.zb = p.d_k; g.map_c = 1;
+    EL_DISPATCH_DTYPE(p.dtype, return (launch_gemm_f32<float, T, float>(g, p.heads, s)));
+    return hipErrorUnknown;
+}
+
+// The scores of a step take R x round_up(n, 4) floats per batch element of the region the key-range partials have
+// (8 x R64 x d_m floats).
+bool scores_fit(const Problem &p)
+{
+    return (int64_t)p.R * ((p.n + 3) / 4 * 4) <= (int64_t)kMaxParts * ((p.R + 63) / 64 * 64) * p.d_m;
+}
+
+// a3-a5 through the scores in memory; Xn normalised, one piece of statistics per row
+hipError_t launch_core_scores(const el_attn_ctx *, const Problem &p, const Workspace &ws, hipStream_t s)
+{
+    const int64_t ldS = (p.n + 3) / 4 * 4;
+    GemmF32 g = gemm_args(p, ws.ELQ, p.H, ws.Xp, p.n, p.d_m);
+    g.M = p.R; g.ldc = ldS; g.za = (int64_t)p.R * p.d_m; g.zb = p.H_batch_stride; g.zc = (int64_t)p.R * ldS;
+    g.lengths = p.lengths; g.use_lengths = 1; g.vec_c = 1;
+    hipError_t e = hipErrorUnknown;
+    EL_DISPATCH_DTYPE(p.dtype, e = (launch_gemm_f32<float, T, float>(g, p.B, s)));
+    if (e != hipSuccess) return e;
+    const dim3 grid(cdiv(p.d_m, 64), cdiv(p.R, 16), p.B), block(512);
+    const size_t es = dtype_size(p.dtype);
+    const bool vec = p.d_m % 4 == 0 && p.H_batch_stride % 4 == 0 && ((uintptr_t)p.H & (4 * es - 1)) == 0;
     EL_DISPATCH_DTYPE(p.dtype,
-        hipLaunchKernelGGL((k_elq<T>), dim3(cdiv(p.d_m, kBlock), p.R, p.B), dim3(kBlock), 0, s,
-                           Qp, (const T *)ctx->w.Wk, elq, p.beam, p.d_m, p.d_k, p.hd, p.R));
+        if (vec) hipLaunchKernelGGL((k_sum_f32<T, true>), grid, block, 0, s, (const float *)ws.Xp, ldS, (const T *)p.H, p.H_batch_stride,
+                                    p.lengths, p.n, p.d_m, p.R, ws.Xn, ws.ML);
+        else hipLaunchKernelGGL((k_sum_f32<T, false>), grid, block, 0, s, (const float *)ws.Xp, ldS, (const T *)p.H, p.H_batch_stride,
+                                p.lengths, p.n, p.d_m, p.R, ws.Xn, ws.ML));
     return hipGetLastError();
 }
 
@@ -284,23 +561,20 @@ hipError_t launch_merge_generic(const el_attn_ctx *, const Problem &p, const Wor
 
 hipError_t launch_vproj_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s)
 {
-    EL_DISPATCH_DTYPE(p.dtype,
-        hipLaunchKernelGGL((k_vproj<T>), dim3(cdiv(p.hd, kBlock), p.B * p.beam), dim3(kBlock), 0, s,
-                           (const float *)ws.Xn, (const T *)ctx->w.Wv, ws.A, p.beam, p.d_m, p.d_k, p.hd, p.R));
-    return hipGetLastError();
+    GemmF32 g = gemm_args(p, ws.Xn, ctx->w.WvTs, ws.A, p.d_k, p.d_m);
+    g.map_a = 1; g.zb = (int64_t)p.d_k * p.d_m; g.ldc = p.hd; g.zc = p.d_k;
+    EL_DISPATCH_DTYPE(p.dtype, return (launch_gemm_f32<float, T, float>(g, p.heads, s)));
+    return hipErrorUnknown;
 }
 
 hipError_t launch_oproj_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const float *bias32, hipStream_t s)
 {
-    const dim3 grid(cdiv(p.d_m, kBlock), p.B * p.beam), block(kBlock);
+    GemmF32 g = gemm_args(p, ws.A, ctx->w.WoTs, p.out, p.d_m, p.hd);
+    g.bias32 = bias32;
     EL_DISPATCH_DTYPE(p.dtype,
-        if (p.out_dtype == EL_F32)
-            hipLaunchKernelGGL((k_oproj<T, float>), grid, block, 0, s, (const float *)ws.A, (const T *)ctx->w.Wo,
-                               bias32, (float *)p.out, p.d_m, p.hd);
-        else
-            hipLaunchKernelGGL((k_oproj<T, T>), grid, block, 0, s, (const float *)ws.A, (const T *)ctx->w.Wo,
-                               bias32, (T *)p.out, p.d_m, p.hd));
-    return hipGetLastError();
+        if (p.out_dtype == EL_F32) return (launch_gemm_f32<float, T, float>(g, 1, s));
+        else return (launch_gemm_f32<float, T, T>(g, 1, s)));
+    return hipErrorUnknown;
 }
 
 // ---------------------------------------------------------------------------------------------

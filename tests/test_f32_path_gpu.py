@@ -1,0 +1,75 @@
+"""GPU parity of the fp32-arithmetic path at the sizes where its kernels change form: contraction lengths that are no
+multiple of 16 or of 4, operands aligned to one element only, more positions than one chunk of the softmax, keys too
+long for scores in memory, the three tile sizes of the products, narrow layers."""
+import numpy as np
+import pytest
+
+from paper_2105_04779_amd import workloads as wl
+from helpers import TOL, gpu_out, make_layer, oracle_out, record, rel_err, to_device
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, B, beam, heads, d_m, d_k, n, lens
+    ("f32", 2, 3, 3, 30, 10, 37, [37, 1]),               # nothing divides anything
+    ("f32", 3, 2, 5, 100, 20, 61, [61, 16, 17]),         # multiples of 4, not of 16
+    ("f32", 2, 4, 5, 320, 64, 1100, [1100, 513]),        # three chunks of 512 positions; a chunk of one position
+    ("f32", 2, 16, 4, 64, 16, 600, [600, 599]),          # n > 8 d_m with 64 rows: no room for the scores
+    ("f32", 40, 4, 8, 512, 64, 40, None),                # 160 rows: the larger tiles
+    ("bf16", 2, 3, 4, 256, 64, 50, [50, 33]),            # 16-bit storage on this path
+    ("f16", 2, 2, 6, 96, 16, 21, [21, 4]),
+    # narrow layers: row tiles of 1 to 4 with and without padding rows, both widths, both head sizes, one position
+    ("f32", 3, 16, 4, 64, 16, 31, [31, 16, 1]),
+    ("f32", 2, 5, 4, 64, 16, 64, [64, 63]),
+    ("f32", 2, 9, 2, 128, 64, 100, [100, 3]),
+    ("f32", 2, 16, 2, 128, 64, 97, [97, 96]),
+    ("f32", 1, 1, 1, 128, 128, 1, [1]),
+    ("f32", 2, 6, 8, 128, 16, 80, [80, 47]),
+    ("bf16", 2, 3, 4, 64, 16, 40, [40, 7]),
+    ("f16", 2, 4, 2, 128, 64, 33, [33, 32]),
+]
+
+
+@pytest.mark.parametrize("dtype,B,beam,heads,d_m,d_k,n,lens", CASES)
+def test_fp32_arithmetic_path(dtype, B, beam, heads, d_m, d_k, n, lens):
+    w = wl.custom(f"f32path_{dtype}_{heads}x{beam}_{d_m}_{n}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=d_k,
+                  n=n, len_lo=1, len_hi=n, index=90)
+    W = wl.weights(w)
+    H, Q, L = wl.batch(w, poison=False)
+    L = L if lens is None else np.asarray(lens, dtype=np.int32)
+    ref = oracle_out(w, W, H, Q, L)
+    for b in range(B):
+        H[b, L[b]:] = np.nan
+    layer = make_layer(w, W)
+    assert not layer.uses_mfma
+    err = rel_err(gpu_out(layer, w, H, Q, L), ref)
+    record(f"{w.name}: err={err:.3e}")
+    # 16-bit storage is widened exactly and every product and sum is fp32, so the fp32 bar holds for it as well
+    assert err <= TOL["f32"]
+    layer.close()
+
+
+@pytest.mark.parametrize("d_m,heads", [(64, 4), (320, 5)])
+def test_operands_aligned_to_one_element(d_m, heads):
+    """H, queries and out one element past a 16-byte boundary, H with a batch stride that is no multiple of four."""
+    import torch
+    w = wl.custom(f"unaligned_{d_m}", dtype="f32", B=2, beam=3, heads=heads, d_m=d_m, d_k=d_m // heads, n=45, index=91)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w)
+    L = np.asarray([45, 18], dtype=np.int32)
+    ref = oracle_out(w, W, H, Q, L)
+    stride = w.n * w.d_m + 3
+    buf = torch.full((1 + w.B * stride,), float("nan"), device="cuda")
+    Hv = torch.as_strided(buf, (w.B, w.n, w.d_m), (stride, w.d_m, 1), 1)
+    Hv.copy_(to_device(H, "f32"))
+    qbuf = torch.empty(1 + Q.size, device="cuda")
+    Qv = qbuf[1:].view(w.B, w.beam, w.d_m)
+    Qv.copy_(to_device(Q, "f32"))
+    obuf = torch.full((1 + Q.size + 1,), 7.0, device="cuda")
+    out = obuf[1:-1].view(w.B, w.beam, w.d_m)
+    layer = make_layer(w, W)
+    layer.decode_step(Hv, torch.from_numpy(L).cuda(), Qv, out=out)
+    torch.cuda.synchronize()
+    assert float(obuf[0]) == 7.0 and float(obuf[-1]) == 7.0
+    assert rel_err(out.cpu().numpy(), ref) <= TOL["f32"]
+    layer.close()
