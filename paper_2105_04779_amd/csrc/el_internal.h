@@ -206,6 +206,9 @@ hipError_t launch_merge_generic(const el_attn_ctx *ctx, const Problem &p, const 
 hipError_t launch_vproj_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s);
 hipError_t launch_oproj_generic(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const float *bias32, hipStream_t s);
 hipError_t launch_vec_f32(int dtype, const void *src, float *dst, int n, hipStream_t s);
+// the whole step of a narrow layer in one launch -- small_step.hip
+bool small_step_applies(const Problem &p);
+hipError_t launch_small_step(const el_attn_ctx *ctx, const Problem &p, hipStream_t s);
 // segment form (decoder-only models): statistics + biased head outputs of one segment; merge of several
 struct SegFinishArgs {
     const void *A;            // [rows, hd] fp16 or fp32: the segment's normalised head outputs without b^V

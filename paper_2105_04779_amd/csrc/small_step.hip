@@ -1,0 +1,252 @@
+// The whole decode step (a1..a7 of Algorithm 3's attention routine) of a narrow fp32-arithmetic layer in ONE launch:
+// one workgroup of eight wavefronts per batch element, every intermediate in LDS.
+//
+// At d_m = 64 or 128 a layer's four weight matrices are 64 or 256 KB: a workgroup can read all of them for itself, and
+// does so before anything else (a wavefront keeps the fragments of its 16 output columns of every projection in
+// registers, up to 128 of them), so the step costs one round trip to memory plus six barriers.  As separate launches
+// every step of the chain pays a launch and a round trip of its own.  Arithmetic and rounding are those of
+// generic_kernels.hip: fp32 operands, fp32 products and sums (16x16x4 MFMA), four consecutive k per lane.
+// Measured, fp32, per call among others: 2 sentences x 2 beams, d_m 64, n 32: 23.5 us as the six launches, 8.5 us here;
+// d_m 128, beam 4, n 256: 28.9 against 23.6 us.
+#include "el_internal.h"
+
+namespace el {
+
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+
+constexpr int kSmallRows = 64;                          // heads * beam
+constexpr int kSmallScores = 64 * 260;                  // floats of the score matrix: rows padded to 16 x (n padded to 16, + 4)
+
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f4 load4(const float *p) { return *(const f4 *)p; }
+__device__ __forceinline__ f4 load4(const bf16_t *p)
+{
+    const u2v u = *(const u2v *)p;
+    return f4{__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u), __uint_as_float(u[1] << 16), __uint_as_float(u[1] & 0xffff0000u)};
+}
+__device__ __forceinline__ f4 load4(const f16_t *p)
+{
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    const h4 h = *(const h4 *)p;
+    return f4{(float)h[0], (float)h[1], (float)h[2], (float)h[3]};
+}
+
+struct SmallArgs {
+    const void *H, *queries, *WqT, *Wk, *WvT, *WoT, *bq;
+    const float *c_out;
+    void *out;
+    const int32_t *lengths;
+    int64_t h_stride;
+    int n, x, heads, d_k;
+    float scale;
+};
+
+} // namespace
+
+template <typename T, typename TO, int D>
+__global__ void __launch_bounds__(512)
+k_small_step(const SmallArgs a)
+{
+    constexpr int LD = D + 4;                           // row stride in LDS: 16 rows x 16 bytes reach all banks
+    constexpr int KS = D / 16;                          // 16-wide slices of k; also 16-column blocks of a projection
+    constexpr int CB = D / 64;
+    __shared__ __attribute__((aligned(16))) float Qp[16 * LD];          // projected queries; later the head outputs A
+    __shared__ __attribute__((aligned(16))) float Eq[kSmallRows * LD];  // expanded queries; later the weighted sums X
+    __shared__ __attribute__((aligned(16))) float Sc[kSmallScores];     // scores, then probabilities
+    __shared__ __attribute__((aligned(16))) float Pb[8 * 1024];         // partial weighted sums
+    __shared__ float Li[kSmallRows];
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = l & 15, q = l >> 4, b = blockIdx.x;
+    const int x = a.x, R = a.heads * x, RT = (R + 15) >> 4;
+    const bool mine = w < KS;                           // this wavefront has a block of projection columns: 16 w ..
+    const int ncol = 16 * w + 4 * q;                    // a lane ends up with four consecutive columns of one row
+
+    f4 wq[KS], wk[KS], wv[KS], wo[KS], aq[KS], hf[KS];
+    int len = a.lengths ? a.lengths[b] : a.n;
+    const T *Hb = (const T *)a.H + (size_t)b * a.h_stride;
+    if (mine) {
+        const size_t off = (size_t)(16 * w + r16) * D + 4 * q;
+        const T *qrow = (const T *)a.queries + ((size_t)b * x + min(r16, x - 1)) * D + 4 * q;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) { wq[s] = load4((const T *)a.WqT + off + 16 * s); aq[s] = load4(qrow + 16 * s); }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) wk[s] = load4((const T *)a.Wk + off + 16 * s);
+    }
+    len = min(max(len, 1), a.n);
+    const int tiles_t = (len + 15) >> 4, LS = 16 * tiles_t + 4;
+    auto load_h = [&](int tt) {
+        const T *hrow = Hb + (size_t)min(16 * tt + r16, len - 1) * D + 4 * q;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) hf[s] = load4(hrow + 16 * s);
+    };
+    if (w < tiles_t * RT) load_h(w / RT);
+    if (mine) {
+        const size_t off = (size_t)(16 * w + r16) * D + 4 * q;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) { wv[s] = load4((const T *)a.WvT + off + 16 * s); wo[s] = load4((const T *)a.WoT + off + 16 * s); }
+    }
+
+    // a1
+    if (mine) {
+        f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma4(wq[s][e], aq[s][e], acc);
+        if (a.bq) acc += load4((const T *)a.bq + ncol);
+        *(f4 *)(Qp + r16 * LD + ncol) = acc * a.scale;
+    }
+    __syncthreads();
+    // a2: head i contracts slices i d_k / 16 .. ; d_k is a multiple of 16
+    if (mine) {
+        f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+        int head = 0;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const f4 v = *(const f4 *)(Qp + r16 * LD + 16 * s + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma4(wk[s][e], v[e], acc);
+            if (16 * (s + 1) % a.d_k == 0) {            // uniform
+                if (r16 < x) *(f4 *)(Eq + (head * x + r16) * LD + ncol) = acc;
+                acc = f4{0.f, 0.f, 0.f, 0.f};
+                ++head;
+            }
+        }
+    }
+    __syncthreads();
+    // a3: tiles of 16 positions x 16 rows
+    for (int tile = w; tile < tiles_t * RT; tile += 8) {
+        const int tt = tile / RT, rt = tile - tt * RT;
+        if (tile != w) load_h(tt);
+        const float *e_row = Eq + min(16 * rt + r16, R - 1) * LD + 4 * q;
+        f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const f4 v = *(const f4 *)(e_row + 16 * s);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma4(hf[s][e], v[e], acc);
+        }
+        *(f4 *)(Sc + (16 * rt + r16) * LS + 16 * tt + 4 * q) = acc;
+    }
+    __syncthreads();
+    // a4: a wavefront per row
+    for (int r = w; r < R; r += 8) {
+        float *row = Sc + r * LS;
+        float m = -INFINITY, sum = 0.f;
+        for (int t = l; t < len; t += 64) m = fmaxf(m, row[t]);
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        for (int t = l; t < 16 * tiles_t; t += 64) {
+            const float p = t < len ? expf(row[t] - m) : 0.f;
+            sum += p;
+            row[t] = p;
+        }
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (l == 0) Li[r] = sum;
+    }
+    __syncthreads();
+    // a5: 16 rows x 64 columns per wavefront, the positions split over the wavefronts that share a tile
+    const int tiles = RT * CB, SP = 8 / tiles;           // RT <= 4, CB <= 2
+    if (w < tiles * SP) {
+        const int tile = w % tiles, sp = w / tiles, rt = tile / CB, d0 = (tile - rt * CB) * 64;
+        f4 acc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = sp; s0 < tiles_t; s0 += 2 * SP) {
+            f4 h[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    h[u][j] = load4(Hb + (size_t)min(16 * (s0 + u * SP) + 4 * q + j, len - 1) * D + d0 + 4 * r16);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (s0 + u * SP >= tiles_t) continue;    // uniform
+                const f4 p = *(const f4 *)(Sc + min(16 * rt + r16, R - 1) * LS + 16 * (s0 + u * SP) + 4 * q);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[e] = mfma4(p[j], h[u][j][e], acc[e]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *(f4 *)(Pb + ((w * 16) + 4 * q + i) * 64 + 4 * r16) = f4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < tiles * 256; i += 512) {
+        const int tile = i >> 8, row = (i >> 4) & 15, quad = i & 15, rt = tile / CB, r = 16 * rt + row;
+        if (r >= R) continue;
+        f4 v = f4{0.f, 0.f, 0.f, 0.f};
+        for (int sp = 0; sp < SP; ++sp) v += *(const f4 *)(Pb + ((sp * tiles + tile) * 16 + row) * 64 + 4 * quad);
+        *(f4 *)(Eq + r * LD + (tile - rt * CB) * 64 + 4 * quad) = v / Li[r];
+    }
+    __syncthreads();
+    // a6: the 16 columns of a wavefront belong to one head
+    if (mine) {
+        const int head = 16 * w / a.d_k;
+        const float *xr = Eq + (head * x + min(r16, x - 1)) * LD + 4 * q;
+        f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const f4 v = *(const f4 *)(xr + 16 * s);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma4(wv[s][e], v[e], acc);
+        }
+        *(f4 *)(Qp + r16 * LD + ncol) = acc;
+    }
+    __syncthreads();
+    // a7
+    if (mine) {
+        f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const f4 v = *(const f4 *)(Qp + r16 * LD + 16 * s + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma4(wo[s][e], v[e], acc);
+        }
+        if (r16 < x) {
+            TO *o = (TO *)a.out + ((size_t)b * x + r16) * D + ncol;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) from_f32(acc[e] + a.c_out[ncol + e], o + e);
+        }
+    }
+}
+
+// Where one workgroup per batch element is the faster form: the weights fit its registers (d_m 64 or 128, head sizes
+// that are whole 16-wide slices), at most 16 beams (one row tile), and its scores and weighted sums, R x n x d_m
+// products each on one compute unit, stay below what the separate launches need for their extra round trips: 2^19
+// (d_m 128, 16 rows, n 256) 23.6 against 28.9 us, 2^20 (d_m 64, 64 rows, n 256) 30.1 against 28.2 us.
+bool small_step_applies(const Problem &p)
+{
+    if ((p.d_m != 64 && p.d_m != 128) || p.d_k % 16 != 0 || p.beam > 16 || p.R > kSmallRows) return false;
+    const int64_t n16 = (p.n + 15) / 16 * 16, r16 = (p.R + 15) / 16 * 16;
+    if (r16 * (n16 + 4) > kSmallScores || r16 * n16 * p.d_m > (int64_t)1 << 19) return false;
+    const size_t four = 4 * dtype_size(p.dtype);         // operands are fetched four elements at a time
+    return p.H_batch_stride % 4 == 0 && ((uintptr_t)p.H & (four - 1)) == 0 && ((uintptr_t)p.queries & (four - 1)) == 0;
+}
+
+template <typename T, typename TO>
+static void launch_small_t(const SmallArgs &a, int d_m, int B, hipStream_t s)
+{
+    if (d_m == 64) hipLaunchKernelGGL((k_small_step<T, TO, 64>), dim3(B), dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((k_small_step<T, TO, 128>), dim3(B), dim3(512), 0, s, a);
+}
+
+hipError_t launch_small_step(const el_attn_ctx *ctx, const Problem &p, hipStream_t s)
+{
+    SmallArgs a;
+    a.H = p.H; a.queries = p.queries; a.WqT = ctx->w.WqT; a.Wk = ctx->w.Wk; a.WvT = ctx->w.WvTs; a.WoT = ctx->w.WoTs; a.bq = ctx->w.bq;
+    a.c_out = ctx->w.c_out; a.out = p.out; a.lengths = p.lengths; a.h_stride = p.H_batch_stride;
+    a.n = p.n; a.x = p.beam; a.heads = p.heads; a.d_k = p.d_k;
+    a.scale = 1.0f / sqrtf((float)p.d_k);
+    const bool f32_out = p.out_dtype == EL_F32;
+    if (p.dtype == EL_F32) launch_small_t<float, float>(a, p.d_m, p.B, s);
+    else if (p.dtype == EL_F16) { if (f32_out) launch_small_t<f16_t, float>(a, p.d_m, p.B, s); else launch_small_t<f16_t, f16_t>(a, p.d_m, p.B, s); }
+    else { if (f32_out) launch_small_t<bf16_t, float>(a, p.d_m, p.B, s); else launch_small_t<bf16_t, bf16_t>(a, p.d_m, p.B, s); }
+    return hipGetLastError();
+}
+
+} // namespace el

@@ -1,6 +1,6 @@
 """GPU parity of the fp32-arithmetic path at the sizes where its kernels change form: contraction lengths that are no
 multiple of 16 or of 4, operands aligned to one element only, more positions than one chunk of the softmax, keys too
-long for scores in memory, the three tile sizes of the products, narrow layers."""
+long for scores in memory, the three tile sizes of the products, and the one-launch step at its edges."""
 import numpy as np
 import pytest
 
@@ -18,7 +18,7 @@ CASES = [
     ("f32", 40, 4, 8, 512, 64, 40, None),                # 160 rows: the larger tiles
     ("bf16", 2, 3, 4, 256, 64, 50, [50, 33]),            # 16-bit storage on this path
     ("f16", 2, 2, 6, 96, 16, 21, [21, 4]),
-    # narrow layers: row tiles of 1 to 4 with and without padding rows, both widths, both head sizes, one position
+    # one launch: row tiles of 1 to 4 with and without padding rows, both widths, both head sizes, one position
     ("f32", 3, 16, 4, 64, 16, 31, [31, 16, 1]),
     ("f32", 2, 5, 4, 64, 16, 64, [64, 63]),
     ("f32", 2, 9, 2, 128, 64, 100, [100, 3]),
