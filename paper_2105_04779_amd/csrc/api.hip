@@ -87,7 +87,7 @@ Workspace carve(const el_attn_ctx *c) { return carve_from(c->ws_base, ws_layout(
 
 void free_weights(el_attn_ctx *c)
 {
-    void *ptrs[] = {c->w.WqT, c->w.Wk, c->w.bq, c->w.WkH, c->w.WvT, c->w.WoT, c->w.WvTs, c->w.WoTs, (void *)c->w.c_out,
+    void *ptrs[] = {c->w.WqT, c->w.Wk, c->w.bq, c->w.WkH, c->w.WvP, c->w.WoT, c->w.WvTs, c->w.WoTs, (void *)c->w.c_out,
                     (void *)c->w.bk32, (void *)c->w.bv32, (void *)c->w.bo32};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -318,7 +318,7 @@ el_status el_attn_prepare(const el_attn_config *cfg,
         {&c->w.WqT, Wq, wbytes, cfg->d_model, c->hd},
         {&c->w.Wk, Wk, wbytes, 0, 0},
         {&c->w.bq, bq, (size_t)c->hd * es, 0, 0},
-        {gemm ? &c->w.WvT : &c->w.WvTs, Wv, wbytes, cfg->d_model, c->hd},
+        {&c->w.WvTs, gemm ? nullptr : Wv, wbytes, cfg->d_model, c->hd},
         {gemm ? &c->w.WoT : &c->w.WoTs, Wo, wbytes, c->hd, cfg->d_model},
         {&c->w.WkH, gemm ? Wk : nullptr, wbytes, 0, 0},
     };
@@ -329,6 +329,10 @@ el_status el_attn_prepare(const el_attn_config *cfg,
                                     : hipMemcpyAsync(*t.dst, t.src, t.bytes, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
     }
+    if (gemm) {
+        if (hipMalloc(&c->w.WvP, wbytes) != hipSuccess) { free_weights(c); delete c; return EL_ERR_ALLOC; }
+        if (launch_pack_wv(cfg->dtype, Wv, c->w.WvP, cfg->d_model, c->hd, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
+    }
     if (hipMalloc((void **)&c->w.c_out, (size_t)cfg->d_model * sizeof(float)) != hipSuccess) {
         free_weights(c); delete c; return EL_ERR_ALLOC;
     }
@@ -336,7 +340,7 @@ el_status el_attn_prepare(const el_attn_config *cfg,
     // everything after a1 of the MFMA projections runs in fp16: bf16 weights of a2, a6, a7 are converted once here
     if (gemm && cfg->dtype == EL_BF16) {
         const size_t nel = (size_t)cfg->d_model * c->hd;
-        for (void *m : {c->w.WkH, c->w.WvT, c->w.WoT})
+        for (void *m : {c->w.WkH, c->w.WoT})
             if (launch_bf16_to_f16(m, m, nel, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
     }
     // fp32 copies of the three biases the segment form needs (b^K enters its statistics, Eq. 7)

@@ -6,7 +6,7 @@
 //   a1  Qp    = (q . W^Q + b^Q) * scale   k_gemm_slab  A = queries (storage dtype), Bt = (W^Q)^T (storage dtype)
 //   a2  ELQ_i = Qp_i . (W_i^K)^T          k_elq_slab   A = Qp (fp16),               Bt = W^K in fp16     per head
 //                                                      (result as a high + low pair of planes in the storage type)
-//   a6  A_i   = X_i . W_i^V               k_vproj_slab A = merge of the pieces,     Bt = (W^V)^T in fp16 per head
+//   a6  A_i   = X_i . W_i^V               k_vproj      A = merge of the pieces,     W^V in fp16 fragments per head
 //   a7  out   = A . W^O + c_out           k_gemm_slab  A = A (fp16),                Bt = (W^O)^T in fp16
 //
 // Storage-dtype operands enter the MFMA exactly (a1 runs in the storage type).  From a2 on everything
@@ -16,7 +16,7 @@
 //
 // k_gemm_slab: a workgroup stages 32 rows of A and 32 rows of Bt over the whole K in LDS with 1 KB
 // LDS-DMA pieces (full cache lines, every byte fetched once per workgroup), then its four wavefronts
-// split K.  k_vproj_slab: the same with the A rows built in LDS from the key-range partials.
+// split K.  k_vproj: weights and merged rows straight in registers, see there.
 // k_elq_slab: the weight slice stays in registers, operand fragments come straight from global memory
 // (a2: K = d_k is tiny).
 #include "el_internal.h"
@@ -41,12 +41,6 @@ struct GemmArgs {
     int lda, ldb, ldc;    // row strides in elements
     int x;                // beam: logical row m = b*x + j
     int c_rB;             // k_elq_slab: padded rows per batch element of the output (logical row m, head i -> row i * x + m % x of element m / x)
-    // k_vproj_slab: A points at the normalised fp16 pieces Xp [slot, Rs, d_m]; ML [slot, Rs, 2]; pm says which
-    // slots belong to a batch element, parts bounds their number
-    const float *ML;
-    PieceMap pm;
-    int parts, Rs;
-    int N_heads;          // k_vproj_slab: heads (the grid is one-dimensional, see the kernel)
 };
 
 template <bool BF> struct Frag;
@@ -176,203 +170,171 @@ k_gemm_slab(const GemmArgs g)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Merge of the key-range partials fused with a6 (A_i = X_i . W_i^V, Eq. 5 / Eq. 8), one workgroup
-// per (16 rows, head).  The head's 64 rows of (W^V)^T are fetched whole into LDS by LDS-DMA while
-// the workgroup builds its 16 merged rows there: each wavefront reads the partials of 4 rows
-// (full-row, coalesced), combines them with the log-sum-exp weights
+// Merge of the pieces fused with a6 (A_i = X_i . W_i^V, Eq. 5 / Eq. 8).  A workgroup of eight wavefronts owns
+// 16 NT of a head's 64 output columns for every `groups`-th tile of 16 rows; wavefront w contracts an eighth of
+// d_m.  Its weights sit in registers in the order the matrix instruction wants them (packed so at prepare time:
+// one load instruction = 1 contiguous KB), and so do its rows: a lane fetches the 16-byte fragments of its own row
+// from every piece and merges them with the log-sum-exp weights it works out for that row,
 //     X = sum_p (w_p l_p) Xhat_p / sum_p (w_p l_p),  w_p = 2^(m_p - M),
-// and stores the row in fp16, XOR-swizzled like the weights.  Then the four wavefronts split K,
-// add their 16 x 64 partial tiles through LDS, and wavefront w finishes columns [16w, 16w+16).
-template <int DM>
-__global__ void __launch_bounds__(256)
-k_vproj_slab(const GemmArgs g)
+// so nothing is exchanged before the products are: no staging, one barrier.  Up to four pieces are in flight at a
+// time; more are folded in with a running maximum.
+// Bound: memory latency in a chain of two (piece table, then statistics and pieces together), then the pieces'
+// bytes.  One column block per workgroup (NT = 1) where a head's four leave compute units idle: the pieces are then
+// read four times, out of L2.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup
+// per 16 rows, the 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024:
+// 38.9 -> 23.0 us; 512 rows, one piece each: 19.7 -> 10.2; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 10.0;
+// 4 rows: 8.6 -> 5.4.
+struct VprojArgs {
+    const u4 *Wp;          // (W^V) in fragments: [head][k / 32][column / 16 % 4][lane]
+    const f16_t *Xp;       // normalised fp16 pieces [slot, Rs, d_m]
+    const float *ML;       // [slot, Rs, 2]
+    f16_t *A;              // [M, heads * 64]
+    PieceMap pm;
+    int M, x, heads, Rs, groups;
+};
+
+template <int DM, int NT>
+__global__ void __launch_bounds__(512)
+k_vproj(const VprojArgs a)
 {
-    constexpr int ROWB = DM * 2;
-    constexpr int A_BYTES = 16 * ROWB, B_BYTES = 64 * ROWB;
-    __shared__ __attribute__((aligned(1024))) char S[A_BYTES + B_BYTES];
-    const int tid = threadIdx.x, l = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = l & 15, q4 = l >> 4;
+    constexpr int KS = DM / 256;                         // 32-wide slices of k per wavefront
+    constexpr int PC = 4;                                // pieces in flight
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    __shared__ f4 red[2][8 * NT * 64];
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = l & 15, q = l >> 4;
     // Workgroup ids that differ by a multiple of 8 share an XCD and its L2.  Heads are dealt out so that an XCD
     // works on as few of them as possible (heads / 8 when that divides): it then pulls only those heads' weights
     // from memory, once, instead of every XCD pulling all of W^V.
-    int m0, head;
+    constexpr int NB = 4 / NT;                           // column blocks of a head
+    int head, nb, group;
     {
-        const int heads = g.N_heads, xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-        const int hp = (heads + 7) >> 3;                 // heads per XCD
-        head = xcd * hp + j % hp;
-        m0 = (j / hp) * 16;
-        if (head >= heads || m0 >= g.M) return;
+        const int xcd = blockIdx.x & 7, hp = (a.heads + 7) >> 3;
+        int j = blockIdx.x >> 3;
+        head = xcd * hp + j % hp; j /= hp;
+        nb = j % NB; group = j / NB;
+        if (head >= a.heads) return;
     }
-    const unsigned s_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)S;
-
-    // Order of the requests: the piece table first (a few scalars; the answer arrives while the first half of
-    // the weights is being requested), then half of the weights, then the statistics and the partial rows
-    // (which still have arithmetic ahead of them), then the rest of the weights (which go straight to LDS).
-    int e_tot = 0, e_lo[4], e_hi[4], b_of[4];
+    int e_tot = 0;
+    if (a.pm.E) e_tot = a.pm.E[a.pm.B];
+    const int tiles = (a.M + 15) >> 4;
+    auto row_of = [&](int tile, int &b, int &j) { const int m = min(16 * tile + r16, a.M - 1); b = m / a.x; j = m - b * a.x; };
+    int b, j, E_b = 0, E_b1 = 0;
+    row_of(group, b, j);
+    if (a.pm.E) { E_b = a.pm.E[b]; E_b1 = a.pm.E[b + 1]; }
+    u4 wv[KS][NT];
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-        b_of[ii] = __builtin_amdgcn_readfirstlane(min(m0 + 4 * w + ii, g.M - 1) / g.x);
-        e_lo[ii] = e_hi[ii] = 0;
-    }
-    if (g.pm.E) {
-        e_tot = g.pm.E[g.pm.B];
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int ii = 0; ii < 4; ++ii) { e_lo[ii] = g.pm.E[b_of[ii]]; e_hi[ii] = g.pm.E[b_of[ii] + 1]; }
-    }
-    // ---- weights of this head: rows 16w..16w+15 of its 64, straight into LDS ----
-    auto weight_rows = [&](int i0, int i1) {
-        if (ROWB == 1536) {                              // 1.5 KB rows: the rows as one block, see k_gemm_slab
-            const char *sbase = (const char *)g.Bt + (size_t)(head * 64 + 16 * w + i0) * g.ldb * 2;
+        for (int t = 0; t < NT; ++t)
+            wv[s][t] = a.Wp[(((size_t)head * (DM / 32) + KS * w + s) * 4 + nb * NT + t) * 64 + l];
+    const PieceCut cut = piece_cut(a.pm, e_tot);
+    int parity = 0;
+    for (int tile = group; tile < tiles; tile += a.groups) {
+        int slot0, np;
+        piece_range(a.pm, cut, b, E_b, E_b1, slot0, np);
+        const size_t row0 = (size_t)slot0 * a.Rs + head * a.x + j;
+        int np_max = np;                                 // most pieces among the 16 rows (uniform)
 #pragma unroll
-            for (int j = 0; j < (i1 - i0) * 3 / 2; ++j) {
-                const int pz = 64 * j + l, r = pz / 96, q = pz - 96 * r;
-                dma_piece(s_lds + A_BYTES + (16 * w + i0) * ROWB + 1024 * j,
-                          (unsigned)(r * g.ldb * 2 + ((q ^ row_swizzle(i0 + r)) << 4)), sbase);
+        for (int o = 1; o < 16; o <<= 1) np_max = max(np_max, __shfl_xor(np_max, o, 64));
+        np_max = __builtin_amdgcn_readfirstlane(np_max);
+        float v[KS][8], m_run = -INFINITY, den = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[s][e] = 0.f;
+        for (int p0 = 0; p0 < np_max; p0 += PC) {
+            f2 ml[PC];
+            h8 xv[PC][KS];
+#pragma unroll
+            for (int p = 0; p < PC; ++p) {
+                if (p0 + p >= np_max) { ml[p] = f2{0.f, 0.f}; continue; }           // uniform
+                const size_t row = row0 + (size_t)min(p0 + p, np - 1) * a.Rs;
+                ml[p] = *(const f2 *)(a.ML + row * 2);
+#pragma unroll
+                for (int s = 0; s < KS; ++s) xv[p][s] = *(const h8 *)(a.Xp + row * DM + 32 * (KS * w + s) + 8 * q);
             }
-            return;
-        }
-#pragma unroll
-        for (int i = i0; i < i1; ++i) {
-            const int rr = 16 * w + i;
-            const char *sbase = (const char *)g.Bt + (size_t)(head * 64 + rr) * g.ldb * 2;
-            const unsigned voff = (unsigned)((l ^ row_swizzle(i)) << 4);
-            if (ROWB == 2048) dma_row_2k(s_lds + A_BYTES + rr * ROWB, voff, sbase);
-            else dma_piece(s_lds + A_BYTES + rr * ROWB, voff, sbase);
-        }
-    };
-    weight_rows(0, 8);
-
-    // ---- merged activation rows 4w..4w+3 ----
-    // Everything this needs is requested before anything is used: the statistics (one (row, part) pair
-    // per lane), then all partial rows (four rows x the slots in use x both halves), so the whole merge
-    // costs one round trip to memory.
-    constexpr int HF = (ROWB + 1023) / 1024;             // 64-lane passes over a row of 16-byte chunks (the last may be half used)
-    constexpr int CPR = ROWB / 16;
-    int slot0[4], np[4];                                 // pieces of the four rows' batch elements (wave-uniform)
-    {
-        // integer divisions are long instruction sequences: the span length is worked out once, and rows of one
-        // batch element (with a beam of four: all four rows of a wavefront) share one look-up
-        const PieceCut cut = piece_cut(g.pm, e_tot);
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            if (ii > 0 && b_of[ii] == b_of[ii - 1]) { slot0[ii] = slot0[ii - 1]; np[ii] = np[ii - 1]; }
-            else {
-                piece_range(g.pm, cut, b_of[ii], e_lo[ii], e_hi[ii], slot0[ii], np[ii]);
-                np[ii] = min(np[ii], kMaxParts);
+            if (p0 + PC >= np_max && tile + a.groups < tiles) {                     // the next tile's table entries
+                row_of(tile + a.groups, b, j);
+                if (a.pm.E) { E_b = a.pm.E[b]; E_b1 = a.pm.E[b + 1]; }
             }
-        }
-    }
-    auto row_src = [&](int ii, int p, int hf) {
-        const int m = min(m0 + 4 * w + ii, g.M - 1);
-        const int r = head * g.x + (m % g.x);
-        return (const h8 *)((const f16_t *)g.A + (((size_t)slot0[ii] + p) * g.Rs + r) * g.lda + hf * 512 + 8 * l);
-    };
-    float mp, lp;
-    {
-        const int ii = l >> 4, p = l & 15;
-        const int m = min(m0 + 4 * w + ii, g.M - 1);
-        const int r = head * g.x + (m % g.x);
-        const int s0 = ii == 0 ? slot0[0] : (ii == 1 ? slot0[1] : (ii == 2 ? slot0[2] : slot0[3]));
-        const int n0 = ii == 0 ? np[0] : (ii == 1 ? np[1] : (ii == 2 ? np[2] : np[3]));
-        const float *ml = g.ML + (((size_t)s0 + min(p, n0 - 1)) * g.Rs + r) * 2;
-        mp = ml[0]; lp = ml[1];
-        if (p >= n0) lp = 0.f;
-    }
-
-    h8 xv[4][HF][kMaxParts];
+            float m_new = m_run;
 #pragma unroll
-    for (int pp = 0; pp < kMaxParts; ++pp) {
-        if (pp >= g.parts) continue;                     // uniform
+            for (int p = 0; p < PC; ++p) {
+                if (p0 + p >= np || !(ml[p][1] > 0.f)) ml[p] = f2{-INFINITY, 0.f};  // no such piece for this row, or an empty one
+                m_new = fmaxf(m_new, ml[p][0]);
+            }
+            if (p0 > 0) {
+                const float c = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+                den *= c;
 #pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            if (pp >= np[ii]) continue;                  // uniform
+                for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int hf = 0; hf < HF; ++hf)
-                if (hf * 64 + l < CPR) xv[ii][hf][pp] = *row_src(ii, pp, hf);
-        }
-    }
-    weight_rows(8, 16);
-    float wgt_lane;
-    {
-        if (!(lp > 0.f)) { lp = 0.f; mp = -INFINITY; }       // an empty part (its maximum was never written)
-        float Mx = mp;
+                    for (int e = 0; e < 8; ++e) v[s][e] *= c;
+            }
+            m_run = m_new;
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) Mx = fmaxf(Mx, __shfl_xor(Mx, o, 64));
-        float wp = lp > 0.f ? exp2f(mp - Mx) * lp : 0.f;
-        float den = wp;
+            for (int p = 0; p < PC; ++p) {
+                if (p0 + p >= np_max) continue;
+                const bool there = ml[p][1] > 0.f;       // an empty piece's row was never written
+                const float wp = there ? exp2f(ml[p][0] - m_new) * ml[p][1] : 0.f;
+                den += wp;
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) den += __shfl_xor(den, o, 64);
-        wgt_lane = den > 0.f ? wp / den : 0.f;
-    }
+                for (int s = 0; s < KS; ++s) {
+                    const h8 xs = there ? xv[p][s] : h8{};
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-        const int ar = 4 * w + ii;
-        float wrow[kMaxParts];
-#pragma unroll
-        for (int pp = 0; pp < kMaxParts; ++pp) {
-            wrow[pp] = __shfl(wgt_lane, 16 * ii + pp, 64);
-            if (pp >= np[ii]) wrow[pp] = 0.f;
-        }
-#pragma unroll
-        for (int hf = 0; hf < HF; ++hf) {
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = 0.f;
-#pragma unroll
-            for (int pp = 0; pp < kMaxParts; ++pp) {
-                if (pp >= g.parts) continue;
-                if (wrow[pp] != 0.f) {                   // an empty part's row was never written
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = fmaf(wrow[pp], (float)xv[ii][hf][pp][e], v[e]);
+                    for (int e = 0; e < 8; ++e) v[s][e] = fmaf(wp, (float)xs[e], v[s][e]);
                 }
             }
-            h8 hv;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) hv[e] = (_Float16)v[e];
-            if (hf * 64 + l < CPR) *(h8 *)(S + ar * ROWB + (((hf * 64 + l) ^ row_swizzle(ar)) << 4)) = hv;
         }
-    }
-
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
-    // ---- multiply: this wavefront's quarter of K ----
-    const __attribute__((address_space(3))) char *Sl = (const __attribute__((address_space(3))) char *)S;
-    const int fsw = row_swizzle(r16);
-    f4 acc[4];
+        const float inv = den > 0.f ? 1.0f / den : 0.f;
+        f4 acc[NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-    constexpr int STEPS = DM / 128;
+        for (int t = 0; t < NT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const int chunk = (4 * (w * STEPS + st) + q4) ^ fsw;
-        const int off = r16 * ROWB + (chunk << 4);
-        const h8 a0 = *(const __attribute__((address_space(3))) h8 *)(Sl + off);
+        for (int s = 0; s < KS; ++s) {
+            h8 xm;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const h8 bt = *(const __attribute__((address_space(3))) h8 *)(Sl + A_BYTES + 16 * t * ROWB + off);
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bt, a0, acc[t], 0, 0, 0);   // transposed tile: lane = row, 4 columns
+            for (int e = 0; e < 8; ++e) xm[e] = (_Float16)(v[s][e] * inv);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)                 // transposed tile: lane = row, 4 columns
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, wv[s][t]), xm, acc[t], 0, 0, 0);
         }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) red[parity][(w * NT + t) * 64 + l] = acc[t];
+        __syncthreads();                                 // the other buffer was read before this barrier's predecessor
+        if (w < NT) {
+            f4 sum = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 8; ++s) sum += red[parity][(s * NT + w) * 64 + l];
+            const int mm = 16 * tile + r16;
+            typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+            if (mm < a.M)
+                *(h4 *)(a.A + (size_t)mm * (a.heads * 64) + head * 64 + 16 * (nb * NT + w) + 4 * q) =
+                    h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
+        }
+        parity ^= 1;
     }
+}
 
-    // ---- add the four K quarters; wavefront w finishes column block w ----
-    __syncthreads();
-    float *red = (float *)S;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) *(f4 *)(red + ((w * 4 + t) * 64 + l) * 4) = acc[t];
-    __syncthreads();
-    f4 sum = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const f4 o = *(const f4 *)(red + ((s * 4 + w) * 64 + l) * 4);
-        sum[0] += o[0]; sum[1] += o[1]; sum[2] += o[2]; sum[3] += o[3];
-    }
-    const int mm = m0 + r16;
-    if (mm >= g.M) return;
-    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-    *(h4 *)((f16_t *)g.C + (size_t)mm * g.ldc + head * 64 + 16 * w + 4 * q4) =
-        h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
+// W^V [d_m, heads * 64] in the storage type -> fp16 fragments of k_vproj (prepare time).
+template <typename T>
+__global__ void k_pack_wv(const T *__restrict__ W, f16_t *__restrict__ Wp, int d_m, int hd)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (size_t)d_m * hd) return;
+    const int e = i & 7, l = (i >> 3) & 63, t = (i >> 9) & 3;
+    const int ks = (int)((i >> 11) % (d_m / 32)), head = (int)((i >> 11) / (d_m / 32));
+    const int col = head * 64 + 16 * t + (l & 15), k = 32 * ks + 8 * (l >> 4) + e;
+    Wp[i] = (f16_t)to_f32(W[(size_t)k * hd + col]);
+}
+
+hipError_t launch_pack_wv(int dtype, const void *W, void *Wp, int d_m, int hd, hipStream_t s)
+{
+    const dim3 grid((unsigned)(((size_t)d_m * hd + 255) / 256)), block(256);
+    if (dtype == EL_BF16) hipLaunchKernelGGL(k_pack_wv<bf16_t>, grid, block, 0, s, (const bf16_t *)W, (f16_t *)Wp, d_m, hd);
+    else hipLaunchKernelGGL(k_pack_wv<f16_t>, grid, block, 0, s, (const f16_t *)W, (f16_t *)Wp, d_m, hd);
+    return hipGetLastError();
 }
 
 // bf16 -> fp16 copy of a weight matrix (prepare time).
@@ -522,19 +484,28 @@ hipError_t launch_elq_mfma(const el_attn_ctx *ctx, const Problem &p, const Works
 }
 
 // merge + a6: A[b*beam+j, head i] = (sum_p w_p Xp[b,p,i*beam+j,:]) . W_i^V       fp16   (d_k = 64)
+template <int DM>
+static void launch_vproj_t(const VprojArgs &a, int nt, hipStream_t s)
+{
+    const dim3 grid(8 * ((a.heads + 7) / 8) * (4 / nt) * a.groups), block(512);
+    if (nt == 1) hipLaunchKernelGGL((k_vproj<DM, 1>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_vproj<DM, 4>), grid, block, 0, s, a);
+}
+
 hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl,
                              hipStream_t s)
 {
-    GemmArgs g = base_args(p);
-    g.A = ws.Xp; g.Bt = ctx->w.WvT; g.C = ws.A; g.ML = ws.ML; g.parts = pl.parts; g.Rs = pl.Rs;
-    g.pm = piece_map(pl, ws, p.B);
-    g.N = p.d_k; g.K = p.d_m; g.lda = p.d_m; g.ldb = p.d_m; g.ldc = p.hd;
-    g.N_heads = p.heads;
-    const int hp = (p.heads + 7) / 8;                    // heads per XCD; 8 * hp * (row tiles) workgroups
-    const dim3 grid(8 * hp * ((g.M + 15) / 16)), block(256);
-    if (p.d_m == 1024) hipLaunchKernelGGL((k_vproj_slab<1024>), grid, block, 0, s, g);
-    else if (p.d_m == 768) hipLaunchKernelGGL((k_vproj_slab<768>), grid, block, 0, s, g);
-    else hipLaunchKernelGGL((k_vproj_slab<512>), grid, block, 0, s, g);
+    VprojArgs a;
+    a.Wp = (const u4 *)ctx->w.WvP; a.Xp = (const f16_t *)ws.Xp; a.ML = ws.ML; a.A = (f16_t *)ws.A;
+    a.pm = piece_map(pl, ws, p.B);
+    a.M = p.B * p.beam; a.x = p.beam; a.heads = p.heads; a.Rs = pl.Rs;
+    const int tiles = (a.M + 15) / 16;
+    const int nt = tiles * p.heads <= 64 ? 1 : 4;
+    const int room = ctx->num_cus / p.heads > 0 ? ctx->num_cus / p.heads : 1;
+    a.groups = tiles < room ? tiles : room;
+    if (p.d_m == 1024) launch_vproj_t<1024>(a, nt, s);
+    else if (p.d_m == 768) launch_vproj_t<768>(a, nt, s);
+    else launch_vproj_t<512>(a, nt, s);
     return hipGetLastError();
 }
 
