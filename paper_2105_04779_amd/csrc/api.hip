@@ -87,7 +87,7 @@ Workspace carve(const el_attn_ctx *c) { return carve_from(c->ws_base, ws_layout(
 
 void free_weights(el_attn_ctx *c)
 {
-    void *ptrs[] = {c->w.WqT, c->w.Wk, c->w.bq, c->w.WkH, c->w.WvP, c->w.WoT, c->w.WvTs, c->w.WoTs, (void *)c->w.c_out,
+    void *ptrs[] = {c->w.WqT, c->w.Wk, c->w.bq, c->w.WqP, c->w.WkP, c->w.WvP, c->w.WoP, c->w.WvTs, c->w.WoTs, (void *)c->w.c_out,
                     (void *)c->w.bk32, (void *)c->w.bv32, (void *)c->w.bo32};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -164,7 +164,7 @@ Problem make_problem(const el_attn_ctx *ctx, const void *H, int64_t stride, cons
     return p;
 }
 
-// a1..a6 of one step; on return the workspace holds the projected queries, the key-range statistics and
+// a1..a6 of one step; on return the workspace holds the projected queries (of a segment), the key-range statistics and
 // the head outputs A (without b^V), in the formats `fmt` names.
 struct StepFormats {
     bool a_f16, qp_f16;     // element type of A and of the projected queries in the workspace
@@ -174,7 +174,7 @@ struct StepFormats {
     float c_to_nat;         // ln 2 where the projected queries carry log2(e)
 };
 
-el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s, StepFormats *fmt)
+el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, bool segment, hipStream_t s, StepFormats *fmt)
 {
     constexpr float kLn2 = 0.6931471805599453f;
     if (el_attn_uses_mfma(ctx)) {
@@ -183,8 +183,7 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
         // a1 + a2: expanded queries in fp16, pre-multiplied by log2(e)/sqrt(d_k) so the core's softmax is an exp2
         const float qscale = 1.4426950408889634f / sqrtf((float)p.d_k);
         if (ctx->use_mfma_gemm) {
-            if (launch_qproj_mfma(ctx, p, ws, qscale, s) != hipSuccess) return EL_ERR_HIP;
-            if (launch_elq_mfma(ctx, p, ws, pl.Rs, s) != hipSuccess) return EL_ERR_HIP;
+            if (launch_qelq_mfma(ctx, p, ws, pl.Rs, qscale, segment, s) != hipSuccess) return EL_ERR_HIP;
         } else {
             if (launch_qproj_generic(ctx, p, ws, s) != hipSuccess) return EL_ERR_HIP;
             if (launch_elq_f16(ctx, p, ws, pl, s) != hipSuccess) return EL_ERR_HIP;
@@ -244,7 +243,7 @@ el_status run_step(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipS
         return EL_OK;
     }
     StepFormats fmt;
-    const el_status st = run_a1_to_a6(ctx, p, ws, s, &fmt);
+    const el_status st = run_a1_to_a6(ctx, p, ws, false, s, &fmt);
     return st != EL_OK ? st : run_a7(ctx, p, ws, ctx->w.c_out, s);
 }
 
@@ -319,8 +318,7 @@ el_status el_attn_prepare(const el_attn_config *cfg,
         {&c->w.Wk, Wk, wbytes, 0, 0},
         {&c->w.bq, bq, (size_t)c->hd * es, 0, 0},
         {&c->w.WvTs, gemm ? nullptr : Wv, wbytes, cfg->d_model, c->hd},
-        {gemm ? &c->w.WoT : &c->w.WoTs, Wo, wbytes, c->hd, cfg->d_model},
-        {&c->w.WkH, gemm ? Wk : nullptr, wbytes, 0, 0},
+        {&c->w.WoTs, Wo, wbytes, c->hd, cfg->d_model},
     };
     for (auto &t : packed) {
         if (!t.src) continue;
@@ -330,19 +328,19 @@ el_status el_attn_prepare(const el_attn_config *cfg,
         if (e != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
     }
     if (gemm) {
-        if (hipMalloc(&c->w.WvP, wbytes) != hipSuccess) { free_weights(c); delete c; return EL_ERR_ALLOC; }
-        if (launch_pack_wv(cfg->dtype, Wv, c->w.WvP, cfg->d_model, c->hd, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
+        // fragments for the MFMA projections
+        struct { void **dst; const void *src; PackKind kind; } frag[] = {
+            {&c->w.WqP, Wq, kPackWq}, {&c->w.WkP, Wk, kPackWk}, {&c->w.WvP, Wv, kPackWv}, {&c->w.WoP, Wo, kPackWo},
+        };
+        for (auto &f : frag) {
+            if (hipMalloc(f.dst, wbytes) != hipSuccess) { free_weights(c); delete c; return EL_ERR_ALLOC; }
+            if (launch_pack(cfg->dtype, f.kind, f.src, *f.dst, cfg->d_model, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
+        }
     }
     if (hipMalloc((void **)&c->w.c_out, (size_t)cfg->d_model * sizeof(float)) != hipSuccess) {
         free_weights(c); delete c; return EL_ERR_ALLOC;
     }
-    if (launch_cout(c, gemm ? c->w.WoT : c->w.WoTs, bv, bo, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
-    // everything after a1 of the MFMA projections runs in fp16: bf16 weights of a2, a6, a7 are converted once here
-    if (gemm && cfg->dtype == EL_BF16) {
-        const size_t nel = (size_t)cfg->d_model * c->hd;
-        for (void *m : {c->w.WkH, c->w.WoT})
-            if (launch_bf16_to_f16(m, m, nel, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
-    }
+    if (launch_cout(c, c->w.WoTs, bv, bo, s) != hipSuccess) { free_weights(c); delete c; return EL_ERR_HIP; }
     // fp32 copies of the three biases the segment form needs (b^K enters its statistics, Eq. 7)
     struct { float **dst; const void *src; int n; } vecs[] = {
         {&c->w.bk32, bk, c->hd}, {&c->w.bv32, bv, c->hd}, {&c->w.bo32, bo, cfg->d_model},
@@ -483,7 +481,7 @@ el_status el_attn_decode_segment(el_attn_ctx *ctx, const void *H, int64_t H_batc
     const Workspace ws = carve(ctx);
     const Problem p = make_problem(ctx, H, H_batch_stride, lengths, queries, nullptr, B, beam, n);
     StepFormats fmt;
-    if ((st = run_a1_to_a6(ctx, p, ws, s, &fmt)) != EL_OK) return st;
+    if ((st = run_a1_to_a6(ctx, p, ws, true, s, &fmt)) != EL_OK) return st;
     SegFinishArgs f;
     f.A = ws.A; f.Qp = ws.Qp; f.ML = ws.ML; f.bk32 = ctx->w.bk32; f.bv32 = ctx->w.bv32;
     f.seg_A = seg_A; f.seg_lse = seg_lse;

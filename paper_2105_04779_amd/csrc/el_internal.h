@@ -165,7 +165,7 @@ struct Workspace {
 
 struct Weights {    // library-owned copies; every product reads both operands along the contraction, hence the transposes
     void *WqT, *Wk, *bq;            // (W^Q)^T and W^K as it is (a head's slice of a row is the contraction), storage dtype
-    void *WkH, *WvP, *WoT;          // MFMA projections: W^K, W^V in fragments, (W^O)^T, all in fp16 (converted from bf16 when needed)
+    void *WqP, *WkP, *WvP, *WoP;    // MFMA projections: all four in fragments; W^Q in the storage type, the others in fp16
     void *WvTs, *WoTs;              // fp32-arithmetic projections: (W^V)^T, (W^O)^T in the storage dtype
     float *c_out;                   // [d_m] = b_o + b_v . W_o, fp32
     float *bk32, *bv32, *bo32;      // [h*d_k], [h*d_k], [d_m] in fp32 (zeros when absent): only the segment form reads them
@@ -268,10 +268,9 @@ hipError_t launch_merge_exp2(const el_attn_ctx *ctx, const Problem &p, const Wor
 // MFMA projection GEMMs -- gemm_mfma.hip
 bool gemm_mfma_supported(int dtype, int d_m, int d_k);
 hipError_t launch_transpose(size_t elem, const void *src, void *dst, int rows, int cols, hipStream_t s);
-hipError_t launch_pack_wv(int dtype, const void *W, void *Wp, int d_m, int hd, hipStream_t s);
-hipError_t launch_bf16_to_f16(const void *src, void *dst, size_t n, hipStream_t s);
-hipError_t launch_qproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, float scale, hipStream_t s);
-hipError_t launch_elq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int Rs, hipStream_t s);
+enum PackKind { kPackWq, kPackWk, kPackWv, kPackWo };
+hipError_t launch_pack(int dtype, PackKind kind, const void *W, void *P, int d_m, hipStream_t s);
+hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int Rs, float scale, bool keep_qp, hipStream_t s);
 hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, hipStream_t s);
 hipError_t launch_oproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const float *bias32, hipStream_t s);
 

@@ -1,196 +1,193 @@
-// Small-M MFMA GEMMs for the projection steps of the EL-attention decode step (steps a1, a2, a6,
-// a7 of Algorithm 3's attention routine; group 2 of Table 1 -- O(d_m^2) per query, weight-read
-// bound).  All four are C[m, n] = sum_k A[m, k] * Bt[n, k] with both operands contiguous along k
-// (W^Q, W^V, W^O are stored transposed at prepare time for exactly this; W^K already has that shape).
+// MFMA kernels for the projection steps of the EL-attention decode step (steps a1, a2, a6, a7 of Algorithm 3's
+// attention routine; group 2 of Table 1 -- O(d_m^2) per query, weight-read bound), for d_k = 64:
 //
-//   a1  Qp    = (q . W^Q + b^Q) * scale   k_gemm_slab  A = queries (storage dtype), Bt = (W^Q)^T (storage dtype)
-//   a2  ELQ_i = Qp_i . (W_i^K)^T          k_elq_slab   A = Qp (fp16),               Bt = W^K in fp16     per head
-//                                                      (result as a high + low pair of planes in the storage type)
-//   a6  A_i   = X_i . W_i^V               k_vproj      A = merge of the pieces,     W^V in fp16 fragments per head
-//   a7  out   = A . W^O + c_out           k_gemm_slab  A = A (fp16),                Bt = (W^O)^T in fp16
+//   a1 + a2  Qp = (q . W^Q + b^Q) * scale, ELQ_i = Qp_i . (W_i^K)^T     k_qelq   (EL-Q as a high + low pair)
+//   a6       A_i = X_i . W_i^V, X merged from the pieces                k_vproj
+//   a7       out = A . W^O + c_out                                      k_oproj
 //
-// Storage-dtype operands enter the MFMA exactly (a1 runs in the storage type).  From a2 on everything
-// is fp16: bf16 weights are converted once at prepare time (exact above 2^-14, |error| <= 2^-25 below),
-// and the intermediates Qp, merged X and A are rounded to fp16 once each (2^-12 relative; the
-// measured end-to-end error stays several times under the 2e-3 bar).  Accumulation is fp32.
+// All three have one shape.  A workgroup of eight wavefronts owns a 64-column block (a head, or 64 output columns)
+// and walks over tiles of 16 rows.  Wavefront w contracts an eighth of the contraction dimension: its slice of the
+// block's weights stays in registers for all tiles, in fragments packed at prepare time in the order the matrix
+// instruction reads them (a load instruction fetches 1 contiguous KB), and the rows' fragments come straight from
+// global memory as well, each byte once per workgroup.  Nothing is staged in LDS; everything a tile needs is
+// requested before the first product; the eight partial tiles meet in LDS.  Weights are the instruction's A operand:
+// a lane ends up with four consecutive columns of one row.  Where 64-column blocks leave compute units idle (few
+// rows), the columns are split further and the rows are read once per part, out of L2.
 //
-// k_gemm_slab: a workgroup stages 32 rows of A and 32 rows of Bt over the whole K in LDS with 1 KB
-// LDS-DMA pieces (full cache lines, every byte fetched once per workgroup), then its four wavefronts
-// split K.  k_vproj: weights and merged rows straight in registers, see there.
-// k_elq_slab: the weight slice stays in registers, operand fragments come straight from global memory
-// (a2: K = d_k is tiny).
+// Storage-dtype operands enter the MFMA exactly (a1 runs in the storage type).  From a2 on everything is fp16: bf16
+// weights are converted once at prepare time (exact above 2^-14, |error| <= 2^-25 below), and the intermediates Qp,
+// merged X and A are rounded to fp16 once each (2^-12 relative; the measured end-to-end error stays several times
+// under the 2e-3 bar).  Accumulation is fp32.
+#include <type_traits>
 #include "el_internal.h"
 
 namespace el {
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef uint16_t s8v __attribute__((ext_vector_type(8)));
 
-enum { C_F32 = 0, C_F16 = 1, C_BF16 = 2 };
+namespace {
 
-struct GemmArgs {
-    const void *A;        // activations (see a_kind)
-    const void *Bt;       // weights [N rows, K contiguous], storage dtype
-    void *C;
-    const void *bias;     // per output column, storage dtype, may be null
-    const float *bias32;  // per output column, fp32, may be null
-    float scale;          // applied to (acc + bias)
-    int M, N, K;          // per batch (head)
-    int lda, ldb, ldc;    // row strides in elements
-    int x;                // beam: logical row m = b*x + j
-    int c_rB;             // k_elq_slab: padded rows per batch element of the output (logical row m, head i -> row i * x + m % x of element m / x)
-};
+template <bool BF> __device__ __forceinline__ f4 mfma16(u4 a, u4 b, f4 c);
+template <> __device__ __forceinline__ f4 mfma16<false>(u4 a, u4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0); }
+template <> __device__ __forceinline__ f4 mfma16<true>(u4 a, u4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0); }
 
-template <bool BF> struct Frag;
-template <> struct Frag<false> {
-    typedef h8 type;
-    static __device__ __forceinline__ f4 mfma(h8 a, h8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
-};
-template <> struct Frag<true> {
-    typedef b8 type;
-    static __device__ __forceinline__ f4 mfma(b8 a, b8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-};
+// Workgroup -> (64-column block, part of its columns, group of row tiles).  Workgroup ids that differ by a multiple of
+// 8 share an XCD and its L2, so each XCD gets one run of the items in block-major order: it then pulls only its own
+// blocks' weights from memory, once, instead of every XCD pulling all of them.
+struct Place { int block, part, group; };
+__device__ __forceinline__ bool place_of(int blocks, int parts, int groups, Place &p)
+{
+    const int items = blocks * parts * groups, per_xcd = (items + 7) >> 3;
+    const int i = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (i >= items) return false;
+    p.block = i / (parts * groups);
+    const int j = i - p.block * (parts * groups);
+    p.part = j % parts; p.group = j / parts;
+    return true;
+}
+inline dim3 place_grid(int blocks, int parts, int groups) { return dim3(8 * ((blocks * parts * groups + 7) / 8)); }
+
+// Groups the row tiles are dealt to: as many workgroups as there are compute units, all with the same number of tiles
+// up to one.
+inline int tile_groups(int tiles, int columns_parts, int num_cus)
+{
+    const int room = num_cus / columns_parts > 0 ? num_cus / columns_parts : 1;
+    const int each = (tiles + room - 1) / room;
+    return (tiles + each - 1) / each;
+}
+
+} // namespace
 
 // ---------------------------------------------------------------------------------------------
-// Slab GEMM: C[M, N] = A[M, K] . Bt[N, K]^T for K = 512, 768 or 1024 (rows of 1, 1.5 or 2 KB).  One workgroup
-// owns a 32 x 32 output tile.  Its 64 operand rows are fetched once, whole, into LDS (row r lands
-// XOR-swizzled by row_swizzle(r % 16), see dma_piece), so global traffic is full cache lines and
-// (M/32 + N/32) passes over the operands in total.  Then wavefront w multiplies k-steps
-// [w K/128, (w+1) K/128) for all four 16 x 16 sub-tiles, the partial tiles are added through LDS
-// and wavefront w finishes sub-tile w.
-template <bool BF, int CK>
-__global__ void __launch_bounds__(256)
-k_gemm_slab(const GemmArgs g)
+// a1 + a2 of one head (Eq. 9's Q_i (W_i^K)^T): Qp = (q . W_i^Q + b_i^Q) * scale of a 16-row tile goes through LDS in
+// fp16 and is contracted with the head's rows of W^K at once; NP 32-column fragments of EL-Q per wavefront (all of
+// d_m / 256, or one with the columns split over workgroups).  W^K is packed so that a pair of products leaves eight
+// consecutive columns in a lane: its high and low halves are 16-byte stores into the core's fragment order.
+// Bound: memory latency up to about 64 rows, the bytes of EL-Q (4 per element) beyond.  One launch against the two it
+// replaces (a1 on 32 x 32 tiles staged in LDS, a2 with its 8 KB of weights per workgroup), d_m 1024: 4 rows 10.4 ->
+// 5.5 us, 256 rows 15.4 -> 11.4 (4.4 of it the stores, 16.8 MB), 512 rows 23.9 -> 17.3, 1280 rows 47.5 -> 29.6.
+struct QelqArgs {
+    const u4 *Wq;          // storage type, [head][k / 32][column / 16 % 4][lane]
+    const u4 *Wk;          // fp16, [head][column / 32][half][k / 32 % 2][lane]
+    const void *q;         // [M, d_m] storage type
+    const void *bq;        // storage type, may be null
+    uint16_t *elq;
+    f16_t *Qp;             // [M, d_m], or null if nobody reads it
+    float scale;
+    int M, x, Rs, groups;
+};
+
+template <int DM, bool BF, int NP>
+__global__ void __launch_bounds__(512)
+k_qelq(const QelqArgs a)
 {
-    typedef typename Frag<BF>::type frag_t;
-    __shared__ __attribute__((aligned(1024))) char S[64 * 2048];
-    const int tid = threadIdx.x, l = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = l & 15, q4 = l >> 4;
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-    const int rowb = g.K * 2;
-    const unsigned s_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)S;
+    constexpr int KS = DM / 256, HEADS = DM / 64, PARTS = DM / 256 / NP, RS = 68;
+    __shared__ __attribute__((aligned(16))) float red[8 * 16 * RS];          // [wavefront][row][column, padded]
+    __shared__ __attribute__((aligned(16))) f16_t Ql[16 * 72];               // rows 144 bytes apart
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = l & 15, q = l >> 4;
+    Place pl;
+    if (!place_of(HEADS, PARTS, a.groups, pl)) return;
+    const int head = pl.block, tiles = (a.M + 15) >> 4;
 
-    // ---- stage: wavefronts 0,1 fetch the A rows, 2,3 the Bt rows ----
-    if (rowb == 1536) {
-        // Rows of 1.5 KB do not split into 1 KB pieces: a wavefront's 16 rows are 24 KB of contiguous LDS, filled by
-        // 24 requests; lane l of request j lands at chunk position p = 64 j + l of that block, which is row
-        // r = p / 96, position q = p % 96, and must hold chunk q ^ swizzle(r) of the row.
-        const char *mbase = w < 2 ? (const char *)g.A : (const char *)g.Bt;
-        const int first = w < 2 ? m0 + 16 * w : n0 + 16 * (w - 2);
-        const int lastv = (w < 2 ? g.M : g.N) - 1, ld = w < 2 ? g.lda : g.ldb;
+    u4 xq[KS], wq[KS][4], wk[NP][2][2];
+    auto load_rows = [&](int tile) {
+        const uint16_t *row = (const uint16_t *)a.q + (size_t)min(16 * tile + r16, a.M - 1) * DM + 8 * q;
 #pragma unroll
-        for (int j = 0; j < 24; ++j) {
-            const int pz = 64 * j + l, r = pz / 96, q = pz - 96 * r;
-            const unsigned voff = (unsigned)min(first + r, lastv) * (unsigned)(ld * 2) + (unsigned)((q ^ row_swizzle(r)) << 4);
-            dma_piece(s_lds + 16 * w * rowb + 1024 * j, voff, mbase);
+        for (int s = 0; s < KS; ++s) xq[s] = *(const u4 *)(row + 32 * (KS * w + s));
+    };
+    load_rows(pl.group);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wq[s][t] = a.Wq[(((size_t)head * (DM / 32) + KS * w + s) * 4 + t) * 64 + l];
+    const int pair0 = (pl.part * 8 + w) * NP;
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) wk[i][h][s] = a.Wk[((((size_t)head * (DM / 32) + pair0 + i) * 2 + h) * 2 + s) * 64 + l];
+    // the thread that adds up: row srow, columns scol and scol + 1 of the head
+    const int srow = threadIdx.x >> 5, scol = 2 * (threadIdx.x & 31);
+    float bias[2] = {0.f, 0.f};
+    if (a.bq)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) bias[e] = BF ? to_f32(((const bf16_t *)a.bq)[head * 64 + scol + e]) : to_f32(((const f16_t *)a.bq)[head * 64 + scol + e]);
+
+    for (int tile = pl.group; tile < tiles; tile += a.groups) {
+        f4 acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[t] = mfma16<BF>(wq[s][t], xq[s], acc[t]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) *(f4 *)(red + (w * 16 + r16) * RS + 16 * t + 4 * q) = acc[t];
+        if (tile + a.groups < tiles) load_rows(tile + a.groups);
+        __syncthreads();
+        {
+            f2 sum = f2{0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 8; ++s) sum += *(const f2 *)(red + (s * 16 + srow) * RS + scol);
+            const h2 v = h2{(_Float16)((sum[0] + bias[0]) * a.scale), (_Float16)((sum[1] + bias[1]) * a.scale)};
+            *(h2 *)(Ql + srow * 72 + scol) = v;
+            if (a.Qp && pl.part == 0 && 16 * tile + srow < a.M) *(h2 *)(a.Qp + (size_t)(16 * tile + srow) * DM + head * 64 + scol) = v;
         }
-    } else
+        __syncthreads();
+        const int m = 16 * tile + r16;
+        u4 qf[2];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int rr = 16 * w + i;
-        const char *sbase;
-        if (w < 2) sbase = (const char *)g.A + (size_t)min(m0 + rr, g.M - 1) * g.lda * 2;
-        else sbase = (const char *)g.Bt + (size_t)min(n0 + rr - 32, g.N - 1) * g.ldb * 2;
-        const unsigned voff = (unsigned)((l ^ row_swizzle(i)) << 4);
-        if (rowb == 2048) dma_row_2k(s_lds + rr * rowb, voff, sbase);
-        else dma_piece(s_lds + rr * rowb, voff, sbase);
-    }
-
-    // bias of this lane's four output columns (sub-tile w), fetched while the slab is in flight
-    const int mt = w >> 1, nt = w & 1;
-    const int ncol = n0 + 16 * nt + 4 * q4;
-    float badd[4] = {0.f, 0.f, 0.f, 0.f};
-    if (ncol < g.N) {
+        for (int s = 0; s < 2; ++s) qf[s] = *(const u4 *)(Ql + r16 * 72 + 32 * s + 8 * q);
+        uint16_t *dst = a.elq + elq_frag_index(m / a.x, head * a.x + m % a.x, 32 * pair0 + 8 * q, 0, a.Rs, DM);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (g.bias) badd[j] = BF ? to_f32(((const bf16_t *)g.bias)[ncol + j]) : to_f32(((const f16_t *)g.bias)[ncol + j]);
-            if (g.bias32) badd[j] += g.bias32[ncol + j];
+        for (int i = 0; i < NP; ++i) {
+            s8v hi, lo;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f4 e = mfma16<false>(wk[i][h][0], qf[0], f4{0.f, 0.f, 0.f, 0.f});
+                e = mfma16<false>(wk[i][h][1], qf[1], e);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    uint16_t vh, vl;
+                    split16<BF>(e[k], vh, vl);
+                    hi[4 * h + k] = vh; lo[4 * h + k] = vl;
+                }
+            }
+            if (m < a.M) {
+                *(s8v *)(dst + i * 1024) = hi;
+                *(s8v *)(dst + i * 1024 + 512) = lo;
+            }
         }
-    }
-
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
-    // ---- multiply: this wavefront's quarter of K ----
-    const __attribute__((address_space(3))) char *Sl = (const __attribute__((address_space(3))) char *)S;
-    const int fsw = row_swizzle(r16);
-    f4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
-    const int steps = g.K / 128;
-    for (int st = 0; st < steps; ++st) {
-        const int chunk = (4 * (w * steps + st) + q4) ^ fsw;
-        const int off = r16 * rowb + (chunk << 4);
-        const frag_t a0 = __builtin_bit_cast(frag_t, *(const __attribute__((address_space(3))) u4 *)(Sl + off));
-        const frag_t a1 = __builtin_bit_cast(frag_t, *(const __attribute__((address_space(3))) u4 *)(Sl + off + 16 * rowb));
-        const frag_t b0 = __builtin_bit_cast(frag_t, *(const __attribute__((address_space(3))) u4 *)(Sl + off + 32 * rowb));
-        const frag_t b1 = __builtin_bit_cast(frag_t, *(const __attribute__((address_space(3))) u4 *)(Sl + off + 48 * rowb));
-        // weights as the MFMA's A operand: the result is the transposed tile, so a lane holds four
-        // consecutive output columns of one row
-        acc[0][0] = Frag<BF>::mfma(b0, a0, acc[0][0]);
-        acc[0][1] = Frag<BF>::mfma(b1, a0, acc[0][1]);
-        acc[1][0] = Frag<BF>::mfma(b0, a1, acc[1][0]);
-        acc[1][1] = Frag<BF>::mfma(b1, a1, acc[1][1]);
-    }
-
-    // ---- add the four K quarters: wavefront w collects sub-tile (mt, nt) ----
-    __syncthreads();                                   // the slab is no longer needed
-    float *red = (float *)S;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) *(f4 *)(red + (((w * 4) + a * 2 + b) * 64 + l) * 4) = acc[a][b];
-    __syncthreads();
-    f4 sum = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const f4 o = *(const f4 *)(red + (((s * 4) + mt * 2 + nt) * 64 + l) * 4);
-        sum[0] += o[0]; sum[1] += o[1]; sum[2] += o[2]; sum[3] += o[3];
-    }
-    const int mm = m0 + 16 * mt + r16;
-    if (mm >= g.M || ncol >= g.N) return;
-    float val[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) val[j] = (sum[j] + badd[j]) * g.scale;
-    const size_t ci = (size_t)mm * g.ldc + ncol;
-    if (CK == C_F32) {
-        *(f4 *)((float *)g.C + ci) = f4{val[0], val[1], val[2], val[3]};
-    } else if (CK == C_F16) {
-        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-        *(h4 *)((f16_t *)g.C + ci) = h4{(_Float16)val[0], (_Float16)val[1], (_Float16)val[2], (_Float16)val[3]};
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) from_f32(val[j], (bf16_t *)g.C + ci + j);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Merge of the pieces fused with a6 (A_i = X_i . W_i^V, Eq. 5 / Eq. 8).  A workgroup of eight wavefronts owns
-// 16 NT of a head's 64 output columns for every `groups`-th tile of 16 rows; wavefront w contracts an eighth of
-// d_m.  Its weights sit in registers in the order the matrix instruction wants them (packed so at prepare time:
-// one load instruction = 1 contiguous KB), and so do its rows: a lane fetches the 16-byte fragments of its own row
-// from every piece and merges them with the log-sum-exp weights it works out for that row,
+// Merge of the pieces fused with a6 (A_i = X_i . W_i^V, Eq. 5 / Eq. 8), NT 16-column blocks of a head per workgroup.
+// A lane fetches the 16-byte fragments of its own row from every piece and merges them with the log-sum-exp weights
+// it works out for that row,
 //     X = sum_p (w_p l_p) Xhat_p / sum_p (w_p l_p),  w_p = 2^(m_p - M),
-// so nothing is exchanged before the products are: no staging, one barrier.  Up to four pieces are in flight at a
-// time; more are folded in with a running maximum.
+// so nothing is exchanged before the products are.  Up to four pieces are in flight at a time; more are folded in
+// with a running maximum.
 // Bound: memory latency in a chain of two (piece table, then statistics and pieces together), then the pieces'
-// bytes.  One column block per workgroup (NT = 1) where a head's four leave compute units idle: the pieces are then
-// read four times, out of L2.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup
-// per 16 rows, the 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024:
-// 38.9 -> 23.0 us; 512 rows, one piece each: 19.7 -> 10.2; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 10.0;
-// 4 rows: 8.6 -> 5.4.
+// bytes.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup per 16 rows, the
+// 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024: 38.9 -> 23.0 us;
+// 512 rows, one piece each: 19.7 -> 10.2; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 10.0; 4 rows: 8.6 -> 5.4.
 struct VprojArgs {
     const u4 *Wp;          // (W^V) in fragments: [head][k / 32][column / 16 % 4][lane]
     const f16_t *Xp;       // normalised fp16 pieces [slot, Rs, d_m]
     const float *ML;       // [slot, Rs, 2]
-    f16_t *A;              // [M, heads * 64]
+    f16_t *A;              // [M, d_m]
     PieceMap pm;
-    int M, x, heads, Rs, groups;
+    int M, x, Rs, groups;
 };
 
 template <int DM, int NT>
@@ -199,28 +196,18 @@ k_vproj(const VprojArgs a)
 {
     constexpr int KS = DM / 256;                         // 32-wide slices of k per wavefront
     constexpr int PC = 4;                                // pieces in flight
-    typedef float f2 __attribute__((ext_vector_type(2)));
     __shared__ f4 red[2][8 * NT * 64];
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
-    // Workgroup ids that differ by a multiple of 8 share an XCD and its L2.  Heads are dealt out so that an XCD
-    // works on as few of them as possible (heads / 8 when that divides): it then pulls only those heads' weights
-    // from memory, once, instead of every XCD pulling all of W^V.
-    constexpr int NB = 4 / NT;                           // column blocks of a head
-    int head, nb, group;
-    {
-        const int xcd = blockIdx.x & 7, hp = (a.heads + 7) >> 3;
-        int j = blockIdx.x >> 3;
-        head = xcd * hp + j % hp; j /= hp;
-        nb = j % NB; group = j / NB;
-        if (head >= a.heads) return;
-    }
+    Place pl;
+    if (!place_of(DM / 64, 4 / NT, a.groups, pl)) return;
+    const int head = pl.block, nb = pl.part;
     int e_tot = 0;
     if (a.pm.E) e_tot = a.pm.E[a.pm.B];
     const int tiles = (a.M + 15) >> 4;
     auto row_of = [&](int tile, int &b, int &j) { const int m = min(16 * tile + r16, a.M - 1); b = m / a.x; j = m - b * a.x; };
     int b, j, E_b = 0, E_b1 = 0;
-    row_of(group, b, j);
+    row_of(pl.group, b, j);
     if (a.pm.E) { E_b = a.pm.E[b]; E_b1 = a.pm.E[b + 1]; }
     u4 wv[KS][NT];
 #pragma unroll
@@ -230,7 +217,7 @@ k_vproj(const VprojArgs a)
             wv[s][t] = a.Wp[(((size_t)head * (DM / 32) + KS * w + s) * 4 + nb * NT + t) * 64 + l];
     const PieceCut cut = piece_cut(a.pm, e_tot);
     int parity = 0;
-    for (int tile = group; tile < tiles; tile += a.groups) {
+    for (int tile = pl.group; tile < tiles; tile += a.groups) {
         int slot0, np;
         piece_range(a.pm, cut, b, E_b, E_b1, slot0, np);
         const size_t row0 = (size_t)slot0 * a.Rs + head * a.x + j;
@@ -297,60 +284,140 @@ k_vproj(const VprojArgs a)
 #pragma unroll
             for (int e = 0; e < 8; ++e) xm[e] = (_Float16)(v[s][e] * inv);
 #pragma unroll
-            for (int t = 0; t < NT; ++t)                 // transposed tile: lane = row, 4 columns
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, wv[s][t]), xm, acc[t], 0, 0, 0);
+            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wv[s][t], __builtin_bit_cast(u4, xm), acc[t]);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) red[parity][(w * NT + t) * 64 + l] = acc[t];
-        __syncthreads();                                 // the other buffer was read before this barrier's predecessor
+        __syncthreads();                                 // (the other buffer was last read before the barrier of the tile before)
         if (w < NT) {
             f4 sum = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < 8; ++s) sum += red[parity][(s * NT + w) * 64 + l];
             const int mm = 16 * tile + r16;
-            typedef _Float16 h4 __attribute__((ext_vector_type(4)));
             if (mm < a.M)
-                *(h4 *)(a.A + (size_t)mm * (a.heads * 64) + head * 64 + 16 * (nb * NT + w) + 4 * q) =
+                *(h4 *)(a.A + (size_t)mm * DM + head * 64 + 16 * (nb * NT + w) + 4 * q) =
                     h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
         }
         parity ^= 1;
     }
 }
 
-// W^V [d_m, heads * 64] in the storage type -> fp16 fragments of k_vproj (prepare time).
+// ---------------------------------------------------------------------------------------------
+// a7: out = A . W^O + bias, NT 16-column blocks of a 64-column block per workgroup.  Bound: memory latency, then the
+// bytes of weights and rows through L2.  Against 32 x 32 tiles staged in LDS, d_m 1024: 256 rows 6.0 -> 5.1 us, 512
+// rows 10.1 -> 7.4, 1280 rows 20.2 -> 12.0.
+struct OprojArgs {
+    const u4 *Wp;          // (W^O) in fragments: [column / 64][k / 32][column / 16 % 4][lane]
+    const f16_t *A;        // [M, d_m]
+    const float *bias32;
+    void *out;
+    int M, groups;
+};
+
+template <int DM, int NT, typename TO>
+__global__ void __launch_bounds__(512)
+k_oproj(const OprojArgs a)
+{
+    constexpr int KS = DM / 256, RS = 16 * NT + 4, TPR = 512 / 16, CPT = 16 * NT / TPR > 0 ? 16 * NT / TPR : 1;   // threads per row, columns per thread
+    __shared__ __attribute__((aligned(16))) float red[2][8 * 16 * RS];       // [wavefront][row][column, padded]
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = l & 15, q = l >> 4;
+    Place pl;
+    if (!place_of(DM / 64, 4 / NT, a.groups, pl)) return;
+    const int tiles = (a.M + 15) >> 4;
+    u4 xa[KS], wo[KS][NT];
+    auto load_rows = [&](int tile) {
+        const f16_t *row = a.A + (size_t)min(16 * tile + r16, a.M - 1) * DM + 8 * q;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) xa[s] = *(const u4 *)(row + 32 * (KS * w + s));
+    };
+    load_rows(pl.group);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            wo[s][t] = a.Wp[(((size_t)pl.block * (DM / 32) + KS * w + s) * 4 + pl.part * NT + t) * 64 + l];
+    const int srow = threadIdx.x / TPR, scol = CPT * (threadIdx.x % TPR), col = pl.block * 64 + pl.part * 16 * NT + scol;
+    const bool adds = scol < 16 * NT;
+    float bias[CPT];
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) bias[e] = adds && a.bias32 ? a.bias32[col + e] : 0.f;
+    int parity = 0;
+    for (int tile = pl.group; tile < tiles; tile += a.groups) {
+        f4 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wo[s][t], xa[s], acc[t]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *(f4 *)(red[parity] + (w * 16 + r16) * RS + 16 * t + 4 * q) = acc[t];
+        if (tile + a.groups < tiles) load_rows(tile + a.groups);
+        __syncthreads();                                 // (the other buffer was last read before the barrier of the tile before)
+        if (adds) {
+            float sum[CPT];
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) sum[e] = 0.f;
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) sum[e] += red[parity][(s * 16 + srow) * RS + scol + e];
+            const int m = 16 * tile + srow;
+            if (m < a.M) {
+                TO *o = (TO *)a.out + (size_t)m * DM + col;
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) from_f32(sum[e] + bias[e], o + e);
+            }
+        }
+        parity ^= 1;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Packing at prepare time
+// W [K, N] -> fragments [N / 64][k / 32][n / 16 % 4][lane = 16 (k / 8 % 4) + n % 16][k % 8]
+template <typename T, typename TO>
+__global__ void k_pack_cols(const T *__restrict__ W, TO *__restrict__ P, int K, int N)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (size_t)K * N) return;
+    const int e = i & 7, l = (i >> 3) & 63, t = (i >> 9) & 3;
+    const int ks = (int)((i >> 11) % (K / 32)), block = (int)((i >> 11) / (K / 32));
+    const T v = W[(size_t)(32 * ks + 8 * (l >> 4) + e) * N + block * 64 + 16 * t + (l & 15)];
+    if constexpr (std::is_same<T, TO>::value) P[i] = v;
+    else P[i] = (TO)to_f32(v);
+}
+
+// W^K [d_m, heads * 64] -> fp16 fragments [head][column / 32][half][k / 32][lane][k % 8]; row n of a half's fragment is
+// column 8 (n / 4) + 4 half + n % 4 of the 32, so that the results of both halves are eight consecutive columns
 template <typename T>
-__global__ void k_pack_wv(const T *__restrict__ W, f16_t *__restrict__ Wp, int d_m, int hd)
+__global__ void k_pack_wk(const T *__restrict__ W, f16_t *__restrict__ P, int d_m, int hd)
 {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= (size_t)d_m * hd) return;
-    const int e = i & 7, l = (i >> 3) & 63, t = (i >> 9) & 3;
-    const int ks = (int)((i >> 11) % (d_m / 32)), head = (int)((i >> 11) / (d_m / 32));
-    const int col = head * 64 + 16 * t + (l & 15), k = 32 * ks + 8 * (l >> 4) + e;
-    Wp[i] = (f16_t)to_f32(W[(size_t)k * hd + col]);
+    const int e = i & 7, l = (i >> 3) & 63, s = (i >> 9) & 1, h = (i >> 10) & 1;
+    const int pair = (int)((i >> 11) % (d_m / 32)), head = (int)((i >> 11) / (d_m / 32)), n = l & 15;
+    const int col = 32 * pair + 8 * (n >> 2) + 4 * h + (n & 3);
+    P[i] = (f16_t)to_f32(W[(size_t)col * hd + head * 64 + 32 * s + 8 * (l >> 4) + e]);
 }
 
-hipError_t launch_pack_wv(int dtype, const void *W, void *Wp, int d_m, int hd, hipStream_t s)
+// W^Q in the storage type, the others in fp16
+hipError_t launch_pack(int dtype, PackKind kind, const void *W, void *P, int d_m, hipStream_t s)
 {
-    const dim3 grid((unsigned)(((size_t)d_m * hd + 255) / 256)), block(256);
-    if (dtype == EL_BF16) hipLaunchKernelGGL(k_pack_wv<bf16_t>, grid, block, 0, s, (const bf16_t *)W, (f16_t *)Wp, d_m, hd);
-    else hipLaunchKernelGGL(k_pack_wv<f16_t>, grid, block, 0, s, (const f16_t *)W, (f16_t *)Wp, d_m, hd);
+    const dim3 grid((unsigned)(((size_t)d_m * d_m + 255) / 256)), block(256);
+    if (kind == kPackWq) hipLaunchKernelGGL((k_pack_cols<uint16_t, uint16_t>), grid, block, 0, s, (const uint16_t *)W, (uint16_t *)P, d_m, d_m);
+    else if (kind == kPackWk) {
+        if (dtype == EL_BF16) hipLaunchKernelGGL(k_pack_wk<bf16_t>, grid, block, 0, s, (const bf16_t *)W, (f16_t *)P, d_m, d_m);
+        else hipLaunchKernelGGL(k_pack_wk<f16_t>, grid, block, 0, s, (const f16_t *)W, (f16_t *)P, d_m, d_m);
+    } else {
+        if (dtype == EL_BF16) hipLaunchKernelGGL((k_pack_cols<bf16_t, f16_t>), grid, block, 0, s, (const bf16_t *)W, (f16_t *)P, d_m, d_m);
+        else hipLaunchKernelGGL((k_pack_cols<f16_t, f16_t>), grid, block, 0, s, (const f16_t *)W, (f16_t *)P, d_m, d_m);
+    }
     return hipGetLastError();
 }
 
-// bf16 -> fp16 copy of a weight matrix (prepare time).
-__global__ void k_bf16_to_f16(const bf16_t *src, f16_t *dst, size_t n)   // src may equal dst
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) dst[i] = (f16_t)to_f32(src[i]);
-}
-
-hipError_t launch_bf16_to_f16(const void *src, void *dst, size_t n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_bf16_to_f16, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const bf16_t *)src, (f16_t *)dst, n);
-    return hipGetLastError();
-}
-
-// Transpose a [rows, cols] matrix of 16- or 32-bit elements (prepare-time packing of W^Q, W^V, W^O).
+// Transpose a [rows, cols] matrix of 16- or 32-bit elements.
 template <typename E>
 __global__ void k_transpose(const E *__restrict__ src, E *__restrict__ dst, int rows, int cols)
 {
@@ -373,122 +440,48 @@ hipError_t launch_transpose(size_t elem, const void *src, void *dst, int rows, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// ---------------------------------------------------------------------------------------------
-// a2, query expansion (Eq. 9's Q_i (W_i^K)^T): ELQ[b, i*x + j, :] = Qp[b*x + j, head i] . (W_i^K)^T with
-// d_k = 64.  One workgroup owns 64 output columns of one head for up to 256 logical rows: its slice
-// of W^K (64 x 64, 8 KB) is read once and stays in registers as MFMA fragments while the four
-// wavefronts walk over the row tiles, so W^K is read once per 256 rows instead of once per 16.
-// Weights are the MFMA's A operand: a lane ends up with four consecutive columns of one row; the
-// 16 x 64 tile then goes through LDS and leaves in the fragment order of the attention core (elq_frag_index),
-// 64 contiguous bytes per row and 32-column fragment.
-template <bool BF>
-__global__ void __launch_bounds__(256)
-k_elq_slab(const GemmArgs g)
-{
-    typedef uint16_t q4 __attribute__((ext_vector_type(4)));
-    constexpr int MT = 4;                               // row tiles per wavefront
-    __shared__ __attribute__((aligned(16))) uint16_t Ct[2][4][MT][16 * 72];   // [plane]; rows 144 bytes apart
-
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int r16 = l & 15, qd = l >> 4;
-    const int n0 = blockIdx.x * 64, head = blockIdx.y;
-    const int mt0 = blockIdx.z * (4 * MT);              // first 16-row tile of this workgroup
-
-    u4 bfr[4][2], afr[MT][2];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            bfr[t][u] = *(const u4 *)((const f16_t *)g.Bt + (size_t)(n0 + 16 * t + r16) * g.ldb + head * 64 + 32 * u + 8 * qd);
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi) {
-        const int m = min((mt0 + w + 4 * mi) * 16 + r16, g.M - 1);
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            afr[mi][u] = *(const u4 *)((const f16_t *)g.A + (size_t)m * g.lda + head * 64 + 32 * u + 8 * qd);
-    }
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, bfr[t][u]), __builtin_bit_cast(h8, afr[mi][u]), acc, 0, 0, 0);
-            q4 hi, lo;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                uint16_t h, l2;
-                split16<BF>(acc[e], h, l2);
-                hi[e] = h; lo[e] = l2;
-            }
-            *(q4 *)(&Ct[0][w][mi][r16 * 72 + 16 * t + 4 * qd]) = hi;
-            *(q4 *)(&Ct[1][w][mi][r16 * 72 + 16 * t + 4 * qd]) = lo;
-        }
-    }
-    // a wavefront reads back only what it wrote: no barrier.  Eight lanes write one 128-byte row piece.
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi) {
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const int row = 8 * hf + (l >> 3), m = (mt0 + w + 4 * mi) * 16 + row;
-            if (m >= g.M) continue;
-            uint16_t *dst = (uint16_t *)g.C + elq_frag_index(m / g.x, head * g.x + m % g.x, n0 + 8 * (l & 7), 0, g.c_rB, g.ldc);
-            *(u4 *)dst = *(const u4 *)(&Ct[0][w][mi][row * 72 + 8 * (l & 7)]);
-            *(u4 *)(dst + 512) = *(const u4 *)(&Ct[1][w][mi][row * 72 + 8 * (l & 7)]);
-        }
-    }
-}
-
 bool gemm_mfma_supported(int dtype, int d_m, int d_k)
 {
     return (dtype == EL_F16 || dtype == EL_BF16) && (d_m == 512 || d_m == 768 || d_m == 1024) && d_k == 64;
 }
 
-static GemmArgs base_args(const Problem &p)
+template <int DM, bool BF>
+static void launch_qelq_t(QelqArgs &a, int num_cus, hipStream_t s)
 {
-    GemmArgs g{};
-    g.scale = 1.0f;
-    g.x = p.beam;
-    g.M = p.B * p.beam;
-    return g;
+    constexpr int FULL = DM / 256;
+    const int tiles = (a.M + 15) / 16, heads = DM / 64;
+    // the columns of EL-Q split over FULL workgroups while all of them run at once
+    const int parts = tiles * heads * FULL <= num_cus ? FULL : 1;
+    a.groups = tile_groups(tiles, heads * parts, num_cus);
+    const dim3 grid = place_grid(heads, parts, a.groups), block(512);
+    if (parts == 1) hipLaunchKernelGGL((k_qelq<DM, BF, FULL>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_qelq<DM, BF, 1>), grid, block, 0, s, a);
 }
 
-template <bool BF, int CK>
-static hipError_t launch_slab(const GemmArgs &g, hipStream_t s)
+// a1 + a2: ELQ[b, i*beam+j, :] = ((q . W_i^Q + b_i^Q) * scale) . (W_i^K)^T      high + low planes in fragment order, Rs
+// rows per b; Qp [B*beam, hd] fp16 as well if `keep_qp`
+hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int Rs, float scale, bool keep_qp, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_gemm_slab<BF, CK>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(256), 0, s, g);
+    QelqArgs a;
+    a.Wq = (const u4 *)ctx->w.WqP; a.Wk = (const u4 *)ctx->w.WkP; a.q = p.queries; a.bq = ctx->w.bq;
+    a.elq = (uint16_t *)ws.ELQ; a.Qp = keep_qp ? (f16_t *)ws.Qp : nullptr; a.scale = scale;
+    a.M = p.B * p.beam; a.x = p.beam; a.Rs = Rs;
+    const bool bf = p.dtype == EL_BF16;
+    if (p.d_m == 1024) { if (bf) launch_qelq_t<1024, true>(a, ctx->num_cus, s); else launch_qelq_t<1024, false>(a, ctx->num_cus, s); }
+    else if (p.d_m == 768) { if (bf) launch_qelq_t<768, true>(a, ctx->num_cus, s); else launch_qelq_t<768, false>(a, ctx->num_cus, s); }
+    else { if (bf) launch_qelq_t<512, true>(a, ctx->num_cus, s); else launch_qelq_t<512, false>(a, ctx->num_cus, s); }
     return hipGetLastError();
 }
 
-// a1: Qp = (q . W^Q + b^Q) * scale        [B*beam, hd] fp16
-hipError_t launch_qproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, float scale, hipStream_t s)
-{
-    GemmArgs g = base_args(p);
-    g.A = p.queries; g.Bt = ctx->w.WqT; g.C = ws.Qp; g.bias = ctx->w.bq; g.scale = scale;
-    g.N = p.hd; g.K = p.d_m; g.lda = p.d_m; g.ldb = p.d_m; g.ldc = p.hd;
-    return p.dtype == EL_BF16 ? launch_slab<true, C_F16>(g, s) : launch_slab<false, C_F16>(g, s);
-}
-
-// a2: ELQ[b, i*beam+j, :] = Qp[b*beam+j, head i] . (W_i^K)^T      high + low planes in fragment order, Rs rows per b
-hipError_t launch_elq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int Rs, hipStream_t s)
-{
-    GemmArgs g = base_args(p);
-    g.A = ws.Qp; g.Bt = ctx->w.WkH; g.C = ws.ELQ;
-    g.N = p.d_m; g.K = p.d_k; g.lda = p.hd; g.ldb = p.hd; g.ldc = p.d_m;
-    g.c_rB = Rs;
-    const dim3 grid(p.d_m / 64, p.heads, (g.M + 255) / 256);
-    if (p.dtype == EL_BF16) hipLaunchKernelGGL(k_elq_slab<true>, grid, dim3(256), 0, s, g);
-    else hipLaunchKernelGGL(k_elq_slab<false>, grid, dim3(256), 0, s, g);
-    return hipGetLastError();
-}
-
-// merge + a6: A[b*beam+j, head i] = (sum_p w_p Xp[b,p,i*beam+j,:]) . W_i^V       fp16   (d_k = 64)
+// merge + a6: A[b*beam+j, head i] = (sum_p w_p Xp[b,p,i*beam+j,:]) . W_i^V       fp16
 template <int DM>
-static void launch_vproj_t(const VprojArgs &a, int nt, hipStream_t s)
+static void launch_vproj_t(VprojArgs &a, int num_cus, hipStream_t s)
 {
-    const dim3 grid(8 * ((a.heads + 7) / 8) * (4 / nt) * a.groups), block(512);
-    if (nt == 1) hipLaunchKernelGGL((k_vproj<DM, 1>), grid, block, 0, s, a);
+    const int tiles = (a.M + 15) / 16, heads = DM / 64;
+    const int parts = tiles * heads <= num_cus / 4 ? 4 : 1;
+    a.groups = tile_groups(tiles, heads * parts, num_cus);
+    const dim3 grid = place_grid(heads, parts, a.groups), block(512);
+    if (parts == 4) hipLaunchKernelGGL((k_vproj<DM, 1>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_vproj<DM, 4>), grid, block, 0, s, a);
 }
 
@@ -498,26 +491,43 @@ hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Wor
     VprojArgs a;
     a.Wp = (const u4 *)ctx->w.WvP; a.Xp = (const f16_t *)ws.Xp; a.ML = ws.ML; a.A = (f16_t *)ws.A;
     a.pm = piece_map(pl, ws, p.B);
-    a.M = p.B * p.beam; a.x = p.beam; a.heads = p.heads; a.Rs = pl.Rs;
-    const int tiles = (a.M + 15) / 16;
-    const int nt = tiles * p.heads <= 64 ? 1 : 4;
-    const int room = ctx->num_cus / p.heads > 0 ? ctx->num_cus / p.heads : 1;
-    a.groups = tiles < room ? tiles : room;
-    if (p.d_m == 1024) launch_vproj_t<1024>(a, nt, s);
-    else if (p.d_m == 768) launch_vproj_t<768>(a, nt, s);
-    else launch_vproj_t<512>(a, nt, s);
+    a.M = p.B * p.beam; a.x = p.beam; a.Rs = pl.Rs;
+    if (p.d_m == 1024) launch_vproj_t<1024>(a, ctx->num_cus, s);
+    else if (p.d_m == 768) launch_vproj_t<768>(a, ctx->num_cus, s);
+    else launch_vproj_t<512>(a, ctx->num_cus, s);
     return hipGetLastError();
 }
 
-// a7: out = A . W^O + c_out
+// a7: out = A . W^O + bias
+template <int DM, typename TO>
+static void launch_oproj_t(OprojArgs &a, int num_cus, hipStream_t s)
+{
+    const int tiles = (a.M + 15) / 16, blocks = DM / 64;
+    const int parts = tiles * blocks * 4 <= num_cus ? 4 : tiles * blocks * 2 <= num_cus ? 2 : 1;
+    a.groups = tile_groups(tiles, blocks * parts, num_cus);
+    const dim3 grid = place_grid(blocks, parts, a.groups), block(512);
+    if (parts == 4) hipLaunchKernelGGL((k_oproj<DM, 1, TO>), grid, block, 0, s, a);
+    else if (parts == 2) hipLaunchKernelGGL((k_oproj<DM, 2, TO>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_oproj<DM, 4, TO>), grid, block, 0, s, a);
+}
+
+template <typename TO>
+static void launch_oproj_d(OprojArgs &a, int d_m, int num_cus, hipStream_t s)
+{
+    if (d_m == 1024) launch_oproj_t<1024, TO>(a, num_cus, s);
+    else if (d_m == 768) launch_oproj_t<768, TO>(a, num_cus, s);
+    else launch_oproj_t<512, TO>(a, num_cus, s);
+}
+
 hipError_t launch_oproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const float *bias32, hipStream_t s)
 {
-    GemmArgs g = base_args(p);
-    g.A = ws.A; g.Bt = ctx->w.WoT; g.C = p.out; g.bias32 = bias32;
-    g.N = p.d_m; g.K = p.hd; g.lda = p.hd; g.ldb = p.hd; g.ldc = p.d_m;
-    if (p.out_dtype == EL_F32) return launch_slab<false, C_F32>(g, s);
-    if (p.dtype == EL_BF16) return launch_slab<false, C_BF16>(g, s);
-    return launch_slab<false, C_F16>(g, s);
+    OprojArgs a;
+    a.Wp = (const u4 *)ctx->w.WoP; a.A = (const f16_t *)ws.A; a.bias32 = bias32; a.out = p.out;
+    a.M = p.B * p.beam;
+    if (p.out_dtype == EL_F32) launch_oproj_d<float>(a, p.d_m, ctx->num_cus, s);
+    else if (p.out_dtype == EL_BF16) launch_oproj_d<bf16_t>(a, p.d_m, ctx->num_cus, s);
+    else launch_oproj_d<f16_t>(a, p.d_m, ctx->num_cus, s);
+    return hipGetLastError();
 }
 
 } // namespace el
