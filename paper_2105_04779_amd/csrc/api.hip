@@ -58,7 +58,7 @@ WsLayout ws_layout_for(const el_attn_ctx *c, int batch, int beam)
     L.off_Xp = o;  o = align_up(o + mb * kMaxParts * Rp * d_m * sizeof(float), 256);
     L.off_ML = o;  o = align_up(o + mb * kMaxParts * Rp * 2 * sizeof(float), 256);
     L.off_Xn = o;  o = align_up(o + mb * Rp * d_m * sizeof(float), 256);
-    L.off_A = o;   o = align_up(o + mb * mx * hd * sizeof(float), 256);
+    L.off_A = o;   o = align_up(o + (mb * mx < 16 ? 16 : mb * mx) * hd * sizeof(float), 256);      // fp16 rows are padded to 16
     L.off_E = o;   o = align_up(o + (mb + 1) * sizeof(int32_t), 256);
     L.total = o;
     L.slots = batch * kMaxParts;

@@ -47,7 +47,7 @@ __global__ void k_merge_exp2(const f16_t *__restrict__ Xp, const float *__restri
         const float mp = ML[rowi * 2], lp = ML[rowi * 2 + 1];
         if (lp > 0.f) {
             const float wgt = exp2f(mp - M) * lp;
-            num = fmaf(wgt, (float)Xp[rowi * d_m + d], num);
+            num = fmaf(wgt, (float)Xp[((size_t)slot0 + p) * Rs * d_m + frag16_index(r, d, d_m)], num);
             den += wgt;
         }
     }

@@ -576,9 +576,10 @@ k_core_stream(const StreamArgs a)
             const float inv = Linv[(pos & 1) * 32 + rowc];
             // A lane holds columns 8 q4 + 4 kg .. + 3 of every 32-column block of its row.  The two lanes of a row
             // trade neighbouring groups (v_permlane32_swap), so that each holds eight consecutive columns and a
-            // store instruction writes 32 contiguous bytes of each row instead of two pieces of 8.
+            // store instruction writes 32 contiguous bytes of each row instead of two pieces of 8, and the next one the
+            // other half of the same fragment rows.
             const bool keep = active && row0 + r32 < a.R;
-            f16_t *x_out = a.Xp + (slot * a.Rs + row0 + rowc) * DM + DS * v + 8 * kg;
+            f16_t *x_out = a.Xp + slot * a.Rs * DM + frag16_index(row0 + rowc, DS * v + 8 * kg, DM);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -591,7 +592,7 @@ k_core_stream(const StreamArgs a)
                         const auto sw = __builtin_amdgcn_permlane32_swap(ga[h], gb[h], false, false);
                         ga[h] = sw[0]; gb[h] = sw[1];
                     }
-                    if (keep) *(u4 *)(x_out + 32 * mb + 16 * qp) = u4{ga[0], ga[1], gb[0], gb[1]};
+                    if (keep) *(u4 *)(x_out + 512 * mb + 16 * qp) = u4{ga[0], ga[1], gb[0], gb[1]};
                 }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)

@@ -89,6 +89,14 @@ __host__ __device__ __forceinline__ size_t elq_frag_index(int b, int row, int co
     return frag * 512 + (size_t)(row & 15) * 32 + (col & 31);
 }
 
+// Row-major 16-bit matrices [rows, K] that a 16x16x32 MFMA reads as 16-row operands are kept in its fragment order too
+// (the pieces X of the core, the head outputs A): 1 KB fragments of 16 rows x 32 columns, [row / 16][column / 32], so
+// that an operand load of a wavefront is contiguous instead of 16 segments of 64 bytes.  Rows are padded to 16.
+__host__ __device__ __forceinline__ size_t frag16_index(int row, int col, int K)
+{
+    return ((size_t)(row >> 4) * (K >> 5) + (col >> 5)) * 512 + (size_t)(row & 15) * 32 + (col & 31);
+}
+
 // ---- compile-time limits -----------------------------------------------------------------
 constexpr int kMaxParts = 8;        // key-range partials per (batch element, row) the workspace holds
 constexpr int kGenericMaxDm = 8192; // widest d_model the generic core kernel covers
@@ -155,10 +163,10 @@ struct Problem {
 struct Workspace {
     float *Qp;      // [B*beam, hd]                 a1 result: fp32 (generic) or fp16 (MFMA GEMMs), scaled
     void *ELQ;      // [B, Rpad, d_m]               fp32 (generic) or fp16 (MFMA core)
-    float *Xp;      // [B, parts, Rpad, d_m]        un-normalised partial weighted sums
+    float *Xp;      // [B, parts, Rpad, d_m]        partial weighted sums: fp16 in fragment order (MFMA), fp32 (generic)
     float *ML;      // [B, parts, Rpad, 2]          running max and sum of each partial
     float *Xn;      // [B, R, d_m]                  merged, normalised weighted sums (generic path)
-    float *A;       // [B*beam, hd]                 a6 result: fp32 (generic) or fp16 (MFMA GEMMs)
+    float *A;       // [B*beam, hd]                 a6 result: fp32 (generic) or fp16 in fragment order (MFMA projections)
     int32_t *E;     // [B+1]                        prefix sum of tile counts (flattened cut of the MFMA core)
     int slots;      // pieces Xp and ML have room for (batch elements the workspace was laid out for x kMaxParts)
 };
@@ -211,7 +219,7 @@ bool small_step_applies(const Problem &p);
 hipError_t launch_small_step(const el_attn_ctx *ctx, const Problem &p, hipStream_t s);
 // segment form (decoder-only models): statistics + biased head outputs of one segment; merge of several
 struct SegFinishArgs {
-    const void *A;            // [rows, hd] fp16 or fp32: the segment's normalised head outputs without b^V
+    const void *A;            // [rows, hd] fp16 (in fragment order) or fp32: the segment's normalised head outputs without b^V
     const void *Qp;           // [rows, hd] fp16 or fp32: projected queries as a1 left them (scaled)
     const float *ML;          // [slot, Rstride, 2] statistics of the pieces (see PieceMap)
     PieceMap pm;
@@ -224,7 +232,7 @@ constexpr int kMaxSegments = 4;
 struct SegMergeArgs {
     const float *A[kMaxSegments];
     const float *lse[kMaxSegments];
-    void *A_out;              // [rows, hd] fp16 or fp32
+    void *A_out;              // [rows, hd] fp16 (in fragment order) or fp32
     int nseg, heads, d_k, hd;
 };
 hipError_t launch_seg_finish(const SegFinishArgs &a, bool a_f16, bool qp_f16, int rows, hipStream_t s);
@@ -249,7 +257,7 @@ struct StreamArgs {
     const int32_t *lengths;
     const uint16_t *elq;     // EL-Q as high + low 16-bit planes in the storage type, scaled by log2(e)/sqrt(d_k),
                              //   in fragment order (see elq_frag_index)
-    f16_t *Xp;               // [slot, Rs, DM] fp16, each piece already divided by its own sum
+    f16_t *Xp;               // [slot, Rs, DM] fp16, each piece already divided by its own sum, in fragment order (frag16_index)
     float *ML;               // [slot, Rs, 2]  (reference max in log2 units, sum)
     int32_t *E;              // [B+1] prefix sum of tile counts (flat cut), written by the kernel; may be null
     int n, B, R, Rs, nblocks;

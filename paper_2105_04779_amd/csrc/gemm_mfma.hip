@@ -183,9 +183,9 @@ k_qelq(const QelqArgs a)
 // 512 rows, one piece each: 19.7 -> 10.2; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 10.0; 4 rows: 8.6 -> 5.4.
 struct VprojArgs {
     const u4 *Wp;          // (W^V) in fragments: [head][k / 32][column / 16 % 4][lane]
-    const f16_t *Xp;       // normalised fp16 pieces [slot, Rs, d_m]
+    const f16_t *Xp;       // normalised fp16 pieces [slot, Rs, d_m] in fragment order
     const float *ML;       // [slot, Rs, 2]
-    f16_t *A;              // [M, d_m]
+    f16_t *A;              // [M, d_m] in fragment order
     PieceMap pm;
     int M, x, Rs, groups;
 };
@@ -221,6 +221,7 @@ k_vproj(const VprojArgs a)
         int slot0, np;
         piece_range(a.pm, cut, b, E_b, E_b1, slot0, np);
         const size_t row0 = (size_t)slot0 * a.Rs + head * a.x + j;
+        const f16_t *x0 = a.Xp + (size_t)slot0 * a.Rs * DM + frag16_index(head * a.x + j, 32 * KS * w + 8 * q, DM);
         int np_max = np;                                 // most pieces among the 16 rows (uniform)
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) np_max = max(np_max, __shfl_xor(np_max, o, 64));
@@ -236,10 +237,10 @@ k_vproj(const VprojArgs a)
 #pragma unroll
             for (int p = 0; p < PC; ++p) {
                 if (p0 + p >= np_max) { ml[p] = f2{0.f, 0.f}; continue; }           // uniform
-                const size_t row = row0 + (size_t)min(p0 + p, np - 1) * a.Rs;
-                ml[p] = *(const f2 *)(a.ML + row * 2);
+                const size_t step = (size_t)min(p0 + p, np - 1) * a.Rs;
+                ml[p] = *(const f2 *)(a.ML + (row0 + step) * 2);
 #pragma unroll
-                for (int s = 0; s < KS; ++s) xv[p][s] = *(const h8 *)(a.Xp + row * DM + 32 * (KS * w + s) + 8 * q);
+                for (int s = 0; s < KS; ++s) xv[p][s] = *(const h8 *)(x0 + step * DM + 512 * s);
             }
             if (p0 + PC >= np_max && tile + a.groups < tiles) {                     // the next tile's table entries
                 row_of(tile + a.groups, b, j);
@@ -295,7 +296,7 @@ k_vproj(const VprojArgs a)
             for (int s = 0; s < 8; ++s) sum += red[parity][(s * NT + w) * 64 + l];
             const int mm = 16 * tile + r16;
             if (mm < a.M)
-                *(h4 *)(a.A + (size_t)mm * DM + head * 64 + 16 * (nb * NT + w) + 4 * q) =
+                *(h4 *)(a.A + frag16_index(mm, head * 64 + 16 * (nb * NT + w) + 4 * q, DM)) =
                     h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
         }
         parity ^= 1;
@@ -308,7 +309,7 @@ k_vproj(const VprojArgs a)
 // rows 10.1 -> 7.4, 1280 rows 20.2 -> 12.0.
 struct OprojArgs {
     const u4 *Wp;          // (W^O) in fragments: [column / 64][k / 32][column / 16 % 4][lane]
-    const f16_t *A;        // [M, d_m]
+    const f16_t *A;        // [M, d_m] in fragment order
     const float *bias32;
     void *out;
     int M, groups;
@@ -327,9 +328,9 @@ k_oproj(const OprojArgs a)
     const int tiles = (a.M + 15) >> 4;
     u4 xa[KS], wo[KS][NT];
     auto load_rows = [&](int tile) {
-        const f16_t *row = a.A + (size_t)min(16 * tile + r16, a.M - 1) * DM + 8 * q;
+        const f16_t *row = a.A + frag16_index(16 * tile + r16, 32 * KS * w + 8 * q, DM);      // (rows past M: padding, their results are dropped)
 #pragma unroll
-        for (int s = 0; s < KS; ++s) xa[s] = *(const u4 *)(row + 32 * (KS * w + s));
+        for (int s = 0; s < KS; ++s) xa[s] = *(const u4 *)(row + 512 * s);
     };
     load_rows(pl.group);
 #pragma unroll

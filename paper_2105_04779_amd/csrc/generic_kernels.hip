@@ -603,13 +603,17 @@ hipError_t launch_vec_f32(int dtype, const void *src, float *dst, int n, hipStre
 //                               is part of the scores ordinary attention reports
 // The key-range statistics (reference exponent, sum relative to it) are folded by the log-sum-exp rule
 // exactly as the merge of the partials does.
+// fp16 head outputs are in fragment order
+template <typename T>
+__device__ __forceinline__ size_t head_index(int m, int cg, int hd) { return sizeof(T) == 2 ? frag16_index(m, cg, hd) : (size_t)m * hd + cg; }
+
 template <typename TA, typename TQ>
 __global__ void k_seg_finish(const SegFinishArgs a)
 {
     const int cg = blockIdx.x * kBlock + threadIdx.x;
     const int m = blockIdx.y;
     if (cg >= a.hd) return;
-    a.seg_A[(size_t)m * a.hd + cg] = to_f32(((const TA *)a.A)[(size_t)m * a.hd + cg]) + a.bv32[cg];
+    a.seg_A[(size_t)m * a.hd + cg] = to_f32(((const TA *)a.A)[head_index<TA>(m, cg, a.hd)]) + a.bv32[cg];
     if (cg % a.d_k != 0) return;
     const int i = cg / a.d_k, b = m / a.beam, j = m % a.beam, r = i * a.beam + j;
     int slot0, np;
@@ -663,7 +667,7 @@ __global__ void k_seg_merge(const SegMergeArgs a)
             den += w;
         }
     }
-    from_f32(den > 0.f ? num / den : 0.f, (TO *)a.A_out + (size_t)m * a.hd + cg);
+    from_f32(den > 0.f ? num / den : 0.f, (TO *)a.A_out + head_index<TO>(m, cg, a.hd));
 }
 
 hipError_t launch_seg_merge(const SegMergeArgs &a, bool out_f16, int rows, hipStream_t s)
