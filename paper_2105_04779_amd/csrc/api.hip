@@ -42,7 +42,7 @@ bool valid_dtype(int dt) { return dt == EL_F32 || dt == EL_F16 || dt == EL_BF16;
 int round_up64(int v) { return (v + 63) / 64 * 64; }
 
 struct WsLayout {
-    size_t off_Qp, off_ELQ, off_Xp, off_ML, off_Xn, off_A, off_E, total;
+    size_t off_Qp, off_ELQ, off_Xp, off_ML, off_Xn, off_A, off_spans, off_pieces, total;
     int slots;
 };
 
@@ -52,16 +52,19 @@ WsLayout ws_layout_for(const el_attn_ctx *c, int batch, int beam)
     const size_t mb = (size_t)batch, mx = (size_t)beam;
     const size_t d_m = (size_t)c->cfg.d_model, hd = (size_t)c->hd, Rp = (size_t)round_up64(c->cfg.heads * beam);
     WsLayout L;
+    // pieces are fp16 on the MFMA path: twice as many in the same bytes
+    const int parts = c->use_mfma_core ? kMaxParts : kMaxPartsGeneric;
     size_t o = 0;
     L.off_Qp = o;  o = align_up(o + mb * mx * hd * sizeof(float), 256);
     L.off_ELQ = o; o = align_up(o + mb * Rp * d_m * sizeof(float), 256);
-    L.off_Xp = o;  o = align_up(o + mb * kMaxParts * Rp * d_m * sizeof(float), 256);
-    L.off_ML = o;  o = align_up(o + mb * kMaxParts * Rp * 2 * sizeof(float), 256);
+    L.off_Xp = o;  o = align_up(o + mb * kMaxPartsGeneric * Rp * d_m * sizeof(float), 256);
+    L.off_ML = o;  o = align_up(o + mb * parts * Rp * 2 * sizeof(float), 256);
     L.off_Xn = o;  o = align_up(o + mb * Rp * d_m * sizeof(float), 256);
     L.off_A = o;   o = align_up(o + (mb * mx < 16 ? 16 : mb * mx) * hd * sizeof(float), 256);      // fp16 rows are padded to 16
-    L.off_E = o;   o = align_up(o + (mb + 1) * sizeof(int32_t), 256);
+    L.slots = batch * parts;
+    L.off_spans = o;  o = align_up(o + (size_t)L.slots * 2 * sizeof(int4), 256);
+    L.off_pieces = o; o = align_up(o + mb * sizeof(int2), 256);
     L.total = o;
-    L.slots = batch * kMaxParts;
     return L;
 }
 
@@ -78,7 +81,8 @@ Workspace carve_from(void *ws_base, const WsLayout &L)
     w.ML = (float *)(base + L.off_ML);
     w.Xn = (float *)(base + L.off_Xn);
     w.A = (float *)(base + L.off_A);
-    w.E = (int32_t *)(base + L.off_E);
+    w.spans = (int4 *)(base + L.off_spans);
+    w.pieces = (int2 *)(base + L.off_pieces);
     w.slots = L.slots;
     return w;
 }
@@ -103,7 +107,7 @@ int auto_parts_generic(const Problem &p)
     if (rows < 1024) parts = (int)((1024 + rows - 1) / rows);
     const int by_len = p.n / 64 > 0 ? p.n / 64 : 1;
     if (parts > by_len) parts = by_len;
-    if (parts > kMaxParts) parts = kMaxParts;
+    if (parts > kMaxPartsGeneric) parts = kMaxPartsGeneric;
     return parts < 1 ? 1 : parts;
 }
 
@@ -179,14 +183,15 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
     constexpr float kLn2 = 0.6931471805599453f;
     if (el_attn_uses_mfma(ctx)) {
         const CorePlan pl = plan_core_mfma(p, ctx->splits_override, ctx->nrg_override, ctx->num_cus, ws.slots);
-        fmt->pm = piece_map(pl, ws, p.B); fmt->Rstride = pl.Rs; fmt->ml_to_nat = kLn2;
+        fmt->pm = piece_map(ws); fmt->Rstride = pl.Rs; fmt->ml_to_nat = kLn2;
         // a1 + a2: expanded queries in fp16, pre-multiplied by log2(e)/sqrt(d_k) so the core's softmax is an exp2
         const float qscale = 1.4426950408889634f / sqrtf((float)p.d_k);
         if (ctx->use_mfma_gemm) {
-            if (launch_qelq_mfma(ctx, p, ws, pl.Rs, qscale, segment, s) != hipSuccess) return EL_ERR_HIP;
+            if (launch_qelq_mfma(ctx, p, ws, pl, qscale, segment, s) != hipSuccess) return EL_ERR_HIP;
         } else {
             if (launch_qproj_generic(ctx, p, ws, s) != hipSuccess) return EL_ERR_HIP;
             if (launch_elq_f16(ctx, p, ws, pl, s) != hipSuccess) return EL_ERR_HIP;
+            if (launch_cut(cut_args(p, pl, ws), s) != hipSuccess) return EL_ERR_HIP;
         }
         // a3-a5 on MFMA; key-range partials
         const bool timed = ctx->ev && ctx->ev_used < ctx->ev_cap;
@@ -204,8 +209,8 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
         if (launch_qproj_generic(ctx, p, ws, s) != hipSuccess) return EL_ERR_HIP;
         if (launch_elq_generic(ctx, p, ws.Qp, (float *)ws.ELQ, s) != hipSuccess) return EL_ERR_HIP;
         const bool scored = scores_fit(p);
-        const int parts = scored ? 1 : ctx->splits_override ? ctx->splits_override : auto_parts_generic(p);
-        fmt->pm.E = nullptr; fmt->pm.parts = parts; fmt->pm.G = 0; fmt->pm.lfloor = 0; fmt->pm.B = p.B; fmt->pm.kcost = 0;
+        const int parts = scored ? 1 : ctx->splits_override ? (ctx->splits_override < kMaxPartsGeneric ? ctx->splits_override : kMaxPartsGeneric) : auto_parts_generic(p);
+        fmt->pm.table = nullptr; fmt->pm.parts = parts;
         fmt->Rstride = p.R; fmt->ml_to_nat = 1.f;
         const bool timed = ctx->ev && ctx->ev_used < ctx->ev_cap;
         if (timed && hipEventRecord(ctx->ev[2 * ctx->ev_used], s) != hipSuccess) return EL_ERR_HIP;
@@ -297,9 +302,9 @@ el_status el_attn_prepare(const el_attn_config *cfg,
     c->cfg = *cfg;
     c->hd = cfg->heads * cfg->d_k;
     c->Rpad_max = round_up64(cfg->heads * cfg->max_beam);
-    c->ws_need = ws_layout(c).total;
     c->use_mfma_core = core_mfma_supported(cfg->dtype, cfg->d_model) && !(cfg->flags & EL_FLAG_FORCE_GENERIC) ? 1 : 0;
     c->use_mfma_gemm = (c->use_mfma_core && gemm_mfma_supported(cfg->dtype, cfg->d_model, cfg->d_k)) ? 1 : 0;
+    c->ws_need = ws_layout(c).total;
 
     hipStream_t s = (hipStream_t)stream;
     forget_foreign_errors();

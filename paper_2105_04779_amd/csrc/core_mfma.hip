@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdlib>
 #include "el_internal.h"
+#include "cut.h"
 
 namespace el {
 
@@ -61,14 +62,15 @@ bool core_mfma_supported(int dtype, int d_m)
     return (dtype == EL_F16 || dtype == EL_BF16) && (d_m == 512 || d_m == 768 || d_m == 1024);
 }
 
-// How the work is cut.  A workgroup takes 16 or 32 of the R = heads x beams rows that share one H (the
+// How much the work is cut.  A workgroup takes 16 or 32 of the R = heads x beams rows that share one H (the
 // row blocks of one span read the same tiles, the second one from L2) and one span of the list of all
 // valid 16-row tiles.  Lengths live on the device, so the host fixes only the number of spans G: one
 // workgroup per compute unit when the longest possible list gives every span at least kMinSpan tiles,
-// fewer otherwise (but not fewer than one span per batch element); the kernel derives the span length from the actual lengths.  The floor on the span
-// length keeps every element within kMaxParts pieces.  Batches beyond kScanMax elements are not cut as
-// one list: one workgroup per (element, row block), scheduled by the hardware.
-constexpr int kMinSpan = 8;
+// fewer otherwise (but not fewer than one span per batch element); build_cut lays the spans over the actual lengths.
+// Batches beyond kScanMax elements are not cut: one workgroup per (element, row block), scheduled by the hardware.
+// With 4 tiles instead of 8 (and twice the piece slots) the core of one sentence of 613 positions and 64 rows takes
+// 12.6 instead of 18.3 us, and the merge of its nine pieces no longer than that of four.
+constexpr int kMinSpan = 4;
 // What moving on to the next batch element costs a workgroup, in tiles of streaming time: the expanded queries of
 // the new element (128 KB for 32 rows) and the write-out of the finished piece.  Spans that cross an element hold
 // that many tiles fewer, so that all workgroups finish together (measured on 64 ragged inputs of 512-1024 rows:
@@ -82,12 +84,9 @@ CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override,
     if (nrg_override == 1) pl.nrg = 1;
     pl.nblocks = (p.R + 16 * pl.nrg - 1) / (16 * pl.nrg);
     pl.Rs = pl.nblocks * 16 * pl.nrg;
+    pl.kcost = kBoundaryCost;
     const int tiles = (p.n + 15) / 16;
-    pl.flat = p.B <= kScanMax && max_slots - p.B >= 1 ? 1 : 0;
-    if (!pl.flat) {
-        pl.G = p.B; pl.lfloor = tiles; pl.kcost = 0; pl.parts = 1; pl.slots = p.B;
-        return pl;
-    }
+    if (p.B > kScanMax) { pl.G = p.B; return pl; }
     long G;
     if (splits_override > 0) {
         G = (long)p.B * splits_override;                   // about that many pieces per element
@@ -101,21 +100,39 @@ CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override,
         G = by_cu < by_len ? by_cu : by_len;
     }
     if (G > max_slots - p.B) G = max_slots - p.B;
+    if (G > kSpanMax) G = kSpanMax;
     if (G < 1) G = 1;
     pl.G = (int)G;
-    pl.lfloor = (tiles + kMaxParts - 2) / (kMaxParts - 1);
-    pl.kcost = kBoundaryCost;
-    pl.parts = kMaxParts;
-    pl.slots = pl.G + p.B;
     return pl;
 }
 
-PieceMap piece_map(const CorePlan &pl, const Workspace &ws, int B)
+CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws)
+{
+    CutArgs c;
+    c.lengths = p.lengths; c.spans = ws.spans; c.pieces = ws.pieces;
+    c.n = p.n; c.B = p.B; c.G = pl.G; c.kcost = pl.kcost;
+    return c;
+}
+
+PieceMap piece_map(const Workspace &ws)
 {
     PieceMap m;
-    m.E = pl.flat ? ws.E : nullptr;
-    m.parts = 1; m.G = pl.G; m.lfloor = pl.lfloor; m.B = B; m.kcost = pl.kcost;
+    m.table = ws.pieces; m.parts = 1;
     return m;
+}
+
+__global__ void __launch_bounds__(64) k_cut(const CutArgs c)
+{
+    __shared__ CutScratch t;
+    CutLengths len;
+    load_cut_lengths(c, threadIdx.x, len);
+    build_cut(c, len, t, threadIdx.x);
+}
+
+hipError_t launch_cut(const CutArgs &c, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_cut, dim3(1), dim3(64), 0, s, c);
+    return hipGetLastError();
 }
 
 hipError_t launch_elq_f16(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl,
@@ -138,9 +155,8 @@ hipError_t launch_core_mfma(const el_attn_ctx *, const Problem &p, const Workspa
     StreamArgs a;
     a.H = p.H; a.h_stride = p.H_batch_stride; a.lengths = p.lengths;
     a.elq = (const uint16_t *)ws.ELQ;
-    a.Xp = (f16_t *)ws.Xp; a.ML = ws.ML; a.E = pl.flat ? ws.E : nullptr;
-    a.n = p.n; a.B = p.B; a.R = p.R; a.Rs = pl.Rs; a.nblocks = pl.nblocks;
-    a.flat = pl.flat; a.G = pl.G; a.lfloor = pl.lfloor; a.kcost = pl.kcost;
+    a.Xp = (f16_t *)ws.Xp; a.ML = ws.ML; a.spans = ws.spans;
+    a.n = p.n; a.B = p.B; a.R = p.R; a.Rs = pl.Rs; a.nblocks = pl.nblocks; a.G = pl.G;
     // H is read once per step; when a batch of it is larger than the 256 MB memory-side cache, keeping its lines
     // out of the caches leaves them to the data that is re-read and raises the streaming rate (measured, core
     // kernel: 1 GB of per-beam histories 216 -> 184 us; 640 MB shared by two row blocks 149 -> 144 us).  Below
@@ -153,7 +169,7 @@ hipError_t launch_merge_exp2(const el_attn_ctx *, const Problem &p, const Worksp
                              hipStream_t s)
 {
     hipLaunchKernelGGL(k_merge_exp2, dim3((p.d_m + 255) / 256, p.R, p.B), dim3(256), 0, s,
-                       (const f16_t *)ws.Xp, (const float *)ws.ML, ws.Xn, p.d_m, p.R, pl.Rs, piece_map(pl, ws, p.B));
+                       (const f16_t *)ws.Xp, (const float *)ws.ML, ws.Xn, p.d_m, p.R, pl.Rs, piece_map(ws));
     return hipGetLastError();
 }
 

@@ -2,13 +2,13 @@
 // products over the hidden states and the softmax between them; Eq. 9 with K = V = H).
 //
 // The valid 16-row tiles of all batch elements form one list (element 0's tiles, then element 1's,
-// ...).  The list is cut into G equal spans; a workgroup walks one span for one block of 16 or 32
+// ...).  The list is cut into G spans (cut.h); a workgroup walks one span for one block of 16 or 32
 // expanded-query rows, so every compute unit streams the same number of bytes whatever the lengths
 // are.  Where a span crosses from one batch element to the next the workgroup closes a PIECE: it
 // writes that element's partial result (normalised by its own sum, with the softmax statistics) to
-// slot `span + element` and goes on with the next element without draining its pipeline; a6 merges
-// an element's pieces by the log-sum-exp rule.  An element that lies inside one span has one piece
-// and needs no merge.
+// its slot (consecutive along a span) and goes on with the next element without draining its
+// pipeline; a6 merges an element's pieces by the log-sum-exp rule.  An element that lies inside one
+// span has one piece and needs no merge.
 //
 // On this hardware an LDS instruction holds its wavefront for about as long as an MFMA does (~32
 // clocks), and a wavefront issues in order, so the work of a tile is spread over eight wavefronts,
@@ -81,13 +81,6 @@ template <> struct Mma<true> {
     static __device__ __forceinline__ f16v s32(u4 a, u4 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0); }
 };
 
-__device__ __forceinline__ int wave_sum(int v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return __builtin_amdgcn_readfirstlane(v);
-}
-
 } // namespace
 
 template <int DM, bool BF16, int RG, bool NT>
@@ -121,7 +114,7 @@ k_core_stream(const StreamArgs a)
     __shared__ float Ax[2 * 32];                                              // per-row rescale factor [tile parity][row]
     __shared__ float Linv[2 * 32];                                            // per-row 1/sum of a piece [parity of its last tile][row]
     __shared__ __attribute__((aligned(1024))) char Dz[ROWB];                  // where fetches of rows that do not exist land
-    __shared__ int Lt[kScanMax];                                              // clamped lengths of all batch elements (flattened cut)
+    __shared__ int Lt[kScanMax];                                              // lengths of the elements after the span's fourth
 
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -134,68 +127,25 @@ k_core_stream(const StreamArgs a)
     const int per_xcd = (nwg + 7) >> 3;
     const int place = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (place >= nwg) return;
-    const int span = place / a.nblocks, rb = place % a.nblocks;   // (the piece slots are span + element: see PieceMap)
+    const int span = place / a.nblocks, rb = place % a.nblocks;
     const int row0 = rb * ROWS;                      // first expanded-query row of this workgroup
 
-    auto clamp_len = [&](int v) { return min(max(v, 1), a.n); };
-
-    // ---- where this span starts: element b0, tile kt0 of it, nspan tiles in all ----
-    int b0, kt0, nspan, len0;
-    if (a.flat) {
-        // Tiles on the cost axis (see PieceMap): element b starts at E[b] + kcost * b with a gap of kcost units, then
-        // its tiles.  This span is [c0, c1) of that axis.
-        for (int i = tid; i < a.B; i += 512) Lt[i] = clamp_len(a.lengths ? a.lengths[i] : a.n);
-        __syncthreads();
-        int part = 0;
-        for (int i = l; i < a.B; i += 64) part += (Lt[i] + kTile - 1) / kTile;
-        const int total = wave_sum(part);
-        const int cspan = flat_cspan(total, a.B, a.G, a.lfloor, a.kcost);
-        const int c0 = span * cspan, c1 = min(c0 + cspan, total + a.kcost * a.B);
-        const bool writer = place == 0 && w == 0 && a.E != nullptr;       // one wavefront publishes the prefix for a6
-        if (writer && l == 0) a.E[0] = 0;
-        // tiles_before(c): tiles at coordinates below c; for c0 also the element and tile the span starts at
-        b0 = -1; kt0 = 0;
-        int t_lo = 0, t_hi = -1, run = 0;                                 // run: tiles of the chunks already scanned
-        for (int c = 0; c * 64 < a.B; ++c) {
-            const int i = c * 64 + l;
-            const int mine = i < a.B ? (Lt[i] + kTile - 1) / kTile : 0;
-            int inc = mine;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int up = __shfl_up(inc, o, 64);
-                if (l >= o) inc += up;
-            }
-            inc += run;                                                   // tiles of elements 0..i
-            if (writer && i < a.B) a.E[i + 1] = inc;
-            const int cend = inc + a.kcost * (i + 1);                    // one past the last coordinate of element i
-            // the first element that ends beyond c0 holds the span's first tile (or the gap before its tiles)
-            const int n0 = __builtin_popcountll(__ballot(i < a.B && cend <= c0));
-            if (b0 < 0 && n0 < 64 && c * 64 + n0 < a.B) {
-                b0 = c * 64 + n0;
-                const int tiles_b = __shfl(mine, n0, 64), end_b = __shfl(cend, n0, 64);
-                kt0 = max(c0 - (end_b - tiles_b), 0);                     // coordinate of its tile 0 is end_b - tiles_b
-                t_lo = __shfl(inc, n0, 64) - tiles_b + kt0;
-            }
-            const int n1 = __builtin_popcountll(__ballot(i < a.B && cend <= c1));
-            if (t_hi < 0 && n1 < 64 && c * 64 + n1 < a.B) {
-                const int tiles_b = __shfl(mine, n1, 64), end_b = __shfl(cend, n1, 64);
-                t_hi = __shfl(inc, n1, 64) - tiles_b + max(c1 - (end_b - tiles_b), 0);
-            }
-            run = __shfl(inc, 63, 64);
-        }
-        if (t_hi < 0) t_hi = total;                                      // c1 is the end of the axis
-        b0 = __builtin_amdgcn_readfirstlane(b0);
-        kt0 = __builtin_amdgcn_readfirstlane(kt0);
-        nspan = __builtin_amdgcn_readfirstlane(t_hi - t_lo);
-        if (nspan <= 0 || b0 < 0) return;            // the axis is shorter than G spans of the floor length, or the span is all gap
-        len0 = __builtin_amdgcn_readfirstlane(Lt[b0]);
-    } else {
-        b0 = span; kt0 = 0;
-        len0 = __builtin_amdgcn_readfirstlane(clamp_len(a.lengths ? a.lengths[b0] : a.n));
-        nspan = (len0 + kTile - 1) / kTile;
-    }
-    // length of an element the span moves on to (only the flattened cut crosses elements)
-    auto next_len = [&](int b) -> int { return __builtin_amdgcn_readfirstlane(a.flat && b < a.B ? Lt[b] : kTile); };
+    // ---- where this span starts: element b0, tile kt0 of it, nspan tiles in all, the slot of its first piece ----
+    typedef int i8v __attribute__((ext_vector_type(8)));
+    const i8v sp = ((const __attribute__((address_space(4))) i8v *)(uintptr_t)a.spans)[span];     // (a scalar load: the table was written by an earlier kernel)
+    const int b0 = sp[0], kt0 = sp[1], nspan = sp[2], len0 = sp[4];
+    if (nspan <= 0) return;                          // fewer tiles than spans, or a span that is all gap
+    const int slot_b = sp[3] - b0;                    // slot of element b's piece = slot_b + b
+    // Lengths of the elements the span moves on to: the table has the first four, the others (at most one per tile) are
+    // fetched while the first tiles are on their way and are read after the first barrier.
+    for (int i = 4 + tid; i < min(nspan + 1, a.B - b0) && i < kScanMax; i += 512)
+        Lt[i] = a.lengths ? min(max(a.lengths[b0 + i], 1), a.n) : a.n;
+    const int lane_len = l == 1 ? sp[5] : l == 2 ? sp[6] : sp[7];                // lane d: length of the span's element d (1 to 3)
+    auto next_len = [&](int b) -> int {
+        const int d = b - b0;
+        if (d <= 3) return __builtin_amdgcn_readlane(lane_len, d);
+        return __builtin_amdgcn_readfirstlane(d <= nspan && b < a.B ? Lt[d] : kTile);
+    };
     // a cursor over the span's tiles: element, tile of it, the element's length
     struct Cursor {
         int b, kt, len;
@@ -347,7 +297,7 @@ k_core_stream(const StreamArgs a)
             if (l % LPR == 0) {
                 Linv[(pos & 1) * 32 + srow] = l_tot > 0.f ? 1.0f / l_tot : 0.f;
                 if (row0 + srow < a.R) {
-                    float *ml_out = a.ML + ((size_t)(a.flat ? span + b : b) * a.Rs + row0 + srow) * 2;
+                    float *ml_out = a.ML + ((size_t)(slot_b + b) * a.Rs + row0 + srow) * 2;
                     ml_out[0] = m_ref; ml_out[1] = l_tot;
                 }
             }
@@ -572,7 +522,7 @@ k_core_stream(const StreamArgs a)
         // accumulators (a lane holds four consecutive columns of one row: 8-byte stores, two lanes side by side),
         // and a fresh start for the next piece
         auto close_piece = [&](int pos, int b) {
-            const size_t slot = (size_t)(a.flat ? span + b : b);
+            const size_t slot = (size_t)(slot_b + b);
             const float inv = Linv[(pos & 1) * 32 + rowc];
             // A lane holds columns 8 q4 + 4 kg .. + 3 of every 32-column block of its row.  The two lanes of a row
             // trade neighbouring groups (v_permlane32_swap), so that each holds eight consecutive columns and a
@@ -652,7 +602,6 @@ static hipError_t launch_t(const StreamArgs &a, int rg, hipStream_t s, hipEvent_
 
 hipError_t launch_core_stream(const StreamArgs &a, int d_m, bool bf16, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    if (a.flat && a.B > kScanMax) return hipErrorInvalidValue;
     if (d_m == 1024) return bf16 ? launch_t<1024, true>(a, rg, s, ev0, ev1) : launch_t<1024, false>(a, rg, s, ev0, ev1);
     if (d_m == 768) return bf16 ? launch_t<768, true>(a, rg, s, ev0, ev1) : launch_t<768, false>(a, rg, s, ev0, ev1);
     if (d_m == 512) return bf16 ? launch_t<512, true>(a, rg, s, ev0, ev1) : launch_t<512, false>(a, rg, s, ev0, ev1);

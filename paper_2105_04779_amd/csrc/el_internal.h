@@ -98,55 +98,33 @@ __host__ __device__ __forceinline__ size_t frag16_index(int row, int col, int K)
 }
 
 // ---- compile-time limits -----------------------------------------------------------------
-constexpr int kMaxParts = 8;        // key-range partials per (batch element, row) the workspace holds
+constexpr int kMaxParts = 16;       // pieces per batch element the workspace of the MFMA core has room for
+constexpr int kMaxPartsGeneric = 8; // key-range partials (fp32) of the generic core
 constexpr int kGenericMaxDm = 8192; // widest d_model the generic core kernel covers
 constexpr int kScanMax = 1024;      // most batch elements whose tiles the streaming core cuts as one list
+constexpr int kSpanMax = 1024;      // most spans of that list
 
-// Where the partial results ("pieces") of batch element b live: `np` consecutive slots from `slot0` in the
-// partial buffers Xp [slot, Rs, d_m] and ML [slot, Rs, 2].
-//   fixed cut      every element is cut into `parts` key ranges: slots b*parts .. b*parts+parts-1;
-//   flattened cut  the 16-row tiles of all elements lie on one axis, element after element, each element preceded
-//                  by a gap of `kcost` units (what moving on to a new element costs a workgroup, in tiles): tile kt
-//                  of element b sits at coordinate E[b] + kcost * (b + 1) + kt, where E [B+1] is the prefix sum of
-//                  the elements' tile counts, written by the core.  The axis is cut into G spans of
-//                  cspan = max(ceil(length / G), lfloor + kcost) units, so a span that crosses into a new element
-//                  holds kcost tiles fewer; the piece of (span g, element b) is slot g + b (unique: along the
-//                  axis, span and element never decrease and one of them grows from piece to piece).
+// Where the partial results ("pieces") of batch element b live: `np` consecutive slots from `slot0` in the partial
+// buffers Xp [slot, Rs, d_m] and ML [slot, Rs, 2].  Generic core: every element has `parts` of them.  MFMA core: looked
+// up in the table of the cut (cut.h).
 struct PieceMap {
-    const int32_t *E;       // null: fixed cut
-    int parts;              // fixed cut: parts per element
-    int G, lfloor, B, kcost; // flattened cut
+    const int2 *table;      // [B] (first slot, pieces); null: slots b * parts ..
+    int parts;
 };
-__host__ __device__ __forceinline__ int flat_cspan(int total_tiles, int B, int G, int lfloor, int kcost)
-{
-    const int length = total_tiles + kcost * B;
-    const int c = (length + G - 1) / G;
-    return c > lfloor + kcost ? c : lfloor + kcost;
-}
-// What every look-up of one launch shares: the span length on the cost axis (a division, done once).
-struct PieceCut { int cspan; };
-__device__ __forceinline__ PieceCut piece_cut(const PieceMap &m, int E_total)       // E_total = E[B]
-{
-    return PieceCut{m.E ? flat_cspan(E_total, m.B, m.G, m.lfloor, m.kcost) : 1};
-}
-__device__ __forceinline__ PieceCut piece_cut(const PieceMap &m) { return piece_cut(m, m.E ? m.E[m.B] : 0); }
-// (E_b, E_b1) = (E[b], E[b+1]), for callers that fetch them ahead of time
-__device__ __forceinline__ void piece_range(const PieceMap &m, const PieceCut &c, int b, int E_b, int E_b1, int &slot0, int &np)
-{
-    if (!m.E) { slot0 = b * m.parts; np = m.parts; return; }
-    const int first = E_b + m.kcost * (b + 1), last = E_b1 + m.kcost * (b + 1) - 1;
-    const int g_lo = first / c.cspan;
-    // an element has at most kMaxParts pieces: the last span is found by stepping, not by a second division
-    int cnt = 1;
-    for (int k = 1; k < kMaxParts; ++k) cnt += last >= (g_lo + k) * c.cspan ? 1 : 0;
-    if (last >= (g_lo + kMaxParts) * c.cspan) cnt = last / c.cspan - g_lo + 1;     // never with a plan that respects kMaxParts
-    slot0 = g_lo + b; np = cnt;
-}
 __device__ __forceinline__ void piece_range(const PieceMap &m, int b, int &slot0, int &np)
 {
-    if (!m.E) { slot0 = b * m.parts; np = m.parts; return; }
-    piece_range(m, piece_cut(m), b, m.E[b], m.E[b + 1], slot0, np);
+    if (!m.table) { slot0 = b * m.parts; np = m.parts; return; }
+    const int2 e = m.table[b];
+    slot0 = e.x; np = e.y;
 }
+
+// What build_cut (cut.h) needs to know
+struct CutArgs {
+    const int32_t *lengths;
+    int4 *spans;            // [G][2]: (element, tile of it, tiles, first slot), (lengths of the first four elements)
+    int2 *pieces;           // [B] (first slot, pieces)
+    int n, B, G, kcost;
+};
 
 // ---- problem description handed to the launchers ------------------------------------------
 struct Problem {
@@ -167,7 +145,8 @@ struct Workspace {
     float *ML;      // [B, parts, Rpad, 2]          running max and sum of each partial
     float *Xn;      // [B, R, d_m]                  merged, normalised weighted sums (generic path)
     float *A;       // [B*beam, hd]                 a6 result: fp32 (generic) or fp16 in fragment order (MFMA projections)
-    int32_t *E;     // [B+1]                        prefix sum of tile counts (flattened cut of the MFMA core)
+    int4 *spans;    // [slots][2]                   the cut of the MFMA core (see CutArgs)
+    int2 *pieces;   // [B]
     int slots;      // pieces Xp and ML have room for (batch elements the workspace was laid out for x kMaxParts)
 };
 
@@ -243,12 +222,8 @@ struct CorePlan {
     int nrg;      // 16-row groups per workgroup (1 or 2)
     int nblocks;  // row blocks (workgroups sharing one H range)
     int Rs;       // padded row count of ELQ / partial buffers = nblocks * 16 * nrg
-    int flat;     // 1: the tiles of all elements are cut as one list into G spans; 0: one workgroup per (element, row block)
-    int G;        // spans (flat) or batch elements (not flat)
-    int lfloor;   // flat: floor on the span length in tiles, so that no element has more than kMaxParts pieces
-    int kcost;    // flat: what crossing into a new element costs a workgroup, in tiles (see PieceMap)
-    int parts;    // most pieces per (batch element, row)
-    int slots;    // piece slots the partial buffers must hold
+    int G;        // spans the tiles of all elements are cut into (more than kScanMax elements: one span each)
+    int kcost;    // what crossing into a new element costs a workgroup, in tiles (see cut.h)
 };
 // Arguments of the streaming core (core_stream.hip)
 struct StreamArgs {
@@ -259,15 +234,16 @@ struct StreamArgs {
                              //   in fragment order (see elq_frag_index)
     f16_t *Xp;               // [slot, Rs, DM] fp16, each piece already divided by its own sum, in fragment order (frag16_index)
     float *ML;               // [slot, Rs, 2]  (reference max in log2 units, sum)
-    int32_t *E;              // [B+1] prefix sum of tile counts (flat cut), written by the kernel; may be null
-    int n, B, R, Rs, nblocks;
-    int flat, G, lfloor, kcost;
+    const int4 *spans;       // the cut (see CutArgs)
+    int n, B, R, Rs, nblocks, G;
     int stream_hint;         // nonzero: fetch H with the non-temporal hint (H far larger than the memory-side cache)
 };
 hipError_t launch_core_stream(const StreamArgs &a, int d_m, bool bf16, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 bool core_mfma_supported(int dtype, int d_m);
 CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots);
-PieceMap piece_map(const CorePlan &pl, const Workspace &ws, int B);
+CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws);
+PieceMap piece_map(const Workspace &ws);
+hipError_t launch_cut(const CutArgs &c, hipStream_t s);      // the cut on its own, for a core that k_qelq does not precede
 hipError_t launch_elq_f16(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, hipStream_t s);
 hipError_t launch_core_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, hipStream_t s,
                             hipEvent_t ev0, hipEvent_t ev1);   // events, if given, bracket the kernel itself
@@ -278,7 +254,7 @@ bool gemm_mfma_supported(int dtype, int d_m, int d_k);
 hipError_t launch_transpose(size_t elem, const void *src, void *dst, int rows, int cols, hipStream_t s);
 enum PackKind { kPackWq, kPackWk, kPackWv, kPackWo };
 hipError_t launch_pack(int dtype, PackKind kind, const void *W, void *P, int d_m, hipStream_t s);
-hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int Rs, float scale, bool keep_qp, hipStream_t s);
+hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, float scale, bool keep_qp, hipStream_t s);   // builds the cut as well
 hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, hipStream_t s);
 hipError_t launch_oproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const float *bias32, hipStream_t s);
 

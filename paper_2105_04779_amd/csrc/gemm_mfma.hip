@@ -20,6 +20,7 @@
 // under the 2e-3 bar).  Accumulation is fp32.
 #include <type_traits>
 #include "el_internal.h"
+#include "cut.h"
 
 namespace el {
 
@@ -42,10 +43,10 @@ template <> __device__ __forceinline__ f4 mfma16<true>(u4 a, u4 b, f4 c) { retur
 // 8 share an XCD and its L2, so each XCD gets one run of the items in block-major order: it then pulls only its own
 // blocks' weights from memory, once, instead of every XCD pulling all of them.
 struct Place { int block, part, group; };
-__device__ __forceinline__ bool place_of(int blocks, int parts, int groups, Place &p)
+__device__ __forceinline__ bool place_of(int blocks, int parts, int groups, int id, Place &p)
 {
     const int items = blocks * parts * groups, per_xcd = (items + 7) >> 3;
-    const int i = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    const int i = (id & 7) * per_xcd + (id >> 3);
     if (i >= items) return false;
     p.block = i / (parts * groups);
     const int j = i - p.block * (parts * groups);
@@ -80,6 +81,8 @@ struct QelqArgs {
     const void *bq;        // storage type, may be null
     uint16_t *elq;
     f16_t *Qp;             // [M, d_m], or null if nobody reads it
+    CutArgs cut;           // the core's cut is built here as well, by one wavefront under this kernel's memory latency: by a
+    int cut_alone;         // workgroup of its own (the first, so that it starts at once) where there is room for one, else by the first one
     float scale;
     int M, x, Rs, groups;
 };
@@ -93,8 +96,16 @@ k_qelq(const QelqArgs a)
     __shared__ __attribute__((aligned(16))) f16_t Ql[16 * 72];               // rows 144 bytes apart
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
+    __shared__ CutScratch cut;
+    const bool cuts = blockIdx.x == 0 && w == (a.cut_alone ? 0 : 7);
+    CutLengths cut_len;
+    if (cuts) load_cut_lengths(a.cut, l, cut_len);
+    if (a.cut_alone && blockIdx.x == 0) {
+        if (cuts) build_cut(a.cut, cut_len, cut, l);
+        return;
+    }
     Place pl;
-    if (!place_of(HEADS, PARTS, a.groups, pl)) return;
+    if (!place_of(HEADS, PARTS, a.groups, blockIdx.x - a.cut_alone, pl)) return;
     const int head = pl.block, tiles = (a.M + 15) >> 4;
 
     u4 xq[KS], wq[KS][4], wk[NP][2][2];
@@ -121,6 +132,8 @@ k_qelq(const QelqArgs a)
     if (a.bq)
 #pragma unroll
         for (int e = 0; e < 2; ++e) bias[e] = BF ? to_f32(((const bf16_t *)a.bq)[head * 64 + scol + e]) : to_f32(((const f16_t *)a.bq)[head * 64 + scol + e]);
+
+    if (cuts) build_cut(a.cut, cut_len, cut, l);
 
     for (int tile = pl.group; tile < tiles; tile += a.groups) {
         f4 acc[4];
@@ -200,29 +213,28 @@ k_vproj(const VprojArgs a)
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
     Place pl;
-    if (!place_of(DM / 64, 4 / NT, a.groups, pl)) return;
+    if (!place_of(DM / 64, 4 / NT, a.groups, blockIdx.x, pl)) return;
     const int head = pl.block, nb = pl.part;
-    int e_tot = 0;
-    if (a.pm.E) e_tot = a.pm.E[a.pm.B];
     const int tiles = (a.M + 15) >> 4;
-    auto row_of = [&](int tile, int &b, int &j) { const int m = min(16 * tile + r16, a.M - 1); b = m / a.x; j = m - b * a.x; };
-    int b, j, E_b = 0, E_b1 = 0;
-    row_of(pl.group, b, j);
-    if (a.pm.E) { E_b = a.pm.E[b]; E_b1 = a.pm.E[b + 1]; }
+    int j, slot0, np;
+    auto look_up = [&](int tile) {
+        const int m = min(16 * tile + r16, a.M - 1), b = m / a.x;
+        j = m - b * a.x;
+        piece_range(a.pm, b, slot0, np);
+    };
+    look_up(pl.group);
     u4 wv[KS][NT];
 #pragma unroll
     for (int s = 0; s < KS; ++s)
 #pragma unroll
         for (int t = 0; t < NT; ++t)
             wv[s][t] = a.Wp[(((size_t)head * (DM / 32) + KS * w + s) * 4 + nb * NT + t) * 64 + l];
-    const PieceCut cut = piece_cut(a.pm, e_tot);
     int parity = 0;
     for (int tile = pl.group; tile < tiles; tile += a.groups) {
-        int slot0, np;
-        piece_range(a.pm, cut, b, E_b, E_b1, slot0, np);
+        const int pieces = np;
         const size_t row0 = (size_t)slot0 * a.Rs + head * a.x + j;
         const f16_t *x0 = a.Xp + (size_t)slot0 * a.Rs * DM + frag16_index(head * a.x + j, 32 * KS * w + 8 * q, DM);
-        int np_max = np;                                 // most pieces among the 16 rows (uniform)
+        int np_max = pieces;                             // most pieces among the 16 rows (uniform)
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) np_max = max(np_max, __shfl_xor(np_max, o, 64));
         np_max = __builtin_amdgcn_readfirstlane(np_max);
@@ -237,19 +249,16 @@ k_vproj(const VprojArgs a)
 #pragma unroll
             for (int p = 0; p < PC; ++p) {
                 if (p0 + p >= np_max) { ml[p] = f2{0.f, 0.f}; continue; }           // uniform
-                const size_t step = (size_t)min(p0 + p, np - 1) * a.Rs;
+                const size_t step = (size_t)min(p0 + p, pieces - 1) * a.Rs;
                 ml[p] = *(const f2 *)(a.ML + (row0 + step) * 2);
 #pragma unroll
                 for (int s = 0; s < KS; ++s) xv[p][s] = *(const h8 *)(x0 + step * DM + 512 * s);
             }
-            if (p0 + PC >= np_max && tile + a.groups < tiles) {                     // the next tile's table entries
-                row_of(tile + a.groups, b, j);
-                if (a.pm.E) { E_b = a.pm.E[b]; E_b1 = a.pm.E[b + 1]; }
-            }
+            if (p0 + PC >= np_max && tile + a.groups < tiles) look_up(tile + a.groups);   // the next tile's table entries
             float m_new = m_run;
 #pragma unroll
             for (int p = 0; p < PC; ++p) {
-                if (p0 + p >= np || !(ml[p][1] > 0.f)) ml[p] = f2{-INFINITY, 0.f};  // no such piece for this row, or an empty one
+                if (p0 + p >= pieces || !(ml[p][1] > 0.f)) ml[p] = f2{-INFINITY, 0.f};  // no such piece for this row, or an empty one
                 m_new = fmaxf(m_new, ml[p][0]);
             }
             if (p0 > 0) {
@@ -324,7 +333,7 @@ k_oproj(const OprojArgs a)
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
     Place pl;
-    if (!place_of(DM / 64, 4 / NT, a.groups, pl)) return;
+    if (!place_of(DM / 64, 4 / NT, a.groups, blockIdx.x, pl)) return;
     const int tiles = (a.M + 15) >> 4;
     u4 xa[KS], wo[KS][NT];
     auto load_rows = [&](int tile) {
@@ -454,19 +463,22 @@ static void launch_qelq_t(QelqArgs &a, int num_cus, hipStream_t s)
     // the columns of EL-Q split over FULL workgroups while all of them run at once
     const int parts = tiles * heads * FULL <= num_cus ? FULL : 1;
     a.groups = tile_groups(tiles, heads * parts, num_cus);
-    const dim3 grid = place_grid(heads, parts, a.groups), block(512);
+    dim3 grid = place_grid(heads, parts, a.groups), block(512);
+    a.cut_alone = (int)grid.x < num_cus || DM == 512 ? 1 : 0;
+    grid.x += a.cut_alone;     // (d_m 512: two workgroups fit a compute unit's registers)
     if (parts == 1) hipLaunchKernelGGL((k_qelq<DM, BF, FULL>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_qelq<DM, BF, 1>), grid, block, 0, s, a);
 }
 
-// a1 + a2: ELQ[b, i*beam+j, :] = ((q . W_i^Q + b_i^Q) * scale) . (W_i^K)^T      high + low planes in fragment order, Rs
+// a1 + a2: ELQ[b, i*beam+j, :] = ((q . W_i^Q + b_i^Q) * scale) . (W_i^K)^T      high + low planes in fragment order, pl.Rs
 // rows per b; Qp [B*beam, hd] fp16 as well if `keep_qp`
-hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, int Rs, float scale, bool keep_qp, hipStream_t s)
+hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, float scale, bool keep_qp, hipStream_t s)
 {
     QelqArgs a;
+    a.cut = cut_args(p, pl, ws);
     a.Wq = (const u4 *)ctx->w.WqP; a.Wk = (const u4 *)ctx->w.WkP; a.q = p.queries; a.bq = ctx->w.bq;
     a.elq = (uint16_t *)ws.ELQ; a.Qp = keep_qp ? (f16_t *)ws.Qp : nullptr; a.scale = scale;
-    a.M = p.B * p.beam; a.x = p.beam; a.Rs = Rs;
+    a.M = p.B * p.beam; a.x = p.beam; a.Rs = pl.Rs;
     const bool bf = p.dtype == EL_BF16;
     if (p.d_m == 1024) { if (bf) launch_qelq_t<1024, true>(a, ctx->num_cus, s); else launch_qelq_t<1024, false>(a, ctx->num_cus, s); }
     else if (p.d_m == 768) { if (bf) launch_qelq_t<768, true>(a, ctx->num_cus, s); else launch_qelq_t<768, false>(a, ctx->num_cus, s); }
@@ -491,7 +503,7 @@ hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Wor
 {
     VprojArgs a;
     a.Wp = (const u4 *)ctx->w.WvP; a.Xp = (const f16_t *)ws.Xp; a.ML = ws.ML; a.A = (f16_t *)ws.A;
-    a.pm = piece_map(pl, ws, p.B);
+    a.pm = piece_map(ws);
     a.M = p.B * p.beam; a.x = p.beam; a.Rs = pl.Rs;
     if (p.d_m == 1024) launch_vproj_t<1024>(a, ctx->num_cus, s);
     else if (p.d_m == 768) launch_vproj_t<768>(a, ctx->num_cus, s);

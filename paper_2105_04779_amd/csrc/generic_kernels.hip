@@ -501,7 +501,7 @@ hipError_t launch_elq_generic(const el_attn_ctx *ctx, const Problem &p, const fl
 // (8 x R64 x d_m floats).
 bool scores_fit(const Problem &p)
 {
-    return (int64_t)p.R * ((p.n + 3) / 4 * 4) <= (int64_t)kMaxParts * ((p.R + 63) / 64 * 64) * p.d_m;
+    return (int64_t)p.R * ((p.n + 3) / 4 * 4) <= (int64_t)kMaxPartsGeneric * ((p.R + 63) / 64 * 64) * p.d_m;
 }
 
 // a3-a5 through the scores in memory; Xn normalised, one piece of statistics per row

@@ -1,0 +1,46 @@
+"""GPU parity of the decode step where the cut of its work changes form: one element cut into many spans, few elements
+cut one by one, spans that run through more elements than the table lists lengths for, and the most pieces per element;
+with the projections' column splits and row-tile groups that belong to these row counts."""
+import numpy as np
+import pytest
+
+from paper_2105_04779_amd import workloads as wl
+from helpers import TOL, gpu_out, make_layer, oracle_out, record, rel_err
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, B, beam, heads, d_m, n, lens, splits
+    ("bf16", 1, 4, 16, 1024, 1000, [1000], 0),              # one sentence: 15 spans, as many pieces to merge
+    ("bf16", 1, 4, 16, 1024, 613, [613], 0),
+    ("f16", 1, 1, 8, 512, 333, [333], 0),
+    ("bf16", 1, 3, 12, 768, 17, [17], 0),                   # two tiles, the second with one row
+    ("bf16", 4, 4, 16, 1024, 410, [410, 205, 1, 333], 0),   # cut per element
+    ("f16", 5, 5, 12, 768, 300, [300, 16, 17, 299, 1], 0),
+    ("bf16", 2, 4, 16, 1024, 700, [700, 350], 16),          # the most pieces
+    ("bf16", 2, 2, 8, 512, 500, [1, 500], 16),
+    ("bf16", 700, 4, 16, 1024, 40, "mixed", 0),             # more than four elements per span, some of one row
+    ("f16", 1000, 2, 8, 512, 33, "mixed", 0),
+    ("bf16", 33, 5, 12, 768, 90, "mixed", 0),               # 165 rows: a last row tile of five
+    ("bf16", 320, 4, 16, 1024, 24, "mixed", 0),             # several row tiles per workgroup of the projections
+]
+
+
+@pytest.mark.parametrize("dtype,B,beam,heads,d_m,n,lens,splits", CASES)
+def test_cuts(dtype, B, beam, heads, d_m, n, lens, splits):
+    w = wl.custom(f"cut_{dtype}_{B}x{beam}_{d_m}_{n}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=64, n=n, index=95)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.asarray([1 + (b * 13) % n for b in range(B)] if isinstance(lens, str) else lens, dtype=np.int32)
+    L[0] = n if isinstance(lens, str) else L[0]
+    ref = oracle_out(w, W, H, Q, L)
+    for b in range(B):
+        H[b, L[b]:] = np.nan
+    layer = make_layer(w, W)
+    assert layer.uses_mfma
+    if splits:
+        layer.set_splits(splits)
+    err = rel_err(gpu_out(layer, w, H, Q, L), ref)
+    record(f"{w.name}: splits={splits} err={err:.3e}")
+    assert err <= TOL[dtype]
+    layer.close()
