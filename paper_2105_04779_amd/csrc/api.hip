@@ -52,18 +52,27 @@ WsLayout ws_layout_for(const el_attn_ctx *c, int batch, int beam)
     const size_t mb = (size_t)batch, mx = (size_t)beam;
     const size_t d_m = (size_t)c->cfg.d_model, hd = (size_t)c->hd, Rp = (size_t)round_up64(c->cfg.heads * beam);
     WsLayout L;
-    // pieces are fp16 on the MFMA path: twice as many in the same bytes
-    const int parts = c->use_mfma_core ? kMaxParts : kMaxPartsGeneric;
+    const size_t xp_bytes = mb * kMaxPartsGeneric * Rp * d_m * sizeof(float);
+    L.slots = batch * (c->use_mfma_core ? kMaxParts : kMaxPartsGeneric);
     size_t o = 0;
     L.off_Qp = o;  o = align_up(o + mb * mx * hd * sizeof(float), 256);
     L.off_ELQ = o; o = align_up(o + mb * Rp * d_m * sizeof(float), 256);
-    L.off_Xp = o;  o = align_up(o + mb * kMaxPartsGeneric * Rp * d_m * sizeof(float), 256);
-    L.off_ML = o;  o = align_up(o + mb * parts * Rp * 2 * sizeof(float), 256);
+    L.off_Xp = o;  o = align_up(o + xp_bytes, 256);
+    L.off_ML = o;  o = align_up(o + mb * kMaxPartsGeneric * Rp * 2 * sizeof(float), 256);
     L.off_Xn = o;  o = align_up(o + mb * Rp * d_m * sizeof(float), 256);
-    L.off_A = o;   o = align_up(o + (mb * mx < 16 ? 16 : mb * mx) * hd * sizeof(float), 256);      // fp16 rows are padded to 16
-    L.slots = batch * parts;
-    L.off_spans = o;  o = align_up(o + (size_t)L.slots * 2 * sizeof(int4), 256);
-    L.off_pieces = o; o = align_up(o + mb * sizeof(int2), 256);
+    L.off_A = o;   o = align_up(o + mb * mx * hd * sizeof(float), 256);
+    L.off_spans = L.off_pieces = 0;
+    if (c->use_mfma_core) {
+        // Pieces are fp16: kMaxParts = 15 of them leave a sixteenth of the fp32 partials' bytes (at least 64 KB per batch
+        // element, Rp >= 64 and d_m >= 512) to the statistics (120 Rp) and the cut (488 bytes per element), so the
+        // workspace is no larger than that of eight fp32 partials.
+        size_t t = L.off_Xp + mb * kMaxParts * Rp * d_m * sizeof(f16_t);
+        L.off_ML = t;     t = align_up(t + mb * kMaxParts * Rp * 2 * sizeof(float), 256);
+        L.off_spans = t;  t = align_up(t + (size_t)L.slots * 2 * sizeof(int4), 256);
+        L.off_pieces = t;
+        // fp16 head outputs are padded to 16 rows; the merged sums are not kept where they are (the projections merge)
+        if (c->use_mfma_gemm) L.off_A = L.off_Xn;
+    }
     L.total = o;
     return L;
 }

@@ -98,7 +98,7 @@ __host__ __device__ __forceinline__ size_t frag16_index(int row, int col, int K)
 }
 
 // ---- compile-time limits -----------------------------------------------------------------
-constexpr int kMaxParts = 16;       // pieces per batch element the workspace of the MFMA core has room for
+constexpr int kMaxParts = 15;       // pieces (fp16) per batch element the workspace of the MFMA core has room for
 constexpr int kMaxPartsGeneric = 8; // key-range partials (fp32) of the generic core
 constexpr int kGenericMaxDm = 8192; // widest d_model the generic core kernel covers
 constexpr int kScanMax = 1024;      // most batch elements whose tiles the streaming core cuts as one list

@@ -17,8 +17,8 @@ CASES = [
     ("bf16", 1, 3, 12, 768, 17, [17], 0),                   # two tiles, the second with one row
     ("bf16", 4, 4, 16, 1024, 410, [410, 205, 1, 333], 0),   # cut per element
     ("f16", 5, 5, 12, 768, 300, [300, 16, 17, 299, 1], 0),
-    ("bf16", 2, 4, 16, 1024, 700, [700, 350], 16),          # the most pieces
-    ("bf16", 2, 2, 8, 512, 500, [1, 500], 16),
+    ("bf16", 2, 4, 16, 1024, 700, [700, 350], 15),          # the most pieces
+    ("bf16", 2, 2, 8, 512, 500, [1, 500], 15),
     ("bf16", 700, 4, 16, 1024, 40, "mixed", 0),             # more than four elements per span, some of one row
     ("f16", 1000, 2, 8, 512, 33, "mixed", 0),
     ("bf16", 33, 5, 12, 768, 90, "mixed", 0),               # 165 rows: a last row tile of five

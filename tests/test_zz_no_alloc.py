@@ -81,3 +81,17 @@ def test_static_step_rejects_what_does_not_fit_and_checks_its_operands():
     assert call(B=8, out=ctypes.c_void_p(out.data_ptr() + 4)) == ea.EL_ERR_INVALID_ARG
     assert call(B=0) == ea.EL_ERR_INVALID_ARG
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,heads,d_k,d_m,B,beam", [("bf16", 16, 64, 1024, 1, 1), ("f16", 8, 64, 512, 9, 5), ("bf16", 12, 64, 768, 6, 4),
+                                                        ("bf16", 8, 128, 1024, 3, 2), ("f32", 4, 16, 64, 7, 3)])
+def test_workspace_is_no_larger_than_eight_fp32_partials_per_element(dtype, heads, d_k, d_m, B, beam):
+    """The bytes that decide what fits the static array: projected and expanded queries, eight fp32 partials with their
+    statistics, merged sums and head outputs, each on a 256-byte boundary, and no more."""
+    from paper_2105_04779_amd import el_attn as ea
+    w = wl.custom("ws_size", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=d_k, n=32, index=65)
+    layer = make_layer(w, wl.weights(w))
+    Rp = (heads * beam + 63) // 64 * 64
+    parts = [B * beam * d_m * 4, B * Rp * d_m * 4, B * 8 * Rp * d_m * 4, B * 8 * Rp * 8, B * Rp * d_m * 4, B * beam * d_m * 4]
+    assert ea.el_attn_workspace_bytes(layer.ctx) <= sum((p + 255) // 256 * 256 for p in parts)
+    layer.close()
