@@ -222,15 +222,16 @@ int32_t el_attn_max_splits(void);
 
 /*
  * Second tuning knob, never semantics: how many 16-row groups of expanded queries one
- * workgroup of the MFMA attention core owns (1 or 2; 0 restores the automatic choice, which
- * is 2 wherever the shape has more than 16 rows).  The row blocks of one span stream the
- * same H tiles (served by the shared L2 after the first touch).
+ * workgroup of the MFMA attention core owns (1 or 2; 0 restores the automatic choice: row blocks
+ * of 2 wherever the shape has more than 16 rows, shared by two workgroups of one group each while
+ * the spans are short).  The row blocks of one span stream the same H tiles (served by the shared
+ * L2 after the first touch).
  */
 el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
 
 /*
  * What the automatic choice would be for a shape on a device with `compute_units` compute units (host
- * arithmetic only, no device needed): rows per workgroup in groups of 16 (*row_groups) and the number of
+ * arithmetic only, no device needed): rows per row block in groups of 16 (*row_groups) and the number of
  * equal spans the list of valid tiles is cut into (*spans; workgroups = spans x row blocks) by the MFMA
  * attention core.  Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or
  * 1024: no MFMA core).

@@ -404,7 +404,7 @@ el_status el_attn_plan_preview(int32_t B, int32_t beam, int32_t heads, int32_t d
     std::memset(&p, 0, sizeof(p));
     p.B = B; p.beam = beam; p.n = n; p.heads = heads; p.d_m = d_model; p.R = heads * beam;
     const CorePlan pl = plan_core_mfma(p, 0, 0, compute_units, B * kMaxParts);
-    *row_groups = pl.nrg;
+    *row_groups = pl.block_groups;
     *spans = pl.G;
     return EL_OK;
 }

@@ -77,15 +77,24 @@ constexpr int kMinSpan = 4;
 // workgroups with a crossing ended 5-6 us after the others).
 constexpr int kBoundaryCost = 4;
 
+// Tiles per span up to which two workgroups of 16 rows share a row block of 32, all of them on the chip at once.  Half the
+// expanded queries to wait for and half the products per tile, against twice the tiles per span where the spans fill the
+// chip.  Whole steps, d_m 1024, beam 4, 32 against 16 rows: one sentence of 613 25.2 -> 23.6 us; twelve layers, 4 sentences
+// 342 -> 321; 8 of 512 27.9 -> 26.4; 16 of 512 (8 tiles) 32.0 -> 28.9; 32 of 512 (16 tiles) equal; d_m 512, 64 of 512 (16
+// tiles) 23.8 -> 24.6.
+constexpr int kHalfBlockTiles = 12;
+
 CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)
 {
     CorePlan pl;
-    pl.nrg = p.R <= 16 ? 1 : 2;
-    if (nrg_override == 1) pl.nrg = 1;
+    const int tiles = (p.n + 15) / 16;
+    pl.block_groups = p.R <= 16 || nrg_override == 1 ? 1 : 2;
+    pl.nrg = pl.block_groups;
+    pl.nblocks = (p.R + 31) / 32;
+    if (nrg_override == 0 && pl.nrg == 2 && (long)p.B * tiles * pl.nblocks * 2 <= (long)kHalfBlockTiles * num_cus) pl.nrg = 1;
     pl.nblocks = (p.R + 16 * pl.nrg - 1) / (16 * pl.nrg);
     pl.Rs = pl.nblocks * 16 * pl.nrg;
     pl.kcost = kBoundaryCost;
-    const int tiles = (p.n + 15) / 16;
     if (p.B > kScanMax) { pl.G = p.B; return pl; }
     long G;
     if (splits_override > 0) {

@@ -220,6 +220,7 @@ hipError_t launch_seg_merge(const SegMergeArgs &a, bool out_f16, int rows, hipSt
 // MFMA attention core -- core_stream.hip (the kernel), core_mfma.hip (planning, launch, helpers)
 struct CorePlan {
     int nrg;      // 16-row groups per workgroup (1 or 2)
+    int block_groups;   // 16-row groups of the row blocks the spans are planned for: nrg, or 2 where two workgroups share one
     int nblocks;  // row blocks (workgroups sharing one H range)
     int Rs;       // padded row count of ELQ / partial buffers = nblocks * 16 * nrg
     int G;        // spans the tiles of all elements are cut into (more than kScanMax elements: one span each)

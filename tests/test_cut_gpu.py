@@ -22,6 +22,9 @@ CASES = [
     ("bf16", 700, 4, 16, 1024, 40, "mixed", 0),             # more than four elements per span, some of one row
     ("f16", 1000, 2, 8, 512, 33, "mixed", 0),
     ("bf16", 33, 5, 12, 768, 90, "mixed", 0),               # 165 rows: a last row tile of five
+    ("bf16", 24, 4, 16, 1024, 512, [500] * 23 + [512], 0),  # the longest spans of 16-row workgroups, and one tile beyond them
+    ("bf16", 24, 4, 16, 1024, 528, [500] * 23 + [528], 0),
+    ("f16", 6, 5, 8, 512, 150, "mixed", 0),                 # 40 rows: three blocks of 16
     ("bf16", 320, 4, 16, 1024, 24, "mixed", 0),             # several row tiles per workgroup of the projections
 ]
 
