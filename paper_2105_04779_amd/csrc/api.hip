@@ -180,14 +180,13 @@ Problem make_problem(const el_attn_ctx *ctx, const void *H, int64_t stride, cons
 // a1..a6 of one step; on return the workspace holds the projected queries (of a segment), the key-range statistics and
 // the head outputs A (without b^V), in the formats `fmt` names.
 struct StepFormats {
-    bool a_f16, qp_f16;     // element type of A and of the projected queries in the workspace
+    bool finished;          // a segment's results are written already; else A and the projected queries are fp32
     PieceMap pm;            // which slots of the statistics [slot, Rstride, 2] belong to a batch element
     int Rstride;
     float ml_to_nat;        // ln 2 where the statistics' maxima are in log2 units
-    float c_to_nat;         // ln 2 where the projected queries carry log2(e)
 };
 
-el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, bool segment, hipStream_t s, StepFormats *fmt)
+el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const SegOut *seg, hipStream_t s, StepFormats *fmt)
 {
     constexpr float kLn2 = 0.6931471805599453f;
     if (el_attn_uses_mfma(ctx)) {
@@ -196,7 +195,7 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
         // a1 + a2: expanded queries in fp16, pre-multiplied by log2(e)/sqrt(d_k) so the core's softmax is an exp2
         const float qscale = 1.4426950408889634f / sqrtf((float)p.d_k);
         if (ctx->use_mfma_gemm) {
-            if (launch_qelq_mfma(ctx, p, ws, pl, qscale, segment, s) != hipSuccess) return EL_ERR_HIP;
+            if (launch_qelq_mfma(ctx, p, ws, pl, qscale, seg != nullptr, s) != hipSuccess) return EL_ERR_HIP;
         } else {
             if (launch_qproj_generic(ctx, p, ws, s) != hipSuccess) return EL_ERR_HIP;
             if (launch_elq_f16(ctx, p, ws, pl, s) != hipSuccess) return EL_ERR_HIP;
@@ -208,9 +207,9 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
         if (launch_core_mfma(ctx, p, ws, pl, s, ev0, ev1) != hipSuccess) return EL_ERR_HIP;
         if (timed) ctx->ev_used++;
         if (ctx->use_mfma_gemm) {
-            // merge of the partials fused into a6
-            if (launch_vproj_mfma(ctx, p, ws, pl, s) != hipSuccess) return EL_ERR_HIP;
-            fmt->a_f16 = fmt->qp_f16 = true; fmt->c_to_nat = kLn2;
+            // merge of the partials fused into a6; a segment's results leave from there
+            if (launch_vproj_mfma(ctx, p, ws, pl, seg, s) != hipSuccess) return EL_ERR_HIP;
+            fmt->finished = true;
             return EL_OK;
         }
         if (launch_merge_exp2(ctx, p, ws, pl, s) != hipSuccess) return EL_ERR_HIP;
@@ -231,7 +230,7 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
         if (!scored && launch_merge_generic(ctx, p, ws, parts, p.R, s) != hipSuccess) return EL_ERR_HIP;
     }
     if (launch_vproj_generic(ctx, p, ws, s) != hipSuccess) return EL_ERR_HIP;
-    fmt->a_f16 = fmt->qp_f16 = false; fmt->c_to_nat = 1.f;
+    fmt->finished = false;
     return EL_OK;
 }
 
@@ -257,7 +256,7 @@ el_status run_step(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipS
         return EL_OK;
     }
     StepFormats fmt;
-    const el_status st = run_a1_to_a6(ctx, p, ws, false, s, &fmt);
+    const el_status st = run_a1_to_a6(ctx, p, ws, nullptr, s, &fmt);
     return st != EL_OK ? st : run_a7(ctx, p, ws, ctx->w.c_out, s);
 }
 
@@ -495,13 +494,14 @@ el_status el_attn_decode_segment(el_attn_ctx *ctx, const void *H, int64_t H_batc
     const Workspace ws = carve(ctx);
     const Problem p = make_problem(ctx, H, H_batch_stride, lengths, queries, nullptr, B, beam, n);
     StepFormats fmt;
-    if ((st = run_a1_to_a6(ctx, p, ws, true, s, &fmt)) != EL_OK) return st;
+    const SegOut seg = {seg_A, seg_lse};
+    if ((st = run_a1_to_a6(ctx, p, ws, &seg, s, &fmt)) != EL_OK || fmt.finished) return st;
     SegFinishArgs f;
     f.A = ws.A; f.Qp = ws.Qp; f.ML = ws.ML; f.bk32 = ctx->w.bk32; f.bv32 = ctx->w.bv32;
     f.seg_A = seg_A; f.seg_lse = seg_lse;
     f.beam = beam; f.heads = p.heads; f.d_k = p.d_k; f.hd = p.hd; f.pm = fmt.pm; f.Rstride = fmt.Rstride;
-    f.ml_to_nat = fmt.ml_to_nat; f.c_to_nat = fmt.c_to_nat;
-    if (launch_seg_finish(f, fmt.a_f16, fmt.qp_f16, B * beam, s) != hipSuccess) return EL_ERR_HIP;
+    f.ml_to_nat = fmt.ml_to_nat;
+    if (launch_seg_finish(f, B * beam, s) != hipSuccess) return EL_ERR_HIP;
     return EL_OK;
 }
 

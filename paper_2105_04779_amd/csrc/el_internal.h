@@ -198,15 +198,16 @@ bool small_step_applies(const Problem &p);
 hipError_t launch_small_step(const el_attn_ctx *ctx, const Problem &p, hipStream_t s);
 // segment form (decoder-only models): statistics + biased head outputs of one segment; merge of several
 struct SegFinishArgs {
-    const void *A;            // [rows, hd] fp16 (in fragment order) or fp32: the segment's normalised head outputs without b^V
-    const void *Qp;           // [rows, hd] fp16 or fp32: projected queries as a1 left them (scaled)
+    const float *A;           // [rows, hd]: the segment's normalised head outputs without b^V
+    const float *Qp;          // [rows, hd]: projected queries as a1 left them (scaled by 1/sqrt(d_k))
     const float *ML;          // [slot, Rstride, 2] statistics of the pieces (see PieceMap)
     PieceMap pm;
     const float *bk32, *bv32;
     float *seg_A, *seg_lse;
     int beam, heads, d_k, hd, Rstride;
-    float ml_to_nat, c_to_nat; // factors that turn ML's maxima / the key-bias dot product into natural-log units
+    float ml_to_nat;          // factor that turns ML's maxima into natural-log units
 };
+struct SegOut { float *A, *lse; };   // a segment's results
 constexpr int kMaxSegments = 4;
 struct SegMergeArgs {
     const float *A[kMaxSegments];
@@ -214,7 +215,7 @@ struct SegMergeArgs {
     void *A_out;              // [rows, hd] fp16 (in fragment order) or fp32
     int nseg, heads, d_k, hd;
 };
-hipError_t launch_seg_finish(const SegFinishArgs &a, bool a_f16, bool qp_f16, int rows, hipStream_t s);
+hipError_t launch_seg_finish(const SegFinishArgs &a, int rows, hipStream_t s);     // around the fp32-arithmetic projections
 hipError_t launch_seg_merge(const SegMergeArgs &a, bool out_f16, int rows, hipStream_t s);
 
 // MFMA attention core -- core_stream.hip (the kernel), core_mfma.hip (planning, launch, helpers)
@@ -256,7 +257,7 @@ hipError_t launch_transpose(size_t elem, const void *src, void *dst, int rows, i
 enum PackKind { kPackWq, kPackWk, kPackWv, kPackWo };
 hipError_t launch_pack(int dtype, PackKind kind, const void *W, void *P, int d_m, hipStream_t s);
 hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, float scale, bool keep_qp, hipStream_t s);   // builds the cut as well
-hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, hipStream_t s);
+hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl, const SegOut *seg, hipStream_t s);   // seg: the segment form
 hipError_t launch_oproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const float *bias32, hipStream_t s);
 
 } // namespace el

@@ -201,12 +201,20 @@ struct VprojArgs {
     f16_t *A;              // [M, d_m] in fragment order
     PieceMap pm;
     int M, x, Rs, groups;
+    // segment form (fp32): head outputs with b^V and, per head, the log-sum-exp with Eq. 7's key-bias term, instead of A
+    const f16_t *Qp;       // [M, d_m], carrying log2(e)/sqrt(d_k)
+    const float *bk32, *bv32;
+    float *seg_A, *seg_lse;
 };
 
-template <int DM, int NT>
+// SEG: the segment form.  What its log-sum-exp needs, the merge has in registers, and the head outputs leave as the fp32
+// sums they are; as a kernel of its own that read them back, with one thread per head for the statistics, this took 8.8 us
+// at 128 rows.
+template <int DM, int NT, bool SEG>
 __global__ void __launch_bounds__(512)
 k_vproj(const VprojArgs a)
 {
+    constexpr float kLn2 = 0.6931471805599453f;
     constexpr int KS = DM / 256;                         // 32-wide slices of k per wavefront
     constexpr int PC = 4;                                // pieces in flight
     __shared__ f4 red[2][8 * NT * 64];
@@ -285,6 +293,18 @@ k_vproj(const VprojArgs a)
             }
         }
         const float inv = den > 0.f ? 1.0f / den : 0.f;
+        if (SEG && nb == 0 && w == 7) {                  // (a wavefront that adds nothing up below)
+            const int m = min(16 * tile + r16, a.M - 1);
+            const f16_t *qp = a.Qp + (size_t)m * DM + head * 64 + 16 * q;
+            const float *bk = a.bk32 + head * 64 + 16 * q;
+            float c = 0.f;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) c = fmaf((float)qp[k], bk[k], c);
+            c += __shfl_xor(c, 16, 64);
+            c += __shfl_xor(c, 32, 64);
+            if (q == 0 && 16 * tile + r16 < a.M)
+                a.seg_lse[(size_t)m * (DM / 64) + head] = den > 0.f ? m_run * kLn2 + logf(den) + c * kLn2 : -INFINITY;
+        }
         f4 acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
@@ -304,7 +324,13 @@ k_vproj(const VprojArgs a)
 #pragma unroll
             for (int s = 0; s < 8; ++s) sum += red[parity][(s * NT + w) * 64 + l];
             const int mm = 16 * tile + r16;
-            if (mm < a.M)
+            if (SEG) {
+                const int col = head * 64 + 16 * (nb * NT + w) + 4 * q;
+                float *o = a.seg_A + (size_t)mm * DM + col;                    // (the caller's: aligned to 4 bytes)
+                if (mm < a.M)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = sum[e] + a.bv32[col + e];
+            } else if (mm < a.M)
                 *(h4 *)(a.A + frag16_index(mm, head * 64 + 16 * (nb * NT + w) + 4 * q, DM)) =
                     h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
         }
@@ -461,12 +487,13 @@ static void launch_qelq_t(QelqArgs &a, int num_cus, hipStream_t s)
     constexpr int FULL = DM / 256;
     const int tiles = (a.M + 15) / 16, heads = DM / 64;
     // the columns of EL-Q split over FULL workgroups while all of them run at once
-    const int parts = tiles * heads * FULL <= num_cus ? FULL : 1;
+    const int parts = tiles * heads * FULL <= num_cus ? FULL : FULL == 4 && tiles * heads * 2 <= num_cus ? 2 : 1;
     a.groups = tile_groups(tiles, heads * parts, num_cus);
     dim3 grid = place_grid(heads, parts, a.groups), block(512);
     a.cut_alone = (int)grid.x < num_cus || DM == 512 ? 1 : 0;
     grid.x += a.cut_alone;     // (d_m 512: two workgroups fit a compute unit's registers)
     if (parts == 1) hipLaunchKernelGGL((k_qelq<DM, BF, FULL>), grid, block, 0, s, a);
+    else if (FULL == 4 && parts == 2) hipLaunchKernelGGL((k_qelq<DM, BF, FULL == 4 ? 2 : 1>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_qelq<DM, BF, 1>), grid, block, 0, s, a);
 }
 
@@ -487,27 +514,30 @@ hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Work
 }
 
 // merge + a6: A[b*beam+j, head i] = (sum_p w_p Xp[b,p,i*beam+j,:]) . W_i^V       fp16
-template <int DM>
+template <int DM, bool SEG>
 static void launch_vproj_t(VprojArgs &a, int num_cus, hipStream_t s)
 {
     const int tiles = (a.M + 15) / 16, heads = DM / 64;
-    const int parts = tiles * heads <= num_cus / 4 ? 4 : 1;
+    const int parts = tiles * heads * 4 <= num_cus ? 4 : tiles * heads * 2 <= num_cus ? 2 : 1;
     a.groups = tile_groups(tiles, heads * parts, num_cus);
     const dim3 grid = place_grid(heads, parts, a.groups), block(512);
-    if (parts == 4) hipLaunchKernelGGL((k_vproj<DM, 1>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_vproj<DM, 4>), grid, block, 0, s, a);
+    if (parts == 4) hipLaunchKernelGGL((k_vproj<DM, 1, SEG>), grid, block, 0, s, a);
+    else if (parts == 2) hipLaunchKernelGGL((k_vproj<DM, 2, SEG>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_vproj<DM, 4, SEG>), grid, block, 0, s, a);
 }
 
 hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl,
-                             hipStream_t s)
+                             const SegOut *seg, hipStream_t s)
 {
     VprojArgs a;
     a.Wp = (const u4 *)ctx->w.WvP; a.Xp = (const f16_t *)ws.Xp; a.ML = ws.ML; a.A = (f16_t *)ws.A;
     a.pm = piece_map(ws);
     a.M = p.B * p.beam; a.x = p.beam; a.Rs = pl.Rs;
-    if (p.d_m == 1024) launch_vproj_t<1024>(a, ctx->num_cus, s);
-    else if (p.d_m == 768) launch_vproj_t<768>(a, ctx->num_cus, s);
-    else launch_vproj_t<512>(a, ctx->num_cus, s);
+    a.Qp = (const f16_t *)ws.Qp; a.bk32 = ctx->w.bk32; a.bv32 = ctx->w.bv32;
+    a.seg_A = seg ? seg->A : nullptr; a.seg_lse = seg ? seg->lse : nullptr;
+    if (p.d_m == 1024) { if (seg) launch_vproj_t<1024, true>(a, ctx->num_cus, s); else launch_vproj_t<1024, false>(a, ctx->num_cus, s); }
+    else if (p.d_m == 768) { if (seg) launch_vproj_t<768, true>(a, ctx->num_cus, s); else launch_vproj_t<768, false>(a, ctx->num_cus, s); }
+    else { if (seg) launch_vproj_t<512, true>(a, ctx->num_cus, s); else launch_vproj_t<512, false>(a, ctx->num_cus, s); }
     return hipGetLastError();
 }
 

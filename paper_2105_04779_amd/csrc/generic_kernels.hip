@@ -607,13 +607,12 @@ hipError_t launch_vec_f32(int dtype, const void *src, float *dst, int n, hipStre
 template <typename T>
 __device__ __forceinline__ size_t head_index(int m, int cg, int hd) { return sizeof(T) == 2 ? frag16_index(m, cg, hd) : (size_t)m * hd + cg; }
 
-template <typename TA, typename TQ>
 __global__ void k_seg_finish(const SegFinishArgs a)
 {
     const int cg = blockIdx.x * kBlock + threadIdx.x;
     const int m = blockIdx.y;
     if (cg >= a.hd) return;
-    a.seg_A[(size_t)m * a.hd + cg] = to_f32(((const TA *)a.A)[head_index<TA>(m, cg, a.hd)]) + a.bv32[cg];
+    a.seg_A[(size_t)m * a.hd + cg] = a.A[(size_t)m * a.hd + cg] + a.bv32[cg];
     if (cg % a.d_k != 0) return;
     const int i = cg / a.d_k, b = m / a.beam, j = m % a.beam, r = i * a.beam + j;
     int slot0, np;
@@ -629,17 +628,15 @@ __global__ void k_seg_finish(const SegFinishArgs a)
         if (ml[1] > 0.f) L += expf((ml[0] - M) * a.ml_to_nat) * ml[1];
     }
     float c = 0.f;
-    const TQ *q = (const TQ *)a.Qp + (size_t)m * a.hd + (size_t)i * a.d_k;
-    for (int k = 0; k < a.d_k; ++k) c = fmaf(to_f32(q[k]), a.bk32[i * a.d_k + k], c);
-    a.seg_lse[(size_t)m * a.heads + i] = L > 0.f ? M * a.ml_to_nat + logf(L) + c * a.c_to_nat : -INFINITY;
+    const float *q = a.Qp + (size_t)m * a.hd + (size_t)i * a.d_k;
+    for (int k = 0; k < a.d_k; ++k) c = fmaf(q[k], a.bk32[i * a.d_k + k], c);
+    a.seg_lse[(size_t)m * a.heads + i] = L > 0.f ? M * a.ml_to_nat + logf(L) + c : -INFINITY;
 }
 
-hipError_t launch_seg_finish(const SegFinishArgs &a, bool a_f16, bool qp_f16, int rows, hipStream_t s)
+hipError_t launch_seg_finish(const SegFinishArgs &a, int rows, hipStream_t s)
 {
     const dim3 grid(cdiv(a.hd, kBlock), rows), block(kBlock);
-    if (a_f16 && qp_f16) hipLaunchKernelGGL((k_seg_finish<f16_t, f16_t>), grid, block, 0, s, a);
-    else if (!a_f16 && !qp_f16) hipLaunchKernelGGL((k_seg_finish<float, float>), grid, block, 0, s, a);
-    else return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_seg_finish, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -124,6 +124,17 @@ def test_prefix_and_suffix_segments_joined(dtype, heads, d_m, d_k, B, x, n1, n2,
     layer.close()
 
 
+@pytest.mark.parametrize("dtype,heads,d_m,B,x", [("bf16", 16, 1024, 29, 4), ("f16", 8, 512, 70, 5), ("bf16", 12, 768, 301, 1)])
+def test_segments_of_many_rows(dtype, heads, d_m, B, x):
+    """Two and all column blocks of a head per workgroup, several row tiles each, a last tile that is not full."""
+    w = wl.custom(f"seg_rows_{dtype}_{d_m}", dtype=dtype, B=B, beam=x, heads=heads, d_m=d_m, d_k=64, n=40, index=73)
+    W = _weights_with_visible_key_bias(w)
+    H, Q, L = _inputs(w, 1, B, x, 40, [1 + (7 * b) % 40 for b in range(B)])
+    layer = make_layer(w, W)
+    _check_segment(f"segments of {B * x} rows {dtype} d{d_m}", w, *_seg_gpu(layer, w, H, L, Q), *_seg_oracle(w, W, H, L, Q))
+    layer.close()
+
+
 def test_statistics_join_with_an_ordinary_attention_cache():
     # The per-beam continuation handled OUTSIDE the library (a caller's key/value cache): its log-sum-exp and head
     # outputs come from the definition (the oracle, as fp32 inputs); the prefix segment comes from the device.
