@@ -158,14 +158,15 @@ hipError_t launch_elq_f16(const el_attn_ctx *ctx, const Problem &p, const Worksp
     return hipGetLastError();
 }
 
-hipError_t launch_core_mfma(const el_attn_ctx *, const Problem &p, const Workspace &ws, const CorePlan &pl,
+hipError_t launch_core_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl,
                             hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
     StreamArgs a;
     a.H = p.H; a.h_stride = p.H_batch_stride; a.lengths = p.lengths;
     a.elq = (const uint16_t *)ws.ELQ;
     a.Xp = (f16_t *)ws.Xp; a.ML = ws.ML; a.spans = ws.spans;
-    a.n = p.n; a.B = p.B; a.R = p.R; a.Rs = pl.Rs; a.nblocks = pl.nblocks; a.G = pl.G;
+    a.n = p.n; a.B = p.B; a.R = p.R; a.Rs = pl.Rs; a.nblocks = pl.nblocks; a.G = pl.G; a.num_cus = ctx->num_cus;
+    a.next_w[0] = ctx->w.WvP; a.next_w[1] = ctx->w.WoP;
     // H is read once per step; when a batch of it is larger than the 256 MB memory-side cache, keeping its lines
     // out of the caches leaves them to the data that is re-read and raises the streaming rate (measured, core
     // kernel: 1 GB of per-beam histories 216 -> 184 us; 640 MB shared by two row blocks 149 -> 144 us).  Below

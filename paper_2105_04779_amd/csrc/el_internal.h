@@ -237,7 +237,8 @@ struct StreamArgs {
     f16_t *Xp;               // [slot, Rs, DM] fp16, each piece already divided by its own sum, in fragment order (frag16_index)
     float *ML;               // [slot, Rs, 2]  (reference max in log2 units, sum)
     const int4 *spans;       // the cut (see CutArgs)
-    int n, B, R, Rs, nblocks, G;
+    const void *next_w[2];   // packed weights of a6 and a7, read ahead for them (null: not those projections)
+    int n, B, R, Rs, nblocks, G, num_cus;
     int stream_hint;         // nonzero: fetch H with the non-temporal hint (H far larger than the memory-side cache)
 };
 hipError_t launch_core_stream(const StreamArgs &a, int d_m, bool bf16, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
