@@ -288,15 +288,15 @@ k_vproj(const VprojArgs a)
 #pragma unroll
                 for (int s = 0; s < KS; ++s)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) v[s][e] *= c;
+                    for (int e = 0; e < 8; ++e) v[s][e] = c != 0.f ? v[s][e] * c : 0.f;
             }
             m_run = m_new;
 #pragma unroll
             for (int p = 0; p < PC; ++p) {
                 if (p0 + p >= np_max) continue;
-                const bool there = ml[p][1] > 0.f;       // an empty piece's row was never written
-                const float wp = there ? exp2f(ml[p][0] - m_new) * ml[p][1] : 0.f;
-                den += wp;
+                const float wp = ml[p][1] > 0.f ? exp2f(ml[p][0] - m_new) * ml[p][1] : 0.f;
+                const bool there = wp != 0.f;            // an empty piece's row was never written, and one whose weight
+                den += wp;                               // underflows may hold fp16 infinities
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
                     const h8 xs = there ? xv[p][s] : h8{};

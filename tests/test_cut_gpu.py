@@ -47,3 +47,29 @@ def test_cuts(dtype, B, beam, heads, d_m, n, lens, splits):
     record(f"{w.name}: splits={splits} err={err:.3e}")
     assert err <= TOL[dtype]
     layer.close()
+
+
+@pytest.mark.parametrize("heads,d_m", [(16, 1024), (12, 768)])
+def test_a_piece_of_vanishing_weight_is_not_multiplied(heads, d_m):
+    """Every head scores its last key +512 and the others -512, whose weights underflow to zero in fp32.  The other keys hold
+    finite bf16 values beyond the fp16 range, so a piece without the last key stores infinities; its weight is exactly
+    zero, and so must its contribution be."""
+    w = wl.custom(f"cut_zero_weight_{d_m}", dtype="bf16", B=1, beam=1, heads=heads, d_m=d_m, d_k=64, n=256, index=96)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.asarray([w.n], dtype=np.int32)
+    # projected queries of ones against W^K's first row of ones: a score is 64 / sqrt(64) times the key's first element
+    W["Wq"][:] = 0.0
+    W["bq"][:] = 1.0
+    W["Wk"][:] = 0.0
+    W["Wk"][0, :] = 1.0
+    H[0, :, 0] = -64.0
+    H[0, -1, 0] = 64.0
+    H[0, :-1, 1:] = 131072.0
+    ref = oracle_out(w, W, H, Q, L)
+    layer = make_layer(w, W)
+    layer.set_splits(8)
+    err = rel_err(gpu_out(layer, w, H, Q, L), ref)
+    record(f"{w.name}: err={err:.3e}")
+    assert err <= TOL["bf16"]
+    layer.close()
