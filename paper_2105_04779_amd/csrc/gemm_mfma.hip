@@ -15,9 +15,9 @@
 // rows), the columns are split further and the rows are read once per part, out of L2.
 //
 // Storage-dtype operands enter the MFMA exactly (a1 runs in the storage type).  From a2 on everything is fp16: bf16
-// weights are converted once at prepare time (exact above 2^-14, |error| <= 2^-25 below), and the intermediates Qp,
-// merged X and A are rounded to fp16 once each (2^-12 relative; the measured end-to-end error stays several times
-// under the 2e-3 bar).  Accumulation is fp32.
+// weights are converted once at prepare time (exact above 2^-14, |error| <= 2^-25 below), and the intermediates Qp, the
+// pieces of X and A are rounded to fp16 once each (2^-12 relative; the measured end-to-end error stays several times
+// under the 2e-3 bar); sums of several pieces enter a6 as a high + low pair.  Accumulation is fp32.
 #include <type_traits>
 #include "el_internal.h"
 #include "cut.h"
@@ -194,6 +194,7 @@ k_qelq(const QelqArgs a)
 // bytes.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup per 16 rows, the
 // 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024: 38.9 -> 23.0 us;
 // 512 rows, one piece each: 19.7 -> 10.2; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 10.0; 4 rows: 8.6 -> 5.4.
+// The low half of merged sums is 0.2 to 0.4 us of that (4 rows 23.1 -> 23.3 us the step, 1280 rows 197.3 -> 199.3).
 struct VprojArgs {
     const u4 *Wp;          // (W^V) in fragments: [head][k / 32][column / 16 % 4][lane]
     const f16_t *Xp;       // normalised fp16 pieces [slot, Rs, d_m] in fragment order
@@ -269,6 +270,7 @@ k_vproj(const VprojArgs a)
     int parity = 0;
     for (int tile = pl.group; tile < tiles; tile += a.groups) {
         if (tile + a.groups < tiles) look_up(tile + a.groups);                      // the next tile's table entries
+        const bool merged = np_max > 1;                  // (uniform)
         float v[KS][8], m_run = -INFINITY, den = 0.f;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
@@ -301,12 +303,12 @@ k_vproj(const VprojArgs a)
                 for (int s = 0; s < KS; ++s) {
                     const h8 xs = there ? xv[p][s] : h8{};
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) v[s][e] = fmaf(wp, (float)xs[e], v[s][e]);
+                    for (int e = 0; e < 8; ++e) v[s][e] = fmaf(merged ? wp : 1.f, (float)xs[e], v[s][e]);
                 }
             }
         }
         if (tile + a.groups < tiles) { locate(); load_pieces(0); }
-        const float inv = den > 0.f ? 1.0f / den : 0.f;
+        const float inv = !(den > 0.f) ? 0.f : merged ? 1.0f / den : 1.f;      // a single piece goes on as it is
         if (SEG && nb == 0 && w == 7) {                  // (a wavefront that adds nothing up below)
             const int m = min(16 * tile + r16, a.M - 1);
             const f16_t *qp = a.Qp + (size_t)m * DM + head * 64 + 16 * q;
@@ -322,13 +324,26 @@ k_vproj(const VprojArgs a)
         f4 acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+        // The pieces were rounded to fp16 once.  Merged sums enter the products as a high + low pair (by truncation: two values per
+        // instruction, never beyond the fp16 range), so that an element cut into pieces is no less precise than one in a single
+        // piece, whose sum is an fp16 value already.  Rounded to fp16 once more they cost up to 13 % of error (d_m 1024, one row of
+        // 128 positions in two pieces: 3.92e-4 -> 4.47e-4 against fp64).
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            h8 xm;
+            u4 part;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) xm[e] = (_Float16)(v[s][e] * inv);
+            for (int k = 0; k < 4; ++k) part[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(v[s][2 * k] * inv, v[s][2 * k + 1] * inv));
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wv[s][t], __builtin_bit_cast(u4, xm), acc[t]);
+            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wv[s][t], part, acc[t]);
+            if (!merged) continue;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const h2 high = __builtin_bit_cast(h2, (unsigned)part[k]);
+                part[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(fmaf(v[s][2 * k], inv, -(float)high[0]),
+                                                                                  fmaf(v[s][2 * k + 1], inv, -(float)high[1])));
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wv[s][t], part, acc[t]);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) red[parity][(w * NT + t) * 64 + l] = acc[t];
