@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2105_04779_amd import workloads as wl
-from helpers import TOL, gpu_out, make_layer, oracle_out, record, rel_err, to_device
+from helpers import TOL, err_report, fmt_report, gpu_out, make_layer, oracle_out, record, rel_err, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,17 @@ def test_operands_aligned_to_one_element(d_m, heads):
     assert float(obuf[0]) == 7.0 and float(obuf[-1]) == 7.0
     assert rel_err(out.cpu().numpy(), ref) <= TOL["f32"]
     layer.close()
+
+
+@pytest.mark.parametrize("d_m,heads,beam,n,bound", [(64, 4, 2, 32, 2.6e-7), (64, 4, 3, 200, 2.9e-7), (128, 2, 4, 150, 3.9e-7), (128, 8, 2, 60, 3.9e-7)])
+def test_one_launch_step_sums_in_short_chains(d_m, heads, beam, n, bound):
+    """Relative 2-norm error of the step against fp64.  m additions one after the other cost about u sqrt(m / 2) of the sum's
+    norm (u = 2.4e-8, one rounding's rms): 1.4e-7 for the 64 terms of a product in one chain, 0.7e-7 in four; products follow
+    each other four times.  Measured with one chain 3.4e-7 to 5.0e-7, with four 1.9e-7 to 2.7e-7; the bounds lie between."""
+    w = wl.custom(f"chains_{d_m}_{heads}", dtype="f32", B=16, beam=beam, heads=heads, d_m=d_m, d_k=d_m // heads, n=n, len_lo=(n + 1) // 2,
+                  len_hi=n, index=92)
+    W = wl.weights(w)
+    H, Q, L = wl.batch(w, poison=False)
+    rep = err_report(gpu_out(make_layer(w, W), w, H, Q, L), oracle_out(w, W, H, Q, L))
+    record(f"{w.name}: {fmt_report(rep)}")
+    assert rep["l2"] <= bound
