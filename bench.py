@@ -27,7 +27,7 @@ ROTATE_BYTES = 768e6           # >= 3x the 256 MB memory-side cache
 ARITH = {
     "bf16": "bf16 MFMA in the attention core (EL-Q and P as high+low bf16 pairs), fp16 MFMA in the projections, fp32 accumulation and softmax",
     "f16": "fp16 MFMA (EL-Q as a high+low fp16 pair), fp32 accumulation and softmax",
-    "f32": "fp32 vector FMA",
+    "f32": "fp32 MFMA, fp32 accumulation and softmax",
 }
 
 
@@ -273,12 +273,12 @@ def measure(a, w, torch, np, el_attn, tm, wl):
     torch.cuda.synchronize()
     core_ms = timed.read_core_timing(core_steps)
     timed.core_timing(0)
-    core_avg_ms = float(np.mean(core_ms))
+    core_avg_ms = float(np.mean(core_ms)) if core_ms else None      # a step in one launch has no core to time
 
     sum_len = int(lens.sum())
     core_bytes = tm.core_algorithmic_bytes(sum_len, w.d_m, w.elem_bytes)
     step_bytes = tm.step_algorithmic_bytes(sum_len, w.B, w.beam, w.d_m, w.heads * w.d_k, w.elem_bytes, 4)
-    achieved = core_bytes / (core_avg_ms * 1e-3) / 1e9
+    achieved = core_bytes / (core_avg_ms * 1e-3) / 1e9 if core_ms else None
     # HBM bytes per launch of that kernel from the committed rocprofv3 counter runs (FETCH_SIZE + WRITE_SIZE,
     # each scaled by what the same counter reads for a plain copy of known size).  The counters cannot be read
     # inside this run, so the stored figure carries the digest of the kernel sources it was taken on: it is
@@ -307,9 +307,9 @@ def measure(a, w, torch, np, el_attn, tm, wl):
                    "n": w.n, "sum_len": sum_len, "h_buffers_rotated": nbuf, "mfma_path": layer.uses_mfma,
                    "splits": a.splits, "layers": L},
         "roofline": {"bound": "hbm", "kernel": "attention core (a3-a5)", "achieved": achieved, "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_detail": traffic_detail,
-                     "bytes_per_launch": core_bytes, "avg_launch_us": core_avg_ms * 1e3,
-                     "min_launch_us": float(np.min(core_ms)) * 1e3},
+                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS if core_ms else None, "traffic": traffic, "traffic_detail": traffic_detail,
+                     "bytes_per_launch": core_bytes, "avg_launch_us": core_avg_ms * 1e3 if core_ms else None,
+                     "min_launch_us": float(np.min(core_ms)) * 1e3 if core_ms else None},
         "step": {"algorithmic_bytes": step_bytes, "event_ms_per_step": ev_ms_per_step, "ms_per_layer": ms_per_step / L,
                  "hbm_frac_whole_step": step_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
                  "flops": L * tm.step_flops(sum_len, w.B, w.beam, w.heads, w.d_m, w.d_k),

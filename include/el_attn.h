@@ -284,7 +284,9 @@ int32_t el_attn_uses_mfma(const el_attn_ctx *ctx);
  * carries the pair itself, so it reads that dispatch's own begin and end).  read() waits for the
  * recorded events, writes the elapsed milliseconds of each step's core kernel to ms_out
  * (at most `capacity`), stores the number written in *count and forgets them.  Steps beyond
- * max_steps are not bracketed.  max_steps = 0 disables timing and releases the events.
+ * max_steps are not bracketed, and neither are steps that run as one launch (narrow layers in fp32
+ * arithmetic: a1..a7 in one kernel, no core of its own).  max_steps = 0 disables timing and releases
+ * the events.
  * Errors: INVALID_ARG (null ctx/ms_out/count, negative sizes), ALLOC, HIP.
  */
 el_status el_attn_core_timing_enable(el_attn_ctx *ctx, int32_t max_steps);

@@ -244,17 +244,8 @@ el_status run_a7(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const 
 // a1..a7
 el_status run_step(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, hipStream_t s)
 {
-    if (!el_attn_uses_mfma(ctx) && small_step_applies(p)) {
-        // one launch; the core's timing brackets the whole of it
-        const bool timed = ctx->ev && ctx->ev_used < ctx->ev_cap;
-        if (timed && hipEventRecord(ctx->ev[2 * ctx->ev_used], s) != hipSuccess) return EL_ERR_HIP;
-        if (launch_small_step(ctx, p, s) != hipSuccess) return EL_ERR_HIP;
-        if (timed) {
-            if (hipEventRecord(ctx->ev[2 * ctx->ev_used + 1], s) != hipSuccess) return EL_ERR_HIP;
-            ctx->ev_used++;
-        }
-        return EL_OK;
-    }
+    // one launch, without an attention core of its own that its timing could bracket
+    if (!el_attn_uses_mfma(ctx) && small_step_applies(p)) return launch_small_step(ctx, p, s) == hipSuccess ? EL_OK : EL_ERR_HIP;
     StepFormats fmt;
     const el_status st = run_a1_to_a6(ctx, p, ws, nullptr, s, &fmt);
     return st != EL_OK ? st : run_a7(ctx, p, ws, ctx->w.c_out, s);

@@ -87,3 +87,17 @@ def test_one_launch_step_sums_in_short_chains(d_m, heads, beam, n, bound):
     rep = err_report(gpu_out(make_layer(w, W), w, H, Q, L), oracle_out(w, W, H, Q, L))
     record(f"{w.name}: {fmt_report(rep)}")
     assert rep["l2"] <= bound
+
+
+@pytest.mark.parametrize("d_m,heads,timed", [(64, 4, 0), (256, 4, 3)])
+def test_core_timing_reports_attention_cores_only(d_m, heads, timed):
+    """A step that runs as one launch has no core kernel (a3-a5) to bracket: it must not report its own time as the core's."""
+    w = wl.custom(f"timing_{d_m}", dtype="f32", B=2, beam=2, heads=heads, d_m=d_m, d_k=d_m // heads, n=32, index=93)
+    layer = make_layer(w, wl.weights(w))
+    H, Q, L = wl.batch(w)
+    layer.core_timing(8)
+    for _ in range(3):
+        gpu_out(layer, w, H, Q, L)
+    ms = layer.read_core_timing(8)
+    assert len(ms) == timed and all(t > 0.0 for t in ms)
+    layer.close()
