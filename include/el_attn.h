@@ -212,9 +212,11 @@ el_status el_attn_expand_query(el_attn_ctx *ctx, const void *queries, float *elq
 /*
  * Tuning knob, never semantics: about how many pieces per batch element the attention core
  * cuts the keys into (the MFMA core cuts the list of all valid 16-row tiles of a batch into
- * B x splits equal spans, one workgroup each per block of rows; the fp32-arithmetic core only
- * cuts keys that are longer than 8 d_model, every element into `splits` key ranges; partial
- * results are merged with the log-sum-exp rule).
+ * B x splits equal spans, one workgroup each per block of rows; the fp32-arithmetic core cuts
+ * every element into `splits` key ranges (8 at most) where the scores of a step do not fit the
+ * workspace, R x n > 8 x R64 x d_model with R = heads * beam, R64 = R rounded up to a multiple of
+ * 64 and n rounded up to a multiple of 4, and not at all elsewhere; partial results are merged
+ * with the log-sum-exp rule).
  * 0 restores the automatic choice.  Must not exceed el_attn_max_splits().
  */
 el_status el_attn_set_splits(el_attn_ctx *ctx, int32_t splits);

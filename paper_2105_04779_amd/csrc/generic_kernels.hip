@@ -227,7 +227,7 @@ k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int
     const float *srow[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) srow[i] = S + ((size_t)b * R + min(r0 + RW * w + i, R - 1)) * ldS;
-    // the scores of one chunk of this wavefront's four rows, all requested together
+    // the scores of one chunk of this wavefront's rows, all requested together
     float sv[RW][PL];
     auto load_scores = [&](int c0) {
 #pragma unroll
@@ -324,8 +324,8 @@ k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// a3-a5 without scores in memory, for keys so long next to d_m that the scores do not fit the workspace
-// (n > 8 d_m): one (row r, key-range part p, batch element b) per workgroup, on the vector ALU.
+// a3-a5 without scores in memory, for keys so long next to d_m that the scores do not fit the workspace (see scores_fit):
+// one (row r, key-range part p, batch element b) per workgroup, on the vector ALU.
 // Writes the un-normalised weighted sum, and the running max / sum of its range.
 template <typename T, int MAXD>
 __global__ void __launch_bounds__(kBlock)
@@ -498,7 +498,10 @@ hipError_t launch_elq_generic(const el_attn_ctx *ctx, const Problem &p, const fl
 }
 
 // The scores of a step take R x round_up(n, 4) floats per batch element of the region the key-range partials have
-// (8 x R64 x d_m floats).
+// (8 x R64 x d_m floats): with 64 rows up to n = 8 d_m, with fewer up to n = 8 d_m 64 / R.  Capacity alone decides, because
+// this path is the faster one everywhere, also where one workgroup per 64 columns streams very long keys (step in us, here
+// against the key-range core): one element, d_m 64, 4 rows, n 8192 93 / 140; d_m 512, 8 rows, n 8192 107 / 794, n 32768
+// 364 / 3058; d_m 1024, 16 rows, n 8192 116 / 1634; d_m 30, 3 rows, n 4000 77 / 79.
 bool scores_fit(const Problem &p)
 {
     return (int64_t)p.R * ((p.n + 3) / 4 * 4) <= (int64_t)kMaxPartsGeneric * ((p.R + 63) / 64 * 64) * p.d_m;

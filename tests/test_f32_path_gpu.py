@@ -4,6 +4,7 @@ long for scores in memory, the three tile sizes of the products, and the one-lau
 import numpy as np
 import pytest
 
+import oracle
 from paper_2105_04779_amd import workloads as wl
 from helpers import TOL, err_report, fmt_report, gpu_out, make_layer, oracle_out, record, rel_err, to_device
 
@@ -100,4 +101,41 @@ def test_core_timing_reports_attention_cores_only(d_m, heads, timed):
         gpu_out(layer, w, H, Q, L)
     ms = layer.read_core_timing(8)
     assert len(ms) == timed and all(t > 0.0 for t in ms)
+    layer.close()
+
+
+KEY_RANGE_CASES = [
+    # dtype, B, heads, beam, d_m, n, splits: R x n beyond 8 x R64 x d_m, so no room for the scores
+    ("f16", 2, 4, 16, 64, 516, 0),               # one element past the line, eight ranges
+    ("bf16", 3, 16, 4, 320, 2570, 0),            # two columns per thread, a length that is no multiple of four
+    ("f32", 1, 16, 4, 640, 5124, 3),             # three columns per thread in use of four; ranges by request
+    ("bf16", 2, 2, 32, 64, 700, 1),              # one range: nothing to merge
+    ("f32", 2, 4, 16, 64, 520, 15),              # more ranges than the partials' room: eight
+    ("f16", 1, 13, 5, 1040, 16420, 0),           # R64 of 128 for 65 rows; eight columns per thread
+]
+
+
+def _key_range_inputs(dtype, B, heads, beam, d_m, n):
+    R = heads * beam
+    assert R * ((n + 3) // 4 * 4) > 8 * ((R + 63) // 64 * 64) * d_m
+    w = wl.custom(f"ranges_{dtype}_{d_m}_{n}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=d_m // heads, n=n, index=94)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w)
+    L = np.asarray([n, n // 2 + 1, 7][:B], dtype=np.int32)
+    return w, W, H, Q, L
+
+
+@pytest.mark.parametrize("dtype,B,heads,beam,d_m,n,splits", KEY_RANGE_CASES)
+def test_keys_too_long_for_scores_in_memory(dtype, B, heads, beam, d_m, n, splits):
+    """The key-range core and its merge, against the oracle's own Eq. 9 order (fp64): H is not projected, which at these
+    lengths is most of the work."""
+    w, W, H, Q, L = _key_range_inputs(dtype, B, heads, beam, d_m, n)
+    ref = oracle.el_reference(H, L, Q, W["Wq"], W["bq"], W["Wk"], W["bk"], W["Wv"], W["bv"], W["Wo"], W["bo"], heads=heads, d_k=w.d_k)
+    for b in range(B):
+        H[b, L[b]:] = np.nan
+    layer = make_layer(w, W)
+    layer.set_splits(splits)
+    err = rel_err(gpu_out(layer, w, H, Q, L), ref)
+    record(f"{w.name} splits={splits}: err={err:.3e}")
+    assert not layer.uses_mfma and err <= TOL["f32"]
     layer.close()

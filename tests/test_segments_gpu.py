@@ -135,6 +135,18 @@ def test_segments_of_many_rows(dtype, heads, d_m, B, x):
     layer.close()
 
 
+@pytest.mark.parametrize("dtype,splits", [("f32", 0), ("f16", 5)])
+def test_segments_of_the_key_range_core(dtype, splits):
+    """64 rows and n > 8 d_m: no room for the scores, so k_seg_finish folds the statistics of several key ranges."""
+    w = wl.custom(f"seg_ranges_{dtype}", dtype=dtype, B=3, beam=16, heads=4, d_m=64, d_k=16, n=600, index=74)
+    W = _weights_with_visible_key_bias(w)
+    H, Q, L = _inputs(w, 1, 3, 16, 600, [600, 301, 5])
+    layer = make_layer(w, W)
+    layer.set_splits(splits)
+    _check_segment(f"segments of key ranges {dtype}", w, *_seg_gpu(layer, w, H, L, Q), *_seg_oracle(w, W, H, L, Q))
+    layer.close()
+
+
 def test_statistics_join_with_an_ordinary_attention_cache():
     # The per-beam continuation handled OUTSIDE the library (a caller's key/value cache): its log-sum-exp and head
     # outputs come from the definition (the oracle, as fp32 inputs); the prefix segment comes from the device.
