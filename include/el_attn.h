@@ -234,9 +234,11 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
 /*
  * What the automatic choice would be for a shape on a device with `compute_units` compute units (host
  * arithmetic only, no device needed): rows per row block in groups of 16 (*row_groups) and the number of
- * equal spans the list of valid tiles is cut into (*spans; workgroups = spans x row blocks) by the MFMA
- * attention core.  Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or
- * 1024: no MFMA core).
+ * spans the list of valid tiles is cut into (*spans) by the MFMA attention core.  Workgroups: spans x row
+ * blocks of 16 *row_groups rows; while spans are short (B x tiles x blocks of 32 rows at most 6 x
+ * compute_units) a block of 32 is two workgroups of 16, so spans x ceil(heads * beam / 16).
+ * Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or 1024: no MFMA
+ * core).
  */
 el_status el_attn_plan_preview(int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n,
                                int32_t compute_units, int32_t *row_groups, int32_t *spans);

@@ -144,7 +144,7 @@ def test_plan_preview_on_the_benchmark_shapes(ea):
         st, rg, sp = ea.el_attn_plan_preview(B, beam, heads, d_m, n, 256)
         assert st == ea.EL_OK
         return rg, sp
-    # rows per workgroup in 16s, spans of the flattened tile list (workgroups = spans x row blocks)
+    # rows per row block in 16s, spans of the tile list
     assert plan(64, 4, 16, 1024, 1024) == (2, 128)   # 64 rows: two blocks of 32, one workgroup per compute unit
     assert plan(320, 4, 16, 1024, 1024) == (2, 128)  # more sentences: longer spans, never more workgroups than units
     assert plan(512, 1, 16, 1024, 1024) == (1, 256)  # per-beam histories: 16 rows, one block
@@ -159,6 +159,14 @@ def test_plan_preview_on_the_benchmark_shapes(ea):
                 blocks = -(-16 * beam // (16 * rg))
                 assert rg == (1 if beam == 1 else 2) and 1 <= sp and sp * blocks <= max(256, blocks)
                 assert sp <= B * (ea.el_attn_max_splits() - 1)             # every piece has a slot
+    # short spans: a block of 32 rows is two workgroups of 16, and still never more workgroups than units
+    assert plan(1, 4, 16, 1024, 613) == (2, 9) and plan(1, 5, 8, 512, 613) == (2, 9)        # 4 x 9 and 3 x 9 workgroups
+    for B in (1, 2, 5, 24, 48):
+        for heads, beam, d_m in ((16, 4, 1024), (12, 5, 768), (8, 5, 512), (8, 3, 512), (12, 3, 768)):
+            for n in (16, 100, 512, 1024):
+                rows, (rg, sp) = heads * beam, plan(B, beam, heads, d_m, n)
+                short = B * -(-n // 16) * -(-rows // 32) <= 6 * 256
+                assert rg == 2 and sp * -(-rows // (16 if short else 32)) <= 256
     I = ea.EL_ERR_INVALID_ARG
     assert ea.el_attn_plan_preview(0, 4, 16, 1024, 64, 256)[0] == I
     assert ea.el_attn_plan_preview(4, 4, 16, 1024, 64, 0)[0] == I
