@@ -1,25 +1,27 @@
 """GPU parity of the decode step where the cut of its work changes form: one element cut into many spans, few elements
-cut one by one, spans that run through more elements than the table lists lengths for, and the most pieces per element;
+cut one by one, spans that run through more elements than the table lists lengths for, and dozens of pieces per element;
 with the projections' column splits and row-tile groups that belong to these row counts."""
 from dataclasses import replace
 
 import numpy as np
 import pytest
+import torch
 
-from paper_2105_04779_amd import workloads as wl
-from helpers import TOL, gpu_out, make_layer, oracle_out, record, rel_err
+import oracle
+from paper_2105_04779_amd import el_attn, workloads as wl
+from helpers import TOL, gpu_out, make_layer, oracle_out, record, rel_err, to_device
 
 pytestmark = pytest.mark.gpu
 
 CASES = [
     # dtype, B, beam, heads, d_m, n, lens, splits
-    ("bf16", 1, 4, 16, 1024, 1000, [1000], 0),              # one sentence: 15 spans, as many pieces to merge
+    ("bf16", 1, 4, 16, 1024, 1000, [1000], 0),              # one sentence: 13 spans of five tiles, as many pieces to merge
     ("bf16", 1, 4, 16, 1024, 613, [613], 0),
     ("f16", 1, 1, 8, 512, 333, [333], 0),
     ("bf16", 1, 3, 12, 768, 17, [17], 0),                   # two tiles, the second with one row
     ("bf16", 4, 4, 16, 1024, 410, [410, 205, 1, 333], 0),   # cut per element
     ("f16", 5, 5, 12, 768, 300, [300, 16, 17, 299, 1], 0),
-    ("bf16", 2, 4, 16, 1024, 700, [700, 350], 15),          # the most pieces
+    ("bf16", 2, 4, 16, 1024, 700, [700, 350], 15),          # the most splits
     ("bf16", 2, 2, 8, 512, 500, [1, 500], 15),
     ("bf16", 700, 4, 16, 1024, 40, "mixed", 0),             # more than four elements per span, some of one row
     ("f16", 1000, 2, 8, 512, 33, "mixed", 0),
@@ -98,4 +100,25 @@ def test_cutting_an_element_costs_no_precision(dtype, heads, d_m, beam, n):
     ratio = (err[0] / err[1]) ** 0.5
     record(f"{w.name}: rms error of two pieces / of one = {ratio:.4f}")
     assert ratio <= 1.04
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype,heads,d_m,beam,n", [("f16", 8, 512, 4, 4096), ("bf16", 12, 768, 1, 4093)])
+def test_dozens_of_pieces_of_one_element(dtype, heads, d_m, beam, n):
+    """A workspace for 64 elements and a call with one: 64 spans of four tiles, all of the same element, merged four pieces at a
+    time; the step and the segment form."""
+    w = wl.custom(f"cut_pieces_{dtype}_{d_m}", dtype=dtype, B=1, beam=beam, heads=heads, d_m=d_m, d_k=64, n=n, index=98)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.asarray([n], dtype=np.int32)
+    st, _, spans = el_attn.el_attn_plan_preview(1, beam, heads, d_m, n, 256)
+    assert st == el_attn.EL_OK and spans <= 14                       # with room for one element only
+    layer = make_layer(w, W, max_batch=64)
+    err = rel_err(gpu_out(layer, w, H, Q, L), oracle_out(w, W, H, Q, L))
+    A, lse = layer.decode_segment(to_device(H, dtype), torch.from_numpy(L).cuda(), to_device(Q, dtype))
+    torch.cuda.synchronize()
+    ref_A, ref_lse = oracle.segment_reference(H, L, Q, W["Wq"], W["bq"], W["Wk"], W["bk"], W["Wv"], W["bv"], heads=heads, d_k=64)
+    err_A, err_lse = rel_err(A.cpu().numpy(), ref_A), float(np.abs(lse.cpu().numpy() - ref_lse).max())
+    record(f"{w.name}: err={err:.3e} seg_A err={err_A:.3e} lse err={err_lse:.3e}")
+    assert err <= TOL[dtype] and err_A <= TOL[dtype] and err_lse <= 5e-3
     layer.close()
