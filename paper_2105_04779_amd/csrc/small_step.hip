@@ -3,11 +3,10 @@
 //
 // At d_m = 64 or 128 a layer's four weight matrices are 64 or 256 KB: a workgroup can read all of them for itself, and
 // does so before anything else (a wavefront keeps the fragments of its 16 output columns of every projection in
-// registers, up to 128 of them), so the step costs one round trip to memory plus six barriers.  As separate launches
+// registers, up to 128 of them), so the step costs one round trip to memory plus seven barriers.  As separate launches
 // every step of the chain pays a launch and a round trip of its own.  Arithmetic and rounding are those of
 // generic_kernels.hip: fp32 operands, fp32 products and sums (16x16x4 MFMA), four consecutive k per lane.
-// Measured, fp32, per call among others: 2 sentences x 2 beams, d_m 64, n 32: 23.5 us as the six launches, 8.5 us here;
-// d_m 128, beam 4, n 256: 28.9 against 23.6 us.
+// Measured, fp32, per call among others: 2 sentences x 2 beams, d_m 64, n 32: 21.5 us as the six launches, 8.5 us here.
 #include "el_internal.h"
 
 namespace el {
@@ -18,7 +17,8 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
 
 constexpr int kSmallRows = 64;                          // heads * beam
-constexpr int kSmallScores = 64 * 260;                  // floats of the score matrix: rows padded to 16 x (n padded to 16, + 4)
+constexpr int kSmallWork = 1 << 19;                     // padded rows x padded n x d_m (see small_step_applies)
+constexpr int kSmallScores = kSmallWork / 64 + 4 * kSmallRows;      // floats of the score matrix, padded rows x (padded n + 4), at d_m >= 64
 
 __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ f4 load4(const float *p) { return *(const f4 *)p; }
@@ -220,15 +220,23 @@ k_small_step(const SmallArgs a)
     }
 }
 
-// Where one workgroup per batch element is the faster form: the weights fit its registers (d_m 64 or 128, head sizes
-// that are whole 16-wide slices), at most 16 beams (one row tile), and its scores and weighted sums, R x n x d_m
-// products each on one compute unit, stay below what the separate launches need for their extra round trips: 2^19
-// (d_m 128, 16 rows, n 256) 23.6 against 28.9 us, 2^20 (d_m 64, 64 rows, n 256) 30.1 against 28.2 us.
+// Where one workgroup per batch element does the whole step: the weights fit its registers (d_m 64 or 128, head sizes that
+// are whole 16-wide slices), at most 16 beams (one row tile), and its scores and weighted sums, R x n x d_m products each on
+// one compute unit, stay below what the separate launches need for their extra round trips.  us, here against separately:
+//                                        1 element    16           256          1024         4096
+//   d_m 64, 4 heads, 2 beams, n 32       8.5 / 21.5   8.8 / 23.1   9.0 / 22.7   29.9 / 36.3  118 / 98
+//   d_m 64, 4 heads, 16 beams, n 64      16.1 / 22.1  16.6 / 22.1  17.1 / 42.0  61.4 / 120   248 / 433
+//   d_m 128, 2 heads, 4 beams, n 100     19.3 / 21.6  19.7 / 22.9  20.1 / 34.2  75.0 / 75.4  296 / 260
+//   d_m 128, 2 heads, 4 beams, n 256     23.0 / 22.4  24.0 / 23.6  26.5 / 41.1  99.9 / 105   429 / 405     2^19
+//   d_m 128, 8 heads, 8 beams, n 64      28.2 / 22.1  29.1 / 22.7  29.3 / 65.0  115 / 202    455 / 803     2^19
+// and 30.1 / 28.2 at 2^20 (d_m 64, 64 rows, n 256, 2 elements).  So the line is right for a batch and generous for a few
+// elements near it; thousands of elements of few rows would be faster separately, because beyond one element per
+// compute unit the workgroups run in rounds that each read the weights again.
 bool small_step_applies(const Problem &p)
 {
     if ((p.d_m != 64 && p.d_m != 128) || p.d_k % 16 != 0 || p.beam > 16 || p.R > kSmallRows) return false;
     const int64_t n16 = (p.n + 15) / 16 * 16, r16 = (p.R + 15) / 16 * 16;
-    if (r16 * (n16 + 4) > kSmallScores || r16 * n16 * p.d_m > (int64_t)1 << 19) return false;
+    if (r16 * n16 * p.d_m > kSmallWork) return false;
     const size_t four = 4 * dtype_size(p.dtype);         // operands are fetched four elements at a time
     return p.H_batch_stride % 4 == 0 && ((uintptr_t)p.H & (four - 1)) == 0 && ((uintptr_t)p.queries & (four - 1)) == 0;
 }

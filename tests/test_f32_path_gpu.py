@@ -28,6 +28,9 @@ CASES = [
     ("f32", 2, 6, 8, 128, 16, 80, [80, 47]),
     ("bf16", 2, 3, 4, 64, 16, 40, [40, 7]),
     ("f16", 2, 4, 2, 128, 64, 33, [33, 32]),
+    ("f32", 2, 16, 4, 64, 16, 128, [128, 113]),          # the largest score matrix, and one column more than it holds
+    ("f32", 2, 16, 4, 64, 16, 129, [129, 128]),
+    ("f32", 2, 4, 4, 128, 32, 256, [256, 241]),          # the same at d_m 128
 ]
 
 
