@@ -21,6 +21,10 @@ HIPCC_FLAGS = [
 ]
 
 
+# kernels that are built around what their wavefronts hold in registers
+NO_SPILL_KERNELS = ("k_core_stream", "k_qelq", "k_vproj", "k_oproj", "k_small_step")
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
@@ -33,8 +37,9 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     # The resource remarks are read back: the attention core keeps 32 rows of expanded queries or a quarter of the
-    # accumulators in each wavefront's registers, and a change that makes the compiler spill any of them costs a
-    # fifth of the kernel's speed without failing a single test.  A spill there fails the build instead.
+    # accumulators in each wavefront's registers, the projections and the one-launch step their slices of the weights,
+    # and a change that makes the compiler spill any of them costs up to a fifth of the kernel's speed without failing a
+    # single test.  A spill there fails the build instead.
     res = subprocess.run(cmd + ["-Rpass-analysis=kernel-resource-usage"], stderr=subprocess.PIPE, text=True)
     spilled = check_core_spills(res.stderr)
     lines = res.stderr.splitlines()
@@ -56,13 +61,13 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
         raise subprocess.CalledProcessError(res.returncode, cmd)
     if spilled:
         os.remove(tmp)
-        raise RuntimeError("register spills in the attention core: " + ", ".join(f"{k}: {v}" for k, v in spilled.items()))
+        raise RuntimeError("register spills: " + ", ".join(f"{k}: {v}" for k, v in spilled.items()))
     os.replace(tmp, LIB)
     return LIB
 
 
 def check_core_spills(remarks: str) -> dict:
-    """{kernel name: spilled VGPRs} for the instances of k_core_stream that spill, from hipcc's
+    """{kernel name: spilled VGPRs} for the instances of NO_SPILL_KERNELS that spill, from hipcc's
     -Rpass-analysis=kernel-resource-usage remarks (a 'Function Name:' line opens each kernel's block)."""
     import re
     out, name = {}, None
@@ -72,7 +77,7 @@ def check_core_spills(remarks: str) -> dict:
             name = m.group(1)
             continue
         m = re.search(r"VGPRs Spill: (\d+)", ln)
-        if m and name and "k_core_stream" in name and int(m.group(1)) > 0:
+        if m and name and any(k in name for k in NO_SPILL_KERNELS) and int(m.group(1)) > 0:
             out[name] = int(m.group(1))
     return out
 

@@ -207,3 +207,12 @@ def test_build_fails_on_register_spills_in_the_attention_core():
     ])
     assert build.check_core_spills(remarks) == {core: 5}
     assert build.check_core_spills("") == {}
+
+
+@pytest.mark.parametrize("kernel", ["k_qelqILi1024ELb1ELi4EE", "k_vprojILi1024ELi4ELb1EE", "k_oprojILi768ELi2EfE", "k_small_stepIffLi128EE"])
+def test_build_fails_on_register_spills_where_weights_live_in_registers(kernel):
+    from paper_2105_04779_amd import build
+    name = "_ZN2el%d%sEvNS_1AE" % (len(kernel), kernel)
+    block = "a.hip:1:1: remark: Function Name: %s [-R]\na.hip:1:1: remark:     SGPRs Spill: 3 [-R]\na.hip:1:1: remark:     VGPRs Spill: %d [-R]\n"
+    assert build.check_core_spills(block % (name, 2)) == {name: 2}
+    assert build.check_core_spills(block % (name, 0)) == {}
