@@ -166,7 +166,7 @@ hipError_t launch_core_mfma(const el_attn_ctx *ctx, const Problem &p, const Work
     a.elq = (const uint16_t *)ws.ELQ;
     a.Xp = (f16_t *)ws.Xp; a.ML = ws.ML; a.spans = ws.spans;
     a.n = p.n; a.B = p.B; a.R = p.R; a.Rs = pl.Rs; a.nblocks = pl.nblocks; a.G = pl.G; a.num_cus = ctx->num_cus;
-    a.next_w[0] = ctx->w.WvP; a.next_w[1] = ctx->w.WoP;
+    a.next_w[0] = ctx->w.WvP; a.next_w[1] = ctx->w.WoP;      // (a segment's a7 belongs to the merge call, usually soon after)
     // H is read once per step; when a batch of it is larger than the 256 MB memory-side cache, keeping its lines
     // out of the caches leaves them to the data that is re-read and raises the streaming rate (measured, core
     // kernel: 1 GB of per-beam histories 216 -> 184 us; 640 MB shared by two row blocks 149 -> 144 us).  Below

@@ -40,11 +40,7 @@ __device__ __forceinline__ void split16(float x, uint16_t &hi, uint16_t &lo)
     }
 }
 
-// ---- LDS staging helpers shared by the MFMA kernels ---------------------------------------
-// 16-byte chunk swizzle inside a tile row: a bijection of the low four chunk bits that makes both
-// the row-wise b128 reads and the transposing b64 reads spread over all LDS banks.
-__device__ __forceinline__ int row_swizzle(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
-
+// ---- LDS staging helpers of the attention core ---------------------------------------------
 // One 1 KB piece of a row, fetched by one wavefront straight into LDS.  `lds_addr` is the
 // LDS byte address the piece starts at (lane i lands at +16 i), `voff` the lane's byte offset from
 // the wave-uniform global base.  Issued through inline assembly so that the compiler does not
