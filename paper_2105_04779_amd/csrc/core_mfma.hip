@@ -81,7 +81,10 @@ constexpr int kBoundaryCost = 4;
 // expanded queries to wait for and half the products per tile, against twice the tiles per span where the spans fill the
 // chip.  Whole steps, d_m 1024, beam 4, 32 against 16 rows: one sentence of 613 25.2 -> 23.6 us; twelve layers, 4 sentences
 // 342 -> 321; 8 of 512 27.9 -> 26.4; 16 of 512 (8 tiles) 32.0 -> 28.9; 32 of 512 (16 tiles) equal; d_m 512, 64 of 512 (16
-// tiles) 23.8 -> 24.6.
+// tiles) 23.8 -> 24.6.  Other widths and row counts, 32 against 16 rows: d_m 768, 60 rows, 16 of 256 to 512 29.6 -> 27.0; 36 rows
+// 29.1 -> 26.7; d_m 512, 40 rows 22.7 -> 21.1, 24 rows 22.0 -> 21.4; d_m 1024, 80 rows 33.2 -> 31.7, 128 rows, 8 of 512 34.1 ->
+// 29.8.  Of 95 such shapes 85 gain, up to 4 us; where the 16-row workgroups of many elements fill the chip, so that their spans
+// cross elements more often, it costs: d_m 768, 60 rows, 48 of 128 to 256 29.8 -> 33.1; d_m 1024, 80 rows, 64 of 64 37.5 -> 40.9.
 constexpr int kHalfBlockTiles = 12;
 
 CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)
