@@ -217,7 +217,8 @@ el_status el_attn_expand_query(el_attn_ctx *ctx, const void *queries, float *elq
  * workspace, R x n > 8 x R64 x d_model with R = heads * beam, R64 = R rounded up to a multiple of
  * 64 and n rounded up to a multiple of 4, and not at all elsewhere; partial results are merged
  * with the log-sum-exp rule).
- * 0 restores the automatic choice.  Must not exceed el_attn_max_splits().
+ * 0 restores the automatic choice (which alone may pick the core of short spans).  Must not exceed
+ * el_attn_max_splits().
  */
 el_status el_attn_set_splits(el_attn_ctx *ctx, int32_t splits);
 int32_t el_attn_max_splits(void);
@@ -237,6 +238,9 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
  * spans the list of valid tiles is cut into (*spans) by the MFMA attention core.  Workgroups: spans x row
  * blocks of 16 *row_groups rows; while spans are short (B x tiles x blocks of 32 rows at most 6 x
  * compute_units) a block of 32 is two workgroups of 16, so spans x ceil(heads * beam / 16).
+ * Small steps (whose elements, cut into spans of 64 positions, fill the device at most once with workgroups of 16
+ * rows; twice or three times where all of them are that short) run on a core that takes a whole span at once; the
+ * figures are then those of the core it stands in for.
  * Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or 1024: no MFMA
  * core).
  */

@@ -1,5 +1,5 @@
 // Planning and launch of the MFMA attention core (steps a3-a5 of the EL-attention decode step; the
-// kernel itself is in core_stream.hip), plus the two small fp32-FMA kernels that stand in for the MFMA
+// kernels themselves are in core_stream.hip and, for short spans, core_short.hip), plus the two small fp32-FMA kernels that stand in for the MFMA
 // projections around it when the head size is not 64: the query expansion as a high + low pair of
 // 16-bit planes (in the fragment order the core loads) and the log-sum-exp merge of the pieces.
 #include <cmath>
@@ -98,6 +98,7 @@ CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override,
     pl.nblocks = (p.R + 16 * pl.nrg - 1) / (16 * pl.nrg);
     pl.Rs = pl.nblocks * 16 * pl.nrg;
     pl.kcost = kBoundaryCost;
+    pl.short_tiles = 0;
     if (p.B > kScanMax) { pl.G = p.B; return pl; }
     long G;
     if (splits_override > 0) {
@@ -118,11 +119,36 @@ CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override,
     return pl;
 }
 
+// The core of short spans (core_short.hip): every element dealt out to workgroups of four tiles and 16 rows, while all of them
+// run at once (spans by the longest possible element).  Beyond that a second round of workgroups waits for the first one's
+// latency, which the streaming core pays once, and more pieces are written and merged.  Whole steps, streaming against short
+// core, 64 rows at d_m 1024 and 512 unless it says so (us; workgroups per compute unit of 256):
+//   d_m 1024    1 element of 613 positions 23.9 / 22.9    4 of 205 to 410, twelve layers 312 / 286    8 of 512 (1) 27.2 / 24.4
+//               2 of 128 22.9 / 20.0    16 of 300 (1.25) 27.1 / 28.1    12 of 512 (1.5) 26.9 / 29.1    128 of 200, 16 rows (2) 34.0 / 38.7
+//   d_m 768     8 of 512, 48 rows (0.75) 23.8 / 21.4    16 of 300 (0.9) 22.8 / 20.6    24 of 300 (1.4) 23.0 / 25.4
+//   d_m 512     24 of 300, 32 rows (0.9) 19.9 / 18.5    64 of 300, 8 rows (1.25) 21.2 / 21.5    128 of 200, 8 rows (2) 21.3 / 23.3
+// Where every element is one span there is no more to merge than before, and a second round pays (at d_m 512 two workgroups fit a
+// compute unit: a third):
+//   d_m 1024    100 of 64 (1.6) 42.8 / 37.9    512 of 64, 16 rows (2) 60.5 / 57.9    200 of 64 (3.1) 69.1 / 69.3    320 of 33 (5) 83.1 / 86.7
+//   d_m 768     200 of 64, 48 rows (2.3) 45.9 / 42.9    512 of 64, 12 rows (2) 42.0 / 39.6    320 of 33 (3.75) 55.7 / 57.0    1000 of 64 (3.9) 78.4 / 81.0
+//   d_m 512     200 of 64, 32 rows (1.6) 28.3 / 24.5    320 of 64 (2.5) 34.9 / 30.7    1000 of 64, 8 rows (3.9) 43.3 / 47.9
+void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
+{
+    if (p.B > kScanMax) return;
+    const int per_element = (p.n + 16 * kShortTiles - 1) / (16 * kShortTiles), blocks = (p.R + 15) / 16;
+    const long spans = (long)p.B * per_element;
+    if (spans > kSpanMax || spans > max_slots) return;
+    const int rounds = per_element > 1 ? 1 : p.d_m == 512 ? 3 : 2;
+    if (spans * blocks > (long)rounds * num_cus) return;
+    pl.nrg = 1; pl.nblocks = blocks; pl.Rs = blocks * 16;
+    pl.G = (int)spans; pl.short_tiles = kShortTiles;
+}
+
 CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws)
 {
     CutArgs c;
     c.lengths = p.lengths; c.spans = ws.spans; c.pieces = ws.pieces;
-    c.n = p.n; c.B = p.B; c.G = pl.G; c.kcost = pl.kcost;
+    c.n = p.n; c.B = p.B; c.G = pl.G; c.kcost = pl.kcost; c.short_tiles = pl.short_tiles;
     return c;
 }
 
@@ -175,6 +201,7 @@ hipError_t launch_core_mfma(const el_attn_ctx *ctx, const Problem &p, const Work
     // kernel: 1 GB of per-beam histories 216 -> 184 us; 640 MB shared by two row blocks 149 -> 144 us).  Below
     // that it costs: the second row block of a span then misses what the first one fetched (128 MB: 42.7 -> 44.6 us).
     a.stream_hint = (double)p.B * p.n * p.d_m * 2.0 >= 256.0 * 1024 * 1024 ? 1 : 0;
+    if (pl.short_tiles) return launch_core_short(a, p.d_m, p.dtype == EL_BF16, s, ev0, ev1);
     return launch_core_stream(a, p.d_m, p.dtype == EL_BF16, pl.nrg, s, ev0, ev1);
 }
 

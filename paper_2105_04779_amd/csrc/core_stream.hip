@@ -126,14 +126,7 @@ k_core_stream(const StreamArgs a)
     const int nwg = a.G * a.nblocks;
     const int per_xcd = (nwg + 7) >> 3;
     if (blockIdx.x >= 8 * per_xcd) {
-        // A workgroup on a compute unit the spans leave idle: pulls the weights of a6 and a7 towards this XCD's L2, one
-        // dword of every 128-byte line, an eighth of either matrix per XCD (the projections deal their column blocks that way).
-        constexpr int LINES = DM * DM * 2 / 8 / 128;
-        for (int t = ((blockIdx.x >> 3) - per_xcd) * 512 + tid; t < 2 * LINES; t += (gridDim.x / 8 - per_xcd) * 512) {
-            const char *src = (const char *)a.next_w[t >= LINES] + ((size_t)(blockIdx.x & 7) * LINES + (t >= LINES ? t - LINES : t)) * 128;
-            const int v = *(const volatile int *)src;
-            asm volatile("" :: "v"(v));
-        }
+        read_ahead<DM>(a, per_xcd);
         return;
     }
     const int place = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -604,12 +597,7 @@ static void launch_one(const StreamArgs &a, dim3 grid, hipStream_t s, hipEvent_t
 template <int DM, bool BF16>
 static hipError_t launch_t(const StreamArgs &a, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    dim3 grid(((a.G * a.nblocks + 7) / 8) * 8);
-    // Where at least a quarter of the compute units is idle, 64 workgroups more read the weights of a6 and a7 ahead: a decoder's
-    // layers come with weights of their own, cold at every step.  Twelve layers, 4 sentences, d_m 1024: 320 -> 311.4 us;
-    // one sentence, one layer (its weights stay in the memory-side cache): 23.7 -> 23.4.  In workgroups that also stream, the
-    // same reads cost 1 us: their other requests return after them.
-    if (a.next_w[0] && (int)grid.x + 64 <= a.num_cus) grid.x += 64;
+    const dim3 grid = core_grid(a);
     const bool nt = a.stream_hint != 0;
     if (rg == 1) { if (nt) launch_one<DM, BF16, 1, true>(a, grid, s, ev0, ev1); else launch_one<DM, BF16, 1, false>(a, grid, s, ev0, ev1); }
     else { if (nt) launch_one<DM, BF16, 2, true>(a, grid, s, ev0, ev1); else launch_one<DM, BF16, 2, false>(a, grid, s, ev0, ev1); }

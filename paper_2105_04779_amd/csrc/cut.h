@@ -51,7 +51,7 @@ __device__ __forceinline__ int small_quotient(int x, int y, float ry)
 //               is slot g + b (unique: along the axis, span and element never decrease and one of them grows).
 //   per element every element is cut into its own spans of at most s tiles: nothing crosses, a piece is a span and has
 //               its number.  The better one for few elements (one sentence: the flattened axis would start with a gap
-//               for nothing).
+//               for nothing), and the only one for the core of short spans, whose s is given.
 // Either way the spans' first tiles follow each other, so a span's tiles are the difference to the next one's.
 // More than kScanMax elements are not cut: a span each.
 __device__ __forceinline__ void build_cut(const CutArgs &a, const CutLengths &len, CutScratch &t, int l)
@@ -82,8 +82,9 @@ __device__ __forceinline__ void build_cut(const CutArgs &a, const CutLengths &le
     const int cspan = (total + a.kcost * a.B + a.G - 1) / a.G;
 
     // per element: sum_b ceil(tiles_b / s) is about total / s + B / 2; two guesses
-    int s = 0;
-    if (a.B == 1) s = (total + a.G - 1) / a.G;
+    int s = a.short_tiles;
+    if (s > 0) {                                             // (enough spans for it by the plan)
+    } else if (a.B == 1) s = (total + a.G - 1) / a.G;
     else if (2 * a.G > a.B) {
         const int guess = (2 * total + 2 * a.G - a.B - 1) / (2 * a.G - a.B);
 #pragma unroll

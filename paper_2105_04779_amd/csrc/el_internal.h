@@ -99,6 +99,7 @@ constexpr int kMaxPartsGeneric = 8; // key-range partials (fp32) of the generic 
 constexpr int kGenericMaxDm = 8192; // widest d_model the generic core kernel covers
 constexpr int kScanMax = 1024;      // most batch elements whose tiles the streaming core cuts as one list
 constexpr int kSpanMax = 1024;      // most spans of that list
+constexpr int kShortTiles = 4;      // tiles that a workgroup of the core of short spans holds in LDS
 
 // Where the partial results ("pieces") of batch element b live: `np` consecutive slots from `slot0` in the partial
 // buffers Xp [slot, Rs, d_m] and ML [slot, Rs, 2].  Generic core: every element has `parts` of them.  MFMA core: looked
@@ -120,6 +121,7 @@ struct CutArgs {
     int4 *spans;            // [G][2]: (element, tile of it, tiles, first slot), (lengths of the first four elements)
     int2 *pieces;           // [B] (first slot, pieces)
     int n, B, G, kcost;
+    int short_tiles;        // nonzero: per element, into spans of at most so many tiles (G is enough of them)
 };
 
 // ---- problem description handed to the launchers ------------------------------------------
@@ -222,6 +224,7 @@ struct CorePlan {
     int Rs;       // padded row count of ELQ / partial buffers = nblocks * 16 * nrg
     int G;        // spans the tiles of all elements are cut into (more than kScanMax elements: one span each)
     int kcost;    // what crossing into a new element costs a workgroup, in tiles (see cut.h)
+    int short_tiles;    // nonzero: every element is cut into spans of at most this many tiles, for the core of short spans
 };
 // Arguments of the streaming core (core_stream.hip)
 struct StreamArgs {
@@ -237,8 +240,32 @@ struct StreamArgs {
     int n, B, R, Rs, nblocks, G, num_cus;
     int stream_hint;         // nonzero: fetch H with the non-temporal hint (H far larger than the memory-side cache)
 };
+// A workgroup of either core on a compute unit that the spans leave idle: pulls the weights of a6 and a7 towards this XCD's L2,
+// one dword of every 128-byte line, an eighth of either matrix per XCD (the projections deal their column blocks that way).
+template <int DM>
+__device__ __forceinline__ void read_ahead(const StreamArgs &a, int per_xcd)
+{
+    constexpr int LINES = DM * DM * 2 / 8 / 128;
+    for (int t = ((blockIdx.x >> 3) - per_xcd) * 512 + threadIdx.x; t < 2 * LINES; t += (gridDim.x / 8 - per_xcd) * 512) {
+        const char *src = (const char *)a.next_w[t >= LINES] + ((size_t)(blockIdx.x & 7) * LINES + (t >= LINES ? t - LINES : t)) * 128;
+        const int v = *(const volatile int *)src;
+        asm volatile("" :: "v"(v));
+    }
+}
+// Workgroups of a core.  Where at least a quarter of the compute units is idle, 64 more read the weights of a6 and a7 ahead: a
+// decoder's layers come with weights of their own, cold at every step.  Streaming core, twelve layers, 4 sentences, d_m 1024: 320 ->
+// 311.4 us; one sentence, one layer (its weights stay in the memory-side cache): 23.7 -> 23.4.  In workgroups that also stream,
+// the same reads cost 1 us: their other requests return after them.
+inline dim3 core_grid(const StreamArgs &a)
+{
+    dim3 grid(((a.G * a.nblocks + 7) / 8) * 8);
+    if (a.next_w[0] && (int)grid.x + 64 <= a.num_cus) grid.x += 64;
+    return grid;
+}
+hipError_t launch_core_short(const StreamArgs &a, int d_m, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);   // core_short.hip
 hipError_t launch_core_stream(const StreamArgs &a, int d_m, bool bf16, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 bool core_mfma_supported(int dtype, int d_m);
+void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl);     // turns the plan into one for the core of short spans where that is the faster one
 CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots);
 CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws);
 PieceMap piece_map(const Workspace &ws);

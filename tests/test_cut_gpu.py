@@ -122,3 +122,46 @@ def test_dozens_of_pieces_of_one_element(dtype, heads, d_m, beam, n):
     record(f"{w.name}: err={err:.3e} seg_A err={err_A:.3e} lse err={err_lse:.3e}")
     assert err <= TOL[dtype] and err_A <= TOL[dtype] and err_lse <= 5e-3
     layer.close()
+
+
+SHORT = [
+    # dtype, B, beam, heads, d_m, n, lens: at most 256 workgroups of 64 positions and 16 rows (two or three times as many where n <= 64)
+    ("bf16", 5, 4, 16, 1024, 200, [200, 1, 16, 17, 64]),            # spans of one to four tiles, of one position and of a full tile
+    ("f16", 6, 3, 16, 1024, 129, [129, 128, 127, 113, 65, 48]),     # 48 rows; a span of one position behind full ones
+    ("bf16", 9, 5, 12, 768, 130, [130, 80, 81, 33, 32, 31, 97, 2, 64]),   # 60 rows: a block of twelve; the 32-column window
+    ("f16", 4, 1, 12, 768, 63, [63, 49, 15, 1]),                    # 12 rows, one span each
+    ("f16", 7, 3, 8, 512, 250, [250, 249, 193, 192, 66, 5, 160]),   # 24 rows
+    ("bf16", 3, 1, 8, 512, 64, None),                               # 8 rows, no lengths
+    ("bf16", 64, 4, 16, 1024, 64, "mixed"),                         # 256 workgroups of one span
+    ("bf16", 1, 4, 16, 1024, 960, [947]),                           # fifteen pieces of one element: as many as there are slots
+]
+
+
+@pytest.mark.parametrize("dtype,B,beam,heads,d_m,n,lens", SHORT)
+def test_short_spans(dtype, B, beam, heads, d_m, n, lens):
+    """The core of short spans against the oracle and against the streaming core (which a set row-group count leaves in charge) on
+    the same call: a batch stride beyond n rows, poisoned rows past the lengths, step and segment form.  Both round the pieces to
+    fp16 once, elsewhere: they agree to twice the bar of either."""
+    w = wl.custom(f"short_{dtype}_{B}x{beam}_{d_m}_{n}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=64, n=n, index=99)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.full(B, n, dtype=np.int32) if lens is None else np.asarray([1 + (b * 13) % n for b in range(B)] if isinstance(lens, str) else lens, dtype=np.int32)
+    ref = oracle_out(w, W, H, Q, L)
+    wide = np.full((B, n + 3, d_m), np.nan, dtype=np.float32)
+    for b in range(B):
+        wide[b, :L[b]] = H[b, :L[b]]
+    Hd, Qd = to_device(wide, dtype)[:, :n], to_device(Q, dtype)
+    Ld = None if lens is None else torch.from_numpy(L).cuda()
+    outs = []
+    for groups in (0, 1):
+        layer = make_layer(w, W)
+        layer.set_row_groups(groups)
+        y = layer.decode_step(Hd, Ld, Qd).float().cpu().numpy()
+        A, lse = layer.decode_segment(Hd, Ld, Qd)
+        outs.append((y, A.cpu().numpy(), lse.cpu().numpy()))
+        layer.close()
+    err = rel_err(outs[0][0], ref)
+    record(f"{w.name}: err={err:.3e} streaming core {rel_err(outs[1][0], ref):.3e}")
+    assert err <= TOL[dtype]
+    for a, b in zip(*outs):
+        assert rel_err(a, b) <= 2 * TOL[dtype]
