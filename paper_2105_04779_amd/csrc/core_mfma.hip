@@ -159,17 +159,18 @@ PieceMap piece_map(const Workspace &ws)
     return m;
 }
 
-__global__ void __launch_bounds__(64) k_cut(const CutArgs c)
+__global__ void __launch_bounds__(64 * kCutWaves) k_cut(const CutArgs c)
 {
     __shared__ CutScratch t;
     CutLengths len;
-    load_cut_lengths(c, threadIdx.x, len);
-    build_cut(c, len, t, threadIdx.x);
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    load_cut_lengths(c, w, l, len);
+    build_cut(c, len, t, w, l);
 }
 
 hipError_t launch_cut(const CutArgs &c, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cut, dim3(1), dim3(64), 0, s, c);
+    hipLaunchKernelGGL(k_cut, dim3(1), dim3(64 * kCutWaves), 0, s, c);
     return hipGetLastError();
 }
 

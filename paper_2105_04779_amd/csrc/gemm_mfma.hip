@@ -81,8 +81,8 @@ struct QelqArgs {
     const void *bq;        // storage type, may be null
     uint16_t *elq;
     f16_t *Qp;             // [M, d_m], or null if nobody reads it
-    CutArgs cut;           // the core's cut is built here as well, by one wavefront under this kernel's memory latency: by a
-    int cut_alone;         // workgroup of its own (the first, so that it starts at once) where there is room for one, else by the first one
+    CutArgs cut;           // the core's cut is built here as well, under this kernel's memory latency: by a workgroup of its own
+    int cut_alone;         // (the first, so that it starts at once) where there is room for one, else by the first one
     float scale;
     int M, x, Rs, groups;
 };
@@ -97,11 +97,11 @@ k_qelq(const QelqArgs a)
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
     __shared__ CutScratch cut;
-    const bool cuts = blockIdx.x == 0 && w == (a.cut_alone ? 0 : 7);
+    const bool cuts = blockIdx.x == 0;
     CutLengths cut_len;
-    if (cuts) load_cut_lengths(a.cut, l, cut_len);
-    if (a.cut_alone && blockIdx.x == 0) {
-        if (cuts) build_cut(a.cut, cut_len, cut, l);
+    if (cuts) load_cut_lengths(a.cut, w, l, cut_len);
+    if (a.cut_alone && cuts) {
+        build_cut(a.cut, cut_len, cut, w, l);
         return;
     }
     Place pl;
@@ -133,7 +133,7 @@ k_qelq(const QelqArgs a)
 #pragma unroll
         for (int e = 0; e < 2; ++e) bias[e] = BF ? to_f32(((const bf16_t *)a.bq)[head * 64 + scol + e]) : to_f32(((const f16_t *)a.bq)[head * 64 + scol + e]);
 
-    if (cuts) build_cut(a.cut, cut_len, cut, l);
+    if (cuts) build_cut(a.cut, cut_len, cut, w, l);
 
     for (int tile = pl.group; tile < tiles; tile += a.groups) {
         f4 acc[4];
