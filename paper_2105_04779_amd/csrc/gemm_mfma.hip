@@ -188,8 +188,9 @@ k_qelq(const QelqArgs a)
 // A lane fetches the 16-byte fragments of its own row from every piece and merges them with the log-sum-exp weights
 // it works out for that row,
 //     X = sum_p (w_p l_p) Xhat_p / sum_p (w_p l_p),  w_p = 2^(m_p - M),
-// so nothing is exchanged before the products are.  Up to four pieces (eight in the narrowest form) are in flight at a time;
-// more are folded in with a running maximum.
+// so nothing is exchanged before the products are.  Up to four pieces are in flight at a time; more are folded in
+// with a running maximum (eight in the form of one column block, a round trip less for 5 to 8 pieces, is 1.3 % of a call
+// slower over 160 shapes of 3 to 15 pieces, with 15 up to 9 %; twelve layers 283.5 us against 279.5 with four).
 // Bound: memory latency in a chain of two (piece table, then statistics and pieces together), then the pieces'
 // bytes.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup per 16 rows, the
 // 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024: 38.9 -> 23.0 us;
@@ -217,7 +218,7 @@ k_vproj(const VprojArgs a)
 {
     constexpr float kLn2 = 0.6931471805599453f;
     constexpr int KS = DM / 256;                         // 32-wide slices of k per wavefront
-    constexpr int PC = NT == 1 ? 8 : 4;                  // pieces in flight (few rows, a span of four tiles per piece: a round trip less for 5 to 8 and 9 to 12)
+    constexpr int PC = 4;                                // pieces in flight
     __shared__ f4 red[2][8 * NT * 64];
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
