@@ -239,8 +239,9 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
  * blocks of 16 *row_groups rows; while spans are short (B x tiles x blocks of 32 rows at most 6 x
  * compute_units) a block of 32 is two workgroups of 16, so spans x ceil(heads * beam / 16).
  * Small steps (whose elements, cut into spans of 64 positions, fill the device at most once with workgroups of 16
- * rows; twice or three times where all of them are that short) run on a core that takes a whole span at once; the
- * figures are then those of the core it stands in for.
+ * rows; twice or three times where all of them are that short; beyond 13 spans an element at most 3/4 compute_units
+ * spans besides) run on a core that takes a whole span at once; the figures are then those of the core it stands
+ * in for.
  * Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or 1024: no MFMA
  * core).
  */

@@ -127,6 +127,10 @@ CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override,
 //               2 of 128 22.9 / 20.0    16 of 300 (1.25) 27.1 / 28.1    12 of 512 (1.5) 26.9 / 29.1    128 of 200, 16 rows (2) 34.0 / 38.7
 //   d_m 768     8 of 512, 48 rows (0.75) 23.8 / 21.4    16 of 300 (0.9) 22.8 / 20.6    24 of 300 (1.4) 23.0 / 25.4
 //   d_m 512     24 of 300, 32 rows (0.9) 19.9 / 18.5    64 of 300, 8 rows (1.25) 21.2 / 21.5    128 of 200, 8 rows (2) 21.3 / 23.3
+// Of 160 shapes of 2 to 13 spans an element all gain, the longest the least (rows of 1 to 4 beams, full lengths, the chip 0.3 to 1 times
+// filled: 13 spans 3 to 12 %, 5 spans 5 to 15 %).  With 15 spans the merge of as many pieces takes it back where nearly every compute
+// unit reads positions of its own: 1 beam, 16 of 960, d_m 1024 37.8 / 38.1, d_m 768 32.6 / 33.2; 11 of 960 33.3 / 32.6, 29.4 / 28.2;
+// 4 beams, 4 of 960, as many workgroups on a quarter of the positions, 29.4 / 26.5.
 // Where every element is one span there is no more to merge than before, and a second round pays (at d_m 512 two workgroups fit a
 // compute unit: a third):
 //   d_m 1024    100 of 64 (1.6) 42.8 / 37.9    512 of 64, 16 rows (2) 60.5 / 57.9    200 of 64 (3.1) 69.1 / 69.3    320 of 33 (5) 83.1 / 86.7
@@ -140,6 +144,7 @@ void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl
     if (spans > kSpanMax || spans > max_slots) return;
     const int rounds = per_element > 1 ? 1 : p.d_m == 512 ? 3 : 2;
     if (spans * blocks > (long)rounds * num_cus) return;
+    if (per_element > 13 && spans > num_cus * 3 / 4) return;
     pl.nrg = 1; pl.nblocks = blocks; pl.Rs = blocks * 16;
     pl.G = (int)spans; pl.short_tiles = kShortTiles;
 }
