@@ -234,19 +234,26 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
 
 /*
  * What the automatic choice would be for a shape on a device with `compute_units` compute units (host
- * arithmetic only, no device needed): rows per row block in groups of 16 (*row_groups) and the number of
- * spans the list of valid tiles is cut into (*spans) by the MFMA attention core.  Workgroups: spans x row
- * blocks of 16 *row_groups rows; while spans are short (B x tiles x blocks of 32 rows at most 6 x
- * compute_units) a block of 32 is two workgroups of 16, so spans x ceil(heads * beam / 16).
+ * arithmetic only, no device needed), in a context prepared for a max_batch of B: rows per row block in groups of
+ * 16 (*row_groups) and the number of spans the list of valid tiles is cut into (*spans) by the MFMA attention core.
+ * Workgroups: spans x row blocks of 16 *row_groups rows; while spans are short (B x tiles x blocks of 32 rows at
+ * most 6 x compute_units) a block of 32 is two workgroups of 16, so spans x ceil(heads * beam / 16).
  * Small steps (whose elements, cut into spans of 64 positions, fill the device at most once with workgroups of 16
  * rows; twice or three times where all of them are that short; beyond 13 spans an element at most 3/4 compute_units
- * spans besides) run on a core that takes a whole span at once; the figures are then those of the core it stands
- * in for.
+ * spans besides) run on a core of their own, which takes a whole span of at most 64 positions at once: row blocks
+ * of 16, and as many spans as elements of n positions need (elements that are shorter leave some of them empty).
  * Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or 1024: no MFMA
  * core).
  */
 el_status el_attn_plan_preview(int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n,
                                int32_t compute_units, int32_t *row_groups, int32_t *spans);
+
+/*
+ * 1 if the automatic choice for that shape, in a context prepared for `max_batch` (a larger one has room for more
+ * spans), is the core of short spans; 0 if not, or if el_attn_plan_preview would not accept the shape.
+ */
+int32_t el_attn_plan_short_core(int32_t max_batch, int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n,
+                                int32_t compute_units);
 
 /*
  * el_attn_decode_step for callers that cannot allocate and have no workspace to bind: code running

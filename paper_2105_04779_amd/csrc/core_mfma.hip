@@ -87,7 +87,7 @@ constexpr int kBoundaryCost = 4;
 // cross elements more often, it costs: d_m 768, 60 rows, 48 of 128 to 256 29.8 -> 33.1; d_m 1024, 80 rows, 64 of 64 37.5 -> 40.9.
 constexpr int kHalfBlockTiles = 12;
 
-CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)
+static CorePlan plan_stream(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)
 {
     CorePlan pl;
     const int tiles = (p.n + 15) / 16;
@@ -136,7 +136,7 @@ CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override,
 //   d_m 1024    100 of 64 (1.6) 42.8 / 37.9    512 of 64, 16 rows (2) 60.5 / 57.9    200 of 64 (3.1) 69.1 / 69.3    320 of 33 (5) 83.1 / 86.7
 //   d_m 768     200 of 64, 48 rows (2.3) 45.9 / 42.9    512 of 64, 12 rows (2) 42.0 / 39.6    320 of 33 (3.75) 55.7 / 57.0    1000 of 64 (3.9) 78.4 / 81.0
 //   d_m 512     200 of 64, 32 rows (1.6) 28.3 / 24.5    320 of 64 (2.5) 34.9 / 30.7    1000 of 64, 8 rows (3.9) 43.3 / 47.9
-void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
+static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
 {
     if (p.B > kScanMax) return;
     const int per_element = (p.n + 16 * kShortTiles - 1) / (16 * kShortTiles), blocks = (p.R + 15) / 16;
@@ -145,8 +145,15 @@ void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl
     const int rounds = per_element > 1 ? 1 : p.d_m == 512 ? 3 : 2;
     if (spans * blocks > (long)rounds * num_cus) return;
     if (per_element > 13 && spans > num_cus * 3 / 4) return;
-    pl.nrg = 1; pl.nblocks = blocks; pl.Rs = blocks * 16;
+    pl.nrg = pl.block_groups = 1; pl.nblocks = blocks; pl.Rs = blocks * 16;
     pl.G = (int)spans; pl.short_tiles = kShortTiles;
+}
+
+CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)
+{
+    CorePlan pl = plan_stream(p, splits_override, nrg_override, num_cus, max_slots);
+    if (!splits_override && !nrg_override) plan_short_spans(p, num_cus, max_slots, pl);
+    return pl;
 }
 
 CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws)

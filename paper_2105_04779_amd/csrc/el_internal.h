@@ -219,7 +219,7 @@ hipError_t launch_seg_merge(const SegMergeArgs &a, bool out_f16, int rows, hipSt
 // MFMA attention core -- core_stream.hip (the kernel), core_mfma.hip (planning, launch, helpers)
 struct CorePlan {
     int nrg;      // 16-row groups per workgroup (1 or 2)
-    int block_groups;   // 16-row groups of the row blocks the spans are planned for: nrg, or 2 where two workgroups share one
+    int block_groups;   // 16-row groups of the row blocks the spans are planned for: nrg, or 2 where two workgroups of the streaming core share one
     int nblocks;  // row blocks (workgroups sharing one H range)
     int Rs;       // padded row count of ELQ / partial buffers = nblocks * 16 * nrg
     int G;        // spans the tiles of all elements are cut into (more than kScanMax elements: one span each)
@@ -265,7 +265,7 @@ inline dim3 core_grid(const StreamArgs &a)
 hipError_t launch_core_short(const StreamArgs &a, int d_m, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);   // core_short.hip
 hipError_t launch_core_stream(const StreamArgs &a, int d_m, bool bf16, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 bool core_mfma_supported(int dtype, int d_m);
-void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl);     // turns the plan into one for the core of short spans where that is the faster one
+// what a step launches: the streaming core or, where neither override is set and it is the faster one, the core of short spans
 CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots);
 CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws);
 PieceMap piece_map(const Workspace &ws);

@@ -144,34 +144,84 @@ def test_plan_preview_on_the_benchmark_shapes(ea):
         st, rg, sp = ea.el_attn_plan_preview(B, beam, heads, d_m, n, 256)
         assert st == ea.EL_OK
         return rg, sp
+
+    def short(B, beam, heads, d_m, n):
+        return ea.el_attn_plan_short_core(B, B, beam, heads, d_m, n, 256)
     # rows per row block in 16s, spans of the tile list
     assert plan(64, 4, 16, 1024, 1024) == (2, 128)   # 64 rows: two blocks of 32, one workgroup per compute unit
     assert plan(320, 4, 16, 1024, 1024) == (2, 128)  # more sentences: longer spans, never more workgroups than units
     assert plan(512, 1, 16, 1024, 1024) == (1, 256)  # per-beam histories: 16 rows, one block
     assert plan(64, 4, 16, 1024, 256) == (2, 128)    # 1024 tiles: still eight per span
-    assert plan(64, 4, 16, 1024, 64) == (2, 64)      # four tiles per sentence: one span per sentence, not spans of eight tiles
-    assert plan(64, 4, 16, 1024, 32) == (2, 64)
-    assert plan(2, 4, 16, 1024, 16) == (2, 2)        # two tiles in all
+    assert plan(200, 4, 16, 1024, 64) == (2, 128)    # four tiles per sentence, too many for the core of short spans
+    # small steps: the core of short spans, four tiles and 16 rows a workgroup
+    assert plan(64, 4, 16, 1024, 64) == (1, 64)      # one span per sentence, 4 x 64 workgroups
+    assert plan(64, 4, 16, 1024, 32) == (1, 64)
+    assert plan(2, 4, 16, 1024, 16) == (1, 2)        # two tiles in all
+    assert plan(1, 4, 16, 1024, 613) == (1, 10) and plan(1, 5, 8, 512, 613) == (1, 10)       # 4 x 10 and 3 x 10 workgroups
+    assert plan(4, 4, 16, 1024, 410) == (1, 28)
     for B in (1, 3, 17, 64, 100, 1000):
         for beam in (1, 2, 4, 5, 8):
             for n in (1, 16, 100, 1024, 4096):
                 rg, sp = plan(B, beam, 16, 1024, n)
                 blocks = -(-16 * beam // (16 * rg))
-                assert rg == (1 if beam == 1 else 2) and 1 <= sp and sp * blocks <= max(256, blocks)
-                assert sp <= B * (ea.el_attn_max_splits() - 1)             # every piece has a slot
-    # short spans: a block of 32 rows is two workgroups of 16, and still never more workgroups than units
-    assert plan(1, 4, 16, 1024, 613) == (2, 9) and plan(1, 5, 8, 512, 613) == (2, 9)        # 4 x 9 and 3 x 9 workgroups
+                if short(B, beam, 16, 1024, n):
+                    assert rg == 1 and sp == B * -(-n // 64) and sp * blocks <= 2 * 256
+                    assert sp <= B * ea.el_attn_max_splits()                   # a span is a piece, and every piece has a slot
+                else:
+                    assert rg == (1 if beam == 1 else 2) and 1 <= sp and sp * blocks <= max(256, blocks)
+                    assert sp <= B * (ea.el_attn_max_splits() - 1)
+    # short spans of the streaming core: a block of 32 rows is two workgroups of 16, and still never more workgroups than units
+    assert plan(16, 4, 16, 1024, 300) == (2, 64) and plan(12, 4, 16, 1024, 512) == (2, 64)   # 4 x 64 workgroups
     for B in (1, 2, 5, 24, 48):
         for heads, beam, d_m in ((16, 4, 1024), (12, 5, 768), (8, 5, 512), (8, 3, 512), (12, 3, 768)):
             for n in (16, 100, 512, 1024):
                 rows, (rg, sp) = heads * beam, plan(B, beam, heads, d_m, n)
-                short = B * -(-n // 16) * -(-rows // 32) <= 6 * 256
-                assert rg == 2 and sp * -(-rows // (16 if short else 32)) <= 256
+                if short(B, beam, heads, d_m, n):
+                    continue
+                halves = B * -(-n // 16) * -(-rows // 32) <= 6 * 256
+                assert rg == 2 and sp * -(-rows // (16 if halves else 32)) <= 256
     I = ea.EL_ERR_INVALID_ARG
     assert ea.el_attn_plan_preview(0, 4, 16, 1024, 64, 256)[0] == I
     assert ea.el_attn_plan_preview(4, 4, 16, 1024, 64, 0)[0] == I
     assert ea.el_attn_plan_preview(4, 4, 10, 640, 64, 256)[0] == ea.EL_ERR_UNSUPPORTED
     assert ea.el_attn_plan_preview(64, 4, 12, 768, 1024, 256)[:2] == (ea.EL_OK, 2)   # 48 rows: two blocks of 32
+    assert ea.el_attn_plan_preview(2**31 - 1, 1, 8, 512, 64, 256) == (ea.EL_OK, 1, 2**31 - 1)      # not cut: a span each
+    for bad in ((4, 0, 4, 16, 1024, 64, 256), (4, 5, 4, 16, 1024, 64, 256), (4, 4, 4, 10, 640, 64, 256), (4, 4, 4, 16, 1024, 64, 0)):
+        assert ea.el_attn_plan_short_core(*bad) == 0
+
+
+def test_lines_of_the_core_of_short_spans(ea):
+    """Which core a step runs on, on both sides of every line of the rule, and what the kernels take for granted of the plan."""
+    def short(B, beam, heads, d_m, n, max_batch=None, units=256):
+        return ea.el_attn_plan_short_core(max_batch or B, B, beam, heads, d_m, n, units)
+    # several spans an element: all workgroups at once
+    assert short(8, 4, 16, 1024, 512) and not short(9, 4, 16, 1024, 512)             # 256 and 288 workgroups
+    assert short(10, 4, 12, 768, 512) and not short(11, 4, 12, 768, 512)             # 240 and 264
+    assert short(16, 4, 8, 512, 512) and not short(17, 4, 8, 512, 512)
+    assert short(4, 4, 16, 1024, 512, units=128) and not short(5, 4, 16, 1024, 512, units=128)
+    # one span an element: two rounds of them, three at d_m 512
+    assert short(128, 4, 16, 1024, 64) and not short(129, 4, 16, 1024, 64) and not short(128, 4, 16, 1024, 65)
+    assert short(170, 4, 12, 768, 64) and not short(171, 4, 12, 768, 64)
+    assert short(384, 4, 8, 512, 64) and not short(385, 4, 8, 512, 64)
+    assert short(768, 1, 8, 512, 64) and not short(769, 1, 8, 512, 64)
+    assert not short(1024, 1, 8, 512, 64) and short(1024, 1, 8, 512, 64, units=512) and not short(1025, 1, 8, 512, 64, units=512)
+    # beyond 13 spans an element: at most three quarters of the compute units in spans
+    assert short(19, 1, 16, 1024, 832) and not short(18, 1, 16, 1024, 833) and short(13, 1, 16, 1024, 896)
+    assert short(12, 1, 16, 1024, 960) and not short(13, 1, 16, 1024, 960)
+    # every piece has a slot: fifteen of an element where the batch is the largest prepared for
+    assert short(1, 4, 16, 1024, 960) and not short(1, 4, 16, 1024, 961) and short(1, 4, 16, 1024, 961, max_batch=2)
+    for units in (64, 256, 304):
+        for d_m, heads in ((512, 8), (768, 12), (1024, 16), (1024, 8), (768, 24)):
+            for beam in (1, 3, 4, 8):
+                for n in (1, 16, 17, 64, 65, 128, 500, 832, 833, 960, 1024, 3000):
+                    for B in (1, 2, 5, 13, 40, 100, 256, 511, 768, 1024, 1025):
+                        for max_batch in (B, 2 * B):
+                            if not short(B, beam, heads, d_m, n, max_batch, units):
+                                continue
+                            spans = B * -(-n // 64)
+                            assert B <= 1024 and spans <= 1024 and spans <= 15 * max_batch
+                            if max_batch == B:
+                                assert ea.el_attn_plan_preview(B, beam, heads, d_m, n, units) == (ea.EL_OK, 1, spans)
 
 
 def test_check_inputs_rejects_bad_arguments_before_any_device_work(ea):
