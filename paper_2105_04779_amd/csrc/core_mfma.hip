@@ -119,6 +119,13 @@ static CorePlan plan_stream(const Problem &p, int splits_override, int nrg_overr
     return pl;
 }
 
+// Elements of thousands of positions (a context prepared for many, called with one to three): the streaming core's cut mostly has
+// spans of five tiles, a fifth fewer pieces, and a further piece costs the merge 0.3 us.  Up to so many more the short core takes
+// back (177 shapes of three to eight more: 1.00 to 1.13 times as fast; 2500 positions, one element, 16 rows, 8 more, streaming
+// against short core: d_m 1024 33.1 / 32.9, d_m 512 25.4 / 24.9); with nine or more it loses, the longer the more: d_m 1024 5200
+// positions, 17 more, 46.7 / 50.1; 7000 56.0 / 61.9; 11500, 36 more, 80.0 / 92.0; d_m 512 56.8 / 63.3.
+constexpr int kMorePieces = 8;
+
 // The core of short spans (core_short.hip): every element dealt out to workgroups of four tiles and 16 rows, while all of them
 // run at once (spans by the longest possible element).  Beyond that a second round of workgroups waits for the first one's
 // latency, which the streaming core pays once, and more pieces are written and merged.  Whole steps, streaming against short
@@ -144,7 +151,12 @@ static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CoreP
     if (spans > kSpanMax || spans > max_slots) return;
     const int rounds = per_element > 1 ? 1 : p.d_m == 512 ? 3 : 2;
     if (spans * blocks > (long)rounds * num_cus) return;
-    if (per_element > 13 && spans > num_cus * 3 / 4) return;
+    if (per_element > 13) {
+        if (spans > num_cus * 3 / 4) return;
+        const int tiles = (p.n + 15) / 16, G = pl.G;                     // (G >= B here), tiles of a span as build_cut has them
+        const int each = p.B == 1 ? (tiles + G - 1) / G : (2 * p.B * tiles + 2 * G - p.B - 1) / (2 * G - p.B);
+        if (per_element - (tiles + each - 1) / each > kMorePieces) return;
+    }
     pl.nrg = pl.block_groups = 1; pl.nblocks = blocks; pl.Rs = blocks * 16;
     pl.G = (int)spans; pl.short_tiles = kShortTiles;
 }

@@ -210,6 +210,11 @@ def test_lines_of_the_core_of_short_spans(ea):
     assert short(12, 1, 16, 1024, 960) and not short(13, 1, 16, 1024, 960)
     # every piece has a slot: fifteen of an element where the batch is the largest prepared for
     assert short(1, 4, 16, 1024, 960) and not short(1, 4, 16, 1024, 961) and short(1, 4, 16, 1024, 961, max_batch=2)
+    # long elements in a context for many: not where this core's cut has more than eight pieces beyond the other one's
+    for B in (1, 2, 3):
+        assert short(B, 1, 16, 1024, 2500, max_batch=64) and not short(B, 1, 16, 1024, 2800, max_batch=64)
+        assert not short(B, 1, 8, 512, 5000, max_batch=64) and not short(B, 1, 8, 512, 12000, max_batch=64)
+    assert short(1, 1, 16, 1024, 8192, max_batch=64) and not short(1, 1, 16, 1024, 8200, max_batch=64)     # spans of four tiles either way
     for units in (64, 256, 304):
         for d_m, heads in ((512, 8), (768, 12), (1024, 16), (1024, 8), (768, 24)):
             for beam in (1, 3, 4, 8):
