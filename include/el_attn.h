@@ -239,7 +239,7 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
  * Workgroups: spans x row blocks of 16 *row_groups rows; while spans are short (B x tiles x blocks of 32 rows at
  * most 6 x compute_units) a block of 32 is two workgroups of 16, so spans x ceil(heads * beam / 16).
  * Small steps (whose elements, cut into spans of 64 positions, fill the device at most once with workgroups of 16
- * rows; twice or three times where all of them are that short; beyond 13 spans an element at most 3/4 compute_units
+ * rows, about twice or three times where all of them are that short; beyond 13 spans an element at most 3/4 compute_units
  * spans besides) run on a core of their own, which takes a whole span of at most 64 positions at once: row blocks
  * of 16, and as many spans as elements of n positions need (elements that are shorter leave some of them empty).
  * Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or 1024: no MFMA

@@ -128,29 +128,36 @@ constexpr int kMorePieces = 8;
 
 // The core of short spans (core_short.hip): every element dealt out to workgroups of four tiles and 16 rows, while all of them
 // run at once (spans by the longest possible element).  Beyond that a second round of workgroups waits for the first one's
-// latency, which the streaming core pays once, and more pieces are written and merged.  Whole steps, streaming against short
-// core, 64 rows at d_m 1024 and 512 unless it says so (us; workgroups per compute unit of 256):
-//   d_m 1024    1 element of 613 positions 23.9 / 22.9    4 of 205 to 410, twelve layers 312 / 286    8 of 512 (1) 27.2 / 24.4
-//               2 of 128 22.9 / 20.0    16 of 300 (1.25) 27.1 / 28.1    12 of 512 (1.5) 26.9 / 29.1    128 of 200, 16 rows (2) 34.0 / 38.7
-//   d_m 768     8 of 512, 48 rows (0.75) 23.8 / 21.4    16 of 300 (0.9) 22.8 / 20.6    24 of 300 (1.4) 23.0 / 25.4
-//   d_m 512     24 of 300, 32 rows (0.9) 19.9 / 18.5    64 of 300, 8 rows (1.25) 21.2 / 21.5    128 of 200, 8 rows (2) 21.3 / 23.3
-// Of 160 shapes of 2 to 13 spans an element all gain, the longest the least (rows of 1 to 4 beams, full lengths, the chip 0.3 to 1 times
-// filled: 13 spans 3 to 12 %, 5 spans 5 to 15 %).  With 15 spans the merge of as many pieces takes it back where nearly every compute
-// unit reads positions of its own: 1 beam, 16 of 960, d_m 1024 37.8 / 38.1, d_m 768 32.6 / 33.2; 11 of 960 33.3 / 32.6, 29.4 / 28.2;
-// 4 beams, 4 of 960, as many workgroups on a quarter of the positions, 29.4 / 26.5.
-// Where every element is one span there is no more to merge than before, and a second round pays (at d_m 512 two workgroups fit a
-// compute unit: a third):
-//   d_m 1024    100 of 64 (1.6) 42.8 / 37.9    512 of 64, 16 rows (2) 60.5 / 57.9    200 of 64 (3.1) 69.1 / 69.3    320 of 33 (5) 83.1 / 86.7
-//   d_m 768     200 of 64, 48 rows (2.3) 45.9 / 42.9    512 of 64, 12 rows (2) 42.0 / 39.6    320 of 33 (3.75) 55.7 / 57.0    1000 of 64 (3.9) 78.4 / 81.0
-//   d_m 512     200 of 64, 32 rows (1.6) 28.3 / 24.5    320 of 64 (2.5) 34.9 / 30.7    1000 of 64, 8 rows (3.9) 43.3 / 47.9
+// latency, which the streaming core pays once, and more pieces are written and merged.  Whole steps in bf16, the streaming core
+// (with the cut built by eight wavefronts, as for the short one) against the short core, 64 rows at d_m 1024, 48 at 768 and 32 at
+// 512 unless it says so (us; workgroups per compute unit of 256):
+//   d_m 1024    1 element of 613 positions 23.4 / 21.8    8 of 512 (1) 28.7 / 25.4    2 of 128 21.9 / 18.5    16 of 300 (1.25) 29.4 / 30.4
+//               12 of 512 (1.5) 30.0 / 30.4    128 of 200, 16 rows (2) 35.4 / 38.1
+//   d_m 768     8 of 512 (0.75) 24.6 / 21.4    16 of 300 (0.9) 25.4 / 21.8    24 of 300 (1.4) 26.5 / 27.0
+//   d_m 512     24 of 300 (0.9) 21.4 / 19.1    32 of 300 (1.25) 21.3 / 20.3    64 of 300, 8 rows (1.25) 21.9 / 20.9    128 of 200, 8 rows (2) 22.6 / 22.0
+// (d_m 512 has two workgroups on a compute unit and would bear more than one round; 34 of 900, 16 rows (2) 23.3 / 24.0).  Of 403
+// shapes of 2 to 13 spans an element, 1 to 8 beams, a half to the whole of a round, all gain, 2 to 22 %.  With more spans the merge of as
+// many pieces takes it back where nearly every compute unit reads positions of its own: 1 beam, 16 of 960 positions d_m 1024
+// 38.1 / 38.0, d_m 768 33.4 / 33.1 (fp16, 17 of 960: 32.3 / 32.9); 17 of 896 36.9 / 36.7, 32.1 / 31.1; 11 of 960 33.2 / 32.0, 29.9 / 27.8;
+// 4 beams, 4 of 960, as many workgroups on a quarter of the positions, 30.7 / 28.1.
+// Where every element is one span there is no more to merge than before, and a second round pays (at d_m 512 a third):
+//   d_m 1024    100 of 64 (1.6) 43.0 / 38.5    128 of 64 (2) 44.4 / 41.7    200 of 64 (3.1) 63.7 / 63.2    320 of 33 (5) 75.1 / 75.5
+//   d_m 768     170 of 64 (2) 41.4 / 39.2    200 of 64 (2.3) 45.9 / 43.8    320 of 33 (3.75) 54.1 / 52.4    1000 of 64, 12 rows (3.9) 57.5 / 62.1
+//   d_m 512     200 of 64 (1.6) 31.9 / 27.7    384 of 64 (3) 38.1 / 34.2    1000 of 64, 8 rows (3.9) 38.6 / 36.6
+// but with one row block only up to 15/8 rounds: where both rounds are full, the streaming core has two elements on every compute
+// unit and nothing idle either.  16 rows, d_m 1024: 460 of 64 51.7 / 46.8, 480 51.3 / 46.9, 512 49.1 / 49.3; 12 rows, d_m 768: 41.2 / 38.1,
+// 41.3 / 38.4, 38.8 / 39.3.  Elements of a single tile gain little in a second round, and none where it is nearly empty: d_m 768, 16
+// positions, 89 elements (1.04) 32.9 / 33.7 with 48 rows, 27.4 / 26.8 with 36; 44 with 96 rows 32.2 / 33.3; of 112 such shapes at
+// d_m 768 and 1024 0.98 to 1.07 times as fast, 1.02 in the mean.
 static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
 {
     if (p.B > kScanMax) return;
     const int per_element = (p.n + 16 * kShortTiles - 1) / (16 * kShortTiles), blocks = (p.R + 15) / 16;
     const long spans = (long)p.B * per_element;
     if (spans > kSpanMax || spans > max_slots) return;
-    const int rounds = per_element > 1 ? 1 : p.d_m == 512 ? 3 : 2;
-    if (spans * blocks > (long)rounds * num_cus) return;
+    // eighths of a round (one row block: see above)
+    const int eighths = per_element > 1 ? 8 : p.d_m == 512 ? 24 : blocks == 1 ? 15 : 16;
+    if (8 * spans * blocks > (long)eighths * num_cus) return;
     if (per_element > 13) {
         if (spans > num_cus * 3 / 4) return;
         const int tiles = (p.n + 15) / 16, G = pl.G;                     // (G >= B here), tiles of a span as build_cut has them

@@ -201,6 +201,8 @@ def test_lines_of_the_core_of_short_spans(ea):
     assert short(4, 4, 16, 1024, 512, units=128) and not short(5, 4, 16, 1024, 512, units=128)
     # one span an element: two rounds of them, three at d_m 512
     assert short(128, 4, 16, 1024, 64) and not short(129, 4, 16, 1024, 64) and not short(128, 4, 16, 1024, 65)
+    assert short(480, 1, 16, 1024, 64) and not short(481, 1, 16, 1024, 64)           # one row block: 15/8 rounds
+    assert short(480, 1, 12, 768, 64) and not short(481, 1, 12, 768, 64)
     assert short(170, 4, 12, 768, 64) and not short(171, 4, 12, 768, 64)
     assert short(384, 4, 8, 512, 64) and not short(385, 4, 8, 512, 64)
     assert short(768, 1, 8, 512, 64) and not short(769, 1, 8, 512, 64)
