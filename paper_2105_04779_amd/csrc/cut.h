@@ -3,9 +3,9 @@
 // batch element are), both read with one load.  The workgroup is one of the launch that precedes the core (k_qelq), which
 // does this under its memory latency: in the core, every workgroup repeated the scan of all lengths (1.7 us of every launch
 // at 64 batch elements) before it could request its first tile.  A wavefront takes 64 elements (and 64 spans) at a time; as
-// the work of one wavefront the cut outlasted that latency where no compute unit is left for it alone (k_qelq, 512 rows of as
-// many elements: 18.0 us, 15.1 without the cut; whole steps, one wavefront -> eight: 512 histories of 1024 211.0 -> 208.1, d_m
-// 768 48 sentences 38.7 -> 38.4).
+// the work of one wavefront the cut outlasted that latency where no compute unit is left for it alone: k_qelq, d_m 1024, 512
+// rows of as many elements, one wavefront 18.2 us, eight 14.8, and 14.5 since they wait for the lengths alone; the whole step
+// with histories of 1024 210.7 -> 207.2 -> 206.6.
 #pragma once
 #include "el_internal.h"
 
@@ -17,18 +17,20 @@ constexpr int kCutChunks = kScanMax / 64, kCutMine = kCutChunks / kCutWaves;
 // LDS: prefix of tiles, lengths, per span its first tile and its element, and per chunk of 64 elements its tiles and, for two
 // guesses, its spans
 struct CutScratch { int E[kScanMax + 1], len[kScanMax + 3], first[kSpanMax + 1], owner[kSpanMax], tiles[kCutChunks], count[2][kCutChunks]; };
-struct CutLengths { int v[kCutMine]; };              // lane l of wavefront w: lengths of elements 64 (w + 8 c) + l
+struct CutLengths { int v[kCutMine]; };              // lane l of wavefront w: lengths of elements 64 (w + 8 c) + l, as the caller wrote them
 
-__device__ __forceinline__ int cut_length(const CutArgs &a, int i) { return a.lengths ? min(max(a.lengths[i], 1), a.n) : a.n; }
+__device__ __forceinline__ int cut_length(const CutArgs &a, int v) { return min(max(v, 1), a.n); }
 
-// All lengths requested at once, and ahead of whatever else the wavefront has to fetch.
+// All lengths requested at once, and ahead of whatever else the workgroup has to fetch: by an index that stays inside the
+// batch, not in a branch, and looked at in build_cut only.  Clamped and masked here, each was waited for before the next
+// request went out, by every wavefront of the one workgroup that the launch waits for.
 __device__ __forceinline__ void load_cut_lengths(const CutArgs &a, int w, int l, CutLengths &t)
 {
 #pragma unroll
-    for (int c = 0; c < kCutMine; ++c) {
-        const int i = 64 * (w + kCutWaves * c) + l;
-        t.v[c] = a.B <= kScanMax && i < a.B ? cut_length(a, i) : 0;
-    }
+    for (int c = 0; c < kCutMine; ++c) t.v[c] = a.n;
+    if (a.lengths && a.B <= kScanMax)
+#pragma unroll
+        for (int c = 0; c < kCutMine; ++c) t.v[c] = a.lengths[min(64 * (w + kCutWaves * c) + l, a.B - 1)];
 }
 
 // inclusive scan over the 64 lanes on the vector ALU (row shifts, then the row totals broadcast); no LDS round trips
@@ -61,17 +63,20 @@ __device__ __forceinline__ int small_quotient(int x, int y, float ry)
 //               for nothing), and the only one for the core of short spans, whose s is given.
 // Either way the spans' first tiles follow each other, so a span's tiles are the difference to the next one's.
 // More than kScanMax elements are not cut: a span each.
-__device__ __forceinline__ void build_cut(const CutArgs &a, const CutLengths &len, CutScratch &t, int w, int l)
+__device__ __forceinline__ void build_cut(const CutArgs &a, const CutLengths &raw, CutScratch &t, int w, int l)
 {
     if (a.B > kScanMax) {
         for (int i = 64 * w + l; i < a.B; i += 64 * kCutWaves) {
-            const int n = cut_length(a, i);
+            const int n = cut_length(a, a.lengths ? a.lengths[i] : a.n);
             a.spans[2 * i] = int4{i, 0, (n + 15) >> 4, i};
             a.spans[2 * i + 1] = int4{n, 16, 16, 16};
             a.pieces[i] = int2{i, 1};
         }
         return;
     }
+    CutLengths len;                                          // (elements that do not exist: none)
+#pragma unroll
+    for (int c = 0; c < kCutMine; ++c) len.v[c] = 64 * (w + kCutWaves * c) + l < a.B ? cut_length(a, raw.v[c]) : 0;
     int end[kCutMine];                                       // tiles up to and including element i: in its chunk, then of all
 #pragma unroll
     for (int c = 0; c < kCutMine; ++c) {

@@ -108,6 +108,14 @@ k_qelq(const QelqArgs a)
     if (!place_of(HEADS, PARTS, a.groups, blockIdx.x - a.cut_alone, pl)) return;
     const int head = pl.block, tiles = (a.M + 15) >> 4;
 
+    // Everything is requested in the order in which it is waited for, and nothing is looked at before all of it is under way
+    // (requests return in order): the lengths, the bias, the rows, W^Q, W^K.  So the cut is built and the products with W^Q are
+    // taken while the rest arrives; with the bias behind the weights, converted at once, both waited for all of them.  A workgroup
+    // that also cuts, 64 rows, d_m 1024: 7.5 -> 7.0 us, 128 rows 8.2 -> 7.9; others, 60 rows 7.1 -> 6.7, 512 rows 14.8 -> 14.5.
+    // the thread that adds up: row srow, columns scol and scol + 1 of the head
+    const int srow = threadIdx.x >> 5, scol = 2 * (threadIdx.x & 31);
+    unsigned bias_bits = 0;                              // both as they are stored
+    if (a.bq) bias_bits = *(const unsigned *)((const uint16_t *)a.bq + head * 64 + scol);
     u4 xq[KS], wq[KS][4], wk[NP][2][2];
     auto load_rows = [&](int tile) {
         const uint16_t *row = (const uint16_t *)a.q + (size_t)min(16 * tile + r16, a.M - 1) * DM + 8 * q;
@@ -126,14 +134,13 @@ k_qelq(const QelqArgs a)
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int s = 0; s < 2; ++s) wk[i][h][s] = a.Wk[((((size_t)head * (DM / 32) + pair0 + i) * 2 + h) * 2 + s) * 64 + l];
-    // the thread that adds up: row srow, columns scol and scol + 1 of the head
-    const int srow = threadIdx.x >> 5, scol = 2 * (threadIdx.x & 31);
-    float bias[2] = {0.f, 0.f};
-    if (a.bq)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) bias[e] = BF ? to_f32(((const bf16_t *)a.bq)[head * 64 + scol + e]) : to_f32(((const f16_t *)a.bq)[head * 64 + scol + e]);
-
     if (cuts) build_cut(a.cut, cut_len, cut, w, l);
+    float bias[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const uint16_t bits = (uint16_t)(bias_bits >> (16 * e));
+        bias[e] = BF ? to_f32(bf16_t{bits}) : to_f32(__builtin_bit_cast(f16_t, bits));
+    }
 
     for (int tile = pl.group; tile < tiles; tile += a.groups) {
         f4 acc[4];

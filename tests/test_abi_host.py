@@ -3,6 +3,7 @@ symbol the header declares, and rejects bad arguments before touching the device
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -273,3 +274,21 @@ def test_build_fails_on_register_spills_where_weights_live_in_registers(kernel):
     block = "a.hip:1:1: remark: Function Name: %s [-R]\na.hip:1:1: remark:     SGPRs Spill: 3 [-R]\na.hip:1:1: remark:     VGPRs Spill: %d [-R]\n"
     assert build.check_core_spills(block % (name, 2)) == {name: 2}
     assert build.check_core_spills(block % (name, 0)) == {}
+
+
+def test_the_query_kernel_waits_for_nothing_before_all_of_it_is_requested(tmp_path):
+    """In every instance of k_qelq the lengths, the bias, the rows and both weight slices are under way before the first wait for
+    memory: looked at earlier, each is a round trip of its own in front of the cut and of the first product."""
+    from paper_2105_04779_amd import build
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    asm = tmp_path / "gemm_mfma.s"
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, *flags, "-S", "--cuda-device-only", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                    "-o", str(asm), os.path.join(build.CSRC, "gemm_mfma.hip")], check=True, capture_output=True)
+    bodies = re.findall(r"^_ZN2el6k_qelqILi(\d+)ELb\dELi(\d)E\S*:\s(.*?)\.end_amdhsa_kernel", asm.read_text(), re.S | re.M)
+    assert len(bodies) == 14
+    for d_m, parts, body in bodies:
+        slices = int(d_m) // 256
+        loads = 2 + 1 + slices + 4 * slices + 4 * int(parts)         # lengths, bias, rows, W^Q, W^K
+        before = body[:re.search(r"s_waitcnt[^\n]*vmcnt", body).start()]
+        assert before.count("global_load") == loads, (d_m, parts, before.count("global_load"))
