@@ -68,8 +68,11 @@ bool core_mfma_supported(int dtype, int d_m)
 // workgroup per compute unit when the longest possible list gives every span at least kMinSpan tiles,
 // fewer otherwise (but not fewer than one span per batch element); build_cut lays the spans over the actual lengths.
 // Batches beyond kScanMax elements are not cut: one workgroup per (element, row block), scheduled by the hardware.
-// With 4 tiles instead of 8 (and twice the piece slots) the core of one sentence of 613 positions and 64 rows takes
-// 12.6 instead of 18.3 us, and the merge of its nine pieces no longer than that of four.
+// 4 was chosen where small steps ran on this core (one sentence of 613 positions and 64 rows: 18.3 us of core with 8 tiles, 12.6
+// with 4).  Those run on the core of short spans now.  What still meets the line are long elements on few compute units, and there
+// twice as many pieces to merge cost more than the shorter spans gain.  Whole steps, 8 tiles against 4: d_m 1024, 1 beam, 16 of 960
+// positions 33.2 / 37.5 us, one of 6000 39.5 / 50.2, of 1024 24.5 / 25.0; 4 beams, one of 1000 25.4 / 25.4; d_m 512, 8 rows, 16 of 960
+// 24.7 / 26.7, one of 6000 30.6 / 37.7.
 constexpr int kMinSpan = 4;
 // What moving on to the next batch element costs a workgroup, in tiles of streaming time: the expanded queries of
 // the new element (128 KB for 32 rows) and the write-out of the finished piece.  Spans that cross an element hold
@@ -79,12 +82,12 @@ constexpr int kBoundaryCost = 4;
 
 // Tiles per span up to which two workgroups of 16 rows share a row block of 32, all of them on the chip at once.  Half the
 // expanded queries to wait for and half the products per tile, against twice the tiles per span where the spans fill the
-// chip.  Whole steps, d_m 1024, beam 4, 32 against 16 rows: one sentence of 613 25.2 -> 23.6 us; twelve layers, 4 sentences
-// 342 -> 321; 8 of 512 27.9 -> 26.4; 16 of 512 (8 tiles) 32.0 -> 28.9; 32 of 512 (16 tiles) equal; d_m 512, 64 of 512 (16
-// tiles) 23.8 -> 24.6.  Other widths and row counts, 32 against 16 rows: d_m 768, 60 rows, 16 of 256 to 512 29.6 -> 27.0; 36 rows
-// 29.1 -> 26.7; d_m 512, 40 rows 22.7 -> 21.1, 24 rows 22.0 -> 21.4; d_m 1024, 80 rows 33.2 -> 31.7, 128 rows, 8 of 512 34.1 ->
-// 29.8.  Of 95 such shapes 85 gain, up to 4 us; where the 16-row workgroups of many elements fill the chip, so that their spans
-// cross elements more often, it costs: d_m 768, 60 rows, 48 of 128 to 256 29.8 -> 33.1; d_m 1024, 80 rows, 64 of 64 37.5 -> 40.9.
+// chip.  Whole steps (those that do not run on the core of short spans), 32 against 16 rows: d_m 1024, 64 rows, 16 of 150 to 300
+// positions 30.3 / 29.2 us, 16 of 512 (8 tiles) 32.5 / 31.2, 24 of 512 (12 tiles) 33.4 / 33.0; 32 rows, 32 of 512 34.6 / 30.3; 128 rows, 8 of
+// 512 33.6 / 31.5; d_m 768, 60 rows, 16 of 256 to 512 29.1 / 26.8; 36 rows 28.3 / 26.1; d_m 512, 40 rows 22.6 / 21.1.  Of 254 such shapes of
+// 24 to 128 rows 169 gain, up to 15 %, and 85 lose, up to 9 %: the 16-row workgroups of many elements fill the chip, so that their spans
+// cross elements more often, and rows that fill blocks of 32 evenly have nothing to gain from blocks of 16: d_m 768, 96 rows, 24 of
+// 150 to 300 29.3 / 32.1; 24 rows, 64 of 200 25.4 / 27.6; d_m 512, 32 rows, 48 of 512 23.6 / 24.9.
 constexpr int kHalfBlockTiles = 12;
 
 static CorePlan plan_stream(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)

@@ -198,8 +198,9 @@ k_qelq(const QelqArgs a)
 // so nothing is exchanged before the products are.  Up to four pieces are in flight at a time; more are folded in
 // with a running maximum (eight in the form of one column block, a round trip less for 5 to 8 pieces, is 1.3 % of a call
 // slower over 160 shapes of 3 to 15 pieces, with 15 up to 9 %; twelve layers 283.5 us against 279.5 with four).
-// Bound: memory latency in a chain of two (piece table, then statistics and pieces together), then the pieces'
-// bytes.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup per 16 rows, the
+// Bound: memory latency in a chain of two (piece table, then statistics and pieces together; a third for more than four
+// pieces, and so on), then the pieces' bytes.  Where the columns of a head are split over workgroups each of them fetches and
+// merges the same rows.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup per 16 rows, the
 // 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024: 38.9 -> 23.0 us;
 // 512 rows, one piece each: 19.7 -> 10.2; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 10.0; 4 rows: 8.6 -> 5.4.
 // The low half of merged sums is 0.2 to 0.4 us of that (4 rows 23.1 -> 23.3 us the step, 1280 rows 197.3 -> 199.3).
@@ -216,8 +217,8 @@ struct VprojArgs {
     float *seg_A, *seg_lse;
 };
 
-// SEG: the segment form.  What its log-sum-exp needs, the merge has in registers, and the head outputs leave as the fp32
-// sums they are; as a kernel of its own that read them back, with one thread per head for the statistics, this took 8.8 us
+// SEG: the segment form.  What its log-sum-exp needs but Qp and b^K (fetched after the merge), the merge has in registers,
+// and the head outputs leave as the fp32 sums they are (b^V fetched between their stores, one element at a time); as a kernel of its own that read them back, with one thread per head for the statistics, this took 8.8 us
 // at 128 rows.
 template <int DM, int NT, bool SEG>
 __global__ void __launch_bounds__(512)

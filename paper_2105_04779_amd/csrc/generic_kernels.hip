@@ -80,7 +80,8 @@ k_cout(const T *__restrict__ bv, const T *__restrict__ bo, const T *__restrict__
 // scores).  One workgroup owns (16 MT) x (16 NT) outputs; its eight wavefronts each take an eighth of k straight from
 // global memory into registers (consecutive slices, so both halves of a cache line go to one wavefront), four
 // 16-wide slices of both operands requested before the first is used (up to K = 512 the whole contraction is one
-// round trip), and add up through LDS.  Bound: memory latency at decode batch sizes, the fp32 matrix rate beyond.
+// round trip), and add up through LDS.  A bias is fetched behind the last barrier, element by element, each waited for.
+// Bound: memory latency at decode batch sizes, the fp32 matrix rate beyond.
 // 64 x 512 x 512: 5.4 us, 119 us for the kernel it replaces (one output per thread, a serial loop over k); the
 // scores of 16 x 32 rows over 300 positions, K = 512: 9.5 us.
 struct GemmF32 {
@@ -645,6 +646,7 @@ hipError_t launch_seg_finish(const SegFinishArgs &a, int rows, hipStream_t s)
 
 // One softmax over the union of the segments' keys, per (row, head):
 //   w_s = exp(lse_s - max_s' lse_s') / sum_s' exp(lse_s' - max),   A = sum_s w_s seg_A_s      (then a7 on A)
+// Bound: memory latency; the statistics are one round trip, then the segments' outputs one each, behind their branches.
 template <typename TO>
 __global__ void k_seg_merge(const SegMergeArgs a)
 {

@@ -3,8 +3,11 @@
 //
 // At d_m = 64 or 128 a layer's four weight matrices are 64 or 256 KB: a workgroup can read all of them for itself, and
 // does so before anything else (a wavefront keeps the fragments of its 16 output columns of every projection in
-// registers, up to 128 of them), so the step costs one round trip to memory plus seven barriers.  As separate launches
-// every step of the chain pays a launch and a round trip of its own.  Arithmetic and rounding are those of
+// registers, up to 128 of them).  As separate launches every step of the chain pays a launch and a round trip of its own.
+// Bound: latency, of seven barriers and of a chain of dependent fetches, which the first one does not end: b^Q is fetched
+// where it is added, a second score tile of a wavefront and the positions of a5 as the compiler orders them, load, wait,
+// products, four to eight times over, and c_out between the stores of the result, which may alias it for all the
+// compiler knows.  Arithmetic and rounding are those of
 // generic_kernels.hip: fp32 operands, fp32 products and sums (16x16x4 MFMA), four consecutive k per lane.
 // Measured, fp32, per call among others: 2 sentences x 2 beams, d_m 64, n 32: 21.5 us as the six launches, 8.5 us here.
 #include "el_internal.h"
