@@ -18,51 +18,20 @@
 // Bound: memory latency (the table of the cut, then tiles and EL-Q together), then the 64 bytes a clock that a compute unit
 // receives: at d_m 1024 128 KB of tiles and 64 KB of EL-Q.
 #include <hip/hip_ext.h>
-#include "el_internal.h"
+#include "mfma.h"
 
 namespace el {
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef short s4 __attribute__((ext_vector_type(4)));
-typedef short s8 __attribute__((ext_vector_type(8)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-#define EL_LDS(T) __attribute__((address_space(3))) T
-
 namespace {
 
-constexpr int kTile = 16, kWaves = 8;
+constexpr int kWaves = 8;
 constexpr int kPos = kTile * kShortTiles;  // positions of a span
-constexpr float kMasked = -1.0e30f;        // score of a position that does not exist: finite, exp2 of it is 0
 
 // A wavefront's slice of a tile lies in LDS as windows of 64 columns (16 rows of 128 bytes), and one of 32 (16 rows of 64
 // bytes) where the slice is 96 columns.  Chunk (16 bytes) c of row r is at chunk position c ^ swizzle(r): 16 rows of one chunk
 // (a score operand) and eight rows of two (half a wavefront's transposing read) hit every bank once.
 __device__ __forceinline__ int swizzle64(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
 __device__ __forceinline__ int swizzle32(int row) { return (row >> 2) & 3; }
-
-// a value against the others of the lane's 16 (DPP, no LDS round trip)
-template <int CTRL> __device__ __forceinline__ float dpp(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true)); }
-__device__ __forceinline__ float max16(float v)
-{
-    v = fmaxf(v, dpp<0xB1>(v)); v = fmaxf(v, dpp<0x4E>(v)); v = fmaxf(v, dpp<0x141>(v));
-    return fmaxf(v, dpp<0x140>(v));
-}
-__device__ __forceinline__ float sum16(float v)
-{
-    v += dpp<0xB1>(v); v += dpp<0x4E>(v); v += dpp<0x141>(v);
-    return v + dpp<0x140>(v);
-}
-
-template <bool BF16> __device__ __forceinline__ f4 mfma(u4 a, u4 b, f4 c)
-{
-    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
-}
 
 } // namespace
 
@@ -151,8 +120,8 @@ k_core_short(const StreamArgs a)
         f4 hi = f4{0.f, 0.f, 0.f, 0.f}, lo = hi;
 #pragma unroll
         for (int c = 0; c < CHK; ++c) {
-            hi = mfma<BF16>(hb[c], elq[c][0], hi);
-            lo = mfma<BF16>(hb[c], elq[c][1], lo);
+            hi = Mma<BF16>::s16(hb[c], elq[c][0], hi);
+            lo = Mma<BF16>::s16(hb[c], elq[c][1], lo);
         }
         sc[t] = hi + lo;
     }
@@ -238,7 +207,7 @@ k_core_short(const StreamArgs a)
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 const s4 lo = tb[u][mb][0], hi = tb[u][mb][1];
-                X[mb] = mfma<BF16>(__builtin_bit_cast(u4, s8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}), P[pl], X[mb]);
+                X[mb] = Mma<BF16>::s16(__builtin_bit_cast(u4, s8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}), P[pl], X[mb]);
             }
     }
     // ---- the piece: normalised, fp16, in fragment order.  A lane holds columns 4 g .. + 3 of every 16-column block of its row; the

@@ -36,50 +36,19 @@
 // Scores arrive pre-multiplied by log2(e)/sqrt(d_k), so the softmax is an exp2 of a difference.
 #include <type_traits>
 #include <hip/hip_ext.h>
-#include "el_internal.h"
+#include "mfma.h"
 
 namespace el {
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef short s4 __attribute__((ext_vector_type(4)));
-typedef short s8 __attribute__((ext_vector_type(8)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-#define EL_LDS(T) __attribute__((address_space(3))) T
-
 namespace {
 
-constexpr int kTile = 16;                 // rows of H per tile
 constexpr float kRescaleStep = 10.0f;     // log2 units: probabilities stay below 2^10
-constexpr float kMasked = -1.0e30f;       // score of a position that does not exist: finite, exp2 of it is 0
 
 // chunk swizzle of a 16-row tile: the two bit pairs of the row number swapped.  A bijection on
 // four bits (row-wise b128 reads of 16 rows hit 16 different chunk positions) whose upper pair
 // runs over all four values inside {8g + k} and {8g + 4 + k}, k = 0..3 (the row sets one
 // transposing read touches), so those reads use every bank exactly twice.
 __device__ __forceinline__ int tile_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-
-// butterfly over the four lanes of a quad on the VALU (DPP quad_perm), no LDS round trip
-__device__ __forceinline__ float quad_xor1(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true)); }
-__device__ __forceinline__ float dpp_half_mirror(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true)); }   // lane i <-> 7 - i of each 8
-__device__ __forceinline__ float dpp_row_mirror(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true)); }    // lane i <-> 15 - i of each 16
-__device__ __forceinline__ float quad_xor2(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true)); }
-
-template <bool BF16> struct Mma;
-template <> struct Mma<false> {
-    static __device__ __forceinline__ f4 s16(u4 a, u4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0); }
-    static __device__ __forceinline__ f16v s32(u4 a, u4 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0); }
-};
-template <> struct Mma<true> {
-    static __device__ __forceinline__ f4 s16(u4 a, u4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0); }
-    static __device__ __forceinline__ f16v s32(u4 a, u4 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0); }
-};
 
 } // namespace
 

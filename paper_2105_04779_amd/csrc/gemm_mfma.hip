@@ -19,25 +19,14 @@
 // pieces of X and A are rounded to fp16 once each (2^-12 relative; the measured end-to-end error stays several times
 // under the 2e-3 bar); sums of several pieces enter a6 as a high + low pair.  Accumulation is fp32.
 #include <type_traits>
-#include "el_internal.h"
+#include "mfma.h"
 #include "cut.h"
 
 namespace el {
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef uint16_t s8v __attribute__((ext_vector_type(8)));
 
 namespace {
-
-template <bool BF> __device__ __forceinline__ f4 mfma16(u4 a, u4 b, f4 c);
-template <> __device__ __forceinline__ f4 mfma16<false>(u4 a, u4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0); }
-template <> __device__ __forceinline__ f4 mfma16<true>(u4 a, u4 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0); }
 
 // Workgroup -> (64-column block, part of its columns, group of row tiles).  Workgroup ids that differ by a multiple of
 // 8 share an XCD and its L2, so each XCD gets one run of the items in block-major order: it then pulls only its own
@@ -149,7 +138,7 @@ k_qelq(const QelqArgs a)
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[t] = mfma16<BF>(wq[s][t], xq[s], acc[t]);
+            for (int t = 0; t < 4; ++t) acc[t] = Mma<BF>::s16(wq[s][t], xq[s], acc[t]);
 #pragma unroll
         for (int t = 0; t < 4; ++t) *(f4 *)(red + (w * 16 + r16) * RS + 16 * t + 4 * q) = acc[t];
         if (tile + a.groups < tiles) load_rows(tile + a.groups);
@@ -173,8 +162,8 @@ k_qelq(const QelqArgs a)
             s8v hi, lo;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                f4 e = mfma16<false>(wk[i][h][0], qf[0], f4{0.f, 0.f, 0.f, 0.f});
-                e = mfma16<false>(wk[i][h][1], qf[1], e);
+                f4 e = Mma<false>::s16(wk[i][h][0], qf[0], f4{0.f, 0.f, 0.f, 0.f});
+                e = Mma<false>::s16(wk[i][h][1], qf[1], e);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     uint16_t vh, vl;
@@ -218,8 +207,8 @@ struct VprojArgs {
 };
 
 // SEG: the segment form.  What its log-sum-exp needs but Qp and b^K (fetched after the merge), the merge has in registers,
-// and the head outputs leave as the fp32 sums they are (b^V fetched between their stores, one element at a time); as a kernel of its own that read them back, with one thread per head for the statistics, this took 8.8 us
-// at 128 rows.
+// and the head outputs leave as the fp32 sums they are (b^V fetched between their stores, one element at a time); as a
+// kernel of its own that read them back, with one thread per head for the statistics, this took 8.8 us at 128 rows.
 template <int DM, int NT, bool SEG>
 __global__ void __launch_bounds__(512)
 k_vproj(const VprojArgs a)
@@ -343,7 +332,7 @@ k_vproj(const VprojArgs a)
 #pragma unroll
             for (int k = 0; k < 4; ++k) part[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(v[s][2 * k] * inv, v[s][2 * k + 1] * inv));
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wv[s][t], part, acc[t]);
+            for (int t = 0; t < NT; ++t) acc[t] = Mma<false>::s16(wv[s][t], part, acc[t]);
             if (!merged) continue;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -352,7 +341,7 @@ k_vproj(const VprojArgs a)
                                                                                   fmaf(v[s][2 * k + 1], inv, -(float)high[1])));
             }
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wv[s][t], part, acc[t]);
+            for (int t = 0; t < NT; ++t) acc[t] = Mma<false>::s16(wv[s][t], part, acc[t]);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) red[parity][(w * NT + t) * 64 + l] = acc[t];
@@ -425,7 +414,7 @@ k_oproj(const OprojArgs a)
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = mfma16<false>(wo[s][t], xa[BUF][s], acc[t]);
+            for (int t = 0; t < NT; ++t) acc[t] = Mma<false>::s16(wo[s][t], xa[BUF][s], acc[t]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) *(f4 *)(red[BUF] + (w * 16 + r16) * RS + 16 * t + 4 * q) = acc[t];
         if (tile + 2 * a.groups < tiles) load_rows(xa[BUF], tile + 2 * a.groups);
