@@ -13,8 +13,9 @@
 //   weighted sum  X^T[d, r] over the slice's columns, 16x16x32 MFMA (two tiles deep), A = H columns through the transposing LDS
 //                 read, B = P (fp16, or a high + low bf16 pair).  The column fragments are read together with the scores'
 //                 operands, so that the tiles' part of LDS is free for the partial scores.
-// Kernel times, streaming core -> here, d_m 1024: one sentence of 613 positions, 64 rows (40 workgroups) 11.2 -> 6.9 us; 4 of 205
-// to 410 10.0 -> 6.9; 128 histories of 37, 16 rows, 11.4 -> 8.2.
+// Kernel times, streaming core -> here, d_m 1024: one sentence of 613 positions, 64 rows (40 workgroups) 10.2 -> 6.6 us; 4 of 205
+// to 410 9.7 -> 7.0; 8 of 512 (256 workgroups) 13.1 -> 9.6; 128 histories of 37, 16 rows, 9.8 -> 6.5.  More pieces take some of it
+// back in the merge (one sentence: ten instead of eight, 5.9 -> 8.1).
 // Bound: memory latency (the table of the cut, then tiles and EL-Q together), then the 64 bytes a clock that a compute unit
 // receives: at d_m 1024 128 KB of tiles and 64 KB of EL-Q.
 #include <hip/hip_ext.h>

@@ -62,7 +62,7 @@ inline int tile_groups(int tiles, int columns_parts, int num_cus)
 // consecutive columns in a lane: its high and low halves are 16-byte stores into the core's fragment order.
 // Bound: memory latency up to about 64 rows, the bytes of EL-Q (4 per element) beyond.  One launch against the two it
 // replaces (a1 on 32 x 32 tiles staged in LDS, a2 with its 8 KB of weights per workgroup), d_m 1024: 4 rows 10.4 ->
-// 5.5 us, 256 rows 15.4 -> 11.4 (4.4 of it the stores, 16.8 MB), 512 rows 23.9 -> 17.3, 1280 rows 47.5 -> 29.6.
+// 4.8 us, 256 rows 15.4 -> 10.3 (4.4 of it the stores, 16.8 MB), 512 rows 23.9 -> 14.6, 1280 rows 47.5 -> 24.2.
 struct QelqArgs {
     const u4 *Wq;          // storage type, [head][k / 32][column / 16 % 4][lane]
     const u4 *Wk;          // fp16, [head][column / 32][half][k / 32 % 2][lane]
@@ -190,8 +190,8 @@ k_qelq(const QelqArgs a)
 // Bound: memory latency in a chain of two (piece table, then statistics and pieces together; a third for more than four
 // pieces, and so on), then the pieces' bytes.  Where the columns of a head are split over workgroups each of them fetches and
 // merges the same rows.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup per 16 rows, the
-// 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024: 38.9 -> 23.0 us;
-// 512 rows, one piece each: 19.7 -> 10.2; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 10.0; 4 rows: 8.6 -> 5.4.
+// 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024: 38.9 -> 17.7 us;
+// 512 rows, one piece each: 19.7 -> 7.9; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 7.8; 4 rows in 8 pieces: 8.6 -> 5.9.
 // The low half of merged sums is 0.2 to 0.4 us of that (4 rows 23.1 -> 23.3 us the step, 1280 rows 197.3 -> 199.3).
 struct VprojArgs {
     const u4 *Wp;          // (W^V) in fragments: [head][k / 32][column / 16 % 4][lane]
