@@ -250,7 +250,9 @@ el_status el_attn_plan_preview(int32_t B, int32_t beam, int32_t heads, int32_t d
 
 /*
  * 1 if the automatic choice for that shape, in a context prepared for `max_batch` (a larger one has room for more
- * spans), is the core of short spans; 0 if not, or if el_attn_plan_preview would not accept the shape.
+ * spans; elements of thousands of positions, which only such a context can cut that finely, stay on the other core
+ * where it leaves many fewer pieces), is the core of short spans; 0 if not, or if el_attn_plan_preview would not
+ * accept the shape.
  */
 int32_t el_attn_plan_short_core(int32_t max_batch, int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n,
                                 int32_t compute_units);

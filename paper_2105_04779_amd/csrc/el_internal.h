@@ -253,9 +253,9 @@ __device__ __forceinline__ void read_ahead(const StreamArgs &a, int per_xcd)
     }
 }
 // Workgroups of a core.  Where at least a quarter of the compute units is idle, 64 more read the weights of a6 and a7 ahead: a
-// decoder's layers come with weights of their own, cold at every step.  Streaming core, twelve layers, 4 sentences, d_m 1024: 320 ->
-// 311.4 us; one sentence, one layer (its weights stay in the memory-side cache): 23.7 -> 23.4.  In workgroups that also stream,
-// the same reads cost 1 us: their other requests return after them.
+// decoder's layers come with weights of their own, cold at every step.  Twelve layers, 4 sentences, d_m 1024: streaming core 320 ->
+// 311.4 us, core of short spans 284.3 -> 277.2; one sentence, one layer (its weights stay in the memory-side cache): 23.7 -> 23.4, 20.9 ->
+// 20.9.  In workgroups that also stream, the same reads cost 1 us: their other requests return after them.
 inline dim3 core_grid(const StreamArgs &a)
 {
     dim3 grid(((a.G * a.nblocks + 7) / 8) * 8);
