@@ -17,7 +17,7 @@
 // Storage-dtype operands enter the MFMA exactly (a1 runs in the storage type).  From a2 on everything is fp16: bf16
 // weights are converted once at prepare time (exact above 2^-14, |error| <= 2^-25 below), and the intermediates Qp, the
 // pieces of X and A are rounded to fp16 once each (2^-12 relative; the measured end-to-end error stays several times
-// under the 2e-3 bar); sums of several pieces enter a6 as a high + low pair.  Accumulation is fp32.
+// under the 2e-3 bar).  Accumulation is fp32.
 #include <type_traits>
 #include "mfma.h"
 #include "cut.h"
@@ -180,54 +180,72 @@ k_qelq(const QelqArgs a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Merge of the pieces fused with a6 (A_i = X_i . W_i^V, Eq. 5 / Eq. 8), NT 16-column blocks of a head per workgroup.
-// A lane fetches the 16-byte fragments of its own row from every piece and merges them with the log-sum-exp weights
-// it works out for that row,
-//     X = sum_p (w_p l_p) Xhat_p / sum_p (w_p l_p),  w_p = 2^(m_p - M),
-// so nothing is exchanged before the products are.  Up to four pieces are in flight at a time; more are folded in
-// with a running maximum (eight in the form of one column block, a round trip less for 5 to 8 pieces, is 1.3 % of a call
-// slower over 160 shapes of 3 to 15 pieces, with 15 up to 9 %; twelve layers 283.5 us against 279.5 with four).
-// Bound: memory latency in a chain of two (piece table, then statistics and pieces together; a third for more than four
-// pieces, and so on), then the pieces' bytes.  Where the columns of a head are split over workgroups each of them fetches and
-// merges the same rows.  Against the kernel it replaces (weights and merged rows staged in LDS, one workgroup per 16 rows, the
-// 128 KB of weights fetched again for every tile): 1280 rows in 448 pieces of 64 rows, d_m 1024: 38.9 -> 17.7 us;
-// 512 rows, one piece each: 19.7 -> 7.9; 256 rows in 191 pieces of 64 (25 MB): 11.7 -> 7.8; 4 rows in 8 pieces: 8.6 -> 5.9.
-// The low half of merged sums is 0.2 to 0.4 us of that (4 rows 23.1 -> 23.3 us the step, 1280 rows 197.3 -> 199.3).
+// Merge of the pieces fused with a6 (A_i = X_i . W_i^V, Eq. 5 / Eq. 8), NT 16-column blocks of a head per workgroup.  The
+// products are taken of the pieces themselves, which are fp16 values and enter them exactly, and their results are what
+// is weighted (log-sum-exp weights, which a lane works out for its own row):
+//     A = sum_p (w_p l_p) (Xhat_p . W^V) / sum_p (w_p l_p),  w_p = 2^(m_p - M).
+// So a fragment goes from memory into the matrix instruction, and the merge is one multiply-add per result instead of a
+// conversion and one per element of X.  Up to four rounds of pieces are in flight (PC); more are folded in with a running maximum.
+//
+// The instruction takes 16 rows: 16 query rows with one piece each a round, or (row_shift < 4) 8, 4, 2 or 1 of them with 2, 4,
+// 8 or 16 of their pieces side by side, added up over the lanes at the end.  Bound: the 64 bytes a clock that a compute unit
+// receives.  A round is 32 KB at d_m 1024, the weights of a whole head 128 KB: with 16 rows a workgroup (4 of them
+// there, or 16 with their dozens of pieces) one sentence of ten pieces took 32 KB + 10 x 32 KB, 7.9 us, though three
+// quarters of the chip were idle; in single rows, 16 pieces a round, 4.6 us.  16 rows in 4 to 7 pieces 7.0 -> 5.0; 32 rows in
+// 8 pieces 7.7 -> 5.3; d_m 768, 20 rows in 5 pieces 6.4 -> 5.0; 1280 rows in 448 pieces of 64 rows (16 rows as before) 18.2 -> 16.6.
+// Behind that memory latency in a chain of two: the piece table, then statistics and pieces together.
 struct VprojArgs {
     const u4 *Wp;          // (W^V) in fragments: [head][k / 32][column / 16 % 4][lane]
     const f16_t *Xp;       // normalised fp16 pieces [slot, Rs, d_m] in fragment order
     const float *ML;       // [slot, Rs, 2]
     f16_t *A;              // [M, d_m] in fragment order
-    PieceMap pm;
+    const int2 *pieces;    // the piece table of the cut
     int M, x, Rs, groups;
+    int row_shift;         // a tile is 1 << row_shift rows
     // segment form (fp32): head outputs with b^V and, per head, the log-sum-exp with Eq. 7's key-bias term, instead of A
     const f16_t *Qp;       // [M, d_m], carrying log2(e)/sqrt(d_k)
     const float *bk32, *bv32;
     float *seg_A, *seg_lse;
 };
 
+// Sum (or maximum) over the lanes of 16 that hold the same row, (1 << rs) of them apart; every lane gets it.
+template <bool MAX>
+__device__ __forceinline__ float over_row(float v, int rs)
+{
+    auto with = [](float x, float y) { return MAX ? fmaxf(x, y) : x + y; };
+    v = with(v, dpp<0x128>(v));                          // row_ror:8, :4, :2, :1
+    if (rs <= 2) v = with(v, dpp<0x124>(v));
+    if (rs <= 1) v = with(v, dpp<0x122>(v));
+    if (rs <= 0) v = with(v, dpp<0x121>(v));
+    return v;
+}
+
 // SEG: the segment form.  What its log-sum-exp needs but Qp and b^K (fetched after the merge), the merge has in registers,
 // and the head outputs leave as the fp32 sums they are (b^V fetched between their stores, one element at a time); as a
 // kernel of its own that read them back, with one thread per head for the statistics, this took 8.8 us at 128 rows.
-template <int DM, int NT, bool SEG>
+// LOOP: several row tiles of 16 per workgroup, as a kernel of its own: together with the single tile's code the widest form spills.
+template <int DM, int NT, bool SEG, bool LOOP>
 __global__ void __launch_bounds__(512)
 k_vproj(const VprojArgs a)
 {
     constexpr float kLn2 = 0.6931471805599453f;
     constexpr int KS = DM / 256;                         // 32-wide slices of k per wavefront
-    constexpr int PC = 4;                                // pieces in flight
+    constexpr int PC = LOOP && DM == 1024 ? 3 : 4;       // rounds of pieces in flight (with a fourth the widest form spills)
     __shared__ f4 red[2][8 * NT * 64];
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
     Place pl;
     if (!place_of(DM / 64, 4 / NT, a.groups, blockIdx.x, pl)) return;
     const int head = pl.block, nb = pl.part;
-    const int tiles = (a.M + 15) >> 4;
+    const int rs = LOOP ? 4 : a.row_shift, at_once = 16 >> rs;      // rows of a tile 1 << rs, pieces of each that the 16 lanes hold side by side
+    const int trow = r16 & ((1 << rs) - 1), piece = r16 >> rs;
+    const int tiles = (a.M + (1 << rs) - 1) >> rs;
     int j, slot0, np;
     auto look_up = [&](int tile) {
-        const int m = min(16 * tile + r16, a.M - 1), b = m / a.x;
+        const int m = min((tile << rs) + trow, a.M - 1), b = m / a.x;
         j = m - b * a.x;
-        piece_range(a.pm, b, slot0, np);
+        const int2 e = a.pieces[b];
+        slot0 = e.x; np = e.y;
     };
     look_up(pl.group);
     u4 wv[KS][NT];
@@ -236,79 +254,115 @@ k_vproj(const VprojArgs a)
 #pragma unroll
         for (int t = 0; t < NT; ++t)
             wv[s][t] = a.Wp[(((size_t)head * (DM / 32) + KS * w + s) * 4 + nb * NT + t) * 64 + l];
-    // The first pieces of a tile are requested before the products of the tile before it, into the registers that its merge
-    // has just left (whole steps, with the two row tiles in flight of a7: 512 histories of 1024, d_m 1024, 210.7 -> 209.5 us;
-    // 1000 rows of d_m 768 67.3 -> 66.6).
-    int pieces, np_max;
+    asm volatile("" ::: "memory");                       // (requested here: the compiler sinks them behind the wait for the piece table, 0.5 us)
+    int pieces, rounds;
+    bool merged;                                         // (uniform)
     size_t row0;
     const f16_t *x0;
     f2 ml[PC];
-    h8 xv[PC][KS];
+    u4 xv[PC][KS];
     auto locate = [&]() {                                // of the tile looked up last
         pieces = np;
         row0 = (size_t)slot0 * a.Rs + head * a.x + j;
         x0 = a.Xp + (size_t)slot0 * a.Rs * DM + frag16_index(head * a.x + j, 32 * KS * w + 8 * q, DM);
-        np_max = pieces;                                 // most pieces among the 16 rows (uniform)
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) np_max = max(np_max, __shfl_xor(np_max, o, 64));
-        np_max = __builtin_amdgcn_readfirstlane(np_max);
+        const int most = __builtin_amdgcn_readfirstlane((int)max16((float)pieces));          // pieces among the rows
+        rounds = (most + at_once - 1) >> (4 - rs);
+        merged = most > 1;
     };
-    auto load_pieces = [&](int p0) {
+    // C rounds from k0 on into registers, the statistics first: the weights are worked out while the rows arrive
+    auto load = [&](auto count, int k0) __attribute__((always_inline)) {
+        constexpr int C = decltype(count)::value;
+        unsigned step[C];
 #pragma unroll
-        for (int p = 0; p < PC; ++p) {
-            if (p0 + p >= np_max) { ml[p] = f2{0.f, 0.f}; continue; }               // uniform
-            const size_t step = (size_t)min(p0 + p, pieces - 1) * a.Rs;
-            ml[p] = *(const f2 *)(a.ML + (row0 + step) * 2);
+        for (int i = 0; i < C; ++i) {
+            step[i] = (unsigned)min((k0 + i) * at_once + piece, pieces - 1) * (unsigned)a.Rs;
+            ml[i] = *(const f2 *)(a.ML + (row0 + step[i]) * 2);
+        }
 #pragma unroll
-            for (int s = 0; s < KS; ++s) xv[p][s] = *(const h8 *)(x0 + step * DM + 512 * s);
+        for (int i = 0; i < C; ++i)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) xv[i][s] = *(const u4 *)(x0 + (size_t)step[i] * DM + 512 * s);
+    };
+    f4 acc[NT];
+    float m_run, den;
+    auto fold = [&](auto count, int k0) __attribute__((always_inline)) {
+        constexpr int C = decltype(count)::value;
+        float wt[C], m_new = m_run;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const bool some = (k0 + i) * at_once + piece < pieces && ml[i][1] > 0.f;         // a piece of this row, and not an empty one
+            ml[i] = some ? ml[i] : f2{-INFINITY, 0.f};
+            m_new = fmaxf(m_new, ml[i][0]);
+        }
+        if (k0 > 0) {
+            const float c = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+            den *= c;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[t][e] = c != 0.f ? acc[t][e] * c : 0.f;
+        }
+        m_run = m_new;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            wt[i] = ml[i][1] > 0.f ? __builtin_amdgcn_exp2f(ml[i][0] - m_new) * ml[i][1] : 0.f;
+            den += wt[i];
+            if (C == 1) wt[i] = merged || wt[i] == 0.f ? wt[i] : 1.f;
+        }
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            f4 part[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) part[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) part[t] = Mma<false>::s16(wv[s][t], xv[i][s], part[t]);
+            // an empty piece's row was never written, and one whose weight underflows may hold fp16 infinities
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[t][e] = fmaf(wt[i] != 0.f ? part[t][e] : 0.f, wt[i], acc[t][e]);
         }
     };
-    locate();
-    load_pieces(0);
+    // Up to PC rounds in straight code, a copy for each number of them: where they are loaded under branches the compiler has the
+    // first product wait for the last piece (256 rows in 191 pieces of 64, whole step: 62.2 -> 61.7 us).
+    auto rounds_from = [&](int k0, bool loads, bool folds) __attribute__((always_inline)) {
+        auto both = [&](auto count) __attribute__((always_inline)) {
+            if (loads) load(count, k0);
+            if (folds) fold(count, k0);
+        };
+        const int c = min(rounds - k0, PC);
+        if (c == 1) both(std::integral_constant<int, 1>{});
+        else if (c == 2) both(std::integral_constant<int, 2>{});
+        else if (PC == 3 || c == 3) both(std::integral_constant<int, 3>{});
+        else both(std::integral_constant<int, PC>{});
+    };
+    auto start = [&]() {
+        m_run = -INFINITY; den = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+    };
     int parity = 0;
-    for (int tile = pl.group; tile < tiles; tile += a.groups) {
-        if (tile + a.groups < tiles) look_up(tile + a.groups);                      // the next tile's table entries
-        const bool merged = np_max > 1;                  // (uniform)
-        float v[KS][8], m_run = -INFINITY, den = 0.f;
+    auto finish = [&](int tile, bool merged) __attribute__((always_inline)) {
+        if (rs < 4) {                                    // the lanes that share a row
+            const float m_all = over_row<true>(m_run, rs), c = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_all);   // (one piece: 1)
+            den = over_row<false>(den * c, rs);
+            m_run = m_all;
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[s][e] = 0.f;
-        for (int p0 = 0; p0 < np_max; p0 += PC) {
-            if (p0 > 0) load_pieces(p0);
-            float m_new = m_run;
-#pragma unroll
-            for (int p = 0; p < PC; ++p) {
-                if (p0 + p >= pieces || !(ml[p][1] > 0.f)) ml[p] = f2{-INFINITY, 0.f};  // no such piece for this row, or an empty one
-                m_new = fmaxf(m_new, ml[p][0]);
-            }
-            if (p0 > 0) {
-                const float c = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-                den *= c;
-#pragma unroll
-                for (int s = 0; s < KS; ++s)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[s][e] = c != 0.f ? v[s][e] * c : 0.f;
-            }
-            m_run = m_new;
-#pragma unroll
-            for (int p = 0; p < PC; ++p) {
-                if (p0 + p >= np_max) continue;
-                const float wp = ml[p][1] > 0.f ? exp2f(ml[p][0] - m_new) * ml[p][1] : 0.f;
-                const bool there = wp != 0.f;            // an empty piece's row was never written, and one whose weight
-                den += wp;                               // underflows may hold fp16 infinities
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    const h8 xs = there ? xv[p][s] : h8{};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[s][e] = fmaf(merged ? wp : 1.f, (float)xs[e], v[s][e]);
-                }
-            }
+                for (int e = 0; e < 4; ++e) acc[t][e] = over_row<false>(c != 0.f ? acc[t][e] * c : 0.f, rs);
         }
-        if (tile + a.groups < tiles) { locate(); load_pieces(0); }
-        const float inv = !(den > 0.f) ? 0.f : merged ? 1.0f / den : 1.f;      // a single piece goes on as it is
+        if (merged) {
+            const float inv = den > 0.f ? 1.0f / den : 0.f;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[t][e] *= inv;
+        }
         if (SEG && nb == 0 && w == 7) {                  // (a wavefront that adds nothing up below)
-            const int m = min(16 * tile + r16, a.M - 1);
+            const int m = min((tile << rs) + trow, a.M - 1);
             const f16_t *qp = a.Qp + (size_t)m * DM + head * 64 + 16 * q;
             const float *bk = a.bk32 + head * 64 + 16 * q;
             float c = 0.f;
@@ -316,32 +370,8 @@ k_vproj(const VprojArgs a)
             for (int k = 0; k < 16; ++k) c = fmaf((float)qp[k], bk[k], c);
             c += __shfl_xor(c, 16, 64);
             c += __shfl_xor(c, 32, 64);
-            if (q == 0 && 16 * tile + r16 < a.M)
+            if (q == 0 && piece == 0 && (tile << rs) + trow < a.M)
                 a.seg_lse[(size_t)m * (DM / 64) + head] = den > 0.f ? m_run * kLn2 + logf(den) + c * kLn2 : -INFINITY;
-        }
-        f4 acc[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-        // The pieces were rounded to fp16 once.  Merged sums enter the products as a high + low pair (by truncation: two values per
-        // instruction, never beyond the fp16 range), so that an element cut into pieces is no less precise than one in a single
-        // piece, whose sum is an fp16 value already.  Rounded to fp16 once more they cost up to 13 % of error (d_m 1024, one row of
-        // 128 positions in two pieces: 3.92e-4 -> 4.47e-4 against fp64).
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            u4 part;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) part[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(v[s][2 * k] * inv, v[s][2 * k + 1] * inv));
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = Mma<false>::s16(wv[s][t], part, acc[t]);
-            if (!merged) continue;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const h2 high = __builtin_bit_cast(h2, (unsigned)part[k]);
-                part[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(fmaf(v[s][2 * k], inv, -(float)high[0]),
-                                                                                  fmaf(v[s][2 * k + 1], inv, -(float)high[1])));
-            }
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = Mma<false>::s16(wv[s][t], part, acc[t]);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) red[parity][(w * NT + t) * 64 + l] = acc[t];
@@ -350,7 +380,7 @@ k_vproj(const VprojArgs a)
             f4 sum = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < 8; ++s) sum += red[parity][(s * NT + w) * 64 + l];
-            const int mm = 16 * tile + r16;
+            const int mm = piece == 0 ? (tile << rs) + trow : a.M;
             if (SEG) {
                 const int col = head * 64 + 16 * (nb * NT + w) + 4 * q;
                 float *o = a.seg_A + (size_t)mm * DM + col;                    // (the caller's: aligned to 4 bytes)
@@ -362,6 +392,27 @@ k_vproj(const VprojArgs a)
                     h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
         }
         parity ^= 1;
+    };
+    locate();
+    start();
+    if (!LOOP) {
+        for (int k0 = 0; k0 < rounds; k0 += PC) rounds_from(k0, true, true);
+        finish(pl.group, merged);
+        return;
+    }
+    // The first pieces of a tile are requested before the tile before it is added up, into the registers that its products
+    // have just left (whole steps, with the two row tiles in flight of a7: 512 histories of 1024, d_m 1024, 210.7 -> 209.5 us;
+    // 1000 rows of d_m 768 67.3 -> 66.6).
+    rounds_from(0, true, false);
+    for (int tile = pl.group; tile < tiles; tile += a.groups) {
+        const bool more = tile + a.groups < tiles;
+        if (more) look_up(tile + a.groups);              // the next tile's table entries
+        start();
+        rounds_from(0, false, true);
+        for (int k0 = PC; k0 < rounds; k0 += PC) rounds_from(k0, true, true);
+        const bool m = merged;
+        if (more) { locate(); rounds_from(0, true, false); }
+        finish(tile, m);
     }
 }
 
@@ -546,15 +597,28 @@ hipError_t launch_qelq_mfma(const el_attn_ctx *ctx, const Problem &p, const Work
 
 // merge + a6: A[b*beam+j, head i] = (sum_p w_p Xp[b,p,i*beam+j,:]) . W_i^V       fp16
 template <int DM, bool SEG>
-static void launch_vproj_t(VprojArgs &a, int num_cus, hipStream_t s)
+static void launch_vproj_t(VprojArgs &a, int pieces, int num_cus, hipStream_t s)
 {
-    const int tiles = (a.M + 15) / 16, heads = DM / 64;
-    const int parts = tiles * heads * 4 <= num_cus ? 4 : tiles * heads * 2 <= num_cus ? 2 : 1;
-    a.groups = tile_groups(tiles, heads * parts, num_cus);
+    const int heads = DM / 64;
+    // Rows and columns of a workgroup: whatever makes a compute unit receive least, in units of a round of pieces (a whole
+    // head's weights are four), while all workgroups run at once; 16 rows and the fewest column parts beyond that.  One sentence
+    // of 613 positions (10 pieces, 4 rows, d_m 1024): 16 rows 7.0 us, 4 rows 4.9, 1 row 4.6; one piece: 16 rows 3.7 us, 1 row 3.9.
+    auto tiles_of = [&](int rs) { return (a.M + (1 << rs) - 1) >> rs; };
+    int parts = 1, shift = 4, least = 0;
+    for (int rs = 4; rs >= 0; --rs)
+        for (int p = 4; p >= 1; p >>= 1) {
+            const int at_once = 16 >> rs;
+            if ((p > 1 || rs < 4) && tiles_of(rs) * heads * p > num_cus) continue;
+            const int cost = 4 / p + (pieces + at_once - 1) / at_once;
+            if (least == 0 || cost < least) { least = cost; parts = p; shift = rs; }
+        }
+    a.row_shift = shift;
+    a.groups = tile_groups(tiles_of(shift), heads * parts, num_cus);
     const dim3 grid = place_grid(heads, parts, a.groups), block(512);
-    if (parts == 4) hipLaunchKernelGGL((k_vproj<DM, 1, SEG>), grid, block, 0, s, a);
-    else if (parts == 2) hipLaunchKernelGGL((k_vproj<DM, 2, SEG>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_vproj<DM, 4, SEG>), grid, block, 0, s, a);
+    if (parts == 4) hipLaunchKernelGGL((k_vproj<DM, 1, SEG, false>), grid, block, 0, s, a);
+    else if (parts == 2) hipLaunchKernelGGL((k_vproj<DM, 2, SEG, false>), grid, block, 0, s, a);
+    else if (tiles_of(shift) <= a.groups) hipLaunchKernelGGL((k_vproj<DM, 4, SEG, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_vproj<DM, 4, SEG, true>), grid, block, 0, s, a);
 }
 
 hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Workspace &ws, const CorePlan &pl,
@@ -562,13 +626,15 @@ hipError_t launch_vproj_mfma(const el_attn_ctx *ctx, const Problem &p, const Wor
 {
     VprojArgs a;
     a.Wp = (const u4 *)ctx->w.WvP; a.Xp = (const f16_t *)ws.Xp; a.ML = ws.ML; a.A = (f16_t *)ws.A;
-    a.pm = piece_map(ws);
+    a.pieces = ws.pieces;
     a.M = p.B * p.beam; a.x = p.beam; a.Rs = pl.Rs;
     a.Qp = (const f16_t *)ws.Qp; a.bk32 = ctx->w.bk32; a.bv32 = ctx->w.bv32;
     a.seg_A = seg ? seg->A : nullptr; a.seg_lse = seg ? seg->lse : nullptr;
-    if (p.d_m == 1024) { if (seg) launch_vproj_t<1024, true>(a, ctx->num_cus, s); else launch_vproj_t<1024, false>(a, ctx->num_cus, s); }
-    else if (p.d_m == 768) { if (seg) launch_vproj_t<768, true>(a, ctx->num_cus, s); else launch_vproj_t<768, false>(a, ctx->num_cus, s); }
-    else { if (seg) launch_vproj_t<512, true>(a, ctx->num_cus, s); else launch_vproj_t<512, false>(a, ctx->num_cus, s); }
+    // pieces of the longest element, about
+    const int pieces = pl.short_tiles ? pl.G / p.B : pl.G > p.B ? (pl.G + p.B - 1) / p.B + 1 : 1;
+    if (p.d_m == 1024) { if (seg) launch_vproj_t<1024, true>(a, pieces, ctx->num_cus, s); else launch_vproj_t<1024, false>(a, pieces, ctx->num_cus, s); }
+    else if (p.d_m == 768) { if (seg) launch_vproj_t<768, true>(a, pieces, ctx->num_cus, s); else launch_vproj_t<768, false>(a, pieces, ctx->num_cus, s); }
+    else { if (seg) launch_vproj_t<512, true>(a, pieces, ctx->num_cus, s); else launch_vproj_t<512, false>(a, pieces, ctx->num_cus, s); }
     return hipGetLastError();
 }
 

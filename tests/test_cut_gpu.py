@@ -138,6 +138,41 @@ def test_dozens_of_pieces_of_one_element(dtype, heads, d_m, beam, n):
     layer.close()
 
 
+@pytest.mark.parametrize("dtype,d_m,B,beam,n,max_batch", [
+    ("bf16", 1024, 1, 1, 960, 1),          # one row, fifteen pieces side by side
+    ("f16", 512, 1, 2, 4096, 64),          # two rows, 64 pieces: four rounds of sixteen
+    ("bf16", 512, 1, 7, 11000, 96),        # seven rows and more rounds than are in flight
+    ("bf16", 1024, 4, 4, 410, 4),          # an element of four rows a tile
+    ("f16", 768, 3, 5, 500, 3),            # tiles of four that straddle elements, the last one of three rows
+    ("f16", 1024, 2, 4, 500, 2),           # tiles of two rows, eight pieces
+    ("bf16", 768, 7, 3, 300, 7),           # 21 rows in tiles of eight
+    ("f16", 1024, 9, 5, 640, 9),           # 45 rows in tiles of eight, two column parts
+    ("bf16", 512, 16, 8, 130, 16),         # 128 rows in tiles of 16
+])
+def test_rows_and_pieces_side_by_side(dtype, d_m, B, beam, n, max_batch):
+    """Few query rows: the merge takes fewer than 16 of them a workgroup and several pieces of each at a time; elements of one
+    piece next to elements of many, lengths from 1 up, step and segment form against the oracle at the step's bar."""
+    heads = d_m // 64
+    w = wl.custom(f"rows_pieces_{dtype}_{d_m}_{B}x{beam}_{n}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=64, n=n, index=101)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.asarray([n if b == B - 1 else 1 + (b * 77) % n for b in range(B)], dtype=np.int32)
+    ref = oracle_out(w, W, H, Q, L)
+    ref_A, ref_lse = oracle.segment_reference(H, L, Q, W["Wq"], W["bq"], W["Wk"], W["bk"], W["Wv"], W["bv"], heads=heads, d_k=64)
+    for b in range(B):
+        H[b, L[b]:] = np.nan
+    layer = make_layer(w, W, max_batch=max_batch)
+    for splits in (0, 15):
+        layer.set_splits(splits)
+        err = rel_err(gpu_out(layer, w, H, Q, L), ref)
+        A, lse = layer.decode_segment(to_device(H, dtype), torch.from_numpy(L).cuda(), to_device(Q, dtype))
+        torch.cuda.synchronize()
+        err_A, err_lse = rel_err(A.cpu().numpy(), ref_A), float(np.abs(lse.cpu().numpy() - ref_lse).max())
+        record(f"{w.name}: splits={splits} err={err:.3e} seg_A err={err_A:.3e} lse err={err_lse:.3e}")
+        assert err <= TOL[dtype] and err_A <= TOL[dtype] and err_lse <= 5e-3
+    layer.close()
+
+
 SHORT = [
     # dtype, B, beam, heads, d_m, n, lens: at most 256 workgroups of 64 positions and 16 rows (two or three times as many where n <= 64)
     ("bf16", 5, 4, 16, 1024, 200, [200, 1, 16, 17, 64]),            # spans of one to four tiles, of one position and of a full tile
