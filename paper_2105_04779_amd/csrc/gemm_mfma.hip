@@ -24,8 +24,6 @@
 
 namespace el {
 
-typedef uint16_t s8v __attribute__((ext_vector_type(8)));
-
 namespace {
 
 // Workgroup -> (64-column block, part of its columns, group of row tiles).  Workgroup ids that differ by a multiple of
@@ -62,7 +60,10 @@ inline int tile_groups(int tiles, int columns_parts, int num_cus)
 // consecutive columns in a lane: its high and low halves are 16-byte stores into the core's fragment order.
 // Bound: memory latency up to about 64 rows, the bytes of EL-Q (4 per element) beyond.  One launch against the two it
 // replaces (a1 on 32 x 32 tiles staged in LDS, a2 with its 8 KB of weights per workgroup), d_m 1024: 4 rows 10.4 ->
-// 4.8 us, 256 rows 15.4 -> 10.3 (4.4 of it the stores, 16.8 MB), 512 rows 23.9 -> 14.6, 1280 rows 47.5 -> 24.2.
+// 4.8 us, 256 rows 15.4 -> 10.3 (4.4 of it the stores, 16.8 MB), 512 rows 23.9 -> 14.6, 1280 rows 47.5 -> 24.2.  The split in
+// bf16 by the instruction that converts pairs (split16_pair) instead of some twenty operations a value, which a SIMD's two
+// wavefronts had no other work to hide under: 4 rows 4.7 -> 4.4, 240 rows of d_m 768 7.6 -> 6.6, 256 rows 10.7 -> 9.5, 512 rows
+// 14.4 -> 13.2, 1280 rows 25.0 -> 20.0.
 struct QelqArgs {
     const u4 *Wq;          // storage type, [head][k / 32][column / 16 % 4][lane]
     const u4 *Wk;          // fp16, [head][column / 32][half][k / 32 % 2][lane]
@@ -159,21 +160,21 @@ k_qelq(const QelqArgs a)
         uint16_t *dst = a.elq + elq_frag_index(m / a.x, head * a.x + m % a.x, 32 * pair0 + 8 * q, 0, a.Rs, DM);
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            s8v hi, lo;
+            u4 hi, lo;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 f4 e = Mma<false>::s16(wk[i][h][0], qf[0], f4{0.f, 0.f, 0.f, 0.f});
                 e = Mma<false>::s16(wk[i][h][1], qf[1], e);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    uint16_t vh, vl;
-                    split16<BF>(e[k], vh, vl);
-                    hi[4 * h + k] = vh; lo[4 * h + k] = vl;
+                for (int k = 0; k < 2; ++k) {
+                    unsigned high, low;
+                    split16_pair<BF>(e[2 * k], e[2 * k + 1], high, low);
+                    hi[2 * h + k] = high; lo[2 * h + k] = low;
                 }
             }
             if (m < a.M) {
-                *(s8v *)(dst + i * 1024) = hi;
-                *(s8v *)(dst + i * 1024 + 512) = lo;
+                *(u4 *)(dst + i * 1024) = hi;
+                *(u4 *)(dst + i * 1024 + 512) = lo;
             }
         }
     }
