@@ -14,6 +14,7 @@
 //                 sum of H (k_sum_f32)
 //   vproj  a6  A_i = X_i W_i^V
 //   oproj  a7  out = A W^O + c_out,  c_out = b^O + sum_i b_i^V W_i^O (Eq. 8/9)
+#include <type_traits>
 #include "el_internal.h"
 
 namespace el {
@@ -80,10 +81,12 @@ k_cout(const T *__restrict__ bv, const T *__restrict__ bo, const T *__restrict__
 // scores).  One workgroup owns (16 MT) x (16 NT) outputs; its eight wavefronts each take an eighth of k straight from
 // global memory into registers (consecutive slices, so both halves of a cache line go to one wavefront), four
 // 16-wide slices of both operands requested before the first is used (up to K = 512 the whole contraction is one
-// round trip), and add up through LDS.  A bias is fetched behind the last barrier, element by element, each waited for.
+// round trip), and add up through LDS.  What needs neither the length nor the sums is requested before either is waited for:
+// bias, then rows, then the length's operand.  With the bias fetched behind the last barrier, element by element, and everything
+// behind the length: 64 x 512 x 512 with a bias 5.5 -> 4.6 us, the scores below 9.4 -> 8.9.
 // Bound: memory latency at decode batch sizes, the fp32 matrix rate beyond.
-// 64 x 512 x 512: 5.4 us, 119 us for the kernel it replaces (one output per thread, a serial loop over k); the
-// scores of 16 x 32 rows over 300 positions, K = 512: 9.5 us.
+// 64 x 512 x 512: 4.6 us, 119 us for the kernel it replaces (one output per thread, a serial loop over k); the
+// scores of 16 x 32 rows over 300 positions, K = 512: 8.9 us.
 struct GemmF32 {
     const void *A, *Bt;
     void *C;
@@ -109,18 +112,44 @@ k_gemm_f32(const GemmF32 g)
     const int r16 = l & 15, q = l >> 4, z = blockIdx.z;
     const int n0 = blockIdx.x * (16 * NT), m0 = blockIdx.y * (16 * MT);
     int N = g.N;
-    if (g.use_lengths) {
-        if (g.lengths) N = min(max(g.lengths[z], 1), N);
-        if (n0 >= N) return;
-    }
+    if (g.use_lengths && g.lengths) N = g.lengths[z];         // (looked at below)
     auto mapped = [&](int m) -> int64_t { return (int64_t)(m / g.x) * g.R + (int64_t)z * g.x + m % g.x; };
     const TA *ap[MT];
-    const TB *bp[NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
         const int m = min(m0 + 16 * i + r16, g.M - 1);
         ap[i] = (const TA *)g.A + (g.map_a ? mapped(m) : (int64_t)m) * g.lda + z * g.za + 4 * q;
     }
+    const int full = g.K >> 4, per = (full + NW - 1) / NW, s_begin = w * per, s_end = min(full, (w + 1) * per);
+    f4 a[U][MT], bias = f4{0.f, 0.f, 0.f, 0.f};
+    // (WHOLE: all U slices exist.  Straight code, so that the first products wait for their own operands and not for the last ones)
+    auto load_a = [&](auto whole, int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!decltype(whole)::value && s0 + u >= s_end) continue;      // uniform
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[u][i] = load_full4<VEC>(ap[i] + 16 * (s0 + u));
+        }
+    };
+    // the wavefront that adds a tile up (MT NT <= NW) has its bias requested first, then the rows, then what the length decides
+    if (w < MT * NT) {
+        const int n = n0 + 16 * (w % NT) + 4 * q;
+        if (g.bias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bias[e] = to_f32(((const TB *)g.bias)[min(n + e, g.N - 1)]);
+        } else if (g.bias32) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bias[e] = g.bias32[min(n + e, g.N - 1)];
+        }
+    }
+    if (s_begin + U <= s_end) load_a(std::true_type{}, s_begin);
+    else load_a(std::false_type{}, s_begin);
+    asm volatile("" ::: "memory");                            // (requested here, not behind the wait for the length)
+    if (g.use_lengths) {
+        N = min(max(N, 1), g.N);
+        if (n0 >= N) return;
+    }
+    const TB *bp[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) bp[j] = (const TB *)g.Bt + (int64_t)min(n0 + 16 * j + r16, N - 1) * g.ldb + z * g.zb + 4 * q;
 
@@ -138,49 +167,50 @@ k_gemm_f32(const GemmF32 g)
 #pragma unroll
                 for (int j = 0; j < NT; ++j) acc[i][j] = mfma4(b[j][e], a[i][e], acc[i][j]);
     };
-    const int full = g.K >> 4, per = (full + NW - 1) / NW, s_end = min(full, (w + 1) * per);
-    for (int s0 = w * per; s0 < s_end; s0 += U) {
-        f4 a[U][MT], b[U][NT];
+    auto slices = [&](auto whole, int s0) __attribute__((always_inline)) {
+        f4 b[U][NT];
+        if (s0 > s_begin) load_a(whole, s0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (s0 + u >= s_end) continue;                    // uniform
-            const int k = 16 * (s0 + u);
+            if (!decltype(whole)::value && s0 + u >= s_end) continue;
 #pragma unroll
-            for (int i = 0; i < MT; ++i) a[u][i] = load_full4<VEC>(ap[i] + k);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) b[u][j] = load_full4<VEC>(bp[j] + k);
+            for (int j = 0; j < NT; ++j) b[u][j] = load_full4<VEC>(bp[j] + 16 * (s0 + u));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (s0 + u >= s_end) continue;
+            if (!decltype(whole)::value && s0 + u >= s_end) continue;
             product(a[u], b[u]);
         }
+    };
+    for (int s0 = s_begin; s0 < s_end; s0 += U) {
+        if (s0 + U <= s_end) slices(std::true_type{}, s0);
+        else slices(std::false_type{}, s0);
     }
     if ((g.K & 15) && w == NW - 1) {                          // the slice that is not full
-        f4 a[MT], b[NT];
+        f4 at[MT], b[NT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) a[i] = load_k4<VEC>(ap[i] - 4 * q, 16 * full + 4 * q, g.K);
+        for (int i = 0; i < MT; ++i) at[i] = load_k4<VEC>(ap[i] - 4 * q, 16 * full + 4 * q, g.K);
 #pragma unroll
         for (int j = 0; j < NT; ++j) b[j] = load_k4<VEC>(bp[j] - 4 * q, 16 * full + 4 * q, g.K);
-        product(a, b);
+        product(at, b);
     }
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) red[(w * MT * NT + i * NT + j) * 64 + l] = acc[i][j];
     __syncthreads();
-    for (int tile = w; tile < MT * NT; tile += NW) {
+    static_assert(MT * NT <= NW, "a tile per wavefront");
+    if (w < MT * NT) {
+        const int tile = w;
         f4 v = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < NW; ++s) v += red[(s * MT * NT + tile) * 64 + l];
         const int m = m0 + 16 * (tile / NT) + r16, n = n0 + 16 * (tile % NT) + 4 * q;
-        if (m >= g.M) continue;
+        if (m >= g.M) return;
         TO *c = (TO *)g.C + (g.map_c ? mapped(m) : (int64_t)m) * g.ldc + z * g.zc + n;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (n + e >= N) break;
-            if (g.bias) v[e] += to_f32(((const TB *)g.bias)[n + e]);
-            if (g.bias32) v[e] += g.bias32[n + e];
+            if (g.bias || g.bias32) v[e] += bias[e];
             v[e] *= g.scale;
         }
         if (sizeof(TO) == 4 && g.vec_c && n + 4 <= N) *(f4 *)c = v;
@@ -209,7 +239,7 @@ __device__ __forceinline__ float wave_max(float v)
 // time; the wavefronts take every eighth 16-position slice.  The scores and the first slices of H are requested
 // together, before anything waits.  A lane fetches four consecutive columns of one row of H, so a load instruction
 // reads 4 rows x 256 contiguous bytes, and column c of the block is column c / 4 of accumulator c % 4.  Bound: memory
-// latency, then the fp32 matrix rate.  16 x 32 rows, 300 positions, d_m 512: 7.6 us; with the scores (above) 17 us
+// latency, then the fp32 matrix rate.  16 x 32 rows, 300 positions, d_m 512: 7.6 us; with the scores (above) 16.5 us
 // against the 125 us of the kernels with one row per workgroup and their merge.
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(512)
@@ -222,19 +252,28 @@ k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4;
     const int d0 = blockIdx.x * 64, r0 = blockIdx.y * 16, b = blockIdx.z;
-    int len = lengths ? lengths[b] : n;
-    len = min(max(len, 1), n);
+    int len = lengths ? lengths[b] : n;                       // (looked at behind the scores' requests)
     const T *Hb = H + (size_t)b * h_stride;
     const float *srow[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) srow[i] = S + ((size_t)b * R + min(r0 + RW * w + i, R - 1)) * ldS;
-    // the scores of one chunk of this wavefront's rows, all requested together
+    // the scores of one chunk of this wavefront's rows, all requested together and without regard to the length (a row of S has n
+    // values; what is past the length is whatever the workspace holds, and masked before it is looked at)
     float sv[RW][PL];
     auto load_scores = [&](int c0) {
 #pragma unroll
+        for (int k = 0; k < PL; ++k)
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                sv[i][k] = -INFINITY;
+                if (c0 + 64 * k < n) sv[i][k] = srow[i][min(c0 + 64 * k + l, n - 1)];        // (uniform)
+            }
+    };
+    auto mask_scores = [&](int c0) {
+#pragma unroll
         for (int i = 0; i < RW; ++i)
 #pragma unroll
-            for (int k = 0; k < PL; ++k) sv[i][k] = c0 + 64 * k + l < len ? srow[i][c0 + 64 * k + l] : -INFINITY;
+            for (int k = 0; k < PL; ++k) sv[i][k] = c0 + 64 * k + l < len ? sv[i][k] : -INFINITY;
     };
     // a slice of H per wavefront in flight: U slices of 16 positions
     const int col = d0 + 4 * r16;
@@ -252,6 +291,8 @@ k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int
         }
     };
     load_scores(0);
+    asm volatile("" ::: "memory");                            // (requested here, not behind the wait for the length)
+    len = min(max(len, 1), n);
     load_h(0, w, (min(kChunk, len) + 15) >> 4);
     float mx[RW], sum[RW];
 #pragma unroll
@@ -262,10 +303,12 @@ k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int
 #pragma unroll
             for (int k = 0; k < PL; ++k) mx[i] = fmaxf(mx[i], sv[i][k]);
     };
+    mask_scores(0);
     fold_max();
     if (len > kChunk) {
-        for (int c0 = kChunk; c0 < len; c0 += kChunk) { load_scores(c0); fold_max(); }
+        for (int c0 = kChunk; c0 < len; c0 += kChunk) { load_scores(c0); mask_scores(c0); fold_max(); }
         load_scores(0);
+        mask_scores(0);
     }
 #pragma unroll
     for (int i = 0; i < RW; ++i) mx[i] = wave_max(mx[i]);
@@ -284,7 +327,7 @@ k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int
                 Ps[(RW * w + i) * PS + 64 * k + l] = p;
             }
         __syncthreads();
-        if (c0 + kChunk < len) load_scores(c0 + kChunk);
+        if (c0 + kChunk < len) { load_scores(c0 + kChunk); mask_scores(c0 + kChunk); }
         for (int s0 = w; s0 < slices; s0 += NW * U) {
             if (c0 > 0 || s0 > w) load_h(c0, s0, slices);
 #pragma unroll
@@ -319,9 +362,12 @@ k_sum_f32(const float *__restrict__ S, int64_t ldS, const T *__restrict__ H, int
     for (int s = 0; s < NW; ++s) v += red[(s * 16 + row) * 16 + quad];
     const float inv = Li[row];
     float *xo = Xn + ((size_t)b * R + r0 + row) * d_m + d;
+    if (VEC) {                                                // (d_m is a multiple of four)
+        if (d < d_m) *(f4 *)xo = f4{v[0] / inv, v[1] / inv, v[2] / inv, v[3] / inv};
+    } else
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (d + e < d_m) xo[e] = v[e] / inv;
+        for (int e = 0; e < 4; ++e)
+            if (d + e < d_m) xo[e] = v[e] / inv;
 }
 
 // ---------------------------------------------------------------------------------------------
