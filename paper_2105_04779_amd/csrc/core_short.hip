@@ -16,8 +16,12 @@
 // Kernel times, streaming core -> here, d_m 1024: one sentence of 613 positions, 64 rows (40 workgroups) 10.2 -> 6.6 us; 4 of 205
 // to 410 9.7 -> 7.0; 8 of 512 (256 workgroups) 13.1 -> 9.6; 128 histories of 37, 16 rows, 9.8 -> 6.5.  More pieces take some of it
 // back in the merge (one sentence: ten instead of eight, 5.9 -> 8.1).
+// The tiles' fragments are read while EL-Q arrives and all partial scores of a position before any is added, instead of everything behind
+// one wait and the partials two by two: whole steps of 96 shapes of one to eight spans an element 1.014 times as fast (0.99 to
+// 1.04), one sentence of 613 positions 17.06 -> 16.62 us, twelve layers 243.7 -> 238.3.
 // Bound: memory latency (the table of the cut, then tiles and EL-Q together), then the 64 bytes a clock that a compute unit
 // receives: at d_m 1024 128 KB of tiles and 64 KB of EL-Q.
+#include <type_traits>
 #include <hip/hip_ext.h>
 #include "mfma.h"
 
@@ -105,37 +109,33 @@ k_core_short(const StreamArgs a)
 #pragma unroll
             for (int pl = 0; pl < 2; ++pl) elq[c][pl] = *(const u4 *)(e + chunk32(c) * 2048 + pl * 1024);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // The tiles have landed when only the EL-Q loads, requested last, are under way (requests return in order): the fragments of scores
+    // and weighted sum are read while those arrive, and the products of a chunk of columns wait for its own two planes alone.
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * CHK) : "memory");
 
     // ---- scores, and the column fragments of the weighted sum ----
     const int s_addr = r16 * 128 + ((g ^ swizzle64(r16)) << 4);                        // chunk c of window c / 2; odd c: ^ 64
     const int s_addr2 = 2048 * WIN + r16 * 64 + ((g ^ swizzle32(r16)) << 4);
-    f4 sc[kShortTiles];
-#pragma unroll
-    for (int t = 0; t < kShortTiles; ++t) {
-        if (t >= nt) continue;
-        u4 hb[CHK];
+    // Fragment of columns 16 mb .. of two tiles: lane 16 g + i (i = 4 k + q) reads rows 8 (g & 1) + k (and + 4) of tile 2 u + g / 2,
+    // columns 4 q .. + 3.
+    s4 tb[2][MB][2];
+    const int tr = 8 * (g & 1) + (r16 >> 2), tq = r16 & 3;
+    const int x64 = tr * 128 + (((tq >> 1) ^ swizzle64(tr)) << 4) + (tq & 1) * 8;              // block mb of a window: ^ 32 (mb & 3); row + 4: + 512, ^ 16
+    const int x32 = 2048 * WIN + tr * 64 + (((tq >> 1) ^ swizzle32(tr)) << 4) + (tq & 1) * 8;  // ^ 32 (mb & 1); row + 4: + 256, ^ 16
+    // In straight code for all four tiles or, for one or two, for two: a tile that does not exist is replaced by the last one
+    // (behind branches a product waits for more reads than its own).
+    auto scores = [&](auto count) __attribute__((always_inline)) {
+        constexpr int NTL = decltype(count)::value;
+        u4 hb[NTL][CHK];
 #pragma unroll
         for (int c = 0; c < CHK; ++c)
-            hb[c] = c < 2 * WIN ? *(const EL_LDS(u4) *)(Tw + t * WSL + (s_addr ^ (64 * (c & 1))) + 2048 * (c >> 1)) : *(const EL_LDS(u4) *)(Tw + t * WSL + s_addr2);
-        f4 hi = f4{0.f, 0.f, 0.f, 0.f}, lo = hi;
 #pragma unroll
-        for (int c = 0; c < CHK; ++c) {
-            hi = Mma<BF16>::s16(hb[c], elq[c][0], hi);
-            lo = Mma<BF16>::s16(hb[c], elq[c][1], lo);
-        }
-        sc[t] = hi + lo;
-    }
-    // Fragment of columns 16 mb .. of two tiles: lane 16 g + i (i = 4 k + q) reads rows 8 (g & 1) + k (and + 4) of tile 2 u + g / 2,
-    // columns 4 q .. + 3.  A tile that does not exist is replaced by the last one.
-    s4 tb[2][MB][2];
-    {
-        const int k = r16 >> 2, q = r16 & 3, t = 8 * (g & 1) + k;
-        const int x64 = t * 128 + (((q >> 1) ^ swizzle64(t)) << 4) + (q & 1) * 8;              // block mb of a window: ^ 32 (mb & 3); row + 4: + 512, ^ 16
-        const int x32 = 2048 * WIN + t * 64 + (((q >> 1) ^ swizzle32(t)) << 4) + (q & 1) * 8;  // ^ 32 (mb & 1); row + 4: + 256, ^ 16
+            for (int t = 0; t < NTL; ++t) {
+                const EL_LDS(char) *F = Tw + min(t, nt - 1) * WSL;
+                hb[t][c] = c < 2 * WIN ? *(const EL_LDS(u4) *)(F + (s_addr ^ (64 * (c & 1))) + 2048 * (c >> 1)) : *(const EL_LDS(u4) *)(F + s_addr2);
+            }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (2 * u >= nt) continue;
+        for (int u = 0; u < NTL / 2; ++u) {
             const EL_LDS(char) *F = Tw + min(2 * u + (g >> 1), nt - 1) * WSL;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
@@ -145,20 +145,34 @@ k_core_short(const StreamArgs a)
                 tb[u][mb][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((EL_LDS(s4) *)(F + (lo ^ 16) + at + (mb < 4 * WIN ? 512 : 256)));
             }
         }
-    }
-    // ---- exchange: partial scores where this wavefront's tiles were (read by now); chunk (four positions) c of row r at c ^ r % 16 ----
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        f4 sc[NTL][2];
 #pragma unroll
-    for (int t = 0; t < kShortTiles; ++t) {
-        if (t < nt) *(f4 *)(T + w * (kShortTiles * WSL) + r16 * (kPos * 4) + (((4 * t + g) ^ r16) << 4)) = sc[t];
-    }
+        for (int t = 0; t < NTL; ++t) sc[t][0] = sc[t][1] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < CHK; ++c)
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                for (int t = 0; t < NTL; ++t) sc[t][pl] = Mma<BF16>::s16(hb[t][c], elq[c][pl], sc[t][pl]);
+        // exchange: partial scores where this wavefront's tiles were (read by now); chunk (four positions) c of row r at c ^ r % 16
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < NTL; ++t)
+            *(f4 *)(T + w * (kShortTiles * WSL) + r16 * (kPos * 4) + (((4 * t + g) ^ r16) << 4)) = sc[t][0] + sc[t][1];
+    };
+    if (nt > 2) scores(std::integral_constant<int, 4>{});
+    else scores(std::integral_constant<int, 2>{});
     __syncthreads();
     // ---- softmax: four rows per wavefront, four positions per lane ----
     if (w < ROWS / 4) {
         const int srow = 4 * w + g, c = r16;
-        f4 s = f4{0.f, 0.f, 0.f, 0.f};
+        f4 s = f4{0.f, 0.f, 0.f, 0.f}, part[kWaves];
 #pragma unroll
-        for (int p = 0; p < kWaves; ++p) s += *(const f4 *)(T + p * (kShortTiles * WSL) + srow * (kPos * 4) + ((c ^ srow) << 4));
+        for (int p = 0; p < kWaves; ++p) part[p] = *(const f4 *)(T + p * (kShortTiles * WSL) + srow * (kPos * 4) + ((c ^ srow) << 4));
+        __builtin_amdgcn_sched_barrier(0);           // (left to itself the compiler reads two at a time and waits for them)
+#pragma unroll
+        for (int p = 0; p < kWaves; ++p) s += part[p];
         float mx = kMasked;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

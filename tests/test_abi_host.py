@@ -292,3 +292,24 @@ def test_the_query_kernel_waits_for_nothing_before_all_of_it_is_requested(tmp_pa
         loads = 2 + 1 + slices + 4 * slices + 4 * int(parts)         # lengths, bias, rows, W^Q, W^K
         before = body[:re.search(r"s_waitcnt[^\n]*vmcnt", body).start()]
         assert before.count("global_load") == loads, (d_m, parts, before.count("global_load"))
+
+
+def test_short_core_counts_its_requests(tmp_path):
+    """k_core_short waits for its tiles by count: as many vector loads as EL-Q fragments are requested behind the last tile, nothing
+    else, and the first read of LDS follows that wait."""
+    from paper_2105_04779_amd import build
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    asm = tmp_path / "core_short.s"
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, *flags, "-S", "--cuda-device-only", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                    "-o", str(asm), os.path.join(build.CSRC, "core_short.hip")], check=True, capture_output=True)
+    bodies = re.findall(r"^_ZN2el12k_core_shortILi(\d+)ELb\dE\S*:\s(.*?)\.end_amdhsa_kernel", asm.read_text(), re.S | re.M)
+    assert len(bodies) == 6
+    for d_m, body in bodies:
+        loads = 2 * (int(d_m) // 256)                                # both planes of each 32-column chunk of a wavefront
+        behind = body[body.rindex("global_load_lds_dwordx4"):]
+        wait = re.search(r"s_waitcnt[^\n]*vmcnt\((\d+)\)", behind)
+        assert int(wait.group(1)) == loads, (d_m, wait.group(0))
+        before = behind[1:wait.start()]                              # (without the request itself)
+        assert len(re.findall(r"^\s*(?:global|buffer|flat|scratch)_(?:load|store)", before, re.M)) == loads, d_m
+        assert "ds_read" not in before
