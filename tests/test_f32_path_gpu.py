@@ -53,6 +53,31 @@ def test_fp32_arithmetic_path(dtype, B, beam, heads, d_m, d_k, n, lens):
     layer.close()
 
 
+@pytest.mark.parametrize("beam,heads,d_m", [(2, 4, 64), (8, 4, 64), (16, 4, 64), (3, 2, 128), (12, 2, 128)])
+def test_one_launch_positions_dealt_to_wavefronts(beam, heads, d_m):
+    """The weighted sum of the one-launch step: one, two, four or eight wavefronts with positions of a tile (fewer than there are for
+    it, and a number that is no power of two), and a second and third round of positions; with biases and without."""
+    wide = 2 * beam * heads <= 32
+    n = 128 if not wide else 300 if d_m == 64 else 256
+    lens = [16, 17, 47, 81, 128, n]
+    w = wl.custom(f"one_launch_{heads}x{beam}_{d_m}", dtype="f32", B=len(lens), beam=beam, heads=heads, d_m=d_m, d_k=d_m // heads, n=n, index=92)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.asarray(lens, dtype=np.int32)
+    for biased in (True, False):
+        if not biased:
+            W = {k: v if k[0] == "W" else np.zeros_like(v) for k, v in W.items()}
+        ref = oracle_out(w, W, H, Q, L)
+        Hp = H.copy()
+        for b in range(len(lens)):
+            Hp[b, L[b]:] = np.nan
+        layer = make_layer(w, W if biased else {k: v for k, v in W.items() if k[0] == "W"})
+        err = rel_err(gpu_out(layer, w, Hp, Q, L), ref)
+        record(f"{w.name}: biased={biased} err={err:.3e}")
+        assert err <= TOL["f32"]
+        layer.close()
+
+
 @pytest.mark.parametrize("d_m,heads", [(64, 4), (320, 5)])
 def test_operands_aligned_to_one_element(d_m, heads):
     """H, queries and out one element past a 16-byte boundary, H with a batch stride that is no multiple of four."""
