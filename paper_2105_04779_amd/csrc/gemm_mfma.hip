@@ -221,8 +221,8 @@ __device__ __forceinline__ float over_row(float v, int rs)
     return v;
 }
 
-// SEG: the segment form.  What its log-sum-exp needs but Qp and b^K (fetched after the merge), the merge has in registers,
-// and the head outputs leave as the fp32 sums they are (b^V fetched between their stores, one element at a time); as a
+// SEG: the segment form.  What its log-sum-exp needs but Qp and b^K, the merge has in registers, and the head outputs leave as
+// the fp32 sums they are, with b^V.  As a
 // kernel of its own that read them back, with one thread per head for the statistics, this took 8.8 us at 128 rows.
 // LOOP: several row tiles of 16 per workgroup, as a kernel of its own: together with the single tile's code the widest form spills.
 template <int DM, int NT, bool SEG, bool LOOP>
@@ -284,6 +284,20 @@ k_vproj(const VprojArgs a)
 #pragma unroll
             for (int s = 0; s < KS; ++s) xv[i][s] = *(const u4 *)(x0 + (size_t)step[i] * DM + 512 * s);
     };
+    // segment form: b^V of the columns that this wavefront adds up, and for the log-sum-exp the row's projected query and b^K; requested
+    // ahead of the tile's pieces (several tiles: Qp and b^K where they are used, registers are short there)
+    f4 bv = f4{0.f, 0.f, 0.f, 0.f}, bk[4];
+    u4 qp[2];
+    auto load_seg = [&](int tile) __attribute__((always_inline)) {
+        const int m = min((tile << rs) + trow, a.M - 1);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) qp[k] = *(const u4 *)(a.Qp + (size_t)m * DM + head * 64 + 16 * q + 8 * k);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bk[k] = *(const f4 *)(a.bk32 + head * 64 + 16 * q + 4 * k);
+    };
+    if (SEG && w < NT) bv = *(const f4 *)(a.bv32 + head * 64 + 16 * (nb * NT + w) + 4 * q);
+    if (SEG && !LOOP && nb == 0 && w == 7) load_seg(pl.group);
+    if (SEG) asm volatile("" ::: "memory");              // (here, and not where they are used)
     f4 acc[NT];
     float m_run, den;
     auto fold = [&](auto count, int k0) __attribute__((always_inline)) {
@@ -364,11 +378,10 @@ k_vproj(const VprojArgs a)
         }
         if (SEG && nb == 0 && w == 7) {                  // (a wavefront that adds nothing up below)
             const int m = min((tile << rs) + trow, a.M - 1);
-            const f16_t *qp = a.Qp + (size_t)m * DM + head * 64 + 16 * q;
-            const float *bk = a.bk32 + head * 64 + 16 * q;
+            if (LOOP) load_seg(tile);
             float c = 0.f;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) c = fmaf((float)qp[k], bk[k], c);
+            for (int k = 0; k < 16; ++k) c = fmaf((float)__builtin_bit_cast(h8, qp[k >> 3])[k & 7], bk[k >> 2][k & 3], c);
             c += __shfl_xor(c, 16, 64);
             c += __shfl_xor(c, 32, 64);
             if (q == 0 && piece == 0 && (tile << rs) + trow < a.M)
@@ -387,7 +400,7 @@ k_vproj(const VprojArgs a)
                 float *o = a.seg_A + (size_t)mm * DM + col;                    // (the caller's: aligned to 4 bytes)
                 if (mm < a.M)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = sum[e] + a.bv32[col + e];
+                    for (int e = 0; e < 4; ++e) o[e] = sum[e] + bv[e];
             } else if (mm < a.M)
                 *(h4 *)(a.A + frag16_index(mm, head * 64 + 16 * (nb * NT + w) + 4 * q, DM)) =
                     h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};

@@ -692,7 +692,7 @@ hipError_t launch_seg_finish(const SegFinishArgs &a, int rows, hipStream_t s)
 
 // One softmax over the union of the segments' keys, per (row, head):
 //   w_s = exp(lse_s - max_s' lse_s') / sum_s' exp(lse_s' - max),   A = sum_s w_s seg_A_s      (then a7 on A)
-// Bound: memory latency; the statistics are one round trip, then the segments' outputs one each, behind their branches.
+// Bound: memory latency, one round trip for the statistics and the outputs of all segments.
 template <typename TO>
 __global__ void k_seg_merge(const SegMergeArgs a)
 {
@@ -700,18 +700,21 @@ __global__ void k_seg_merge(const SegMergeArgs a)
     const int m = blockIdx.y;
     if (cg >= a.hd) return;
     const int i = cg / a.d_k;
-    float ls[kMaxSegments], M = -INFINITY;
+    float ls[kMaxSegments], x[kMaxSegments], M = -INFINITY;
+    // (all requested before any is waited for)
 #pragma unroll
     for (int s = 0; s < kMaxSegments; ++s) {
-        ls[s] = s < a.nseg ? a.lse[s][(size_t)m * a.heads + i] : -INFINITY;
-        M = fmaxf(M, ls[s]);
+        ls[s] = -INFINITY; x[s] = 0.f;
+        if (s < a.nseg) { ls[s] = a.lse[s][(size_t)m * a.heads + i]; x[s] = a.A[s][(size_t)m * a.hd + cg]; }
     }
+#pragma unroll
+    for (int s = 0; s < kMaxSegments; ++s) M = fmaxf(M, ls[s]);
     float num = 0.f, den = 0.f;
 #pragma unroll
     for (int s = 0; s < kMaxSegments; ++s) {
         if (s < a.nseg && ls[s] > -INFINITY) {
             const float w = expf(ls[s] - M);
-            num = fmaf(w, a.A[s][(size_t)m * a.hd + cg], num);
+            num = fmaf(w, x[s], num);
             den += w;
         }
     }
