@@ -242,6 +242,9 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
  * rows, about twice or three times where all of them are that short; beyond 13 spans an element at most 3/4 compute_units
  * spans besides) run on a core of their own, which takes a whole span of at most 64 positions at once: row blocks
  * of 16, and as many spans as elements of n positions need (elements that are shorter leave some of them empty).
+ * Steps just beyond those run on wide workgroups of that core, 128 positions at d_model 512, 96 at 768 and 64 at 1024
+ * with rows in blocks of 32, while these fill the device at most once; this function and el_attn_plan_short_core
+ * describe the choice without them.
  * Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or 1024: no MFMA
  * core).
  */

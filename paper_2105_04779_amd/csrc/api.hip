@@ -393,7 +393,7 @@ static el_status preview(int32_t max_batch, int32_t B, int32_t beam, int32_t hea
     std::memset(&p, 0, sizeof(p));
     p.B = B; p.beam = beam; p.n = n; p.heads = heads; p.d_m = d_model; p.R = heads * beam;
     const int64_t slots = (int64_t)max_batch * kMaxParts;
-    *pl = plan_core_mfma(p, 0, 0, compute_units, slots < INT32_MAX ? (int)slots : INT32_MAX);
+    *pl = plan_core_mfma(p, 0, 0, compute_units, slots < INT32_MAX ? (int)slots : INT32_MAX, false);
     return EL_OK;
 }
 

@@ -171,10 +171,49 @@ static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CoreP
     pl.G = (int)spans; pl.short_tiles = kShortTiles;
 }
 
-CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)
+// The same core with workgroups of twice the work or more: what fills a compute unit's LDS (eight tiles at d_m 512, six at 768,
+// four at 1024) and, beyond 16 rows, 32 of them, where all of those run at once and the smaller ones would not.  Half the pieces and
+// half the expanded queries to receive or less, against a longer way through each workgroup.  Whole steps in bf16, the streaming core
+// against this one, a half to the whole of a round (us):
+//   d_m 512    8 rows, 32 of 768 to 1024 positions 21.0 / 19.4, 25 of them 20.4 / 17.4    32 rows, 64 of 256 to 512 23.3 / 23.5 (fp16 23.4 / 22.9),
+//              25 of 768 to 1024 23.5 / 21.0    40 rows, 30 of 384 to 512 24.2 / 20.9    64 rows, 30 of 300 to 500 25.4 / 22.3
+//   d_m 768    12 rows, 60 of 285 to 380 24.0 / 22.4    24 rows, 42 of 427 to 570 27.7 / 26.0    48 rows, 18 of them 25.5 / 22.7    60 rows, 40 of 200 to
+//              280 32.0 / 26.7    72 rows, 20 of 285 to 380 28.9 / 25.1
+//   d_m 1024   32 rows, 64 of 144 to 192 29.4 / 27.1    64 rows, 31 of 192 to 256 29.8 / 27.6, 15 of 384 to 512 28.7 / 27.4    96 rows, 20 of 192 to
+//              256 30.0 / 27.0    128 rows, 15 of them 30.9 / 26.9
+// Beyond one round it loses, also where the second is nearly empty (d_m 768, 48 rows, 40 of 200 to 300 27.8 / 31.5; 12 rows, 160 of 211
+// 30.6 / 31.1).  Inside it does so where one row block and many spans of an element have nearly every compute unit read positions of
+// its own and leave the merge as many pieces: d_m 1024, 32 rows, 20 of 400 to 700 25.0 / 27.4, 42 of 288 to 384 28.5 / 28.9, but 30 of
+// them (180 spans) 26.7 / 25.8 and 60 of 192 to 256 (four spans each) 29.7 / 28.9; d_m 768, 12 rows, 20 of 750 to 1000 (eleven) 22.2 / 22.5, 25 of
+// 675 to 900 (ten) 23.8 / 23.1.
+// A second round of the smaller workgroups (elements of one span) gives way to one of these at d_m 768 (100 of 64, 48 rows, 30.3 / 28.8;
+// 128 of 16, 60 rows, 29.8 / 29.6), and at 1024 where 32-row blocks pad no further than 16-row ones (64 rows, 128 of 64 38.1 / 37.1, but 48
+// rows 34.3 / 34.8); at 512 two of the smaller ones share a compute unit (200 of 64, 32 rows, 26.1 / 28.2).
+static void plan_wide_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
+{
+    if (p.B > kScanMax) return;
+    const int tiles = p.d_m == 512 ? 8 : p.d_m == 768 ? 6 : 4, rg = p.R > 16 ? 2 : 1;
+    if (tiles == kShortTiles && rg == 1) return;                         // (nothing wider)
+    const int per_element = (p.n + 16 * tiles - 1) / (16 * tiles), blocks = (p.R + 16 * rg - 1) / (16 * rg);
+    const long spans = (long)p.B * per_element;
+    if (spans > kSpanMax || spans > max_slots || spans * blocks > num_cus || per_element > 13) return;
+    if (blocks == 1 && p.d_m == 1024 && per_element > 4 && 4 * spans > 3L * num_cus) return;
+    if (rg == 1 && p.d_m == 768 && per_element > 10) return;
+    if (pl.short_tiles) {
+        if ((long)pl.G * pl.nblocks <= num_cus || p.d_m == 512) return;
+        if (p.d_m == 1024 && 2 * blocks != pl.nblocks) return;
+    }
+    pl.nrg = pl.block_groups = rg; pl.nblocks = blocks; pl.Rs = blocks * 16 * rg;
+    pl.G = (int)spans; pl.short_tiles = tiles;
+}
+
+CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots, bool wide)
 {
     CorePlan pl = plan_stream(p, splits_override, nrg_override, num_cus, max_slots);
-    if (!splits_override && !nrg_override) plan_short_spans(p, num_cus, max_slots, pl);
+    if (!splits_override && !nrg_override) {
+        plan_short_spans(p, num_cus, max_slots, pl);
+        if (wide) plan_wide_spans(p, num_cus, max_slots, pl);
+    }
     return pl;
 }
 
@@ -236,7 +275,7 @@ hipError_t launch_core_mfma(const el_attn_ctx *ctx, const Problem &p, const Work
     // kernel: 1 GB of per-beam histories 216 -> 184 us; 640 MB shared by two row blocks 149 -> 144 us).  Below
     // that it costs: the second row block of a span then misses what the first one fetched (128 MB: 42.7 -> 44.6 us).
     a.stream_hint = (double)p.B * p.n * p.d_m * 2.0 >= 256.0 * 1024 * 1024 ? 1 : 0;
-    if (pl.short_tiles) return launch_core_short(a, p.d_m, p.dtype == EL_BF16, s, ev0, ev1);
+    if (pl.short_tiles) return launch_core_short(a, p.d_m, p.dtype == EL_BF16, pl.short_tiles, pl.nrg, s, ev0, ev1);
     return launch_core_stream(a, p.d_m, p.dtype == EL_BF16, pl.nrg, s, ev0, ev1);
 }
 

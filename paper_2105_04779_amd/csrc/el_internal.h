@@ -99,7 +99,7 @@ constexpr int kMaxPartsGeneric = 8; // key-range partials (fp32) of the generic 
 constexpr int kGenericMaxDm = 8192; // widest d_model the generic core kernel covers
 constexpr int kScanMax = 1024;      // most batch elements whose tiles the streaming core cuts as one list
 constexpr int kSpanMax = 1024;      // most spans of that list
-constexpr int kShortTiles = 4;      // tiles that a workgroup of the core of short spans holds in LDS
+constexpr int kShortTiles = 4;      // tiles that a workgroup of the core of short spans holds in LDS (its wide ones: up to 8, see plan_wide_spans)
 
 // Where the partial results ("pieces") of batch element b live: `np` consecutive slots from `slot0` in the partial
 // buffers Xp [slot, Rs, d_m] and ML [slot, Rs, 2].  Generic core: every element has `parts` of them.  MFMA core: looked
@@ -262,11 +262,12 @@ inline dim3 core_grid(const StreamArgs &a)
     if (a.next_w[0] && (int)grid.x + 64 <= a.num_cus) grid.x += 64;
     return grid;
 }
-hipError_t launch_core_short(const StreamArgs &a, int d_m, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);   // core_short.hip
+hipError_t launch_core_short(const StreamArgs &a, int d_m, bool bf16, int tiles, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);   // core_short.hip
 hipError_t launch_core_stream(const StreamArgs &a, int d_m, bool bf16, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 bool core_mfma_supported(int dtype, int d_m);
 // what a step launches: the streaming core or, where neither override is set and it is the faster one, the core of short spans
-CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots);
+// (wide: the wide workgroups of the core of short spans are allowed; the previews show the plan without)
+CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots, bool wide = true);
 CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws);
 PieceMap piece_map(const Workspace &ws);
 hipError_t launch_cut(const CutArgs &c, hipStream_t s);      // the cut on its own, for a core that k_qelq does not precede

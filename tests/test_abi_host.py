@@ -303,13 +303,13 @@ def test_short_core_counts_its_requests(tmp_path):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     subprocess.run([hipcc, *flags, "-S", "--cuda-device-only", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
                     "-o", str(asm), os.path.join(build.CSRC, "core_short.hip")], check=True, capture_output=True)
-    bodies = re.findall(r"^_ZN2el12k_core_shortILi(\d+)ELb\dE\S*:\s(.*?)\.end_amdhsa_kernel", asm.read_text(), re.S | re.M)
-    assert len(bodies) == 6
-    for d_m, body in bodies:
-        loads = 2 * (int(d_m) // 256)                                # both planes of each 32-column chunk of a wavefront
-        behind = body[body.rindex("global_load_lds_dwordx4"):]
-        wait = re.search(r"s_waitcnt[^\n]*vmcnt\((\d+)\)", behind)
-        assert int(wait.group(1)) == loads, (d_m, wait.group(0))
-        before = behind[1:wait.start()]                              # (without the request itself)
-        assert len(re.findall(r"^\s*(?:global|buffer|flat|scratch)_(?:load|store)", before, re.M)) == loads, d_m
-        assert "ds_read" not in before
+    bodies = re.findall(r"^_ZN2el12k_core_shortILi(\d+)ELb\dELi\dELi(\d)E\S*:\s(.*?)\.end_amdhsa_kernel", asm.read_text(), re.S | re.M)
+    assert len(bodies) == 16
+    for d_m, blocks, body in bodies:
+        loads = 2 * (int(d_m) // 256) * int(blocks)                  # both planes of each 32-column chunk of a wavefront, per 16 rows
+        # the wait is written out (the compiler's own have no marks around them); the block that it ends starts behind the last tile
+        wait = re.search(r"ASMSTART\s+s_waitcnt vmcnt\((\d+)\)", body)
+        assert int(wait.group(1)) == loads, (d_m, blocks, wait.group(0))
+        block = re.split(r"^\.LBB\S+:", body[:wait.start()], flags=re.M)[-1].rsplit("global_load_lds_dwordx4", 1)[-1]
+        assert len(re.findall(r"^\s*(?:global|buffer|flat|scratch)_(?:load|store)", block, re.M)) == loads, (d_m, blocks)
+        assert "ds_read" not in body[:wait.start()]

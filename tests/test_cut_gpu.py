@@ -218,3 +218,55 @@ def test_short_spans(dtype, B, beam, heads, d_m, n, lens):
     assert err <= TOL[dtype]
     for a, b in zip(*outs):
         assert rel_err(a, b) <= 2 * TOL[dtype]
+
+
+WIDE = [
+    # dtype, B, beam, heads, d_m, n, lens: more than 256 workgroups of 64 positions and 16 rows, at most 256 of 128 (d_m 512) or 96
+    # (d_m 768) positions and, beyond 16 rows, of 32
+    ("f16", 100, 1, 8, 512, 256, "mixed"),                          # 8 rows, spans of one to eight tiles
+    ("bf16", 70, 4, 8, 512, 250, "mixed"),                          # 32 rows
+    ("f16", 60, 3, 8, 512, 300, "mixed"),                           # 24 rows: half a row group of padding
+    ("bf16", 50, 5, 8, 512, 129, [129, 128, 113, 64, 65, 1, 80, 16, 17, 97] * 5),   # 40 rows: two blocks; spans of one position
+    ("bf16", 100, 1, 12, 768, 190, "mixed"),                        # 12 rows, spans of one to six tiles
+    ("f16", 60, 2, 12, 768, 290, "mixed"),                          # 24 rows
+    ("bf16", 30, 5, 12, 768, 300, [300, 97, 96, 95, 64, 65, 1, 33, 193, 16] * 3),   # 60 rows: two blocks, the second of 28
+    ("f16", 120, 3, 12, 768, 96, None),                             # 36 rows, one span each, no lengths
+    ("bf16", 100, 5, 12, 768, 64, "mixed"),                         # instead of a second round of the small workgroups
+    ("bf16", 31, 4, 16, 1024, 250, "mixed"),                        # 64 rows: two blocks of 32, four tiles
+    ("f16", 70, 2, 16, 1024, 129, "mixed"),                         # 32 rows
+    ("bf16", 24, 5, 16, 1024, 150, [150, 1, 64, 65, 80, 129] * 4),  # 80 rows: the last block half empty
+]
+
+
+@pytest.mark.parametrize("dtype,B,beam,heads,d_m,n,lens", WIDE)
+def test_wide_short_spans(dtype, B, beam, heads, d_m, n, lens):
+    """The wide workgroups of the core of short spans against the oracle and against the streaming core on the same call, twice
+    with the same bits."""
+    positions, rows = {512: 128, 768: 96, 1024: 64}[d_m], heads * beam
+    block = 32 if rows > 16 else 16
+    units = compute_units()
+    assert B * -(-n // 64) * -(-rows // 16) > units >= B * -(-n // positions) * -(-rows // block)
+    w = wl.custom(f"wide_{dtype}_{B}x{beam}_{d_m}_{n}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=64, n=n, index=103)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.full(B, n, dtype=np.int32) if lens is None else np.asarray([1 + (b * 13) % n for b in range(B)] if isinstance(lens, str) else lens, dtype=np.int32)
+    ref = oracle_out(w, W, H, Q, L)
+    far = np.full((B, n + 3, d_m), np.nan, dtype=np.float32)
+    for b in range(B):
+        far[b, :L[b]] = H[b, :L[b]]
+    Hd, Qd = to_device(far, dtype)[:, :n], to_device(Q, dtype)
+    Ld = None if lens is None else torch.from_numpy(L).cuda()
+    outs = []
+    for groups in (0, 1):
+        layer = make_layer(w, W)
+        layer.set_row_groups(groups)
+        y = layer.decode_step(Hd, Ld, Qd)
+        assert torch.equal(y, layer.decode_step(Hd, Ld, Qd))
+        A, lse = layer.decode_segment(Hd, Ld, Qd)
+        outs.append((y.float().cpu().numpy(), A.cpu().numpy(), lse.cpu().numpy()))
+        layer.close()
+    err = rel_err(outs[0][0], ref)
+    record(f"{w.name}: err={err:.3e} streaming core {rel_err(outs[1][0], ref):.3e}")
+    assert err <= TOL[dtype]
+    for a, b in zip(*outs):
+        assert rel_err(a, b) <= 2 * TOL[dtype]
