@@ -88,6 +88,8 @@ constexpr int kBoundaryCost = 4;
 // 24 to 128 rows 169 gain, up to 15 %, and 85 lose, up to 9 %: the 16-row workgroups of many elements fill the chip, so that their spans
 // cross elements more often, and rows that fill blocks of 32 evenly have nothing to gain from blocks of 16: d_m 768, 96 rows, 24 of
 // 150 to 300 29.3 / 32.1; 24 rows, 64 of 200 25.4 / 27.6; d_m 512, 32 rows, 48 of 512 23.6 / 24.9.
+// The wide workgroups of the core of short spans (plan_wide_spans) have since taken most of these; what still meets this line is
+// d_m 1024 between one round of those and 12 tiles, and shapes that miss their round by the padding of a last span.
 constexpr int kHalfBlockTiles = 12;
 
 static CorePlan plan_stream(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots)
