@@ -81,12 +81,19 @@ k_cout(const T *__restrict__ bv, const T *__restrict__ bo, const T *__restrict__
 // scores).  One workgroup owns (16 MT) x (16 NT) outputs; its eight wavefronts each take an eighth of k straight from
 // global memory into registers (consecutive slices, so both halves of a cache line go to one wavefront), four
 // 16-wide slices of both operands requested before the first is used (up to K = 512 the whole contraction is one
-// round trip), and add up through LDS.  What needs neither the length nor the sums is requested before either is waited for:
-// bias, then rows, then the length's operand.  With the bias fetched behind the last barrier, element by element, and everything
-// behind the length: 64 x 512 x 512 with a bias 5.5 -> 4.6 us, the scores below 9.4 -> 8.9.
+// round trip), and add up through LDS.
 // Bound: memory latency at decode batch sizes, the fp32 matrix rate beyond.
 // 64 x 512 x 512: 4.6 us, 119 us for the kernel it replaces (one output per thread, a serial loop over k); the
 // scores of 16 x 32 rows over 300 positions, K = 512: 8.9 us.
+// Three forms (launch_gemm_f32 has the rule):
+//   early     what needs neither the length nor the sums is requested before either is waited for: bias, then rows, then the length's
+//             operand; groups of four slices in straight code, so that the first products wait for their own operands and not for the
+//             last ones.  With the bias fetched behind the last barrier, element by element, and everything behind the length: 64 x
+//             512 x 512 with a bias 5.5 -> 4.6 us, the scores above 9.4 -> 8.9.  Rows held across the wait for the length take 66
+//             registers instead of 49 (16 x 16 outputs), 104 instead of 68 (32 x 16): a workgroup less on a compute unit.
+//   straight  the groups in straight code, everything behind the length
+//   branched  every slice behind its own branch, the bias behind the last products: the fewest instructions
+enum GemmForm { kGemmEarly, kGemmStraight, kGemmBranched };
 struct GemmF32 {
     const void *A, *Bt;
     void *C;
@@ -102,17 +109,23 @@ struct GemmF32 {
     int use_lengths, vec_c;
 };
 
-template <typename TA, typename TB, typename TO, bool VEC, int MT, int NT>
+template <typename TA, typename TB, typename TO, bool VEC, int MT, int NT, GemmForm FORM>
 __global__ void __launch_bounds__(64 * kGemmWaves)
 k_gemm_f32(const GemmF32 g)
 {
     constexpr int NW = kGemmWaves, U = 4;
+    constexpr bool EARLY = FORM == kGemmEarly;
     __shared__ f4 red[NW * MT * NT * 64];
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = l & 15, q = l >> 4, z = blockIdx.z;
     const int n0 = blockIdx.x * (16 * NT), m0 = blockIdx.y * (16 * MT);
     int N = g.N;
-    if (g.use_lengths && g.lengths) N = g.lengths[z];         // (looked at below)
+    if (EARLY) {
+        if (g.use_lengths && g.lengths) N = g.lengths[z];     // (looked at below)
+    } else if (g.use_lengths) {
+        if (g.lengths) N = min(max(g.lengths[z], 1), N);
+        if (n0 >= N) return;
+    }
     auto mapped = [&](int m) -> int64_t { return (int64_t)(m / g.x) * g.R + (int64_t)z * g.x + m % g.x; };
     const TA *ap[MT];
 #pragma unroll
@@ -121,18 +134,18 @@ k_gemm_f32(const GemmF32 g)
         ap[i] = (const TA *)g.A + (g.map_a ? mapped(m) : (int64_t)m) * g.lda + z * g.za + 4 * q;
     }
     const int full = g.K >> 4, per = (full + NW - 1) / NW, s_begin = w * per, s_end = min(full, (w + 1) * per);
-    f4 a[U][MT], bias = f4{0.f, 0.f, 0.f, 0.f};
-    // (WHOLE: all U slices exist.  Straight code, so that the first products wait for their own operands and not for the last ones)
-    auto load_a = [&](auto whole, int s0) __attribute__((always_inline)) {
+    f4 first[U][MT], bias = f4{0.f, 0.f, 0.f, 0.f};
+    // (WHOLE: all U slices of the group exist)
+    auto load_first = [&](auto whole, int s0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (!decltype(whole)::value && s0 + u >= s_end) continue;      // uniform
 #pragma unroll
-            for (int i = 0; i < MT; ++i) a[u][i] = load_full4<VEC>(ap[i] + 16 * (s0 + u));
+            for (int i = 0; i < MT; ++i) first[u][i] = load_full4<VEC>(ap[i] + 16 * (s0 + u));
         }
     };
-    // the wavefront that adds a tile up (MT NT <= NW) has its bias requested first, then the rows, then what the length decides
-    if (w < MT * NT) {
+    // (the bias in two places, written out: as a lambda it has the compiler fetch the arguments one by one, each waited for)
+    if (EARLY && w < MT * NT) {                                    // the wavefront that adds a tile up
         const int n = n0 + 16 * (w % NT) + 4 * q;
         if (g.bias) {
 #pragma unroll
@@ -142,12 +155,14 @@ k_gemm_f32(const GemmF32 g)
             for (int e = 0; e < 4; ++e) bias[e] = g.bias32[min(n + e, g.N - 1)];
         }
     }
-    if (s_begin + U <= s_end) load_a(std::true_type{}, s_begin);
-    else load_a(std::false_type{}, s_begin);
-    asm volatile("" ::: "memory");                            // (requested here, not behind the wait for the length)
-    if (g.use_lengths) {
-        N = min(max(N, 1), g.N);
-        if (n0 >= N) return;
+    if (EARLY) {
+        if (s_begin + U <= s_end) load_first(std::true_type{}, s_begin);
+        else load_first(std::false_type{}, s_begin);
+        asm volatile("" ::: "memory");                        // (requested here, not behind the wait for the length)
+        if (g.use_lengths) {
+            N = min(max(N, 1), g.N);
+            if (n0 >= N) return;
+        }
     }
     const TB *bp[NT];
 #pragma unroll
@@ -167,24 +182,53 @@ k_gemm_f32(const GemmF32 g)
 #pragma unroll
                 for (int j = 0; j < NT; ++j) acc[i][j] = mfma4(b[j][e], a[i][e], acc[i][j]);
     };
-    auto slices = [&](auto whole, int s0) __attribute__((always_inline)) {
-        f4 b[U][NT];
-        if (s0 > s_begin) load_a(whole, s0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!decltype(whole)::value && s0 + u >= s_end) continue;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) b[u][j] = load_full4<VEC>(bp[j] + 16 * (s0 + u));
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!decltype(whole)::value && s0 + u >= s_end) continue;
-            product(a[u], b[u]);
-        }
+    // Where in the instruction stream a group starts: 16 bytes past a multiple of 32.  At a multiple of 32, which is where it may land with
+    // whatever comes before it, 32 x 32 outputs take 1.09 times as long (K = 512, 512 rows of 512: 13.4 against 12.2 us).
+    auto place = [&]() __attribute__((always_inline)) {
+        if (MT > 1) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     };
-    for (int s0 = s_begin; s0 < s_end; s0 += U) {
-        if (s0 + U <= s_end) slices(std::true_type{}, s0);
-        else slices(std::false_type{}, s0);
+    if constexpr (FORM == kGemmBranched) {
+        for (int s0 = s_begin; s0 < s_end; s0 += U) {
+            f4 a[U][MT], b[U][NT];
+            place();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (s0 + u >= s_end) continue;                // uniform
+#pragma unroll
+                for (int i = 0; i < MT; ++i) a[u][i] = load_full4<VEC>(ap[i] + 16 * (s0 + u));
+#pragma unroll
+                for (int j = 0; j < NT; ++j) b[u][j] = load_full4<VEC>(bp[j] + 16 * (s0 + u));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (s0 + u >= s_end) continue;
+                product(a[u], b[u]);
+            }
+        }
+    } else {
+        auto group = [&](auto whole, int s0) __attribute__((always_inline)) {
+            f4 a[U][MT], b[U][NT];
+            if (!EARLY) place();
+            else if (s0 > s_begin) load_first(whole, s0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (!decltype(whole)::value && s0 + u >= s_end) continue;
+                if (!EARLY)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) a[u][i] = load_full4<VEC>(ap[i] + 16 * (s0 + u));
+#pragma unroll
+                for (int j = 0; j < NT; ++j) b[u][j] = load_full4<VEC>(bp[j] + 16 * (s0 + u));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (!decltype(whole)::value && s0 + u >= s_end) continue;
+                product(EARLY ? first[u] : a[u], b[u]);
+            }
+        };
+        for (int s0 = s_begin; s0 < s_end; s0 += U) {
+            if (s0 + U <= s_end) group(std::true_type{}, s0);
+            else group(std::false_type{}, s0);
+        }
     }
     if ((g.K & 15) && w == NW - 1) {                          // the slice that is not full
         f4 at[MT], b[NT];
@@ -193,6 +237,16 @@ k_gemm_f32(const GemmF32 g)
 #pragma unroll
         for (int j = 0; j < NT; ++j) b[j] = load_k4<VEC>(bp[j] - 4 * q, 16 * full + 4 * q, g.K);
         product(at, b);
+    }
+    if (!EARLY && w < MT * NT) {
+        const int n = n0 + 16 * (w % NT) + 4 * q;
+        if (g.bias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bias[e] = to_f32(((const TB *)g.bias)[min(n + e, g.N - 1)]);
+        } else if (g.bias32) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bias[e] = g.bias32[min(n + e, g.N - 1)];
+        }
     }
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -499,6 +553,13 @@ hipError_t launch_cout(const el_attn_ctx *ctx, const void *WoT, const void *bv, 
 
 // 32 x 32 outputs per workgroup where that still leaves two workgroups per compute unit of a full chip, 32 x 16
 // where it leaves one (less operand traffic); 16 x 16 below, where workgroups are what is missing.
+// Early where all workgroups run at once and a little beyond (16 x 16 outputs: three on a compute unit; 32 x 16: two), so that nothing
+// else hides the wait; straight for operands fetched four at a time and K >= 512, where a group is whole; branched for the rest.  Times of the products of 520 calls
+// of d_m 256 to 1024 in proportion to the form with everything behind the length and the bias behind the last barrier, early / straight / branched:
+//   16 x 16           to 512 workgroups 0.91 / 0.95 / 0.96    640 0.93 / 0.98 / 0.98    896 0.92 / 0.99 / 0.99    1024 1.04 / 0.98 / 0.98    4096 1.10 / 1.01 / 1.01
+//   32 x 16, K < 512  256 0.91 / 0.96 / 0.95    512 0.95 / 0.95 / 0.94    640 1.20 / 0.96 / 0.96    K >= 512  256 0.93 / 0.88 / 0.96    512 0.93 / 0.90 / 1.03    768 1.18 / 0.94 / 1.04
+//   32 x 32, K < 512  512 0.97 / 0.95 / 0.93    1024 1.04 / 0.98 / 0.98    4096 1.15 / 1.00 / 0.98       K >= 512  512 0.86 / 0.84 / 0.91    1024 0.84 / 0.82 / 0.90    4096 0.87 / 0.81 / 0.89
+// (unaligned operands, 32 x 32, scores: 1.05 / 1.09 / 0.99).
 template <typename TA, typename TB, typename TO>
 static hipError_t launch_gemm_f32(const GemmF32 &g, int batches, hipStream_t s)
 {
@@ -508,10 +569,17 @@ static hipError_t launch_gemm_f32(const GemmF32 &g, int batches, hipStream_t s)
     const int tm = g.M > 16 && (long)cdiv(g.N, 16) * cdiv(g.M, 32) * batches >= 256 ? 2 : 1;
     const int tn = tm == 2 && (long)cdiv(g.N, 32) * cdiv(g.M, 32) * batches >= 512 ? 2 : 1;
     const dim3 grid(cdiv(g.N, 16 * tn), cdiv(g.M, 16 * tm), batches), block(64 * kGemmWaves);
-#define EL_GEMM_F32(V, MT, NT) hipLaunchKernelGGL((k_gemm_f32<TA, TB, TO, V, MT, NT>), grid, block, 0, s, g)
-    if (tn == 2) { if (vec) EL_GEMM_F32(true, 2, 2); else EL_GEMM_F32(false, 2, 2); }
-    else if (tm == 2) { if (vec) EL_GEMM_F32(true, 2, 1); else EL_GEMM_F32(false, 2, 1); }
-    else { if (vec) EL_GEMM_F32(true, 1, 1); else EL_GEMM_F32(false, 1, 1); }
+    const bool early = (long)grid.x * grid.y * grid.z <= (tm == 1 ? 896 : 512), straight = vec && g.K >= 512;
+#define EL_GEMM_F32(V, MT, NT, FORM) hipLaunchKernelGGL((k_gemm_f32<TA, TB, TO, V, MT, NT, FORM>), grid, block, 0, s, g)
+#define EL_GEMM_F32_VEC(MT, NT, FORM) do { if (vec) EL_GEMM_F32(true, MT, NT, FORM); else EL_GEMM_F32(false, MT, NT, FORM); } while (0)
+    if (tn == 2 && straight) EL_GEMM_F32(true, 2, 2, kGemmStraight);
+    else if (tn == 2) EL_GEMM_F32_VEC(2, 2, kGemmBranched);
+    else if (tm == 2 && straight) EL_GEMM_F32(true, 2, 1, kGemmStraight);
+    else if (tm == 2 && early) EL_GEMM_F32_VEC(2, 1, kGemmEarly);
+    else if (tm == 2) EL_GEMM_F32_VEC(2, 1, kGemmBranched);
+    else if (early) EL_GEMM_F32_VEC(1, 1, kGemmEarly);
+    else EL_GEMM_F32_VEC(1, 1, kGemmBranched);
+#undef EL_GEMM_F32_VEC
 #undef EL_GEMM_F32
     return hipGetLastError();
 }

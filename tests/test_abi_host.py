@@ -313,3 +313,24 @@ def test_short_core_counts_its_requests(tmp_path):
         block = re.split(r"^\.LBB\S+:", body[:wait.start()], flags=re.M)[-1].rsplit("global_load_lds_dwordx4", 1)[-1]
         assert len(re.findall(r"^\s*(?:global|buffer|flat|scratch)_(?:load|store)", block, re.M)) == loads, (d_m, blocks)
         assert "ds_read" not in body[:wait.start()]
+
+
+def test_fp32_products_leave_room_for_workgroups(tmp_path):
+    """k_gemm_f32 in the forms for more workgroups than run at once: registers for four workgroups of eight wavefronts on a compute
+    unit (16 x 16 outputs), three (32 x 16) or two (32 x 32), whatever the types and the alignment; 512 registers a lane of a SIMD
+    and two of a workgroup's wavefronts on each.  Rows held across the wait for the length cost one of them."""
+    from paper_2105_04779_amd import build
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    res = subprocess.run([hipcc, *flags, "-S", "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-I", os.path.join(build.ROOT, "include"),
+                          "-I", build.CSRC, "-o", str(tmp_path / "generic.s"), os.path.join(build.CSRC, "generic_kernels.hip")],
+                         check=True, capture_output=True, text=True)
+    found = re.findall(r"Function Name: (\S*k_gemm_f32I\S*?Lb\dELi(\d)ELi(\d)E\S*).*?VGPRs: (\d+)", res.stderr, re.S)
+    forms = set()
+    for name, rows, cols, registers in found:
+        form = re.search(r"GemmFormE(\d)", name)
+        forms.add((rows, cols, form and form.group(1)))
+        if form and form.group(1) == "0":                            # early: all workgroups run at once
+            continue
+        assert int(registers) <= {("1", "1"): 64, ("2", "1"): 80, ("2", "2"): 128}[rows, cols], (name, registers)
+    assert forms == {("1", "1", "0"), ("1", "1", "2"), ("2", "1", "0"), ("2", "1", "1"), ("2", "1", "2"), ("2", "2", "1"), ("2", "2", "2")}

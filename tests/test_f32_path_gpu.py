@@ -78,6 +78,40 @@ def test_one_launch_positions_dealt_to_wavefronts(beam, heads, d_m):
         layer.close()
 
 
+@pytest.mark.parametrize("B,beam,d_m,n", [
+    (224, 2, 96, 64),            # scores: 896 workgroups of 16 x 16 outputs, requested early, and four more
+    (225, 2, 96, 64),
+    (128, 4, 96, 64),            # 512 of 32 x 16, early, and four more
+    (129, 4, 96, 64),
+    (256, 4, 96, 61),            # 512 of 32 x 32
+    (64, 4, 528, 57),            # K >= 512: a whole group of slices, one that is not, and a slice of its own; 32 x 16 outputs
+    (32, 16, 528, 64),           # 32 x 32 outputs
+])
+@pytest.mark.parametrize("off", [0, 1])
+def test_forms_of_the_fp32_products(B, beam, d_m, n, off):
+    """Both sides of the lines between the forms of the fp32 products, with operands on a 16-byte boundary and one element past it;
+    lengths from 1 up, so that most workgroups of a short element have nothing to do."""
+    import torch
+    w = wl.custom(f"forms_{B}x{beam}_{d_m}_{n}", dtype="f32", B=B, beam=beam, heads=6, d_m=d_m, d_k=d_m // 6, n=n, index=95)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.asarray([1 + (b * 13) % n for b in range(B)], dtype=np.int32)
+    ref = oracle_out(w, W, H, Q, L)
+    for b in range(B):
+        H[b, L[b]:] = np.nan
+
+    def placed(x):
+        t = torch.empty(x.size + 4, device="cuda")[off:off + x.size].view(*x.shape)
+        t.copy_(torch.from_numpy(x))
+        return t
+    layer = make_layer(w, W)
+    y = layer.decode_step(placed(H), torch.from_numpy(L).cuda(), placed(Q))
+    err = rel_err(y.cpu().numpy(), ref)
+    record(f"{w.name}: off={off} err={err:.3e}")
+    assert not layer.uses_mfma and err <= TOL["f32"]
+    layer.close()
+
+
 @pytest.mark.parametrize("d_m,heads", [(64, 4), (320, 5)])
 def test_operands_aligned_to_one_element(d_m, heads):
     """H, queries and out one element past a 16-byte boundary, H with a batch stride that is no multiple of four."""
