@@ -234,7 +234,9 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
 
 /*
  * What the automatic choice would be for a shape on a device with `compute_units` compute units (host
- * arithmetic only, no device needed), in a context prepared for a max_batch of B: rows per row block in groups of
+ * arithmetic only, no device needed), in a context prepared for a max_batch of B, between the streaming core and the
+ * small workgroups of the core of short spans (el_attn_plan_step has the plan that a step is launched with, wide
+ * workgroups included): rows per row block in groups of
  * 16 (*row_groups) and the number of spans the list of valid tiles is cut into (*spans) by the MFMA attention core.
  * Workgroups: spans x row blocks of 16 *row_groups rows; while spans are short (B x tiles x blocks of 32 rows at
  * most 6 x compute_units) a block of 32 is two workgroups of 16, so spans x ceil(heads * beam / 16).
@@ -242,9 +244,6 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups);
  * rows, about twice or three times where all of them are that short; beyond 13 spans an element at most 3/4 compute_units
  * spans besides) run on a core of their own, which takes a whole span of at most 64 positions at once: row blocks
  * of 16, and as many spans as elements of n positions need (elements that are shorter leave some of them empty).
- * Steps just beyond those run on wide workgroups of that core, 128 positions at d_model 512, 96 at 768 and 64 at 1024
- * with rows in blocks of 32, while these fill the device at most once; this function and el_attn_plan_short_core
- * describe the choice without them.
  * Errors: INVALID_ARG (null outputs, sizes < 1), UNSUPPORTED (d_model other than 512, 768 or 1024: no MFMA
  * core).
  */
@@ -252,13 +251,26 @@ el_status el_attn_plan_preview(int32_t B, int32_t beam, int32_t heads, int32_t d
                                int32_t compute_units, int32_t *row_groups, int32_t *spans);
 
 /*
- * 1 if the automatic choice for that shape, in a context prepared for `max_batch` (a larger one has room for more
+ * 1 if that choice for the shape, in a context prepared for `max_batch` (a larger one has room for more
  * spans; elements of thousands of positions, which only such a context can cut that finely, stay on the other core
  * where it leaves many fewer pieces), is the core of short spans; 0 if not, or if el_attn_plan_preview would not
  * accept the shape.
  */
 int32_t el_attn_plan_short_core(int32_t max_batch, int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n,
                                 int32_t compute_units);
+
+/*
+ * The plan a step or segment of that shape is launched with while neither tuning knob is set (host arithmetic only), in a
+ * context prepared for `max_batch`, on a device with `compute_units` compute units:
+ *   *positions    0: the streaming core; else the core of short spans, and the most positions that a workgroup of it takes at
+ *                 once: 64 in its small workgroups; 128 (d_model 512), 96 (768) or 64 (1024) in its wide ones, which take the
+ *                 steps just beyond one round of the small ones while they fill the device at most once
+ *   *row_groups   rows of a workgroup in groups of 16 (1 or 2; small workgroups: 1; wide ones: 2 beyond 16 rows)
+ *   *spans        spans; spans x ceil(heads * beam / (16 *row_groups)) workgroups
+ * el_attn_decode_step_static plans with a max_batch of its B.  Errors: as el_attn_plan_preview, and INVALID_ARG for B > max_batch.
+ */
+el_status el_attn_plan_step(int32_t max_batch, int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n,
+                            int32_t compute_units, int32_t *positions, int32_t *row_groups, int32_t *spans);
 
 /*
  * el_attn_decode_step for callers that cannot allocate and have no workspace to bind: code running

@@ -190,7 +190,7 @@ el_status run_a1_to_a6(el_attn_ctx *ctx, const Problem &p, const Workspace &ws, 
 {
     constexpr float kLn2 = 0.6931471805599453f;
     if (el_attn_uses_mfma(ctx)) {
-        const CorePlan pl = plan_core_mfma(p, ctx->splits_override, ctx->nrg_override, ctx->num_cus, ws.slots);
+        const CorePlan pl = plan_core_mfma(p, ctx->splits_override, ctx->nrg_override, ctx->num_cus, ws.slots, true);
         fmt->pm = piece_map(ws); fmt->Rstride = pl.Rs; fmt->ml_to_nat = kLn2;
         // a1 + a2: expanded queries in fp16, pre-multiplied by log2(e)/sqrt(d_k) so the core's softmax is an exp2
         const float qscale = 1.4426950408889634f / sqrtf((float)p.d_k);
@@ -384,8 +384,10 @@ el_status el_attn_set_row_groups(el_attn_ctx *ctx, int32_t row_groups)
     return EL_OK;
 }
 
-// The automatic plan of a shape, with the piece slots of a workspace prepared for max_batch batch elements.
-static el_status preview(int32_t max_batch, int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n, int32_t compute_units, CorePlan *pl)
+// The automatic plan of a shape, with the piece slots of a workspace prepared for max_batch batch elements; `wide`: as it is
+// launched, with the wide workgroups of the core of short spans.
+static el_status preview(int32_t max_batch, int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n, int32_t compute_units, bool wide,
+                         CorePlan *pl)
 {
     if (B < 1 || B > max_batch || beam < 1 || heads < 1 || n < 1 || compute_units < 1) return EL_ERR_INVALID_ARG;
     if (!core_mfma_supported(EL_BF16, d_model)) return EL_ERR_UNSUPPORTED;
@@ -393,7 +395,7 @@ static el_status preview(int32_t max_batch, int32_t B, int32_t beam, int32_t hea
     std::memset(&p, 0, sizeof(p));
     p.B = B; p.beam = beam; p.n = n; p.heads = heads; p.d_m = d_model; p.R = heads * beam;
     const int64_t slots = (int64_t)max_batch * kMaxParts;
-    *pl = plan_core_mfma(p, 0, 0, compute_units, slots < INT32_MAX ? (int)slots : INT32_MAX, false);
+    *pl = plan_core_mfma(p, 0, 0, compute_units, slots < INT32_MAX ? (int)slots : INT32_MAX, wide);
     return EL_OK;
 }
 
@@ -402,7 +404,7 @@ el_status el_attn_plan_preview(int32_t B, int32_t beam, int32_t heads, int32_t d
 {
     if (!row_groups || !spans) return EL_ERR_INVALID_ARG;
     CorePlan pl;
-    const el_status st = preview(B, B, beam, heads, d_model, n, compute_units, &pl);
+    const el_status st = preview(B, B, beam, heads, d_model, n, compute_units, false, &pl);
     if (st != EL_OK) return st;
     *row_groups = pl.block_groups;
     *spans = pl.G;
@@ -413,7 +415,20 @@ int32_t el_attn_plan_short_core(int32_t max_batch, int32_t B, int32_t beam, int3
                                 int32_t compute_units)
 {
     CorePlan pl;
-    return preview(max_batch, B, beam, heads, d_model, n, compute_units, &pl) == EL_OK && pl.short_tiles ? 1 : 0;
+    return preview(max_batch, B, beam, heads, d_model, n, compute_units, false, &pl) == EL_OK && pl.short_tiles ? 1 : 0;
+}
+
+el_status el_attn_plan_step(int32_t max_batch, int32_t B, int32_t beam, int32_t heads, int32_t d_model, int32_t n,
+                            int32_t compute_units, int32_t *positions, int32_t *row_groups, int32_t *spans)
+{
+    if (!positions || !row_groups || !spans) return EL_ERR_INVALID_ARG;
+    CorePlan pl;
+    const el_status st = preview(max_batch, B, beam, heads, d_model, n, compute_units, true, &pl);
+    if (st != EL_OK) return st;
+    *positions = 16 * pl.short_tiles;
+    *row_groups = pl.nrg;
+    *spans = pl.G;
+    return EL_OK;
 }
 
 el_status el_attn_check_step_operands(const el_attn_config *cfg, int32_t mfma, const void *H, int64_t H_batch_stride,

@@ -266,8 +266,9 @@ hipError_t launch_core_short(const StreamArgs &a, int d_m, bool bf16, int tiles,
 hipError_t launch_core_stream(const StreamArgs &a, int d_m, bool bf16, int rg, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 bool core_mfma_supported(int dtype, int d_m);
 // what a step launches: the streaming core or, where neither override is set and it is the faster one, the core of short spans
-// (wide: the wide workgroups of the core of short spans are allowed; the previews show the plan without)
-CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots, bool wide = true);
+// (wide: the wide workgroups of the core of short spans are allowed, as they are in a step; el_attn_plan_preview and
+// el_attn_plan_short_core ask without them, el_attn_plan_step with them)
+CorePlan plan_core_mfma(const Problem &p, int splits_override, int nrg_override, int num_cus, int max_slots, bool wide);
 CutArgs cut_args(const Problem &p, const CorePlan &pl, const Workspace &ws);
 PieceMap piece_map(const Workspace &ws);
 hipError_t launch_cut(const CutArgs &c, hipStream_t s);      // the cut on its own, for a core that k_qelq does not precede

@@ -21,7 +21,7 @@ DTYPE_CODES = {"f32": EL_F32, "f16": EL_F16, "bf16": EL_BF16}
 EXPORTED_SYMBOLS = (
     "el_attn_prepare", "el_attn_workspace_bytes", "el_attn_bind_workspace", "el_attn_decode_step",
     "el_attn_expand_query", "el_attn_set_splits", "el_attn_max_splits", "el_attn_set_row_groups",
-    "el_attn_uses_mfma", "el_attn_plan_preview", "el_attn_plan_short_core", "el_attn_check_step_operands",
+    "el_attn_uses_mfma", "el_attn_plan_preview", "el_attn_plan_short_core", "el_attn_plan_step", "el_attn_check_step_operands",
     "el_attn_decode_step_static",
     "el_attn_core_timing_enable", "el_attn_core_timing_read",
     "el_attn_gather_batch", "el_attn_check_inputs",
@@ -81,6 +81,8 @@ def _load():
     lib.el_attn_plan_preview.restype = ctypes.c_int
     lib.el_attn_plan_short_core.argtypes = [i32] * 7
     lib.el_attn_plan_short_core.restype = i32
+    lib.el_attn_plan_step.argtypes = [i32] * 7 + [ctypes.POINTER(i32)] * 3
+    lib.el_attn_plan_step.restype = ctypes.c_int
     lib.el_attn_uses_mfma.argtypes = [vp]
     lib.el_attn_uses_mfma.restype = i32
     lib.el_attn_check_step_operands.argtypes = [ctypes.POINTER(ElAttnConfig), i32, vp, i64, vp, vp, vp, i32, i32, i32]
@@ -171,6 +173,13 @@ def el_attn_plan_preview(B, beam, heads, d_model, n, compute_units):
 
 def el_attn_plan_short_core(max_batch, B, beam, heads, d_model, n, compute_units) -> int:
     return int(lib.el_attn_plan_short_core(max_batch, B, beam, heads, d_model, n, compute_units))
+
+
+def el_attn_plan_step(max_batch, B, beam, heads, d_model, n, compute_units):
+    """Returns (status, positions, row_groups, spans)."""
+    out = [ctypes.c_int32(0) for _ in range(3)]
+    st = lib.el_attn_plan_step(max_batch, B, beam, heads, d_model, n, compute_units, *map(ctypes.byref, out))
+    return (st, *(v.value for v in out))
 
 
 def el_attn_uses_mfma(ctx) -> int:

@@ -232,6 +232,56 @@ def test_lines_of_the_core_of_short_spans(ea):
                                 assert ea.el_attn_plan_preview(B, beam, heads, d_m, n, units) == (ea.EL_OK, 1, spans)
 
 
+def test_plan_of_a_step_is_the_one_launched(ea):
+    """el_attn_plan_step on both sides of every line of the wide workgroups' rule (256 compute units): which core, how many
+    positions and rows a workgroup takes, how many spans.  The two previews go on describing the choice without them."""
+    def plan(B, beam, d_m, n, max_batch=None, units=256):
+        st, *p = ea.el_attn_plan_step(max_batch or B, B, beam, d_m // 64, d_m, n, units)
+        assert st == ea.EL_OK
+        return tuple(p)
+    # shapes that the previews have on the streaming core
+    assert plan(16, 4, 1024, 300) == (64, 2, 80) and plan(12, 4, 1024, 512) == (64, 2, 96) and plan(64, 4, 512, 512) == (128, 2, 256)
+    assert not ea.el_attn_plan_short_core(12, 12, 4, 16, 1024, 512, 256) and ea.el_attn_plan_preview(12, 4, 16, 1024, 512, 256) == (ea.EL_OK, 2, 64)
+    # ... or with a second round of the small workgroups: not at d_m 512, and at 1024 only where 32-row blocks pad no further
+    assert plan(100, 4, 768, 64) == (96, 2, 100) and plan(100, 5, 768, 64) == (96, 2, 100)
+    assert plan(128, 4, 1024, 64) == (64, 2, 128) and plan(100, 3, 1024, 64) == (64, 1, 100)
+    assert plan(200, 4, 512, 64) == (64, 1, 200)
+    # one round of the small workgroups stays theirs, one round of the wide ones is the end
+    assert plan(16, 4, 512, 512) == (64, 1, 128) and plan(17, 4, 512, 512) == (128, 2, 68)
+    assert plan(65, 4, 512, 512)[0] == 0 and plan(64, 1, 512, 512) == (128, 1, 256) and plan(65, 1, 512, 512)[0] == 0
+    assert plan(85, 1, 768, 288) == (96, 1, 255) and plan(86, 1, 768, 288)[0] == 0
+    assert plan(32, 4, 1024, 256) == (64, 2, 128) and plan(33, 4, 1024, 256)[0] == 0
+    assert plan(64, 4, 512, 512, units=304) == (128, 2, 256) and plan(76, 4, 512, 512, units=304) == (128, 2, 304) and plan(77, 4, 512, 512, units=304)[0] == 0
+    # one row block and many spans of an element
+    assert plan(38, 2, 1024, 320) == (64, 2, 190) and plan(39, 2, 1024, 320)[0] == 0 and plan(64, 2, 1024, 256) == (64, 2, 256)
+    assert plan(25, 1, 768, 960) == (96, 1, 250) and plan(23, 1, 768, 961)[0] == 0
+    assert plan(19, 2, 768, 1248) == (96, 2, 247) and plan(18, 2, 768, 1249)[0] == 0
+    assert plan(512, 1, 1024, 1024) == (0, 1, 256) and plan(64, 4, 1024, 1024) == (0, 2, 128)
+    # d_m 1024 and 16 rows: nothing wider
+    assert plan(300, 1, 1024, 64) == (64, 1, 300) and plan(260, 1, 1024, 65)[0] == 0
+    tiles = {512: 128, 768: 96, 1024: 64}
+    for units in (64, 256, 304):
+        for d_m in (512, 768, 1024):
+            for beam in (1, 2, 3, 4, 5, 8):
+                for n in (1, 16, 64, 65, 96, 97, 128, 129, 300, 512, 960, 1024, 3000):
+                    for B in (1, 5, 13, 32, 64, 100, 200, 256, 300, 1024, 1025):
+                        for max_batch in (B, 2 * B):
+                            positions, groups, spans = plan(B, beam, d_m, n, max_batch, units)
+                            rows = beam * d_m // 64
+                            small = ea.el_attn_plan_short_core(max_batch, B, beam, d_m // 64, d_m, n, units)
+                            if positions == 0:
+                                assert not small and groups in (1, 2) and spans >= 1
+                            elif small and (positions, groups) == (64, 1):
+                                assert spans == B * -(-n // 64) <= min(1024, 15 * max_batch)
+                            else:
+                                assert positions == tiles[d_m] and groups == (2 if rows > 16 else 1) and (positions, groups) != (64, 1)
+                                assert spans == B * -(-n // positions) and spans * -(-rows // (16 * groups)) <= units and spans <= 13 * B
+    I = ea.EL_ERR_INVALID_ARG
+    assert ea.el_attn_plan_step(4, 5, 4, 16, 1024, 64, 256)[0] == I and ea.el_attn_plan_step(4, 4, 4, 16, 1024, 64, 0)[0] == I
+    assert ea.el_attn_plan_step(4, 4, 4, 10, 640, 64, 256)[0] == ea.EL_ERR_UNSUPPORTED
+    assert ea.lib.el_attn_plan_step(4, 4, 4, 16, 1024, 64, 256, None, ctypes.byref(ctypes.c_int32()), ctypes.byref(ctypes.c_int32())) == I
+
+
 def test_check_inputs_rejects_bad_arguments_before_any_device_work(ea):
     I = ea.EL_ERR_INVALID_ARG
     A, Rp = ctypes.c_void_p(0x10000), ctypes.c_void_p(0x20000)   # never dereferenced

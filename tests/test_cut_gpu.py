@@ -270,3 +270,30 @@ def test_wide_short_spans(dtype, B, beam, heads, d_m, n, lens):
     assert err <= TOL[dtype]
     for a, b in zip(*outs):
         assert rel_err(a, b) <= 2 * TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,B,beam,heads,d_m,n,lens", WIDE)
+def test_wide_cases_run_on_wide_workgroups(dtype, B, beam, heads, d_m, n, lens):
+    """The cases above are launched on the wide workgroups of this device, and not on a core that would pass them as well."""
+    positions, rows = {512: 128, 768: 96, 1024: 64}[d_m], heads * beam
+    assert el_attn.el_attn_plan_step(B, B, beam, heads, d_m, n, compute_units()) == (el_attn.EL_OK, positions, 2 if rows > 16 else 1, B * -(-n // positions))
+
+
+@pytest.mark.parametrize("dtype,B,beam,heads,d_m,n", [("bf16", 33, 5, 12, 768, 90), ("f16", 16, 4, 16, 1024, 300)])
+def test_streaming_core_of_shapes_of_the_wide_workgroups(dtype, B, beam, heads, d_m, n):
+    """Shapes whose automatic choice is the wide workgroups, on the streaming core with row blocks of 16 and of 32."""
+    assert el_attn.el_attn_plan_step(B, B, beam, heads, d_m, n, compute_units())[1:3] == ({768: 96, 1024: 64}[d_m], 2)
+    w = wl.custom(f"wide_streamed_{dtype}_{B}x{beam}_{d_m}_{n}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=64, n=n, index=104)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    L = np.asarray([n if b == 0 else 1 + (b * 13) % n for b in range(B)], dtype=np.int32)
+    ref = oracle_out(w, W, H, Q, L)
+    for b in range(B):
+        H[b, L[b]:] = np.nan
+    layer = make_layer(w, W)
+    for groups in (0, 1, 2):
+        layer.set_row_groups(groups)
+        err = rel_err(gpu_out(layer, w, H, Q, L), ref)
+        record(f"{w.name}: row groups={groups} err={err:.3e}")
+        assert err <= TOL[dtype]
+    layer.close()
