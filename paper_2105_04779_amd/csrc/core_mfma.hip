@@ -177,7 +177,7 @@ static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CoreP
 // four at 1024) and, beyond 16 rows, 32 of them, where all of those run at once and the smaller ones would not.  Half the pieces and
 // half the expanded queries to receive or less, against a longer way through each workgroup.  Whole steps in bf16, the streaming core
 // against this one, a half to the whole of a round (us):
-//   d_m 512    8 rows, 32 of 768 to 1024 positions 21.0 / 19.4, 25 of them 20.4 / 17.4    32 rows, 64 of 256 to 512 23.3 / 23.5 (fp16 23.4 / 22.9),
+//   d_m 512    8 rows, 32 of 768 to 1024 positions 21.0 / 19.4, 25 of them 20.4 / 17.4    32 rows, 64 of 256 to 512 23.7 / 23.4 (fp16 23.2 / 23.0),
 //              25 of 768 to 1024 23.5 / 21.0    40 rows, 30 of 384 to 512 24.2 / 20.9    64 rows, 30 of 300 to 500 25.4 / 22.3
 //   d_m 768    12 rows, 60 of 285 to 380 24.0 / 22.4    24 rows, 42 of 427 to 570 27.7 / 26.0    48 rows, 18 of them 25.5 / 22.7    60 rows, 40 of 200 to
 //              280 32.0 / 26.7    72 rows, 20 of 285 to 380 28.9 / 25.1
@@ -191,6 +191,11 @@ static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CoreP
 // A second round of the smaller workgroups (elements of one span) gives way to one of these at d_m 768 (100 of 64, 48 rows, 30.3 / 28.8;
 // 128 of 16, 60 rows, 29.8 / 29.6), and at 1024 where 32-row blocks pad no further than 16-row ones (64 rows, 128 of 64 38.1 / 37.1, but 48
 // rows 34.3 / 34.8); at 512 two of the smaller ones share a compute unit (200 of 64, 32 rows, 26.1 / 28.2).
+// Nor where the streaming core has an element on nearly every compute unit and nothing crosses: single queries over histories, which
+// are of one length as a rule, d_m 512, fp16 (bf16): 256 of 128 positions 20.4 / 21.0 (20.9 / 21.3), 256 of 108 20.0 / 20.5 (20.4 /
+// 20.8), 254 of 128 20.4 / 20.8, 248 of 128 20.8 / 20.9, 244 21.0 / 21.0, but 230 of 128 22.4 / 20.3 (22.8 / 20.6).  Two and three queries over inputs of one
+// length lose as much in fp16 (256 of 128, 16 rows, 23.4 / 23.7, 24 rows 28.4 / 29.1; bf16 24.2 / 23.9, 29.5 / 29.7), but their inputs
+// differ in length, and 256 of 64 to 128 gain: 16 rows 25.3 / 23.2, 24 rows 31.0 / 27.8; four gain either way (128 each, 30.5 / 30.0).
 static void plan_wide_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
 {
     if (p.B > kScanMax) return;
@@ -201,6 +206,7 @@ static void plan_wide_spans(const Problem &p, int num_cus, int max_slots, CorePl
     if (spans > kSpanMax || spans > max_slots || spans * blocks > num_cus || per_element > 13) return;
     if (blocks == 1 && p.d_m == 1024 && per_element > 4 && 4 * spans > 3L * num_cus) return;
     if (rg == 1 && p.d_m == 768 && per_element > 10) return;
+    if (p.d_m == 512 && p.beam == 1 && per_element == 1 && 16 * spans > 15L * num_cus) return;
     if (pl.short_tiles) {
         if ((long)pl.G * pl.nblocks <= num_cus || p.d_m == 512) return;
         if (p.d_m == 1024 && 2 * blocks != pl.nblocks) return;

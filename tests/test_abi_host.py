@@ -282,6 +282,17 @@ def test_plan_of_a_step_is_the_one_launched(ea):
     assert ea.lib.el_attn_plan_step(4, 4, 4, 16, 1024, 64, 256, None, ctypes.byref(ctypes.c_int32()), ctypes.byref(ctypes.c_int32())) == I
 
 
+def test_single_queries_of_one_length_stay_on_the_streaming_core(ea):
+    """d_m 512, one query per history, a span each on more than 15/16 of the compute units: an element a workgroup on either core, and
+    the streaming core is the faster one."""
+    def positions(B, beam, n, d_m=512, units=256):
+        return ea.el_attn_plan_step(B, B, beam, d_m // 64, d_m, n, units)[1]
+    assert positions(240, 1, 128) == 128 and positions(241, 1, 128) == 0 and positions(256, 1, 128) == 0 and positions(257, 1, 128) == 0
+    assert positions(241, 1, 65) == 0 and positions(241, 1, 64) == 64 and positions(128, 1, 129) == 128 and positions(285, 1, 128, units=304) == 128
+    assert positions(256, 2, 128) == positions(256, 3, 128) == positions(256, 4, 128) == 128
+    assert positions(256, 1, 96, d_m=768) == 96
+
+
 def test_check_inputs_rejects_bad_arguments_before_any_device_work(ea):
     I = ea.EL_ERR_INVALID_ARG
     A, Rp = ctypes.c_void_p(0x10000), ctypes.c_void_p(0x20000)   # never dereferenced
