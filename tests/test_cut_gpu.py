@@ -173,6 +173,33 @@ def test_rows_and_pieces_side_by_side(dtype, d_m, B, beam, n, max_batch):
     layer.close()
 
 
+@pytest.mark.parametrize("dtype,d_m,B,beam,n", [("bf16", 1024, 130, 2, 480), ("f16", 768, 120, 3, 480), ("bf16", 512, 270, 2, 640)])
+def test_row_tiles_of_one_and_of_many_rounds(dtype, d_m, B, beam, n):
+    """More query rows than the merge has workgroups for in tiles of 16 (256, 336 and 512), one element of as many as thirty pieces
+    among elements of a single one, at the start, in the middle and at the end: a workgroup folds in more rounds of a tile than it
+    has in flight, before and after tiles of one round.  Step and segment form against the oracle at the step's bar."""
+    heads = d_m // 64
+    assert B * beam > 16 * (compute_units() // heads)
+    w = wl.custom(f"row_tiles_{dtype}_{d_m}", dtype=dtype, B=B, beam=beam, heads=heads, d_m=d_m, d_k=64, n=n, index=105)
+    W = wl.weights(w)
+    H, Q, _ = wl.batch(w, poison=False)
+    Hd, Qd = to_device(H, dtype), to_device(Q, dtype)
+    layer = make_layer(w, W)
+    for at in (0, B // 2, B - 1):
+        L = np.asarray([n if b == at else 1 + (b * 7) % 16 for b in range(B)], dtype=np.int32)
+        Ld = torch.from_numpy(L).cuda()
+        ref = oracle_out(w, W, H, Q, L)
+        ref_A, ref_lse = oracle.segment_reference(H, L, Q, W["Wq"], W["bq"], W["Wk"], W["bk"], W["Wv"], W["bv"], heads=heads, d_k=64)
+        err = rel_err(layer.decode_step(Hd, Ld, Qd).float().cpu().numpy(), ref)
+        A, lse = layer.decode_segment(Hd, Ld, Qd)
+        err_A, err_lse = rel_err(A.cpu().numpy(), ref_A), float(np.abs(lse.cpu().numpy() - ref_lse).max())
+        long = rel_err(A.cpu().numpy()[at * beam:(at + 1) * beam], ref_A[at * beam:(at + 1) * beam])
+        record(f"{w.name}: long element {at} err={err:.3e} seg_A err={err_A:.3e} (its own {long:.3e}) lse err={err_lse:.3e}")
+        # (the long element's head outputs are small beside those of one position: held to the bar by themselves as well)
+        assert err <= TOL[dtype] and err_A <= TOL[dtype] and long <= TOL[dtype] and err_lse <= 5e-3
+    layer.close()
+
+
 SHORT = [
     # dtype, B, beam, heads, d_m, n, lens: at most 256 workgroups of 64 positions and 16 rows (two or three times as many where n <= 64)
     ("bf16", 5, 4, 16, 1024, 200, [200, 1, 16, 17, 64]),            # spans of one to four tiles, of one position and of a full tile
