@@ -22,7 +22,7 @@ HIPCC_FLAGS = [
 
 
 # kernels that are built around what their wavefronts hold in registers
-NO_SPILL_KERNELS = ("k_core_stream", "k_core_short", "k_qelq", "k_vproj", "k_oproj", "k_small_step")
+NO_SPILL_KERNELS = ("k_core_stream", "k_core_short", "k_qelq", "k_vproj", "k_oproj", "k_small_step", "k_gemm_f32")
 
 
 def sources():

@@ -68,11 +68,10 @@ bool core_mfma_supported(int dtype, int d_m)
 // workgroup per compute unit when the longest possible list gives every span at least kMinSpan tiles,
 // fewer otherwise (but not fewer than one span per batch element); build_cut lays the spans over the actual lengths.
 // Batches beyond kScanMax elements are not cut: one workgroup per (element, row block), scheduled by the hardware.
-// 4 was chosen where small steps ran on this core (one sentence of 613 positions and 64 rows: 18.3 us of core with 8 tiles, 12.6
-// with 4).  Those run on the core of short spans now.  What still meets the line are long elements on few compute units, and there
-// twice as many pieces to merge cost more than the shorter spans gain.  Whole steps, 8 tiles against 4: d_m 1024, 1 beam, 16 of 960
-// positions 33.2 / 37.5 us, one of 6000 39.5 / 50.2, of 1024 24.5 / 25.0; 4 beams, one of 1000 25.4 / 25.4; d_m 512, 8 rows, 16 of 960
-// 24.7 / 26.7, one of 6000 30.6 / 37.7.
+// What meets the line are long elements on few compute units, in a context prepared for many, and what the tuning knobs keep off the core
+// of short spans.  Whole steps on this core, 8 tiles against 4 (a further piece is cheap since the merge takes several of them side by
+// side; before it did, 8 was the faster one): d_m 1024, 1 beam, 16 of 960 positions 26.1 / 25.2 us, one of 6000 24.9 / 25.8, of 1024 21.5 / 19.2;
+// 4 beams, one of 1000 22.5 / 20.5; d_m 512, 8 rows, 16 of 960 19.6 / 19.2, one of 6000 20.4 / 20.4.
 constexpr int kMinSpan = 4;
 // What moving on to the next batch element costs a workgroup, in tiles of streaming time: the expanded queries of
 // the new element (128 KB for 32 rows) and the write-out of the finished piece.  Spans that cross an element hold
@@ -125,35 +124,34 @@ static CorePlan plan_stream(const Problem &p, int splits_override, int nrg_overr
 }
 
 // Elements of thousands of positions (a context prepared for many, called with one to three): the streaming core's cut mostly has
-// spans of five tiles, a fifth fewer pieces, and a further piece costs the merge 0.3 us.  Up to so many more the short core takes
-// back (177 shapes of three to eight more: 1.00 to 1.13 times as fast; 2500 positions, one element, 16 rows, 8 more, streaming
-// against short core: d_m 1024 33.1 / 32.9, d_m 512 25.4 / 24.9); with nine or more it loses, the longer the more: d_m 1024 5200
-// positions, 17 more, 46.7 / 50.1; 7000 56.0 / 61.9; 11500, 36 more, 80.0 / 92.0; d_m 512 56.8 / 63.3.
+// spans of five tiles, a fifth fewer pieces.  The line was drawn where a further piece cost the merge 0.3 us (177 shapes of three to
+// eight more: 1.00 to 1.13 times as fast).  Since the merge takes several pieces side by side it lies on the safe side; one element, 16
+// rows, streaming against short core: d_m 1024 2500 positions (8 more) 21.1 / 18.2, 5200 (17 more) 25.0 / 22.6, 7000 26.9 / 25.4, 11500 (36
+// more) 32.6 / 33.1; d_m 512 17.7 / 15.7, 20.3 / 18.2, 11500 25.6 / 25.0.
 constexpr int kMorePieces = 8;
 
 // The core of short spans (core_short.hip): every element dealt out to workgroups of four tiles and 16 rows, while all of them
 // run at once (spans by the longest possible element).  Beyond that a second round of workgroups waits for the first one's
 // latency, which the streaming core pays once, and more pieces are written and merged.  Whole steps in bf16, the streaming core
-// (with the cut built by eight wavefronts, as for the short one) against the short core, 64 rows at d_m 1024, 48 at 768 and 32 at
-// 512 unless it says so (us; workgroups per compute unit of 256):
-//   d_m 1024    1 element of 613 positions 23.4 / 21.8    8 of 512 (1) 28.7 / 25.4    2 of 128 21.9 / 18.5    16 of 300 (1.25) 29.4 / 30.4
-//               12 of 512 (1.5) 30.0 / 30.4    128 of 200, 16 rows (2) 35.4 / 38.1
-//   d_m 768     8 of 512 (0.75) 24.6 / 21.4    16 of 300 (0.9) 25.4 / 21.8    24 of 300 (1.4) 26.5 / 27.0
-//   d_m 512     24 of 300 (0.9) 21.4 / 19.1    32 of 300 (1.25) 21.3 / 20.3    64 of 300, 8 rows (1.25) 21.9 / 20.9    128 of 200, 8 rows (2) 22.6 / 22.0
-// (d_m 512 has two workgroups on a compute unit and would bear more than one round; 34 of 900, 16 rows (2) 23.3 / 24.0).  Of 403
-// shapes of 2 to 13 spans an element, 1 to 8 beams, a half to the whole of a round, all gain, 2 to 22 %.  With more spans the merge of as
-// many pieces takes it back where nearly every compute unit reads positions of its own: 1 beam, 16 of 960 positions d_m 1024
-// 38.1 / 38.0, d_m 768 33.4 / 33.1 (fp16, 17 of 960: 32.3 / 32.9); 17 of 896 36.9 / 36.7, 32.1 / 31.1; 11 of 960 33.2 / 32.0, 29.9 / 27.8;
-// 4 beams, 4 of 960, as many workgroups on a quarter of the positions, 30.7 / 28.1.
+// against the short core, elements of one length, 64 rows at d_m 1024, 48 at 768 and 32 at 512 unless it says so (us; workgroups per
+// compute unit of 256):
+//   d_m 1024    1 element of 613 positions 20.0 / 17.3    8 of 512 (1) 26.2 / 22.7    2 of 128 20.6 / 16.1    16 of 300 (1.25) 27.5 / 27.6
+//               12 of 512 (1.5) 27.5 / 26.8    128 of 200, 16 rows (2) 34.6 / 36.3
+//   d_m 768     8 of 512 (0.75) 21.8 / 17.8    16 of 300 (0.9) 23.1 / 19.1    24 of 300 (1.4) 25.5 / 25.2
+//   d_m 512     24 of 300 (0.9) 19.3 / 16.5    32 of 300 (1.25) 20.2 / 18.5    64 of 300, 8 rows (1.25) 19.8 / 18.4    128 of 200, 8 rows (2) 21.8 / 19.8
+// (d_m 512 has two workgroups on a compute unit and bears more than one round; 34 of 900, 16 rows (2) 21.2 / 20.8.  Most steps beyond one
+// round run on the wide workgroups below.)  The line of 13 spans an element is from a merge that took one piece after another (1 beam, 17
+// of 960 positions, fp16, d_m 768, 32.3 / 32.9); it lies on the safe side now: 1 beam, 16 of 960 positions d_m 1024 25.3 / 23.0, d_m 768 22.2
+// / 19.9 (fp16, 17 of 960: 27.7 / 25.2, 21.9 / 20.2); 17 of 896 26.6 / 25.0, 22.1 / 19.7; 11 of 960 23.5 / 20.5, 21.7 / 18.2; 4 beams, 4 of 960
+// 24.8 / 21.2.
 // Where every element is one span there is no more to merge than before, and a second round pays (at d_m 512 a third):
-//   d_m 1024    100 of 64 (1.6) 43.0 / 38.5    128 of 64 (2) 44.4 / 41.7    200 of 64 (3.1) 63.7 / 63.2    320 of 33 (5) 75.1 / 75.5
-//   d_m 768     170 of 64 (2) 41.4 / 39.2    200 of 64 (2.3) 45.9 / 43.8    320 of 33 (3.75) 54.1 / 52.4    1000 of 64, 12 rows (3.9) 57.5 / 62.1
-//   d_m 512     200 of 64 (1.6) 31.9 / 27.7    384 of 64 (3) 38.1 / 34.2    1000 of 64, 8 rows (3.9) 38.6 / 36.6
+//   d_m 1024    100 of 64 (1.6) 39.7 / 34.5    128 of 64 (2) 41.9 / 38.5    200 of 64 (3.1) 57.9 / 55.5    320 of 33 (5) 70.2 / 69.3
+//   d_m 768     170 of 64 (2) 38.2 / 35.3    200 of 64 (2.3) 42.7 / 39.4    320 of 33 (3.75) 50.5 / 47.4    1000 of 64, 12 rows (3.9) 55.3 / 57.9
+//   d_m 512     200 of 64 (1.6) 29.5 / 24.8    384 of 64 (3) 36.7 / 31.9    1000 of 64, 8 rows (3.9) 37.0 / 34.9
 // but with one row block only up to 15/8 rounds: where both rounds are full, the streaming core has two elements on every compute
-// unit and nothing idle either.  16 rows, d_m 1024: 460 of 64 51.7 / 46.8, 480 51.3 / 46.9, 512 49.1 / 49.3; 12 rows, d_m 768: 41.2 / 38.1,
-// 41.3 / 38.4, 38.8 / 39.3.  Elements of a single tile gain little in a second round, and none where it is nearly empty: d_m 768, 16
-// positions, 89 elements (1.04) 32.9 / 33.7 with 48 rows, 27.4 / 26.8 with 36; 44 with 96 rows 32.2 / 33.3; of 112 such shapes at
-// d_m 768 and 1024 0.98 to 1.07 times as fast, 1.02 in the mean.
+// unit and nothing idle either.  16 rows, d_m 1024: 460 of 64 49.8 / 44.1, 480 49.6 / 44.2, 512 47.2 / 46.4; 12 rows, d_m 768: 39.3 / 35.6,
+// 39.4 / 36.2, 37.1 / 37.0.  Elements of a single tile gain least in a second round that is nearly empty: d_m 768, 16 positions, 89
+// elements (1.04) 30.3 / 29.6 with 48 rows, 26.8 / 25.4 with 36; 44 with 96 rows 30.5 / 29.3.
 static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
 {
     if (p.B > kScanMax) return;

@@ -14,15 +14,16 @@
 //   weighted sum  X^T[d, r] over the slice's columns, 16x16x32 MFMA (two tiles deep), A = H columns through the transposing LDS
 //                 read, B = P (fp16, or a high + low bf16 pair).  The column fragments are read together with the scores'
 //                 operands, so that the tiles' part of LDS is free for the partial scores.
-// Kernel times, streaming core -> here, d_m 1024: one sentence of 613 positions, 64 rows (40 workgroups) 10.2 -> 6.6 us; 4 of 205
-// to 410 9.7 -> 7.0; 8 of 512 (256 workgroups) 13.1 -> 9.6; 128 histories of 37, 16 rows, 9.8 -> 6.5.  More pieces take some of it
-// back in the merge (one sentence: ten instead of eight, 5.9 -> 8.1).
+// Kernel times, streaming core -> here, d_m 1024: one sentence of 613 positions, 64 rows (40 workgroups) 10.2 -> 6.3 us; 4 of 205
+// to 410 10.0 -> 6.6; 8 of 512 (256 workgroups) 13.9 -> 9.5; 128 histories of 37, 16 rows, 9.7 -> 6.4.  More pieces take some of it
+// back in the merge (one sentence: ten instead of eight, 4.0 -> 4.6).
 // The tiles' fragments are read while EL-Q arrives and all partial scores of a position before any is added, instead of everything behind
 // one wait and the partials two by two: whole steps of 96 shapes of one to eight spans an element 1.014 times as fast (0.99 to
 // 1.04), one sentence of 613 positions 17.06 -> 16.62 us, twelve layers 243.7 -> 238.3.
 // Bound: memory latency (the table of the cut, then tiles and EL-Q together), then the 64 bytes a clock that a compute unit
-// receives: at d_m 1024 128 KB of tiles and 64 KB of EL-Q (128 KB with 32 rows).  A wide workgroup has up to twice the products behind
-// the wait: 64 of them a wavefront for the scores of eight tiles, in two groups, so that their results and operands fit the registers.
+// receives: at d_m 1024 128 KB of tiles and 64 KB of EL-Q (128 KB with 32 rows).  Behind the wait a wavefront of a wide workgroup of 32
+// rows has 64 products for the scores instead of 16 at d_m 512, 72 instead of 24 at 768 and 64 instead of 32 at 1024, in groups of four
+// tiles (two at 1024), so that their results and operands fit the registers.
 #include <type_traits>
 #include <hip/hip_ext.h>
 #include "mfma.h"

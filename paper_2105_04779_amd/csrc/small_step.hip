@@ -273,16 +273,16 @@ k_small_step(const SmallArgs a)
 
 // Where one workgroup per batch element does the whole step: the weights fit its registers (d_m 64 or 128, head sizes that
 // are whole 16-wide slices), at most 16 beams (one row tile), and its scores and weighted sums, R x n x d_m products each on
-// one compute unit, stay below what the separate launches need for their extra round trips.  us, here against separately (before
-// the requests were drawn together on either side, which took a sixth off here and a fifteenth there):
+// one compute unit, stay below what the separate launches need for their extra round trips.  us, here against separately (up to 16
+// elements the separate side is the host's 22 us for six launches where it takes longer than the device):
 //                                        1 element    16           256          1024         4096
-//   d_m 64, 4 heads, 2 beams, n 32       8.5 / 21.5   8.8 / 23.1   9.0 / 22.7   29.9 / 36.3  118 / 98
-//   d_m 64, 4 heads, 16 beams, n 64      16.1 / 22.1  16.6 / 22.1  17.1 / 42.0  61.4 / 120   248 / 433
-//   d_m 128, 2 heads, 4 beams, n 100     19.3 / 21.6  19.7 / 22.9  20.1 / 34.2  75.0 / 75.4  296 / 260
-//   d_m 128, 2 heads, 4 beams, n 256     23.0 / 22.4  24.0 / 23.6  26.5 / 41.1  99.9 / 105   429 / 405     2^19
-//   d_m 128, 8 heads, 8 beams, n 64      28.2 / 22.1  29.1 / 22.7  29.3 / 65.0  115 / 202    455 / 803     2^19
-// and 30.1 / 28.2 at 2^20 (d_m 64, 64 rows, n 256, 2 elements).  So the line is right for a batch and generous for a few
-// elements near it; thousands of elements of few rows would be faster separately, because beyond one element per
+//   d_m 64, 4 heads, 2 beams, n 32       6.3 / 22.1   6.6 / 23.1   6.9 / 22.5   23.5 / 33.2  91.9 / 91.5
+//   d_m 64, 4 heads, 16 beams, n 64      12.0 / 22.2  12.4 / 23.0  12.7 / 38.4  46.9 / 112   184 / 402
+//   d_m 128, 2 heads, 4 beams, n 100     15.8 / 22.0  16.1 / 23.2  16.5 / 30.6  62.0 / 72.2  244 / 247
+//   d_m 128, 2 heads, 4 beams, n 256     20.0 / 21.7  20.4 / 22.7  21.2 / 38.1  82.3 / 102   330 / 392     2^19
+//   d_m 128, 8 heads, 8 beams, n 64      23.6 / 18.2  24.1 / 19.2  24.8 / 60.8  95.3 / 188   378 / 746     2^19
+// and 25.5 / 18.6 at 2^20 (d_m 64, 64 rows, n 256, 2 elements).  So the line is right for a batch and generous for a few
+// elements near it; thousands of elements of few rows come out even, because beyond one element per
 // compute unit the workgroups run in rounds that each read the weights again.
 bool small_step_applies(const Problem &p)
 {
