@@ -191,9 +191,10 @@ static void plan_short_spans(const Problem &p, int num_cus, int max_slots, CoreP
 // rows 34.3 / 34.8); at 512 two of the smaller ones share a compute unit (200 of 64, 32 rows, 26.1 / 28.2).
 // Nor where the streaming core has an element on nearly every compute unit and nothing crosses: single queries over histories, which
 // are of one length as a rule, d_m 512, fp16 (bf16): 256 of 128 positions 20.4 / 21.0 (20.9 / 21.3), 256 of 108 20.0 / 20.5 (20.4 /
-// 20.8), 254 of 128 20.4 / 20.8, 248 of 128 20.8 / 20.9, 244 21.0 / 21.0, but 230 of 128 22.4 / 20.3 (22.8 / 20.6).  Two and three queries over inputs of one
-// length lose as much in fp16 (256 of 128, 16 rows, 23.4 / 23.7, 24 rows 28.4 / 29.1; bf16 24.2 / 23.9, 29.5 / 29.7), but their inputs
-// differ in length, and 256 of 64 to 128 gain: 16 rows 25.3 / 23.2, 24 rows 31.0 / 27.8; four gain either way (128 each, 30.5 / 30.0).
+// 20.8); as graph replays 254 of 128 21.0 / 21.5 (21.5 / 21.8), 248 21.3 / 21.3 (21.5 / 21.8), 236 21.1 / 20.9; 230, where spans cross,
+// 22.4 / 20.3 (22.8 / 20.6), and so would 256 of mixed length, 64 to 128, 22.7 / 20.0.  Two and three queries over inputs of one length lose as
+// much in fp16 (256 of 128, 16 rows, 23.4 / 23.7, 24 rows 28.4 / 29.1; bf16 24.2 / 23.9, 29.5 / 29.7), but inputs differ in length as a rule,
+// and 256 of 64 to 128 gain: 16 rows 25.3 / 23.2, 24 rows 31.0 / 27.8; four gain either way (128 each, 30.5 / 30.0).
 static void plan_wide_spans(const Problem &p, int num_cus, int max_slots, CorePlan &pl)
 {
     if (p.B > kScanMax) return;
